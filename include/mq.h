@@ -173,7 +173,9 @@ mq_status mq_linear_fwd_multi(const uint16_t *X, const uint8_t *Q, const float *
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and limits
  * as mq_linear_fwd_multi without `ws`; the per-token sums of X that the forward keeps between its
  * pre-pass and its epilogue live in a fixed device array inside the library (1 MiB, one copy per GPU,
- * held until the process ends).  No hipMalloc, hipFree or other allocating call is made.
+ * held until the process ends).  No hipMalloc, hipFree or other allocating call is made.  (For few tokens
+ * mq_linear_fwd_multi splits K over workgroups through its workspace; this form never does, so there the order of the
+ * fp32 sums differs between the two.)
  *   - M <= 262144 tokens (MQ_ERR_SHAPE beyond: the built-in scratch holds one float per token).
  *   - Every call on one GPU uses that GPU's array: calls that overlap in time on the same GPU (two
  *     streams, two host threads) race and must be serialised by the caller.  Calls on different GPUs

@@ -189,7 +189,6 @@ __global__ __launch_bounds__(256) void affine_bwd_finish_kernel(const float *px,
     if (ds) ds[k] = (float)(-(p1 - dv * p0) / (sv * sv) + r1);
 }
 
-inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // row ranges so that about 2048 workgroups exist
 inline int splits_for(int64_t rows, int64_t cols) {

@@ -114,7 +114,6 @@ __global__ void clip_zero_kernel(float *a, float *b, float *c, float *d, int n) 
     if (d) d[i] = 0.f;
 }
 
-inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 }  // namespace
 

@@ -41,6 +41,7 @@ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline mq_status launch_status() { return hipGetLastError() == hipSuccess ? MQ_OK : MQ_ERR_DEVICE; }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // workspace of mq_ffn_mixnmatch (mq_ffn.hip)
 size_t ffn_workspace_bytes(int64_t B, int64_t F, int64_t d);

@@ -55,7 +55,6 @@ __global__ __launch_bounds__(256) void gate_train_kernel(GateArgs a) {
     }
 }
 
-inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct FfnLayout {
     size_t act, h0, h1, split, split_bytes, total;

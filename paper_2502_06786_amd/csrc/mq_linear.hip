@@ -23,149 +23,13 @@
 #include <mutex>
 #include <type_traits>
 
-#include "mq_gemv.h"
+#include "mq_linear.h"
 
 namespace mq {
-
-typedef __attribute__((address_space(3))) void *lds_ptr;
-
-constexpr int BKT = 64;                  // contraction elements per LDS stage
-constexpr uint32_t kOOB = 0x80000000u;   // buffer offset beyond any descriptor built here
-constexpr uint32_t kMagic128 = 0x43004300u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint64_t bytes) {
-    const uint32_t rec = bytes > 0x7FFFFFFFull ? 0x7FFFFFFFu : (uint32_t)bytes;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)rec, 0x00020000);
-}
-
-__device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-__device__ __forceinline__ f32x16 mfma32(const u32x4 &a, const u32x4 &b, const f32x16 &c) {
-    Frag8 fa, fb;
-    fa.u = a;
-    fb.u = b;
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.b, fb.b, c, 0, 0, 0);
-}
-
-// ---- LDS tiles ------------------------------------------------------------------------------
-// bf16 tile: ROWS x 64 elements, 128-byte rows of eight 16-byte chunks; chunk c of row r is stored
-// at chunk position c ^ ((r >> 1) & 7).  u8 tile: ROWS x 64 bytes, four chunks per row; chunk c of
-// row r at position c ^ ((r >> 2) & 3).  The LDS has 64 four-byte banks and serves a 16-byte read
-// sixteen lanes at a time, so sixteen consecutive rows must land on sixteen distinct 16-byte bank
-// groups of a 256-byte window; both swizzles do that (measured: same rate as a contiguous read).  A direct-to-LDS load writes lane l of a wave at base + 16 l, so the swizzle is
-// applied by choosing which global chunk each lane fetches.
-
-// Per-lane byte offset (row * ld_bytes + chunk * 16) of instruction `inst` of this wave for a bf16
-// tile, and the element column of the chunk (for the tail predicate).
-template <int NWAVES>
-__device__ __forceinline__ void bf16_tile_lane(int wave, int lane, int inst, uint32_t ld_bytes,
-                                               uint32_t &voff, int &col) {
-    const int slot = (wave + inst * NWAVES) * 64 + lane;
-    const int row = slot >> 3, p = slot & 7, c = p ^ ((row >> 1) & 7);
-    voff = (uint32_t)row * ld_bytes + (uint32_t)c * 16u;
-    col = c * 8;
-}
-template <int NWAVES>
-__device__ __forceinline__ void u8_tile_lane(int wave, int lane, int inst, uint32_t ld_bytes,
-                                             uint32_t &voff, int &col) {
-    const int slot = (wave + inst * NWAVES) * 64 + lane;
-    const int row = slot >> 2, p = slot & 3, c = p ^ ((row >> 2) & 3);
-    voff = (uint32_t)row * ld_bytes + (uint32_t)c * 16u;
-    col = c * 16;
-}
-
-// ---- code -> bf16 operand conversions ---------------------------------------------------------
-// Eight int8 codes (two dwords, k ascending) -> eight bf16 of the same value.
-__device__ __forceinline__ u32x4 codes_to_bf16_r8(uint32_t d0, uint32_t d1) {
-    auto two = [](float lo, float hi) {
-        return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-    };
-    return u32x4{two((float)(d0 & 0xFFu), (float)((d0 >> 8) & 0xFFu)),
-                 two((float)((d0 >> 16) & 0xFFu), (float)(d0 >> 24)),
-                 two((float)(d1 & 0xFFu), (float)((d1 >> 8) & 0xFFu)),
-                 two((float)((d1 >> 16) & 0xFFu), (float)(d1 >> 24))};
-}
-
-// Bytes of two dwords placed in 16-bit lanes, k ascending.  HIGH: byte << 8 (for the saturating
-// add), else byte in the low half.
-template <bool HIGH>
-__device__ __forceinline__ u32x4 place_bytes(uint32_t d0, uint32_t d1) {
-    constexpr uint32_t s01 = HIGH ? 0x010C000Cu : 0x0C010C00u;
-    constexpr uint32_t s23 = HIGH ? 0x030C020Cu : 0x0C030C02u;
-    return u32x4{__builtin_amdgcn_perm(0u, d0, s01), __builtin_amdgcn_perm(0u, d0, s23),
-                 __builtin_amdgcn_perm(0u, d1, s01), __builtin_amdgcn_perm(0u, d1, s23)};
-}
-
-// r-bit slice of section 3.2 as bf16(128 + code), from bytes placed by place_bytes<!EP>.
-// half2 = half in both 16-bit lanes (shifted left by 8 unless EP); sh = s (+ 8 unless EP).
-template <bool EP>
-__device__ __forceinline__ u32x4 sliced_to_bf16(const u32x4 &placed, uint32_t half2, uint32_t sh) {
-    u32x4 out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if constexpr (EP) {
-            out[i] = (((placed[i] + half2) >> sh) & 0x00FF00FFu) | kMagic128;
-        } else {
-            const uint32_t pv = placed[i];
-            u16x2 t = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, pv), __builtin_bit_cast(u16x2, half2));
-            const unsigned short s16 = (unsigned short)sh;
-            t = t >> u16x2{s16, s16};
-            out[i] = __builtin_bit_cast(uint32_t, t) | kMagic128;
-        }
-    }
-    return out;
-}
-
-struct SliceParam {  // wave-uniform per bit-width
-    uint32_t half2;  // half (<< 8 unless EP) in both 16-bit lanes
-    uint32_t sh;     // shift that leaves the code
-};
-
-template <bool EP>
-__device__ __forceinline__ SliceParam slice_param(int r) {
-    const uint32_t s = 8 - r, half = (1u << s) >> 1;
-    SliceParam p;
-    if constexpr (EP) {
-        p.half2 = half | (half << 16);
-        p.sh = s;
-    } else {
-        p.half2 = (half << 8) | (half << 24);
-        p.sh = s + 8;
-    }
-    return p;
-}
 
 // ============================================================================================
 // forward
 // ============================================================================================
-struct FwdArgs {
-    const uint16_t *X;
-    const uint8_t *Q;
-    const float *alpha, *zero, *rowsum;
-    uint16_t *Y[3];
-    int M, N, K;
-    int r[3];  // bit-width per slot; slot 0 is the r = 8 slot when HAS8
-    int tiles_m, tiles_n;
-    // LOSS kernels only (slot order as Y): the L2 objective is evaluated on the rounded outputs
-    // while they sit in the staging tiles.  Y[i] may then be NULL (that output is not stored).
-    const uint16_t *T;
-    uint16_t *dY[3];
-    int teacher[3];  // slot of the teacher, or -1 for the target T
-    float coef[3];   // lambda_i * 2 / (M N)
-    int mix;
-    float *partial;  // [workgroup][4] sums of squared differences
-    const float *bias;  // [N] added to every output before it is rounded, or null
-    // plain kernels only: the layer is the stacked gate / up projection of a gated unit (channels (g, u) pairs)
-    // and A[i] [M, N / 2] receives act(g) u of the rounded outputs; gate = 0 none, 1 GELU-tanh, 2 SiLU
-    uint16_t *A[3];
-    int gate;
-};
-
-constexpr int FWD_BN = 128;
-constexpr int FWD_Q_TILE = FWD_BN * 64;
-constexpr int FWD_STAGES = 4;
-// 32-token blocks per wave: the accumulators (16 NR MB registers) must leave room for the operands
-constexpr int fwd_mb(int nr) { return nr == 3 ? 5 : 6; }
 constexpr int fwd_lds(int mb, int nr) {
     const int stages = FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE), staging = nr * mb * 32 * (FWD_BN * 2 + 8);
     return stages > staging ? stages : staging;
@@ -183,9 +47,6 @@ template <int NR, bool HAS8, bool EP, int MB, bool LOSS>
 __global__ __launch_bounds__(256) void fwd_kernel(FwdArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     constexpr int BM = 32 * MB;
-    constexpr int X_TILE = BM * 128;
-    constexpr int STAGE = X_TILE + FWD_Q_TILE;
-    constexpr int LPS = MB + 2;  // direct-to-LDS loads per wave and stage
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, l32 = lane & 31;
@@ -227,175 +88,9 @@ __global__ __launch_bounds__(256) void fwd_kernel(FwdArgs a) {
     const int tn = (int)(lid % width) / gsz;
     const int m0 = tm * BM, n0 = tn * FWD_BN;
 
-    const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.X + (size_t)m0 * a.K, (uint64_t)(a.M - m0) * a.K * 2);
-    const __amdgpu_buffer_rsrc_t rQ = make_rsrc(a.Q + (size_t)n0 * a.K, (uint64_t)(a.N - n0) * a.K);
-
-    // global -> LDS: lane offsets of the wave's first X / Q instruction; instruction i is 32 (X) or
-    // 64 (Q) rows further down with the same chunk
-    uint32_t xoff0, qoff0;
-    int xcol, qcol;
-    bf16_tile_lane<4>(wave, lane, 0, (uint32_t)a.K * 2u, xoff0, xcol);
-    u8_tile_lane<4>(wave, lane, 0, (uint32_t)a.K, qoff0, qcol);
-    const uint32_t xstep = 32u * (uint32_t)a.K * 2u, qstep = 64u * (uint32_t)a.K;
-
-    // Stage kt -> LDS buffer kt % 4, as MB + 2 loads per wave (MB of X, then 2 of Q).  Branch-free:
-    // a stage past the end of K (or a chunk past K in the last stage) is requested at an
-    // out-of-range offset, which the buffer unit answers with zeros without touching memory, so
-    // the number of loads in flight is the same in every iteration.
-    auto issue_one = [&](int kt, int i) {
-        const int k0 = kt * BKT;
-        uint8_t *xs = smem + (kt & 3) * STAGE;
-        if (i < MB) {
-            // (an out-of-range base stays out of range: kOOB + i * xstep < 2^32 for every legal K)
-            const uint32_t xb = (k0 + xcol < a.K) ? xoff0 + (uint32_t)k0 * 2u : kOOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, (lds_ptr)(xs + (wave + i * 4) * 1024), 16,
-                                                     xb + (uint32_t)i * xstep, 0, 0, 0);
-        } else {
-            const uint32_t qb = (k0 + qcol < a.K) ? qoff0 + (uint32_t)k0 : kOOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rQ, (lds_ptr)(xs + X_TILE + (wave + (i - MB) * 4) * 1024), 16,
-                                                     qb + (uint32_t)(i - MB) * qstep, 0, 0, 0);
-        }
-    };
-    auto issue = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < MB + 2; ++i) issue_one(kt, i);
-    };
-
-    // LDS fragment addresses (byte offsets inside a stage)
-    const int nl = wave * 32 + l32;
-    const uint32_t qa0 = X_TILE + nl * 64 + ((h ^ ((nl >> 2) & 3)) << 4);
-    const uint32_t qa1 = X_TILE + nl * 64 + (((h + 2) ^ ((nl >> 2) & 3)) << 4);
-    uint32_t xa[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int cx = 2 * h + 4 * (t >> 1) + (t & 1);
-        xa[t] = l32 * 128 + ((cx ^ ((l32 >> 1) & 7)) << 4);
-    }
-
-    SliceParam sp[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) sp[i] = slice_param<EP>(a.r[i]);
-
-    // Dword w (two consecutive k) of the code operand of slot i, from the 8 code bytes (d0, d1).
-    auto convert_piece = [&](int i, int w, uint32_t d0, uint32_t d1) -> uint32_t {
-        const uint32_t d = w < 2 ? d0 : d1;
-        if (HAS8 && i == 0) {
-            const float lo = (w & 1) ? (float)((d >> 16) & 0xFFu) : (float)(d & 0xFFu);
-            const float hi = (w & 1) ? (float)(d >> 24) : (float)((d >> 8) & 0xFFu);
-            return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-        }
-        if constexpr (EP) {
-            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x0C030C02u : 0x0C010C00u);
-            return (((placed + sp[i].half2) >> sp[i].sh) & 0x00FF00FFu) | kMagic128;
-        } else {
-            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x030C020Cu : 0x010C000Cu);
-            u16x2 t = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, placed),
-                                                    __builtin_bit_cast(u16x2, sp[i].half2));
-            const unsigned short s16 = (unsigned short)sp[i].sh;
-            t = t >> u16x2{s16, s16};
-            return __builtin_bit_cast(uint32_t, t) | kMagic128;
-        }
-    };
-
     f32x16 acc[NR][MB];
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
-#pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int nkt = (a.K + BKT - 1) / BKT;
-    issue(0);
-    issue(1);
-    issue(2);
-    // stage 0 must have landed before the first operand fetch; stages 1 and 2 may stay in flight
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPS) : "memory");
-    __syncthreads();
-
-    u32x4 xf[MB];      // activation operands of the current k step (refilled as soon as they are consumed)
-    u32x4 raw[2];      // 32 code bytes of this lane's channel: four k steps of one stage
-    u32x4 wf[NR];      // code operands of the current k step
-    raw[0] = *reinterpret_cast<const u32x4 *>(smem + qa0);
-    raw[1] = *reinterpret_cast<const u32x4 *>(smem + qa1);
-#pragma unroll
-    for (int j = 0; j < MB; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + j * 4096);
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) wf[i][w] = convert_piece(i, w, raw[0][0], raw[0][1]);
-
-    // One stage of 64 k: four 16-wide steps of NR * MB MFMAs.  A wave issues in order, so whatever
-    // is queued behind an MFMA that waits for the matrix pipe waits with it; the other work of a
-    // step is therefore cut into one small group per MFMA, fenced so that the compiler keeps it
-    // there:  group q < MB requests operand block q of step t + 1 from LDS (it then has the rest
-    // of the step to arrive), groups 1 .. 4 NR each produce one dword of the next code operands,
-    // the last groups of step 0 issue the global loads of stage kt + 3, and step 2 fetches the
-    // code bytes of the next stage.  MORE (compile time): there is a next stage.
-    auto tile = [&](auto more_tag, int kt) {
-        constexpr bool MORE = decltype(more_tag)::value;
-        constexpr int NM = NR * MB;
-        static_assert(4 * NR <= NM, "not enough MFMAs to hide the operand work");
-        constexpr int CQ = 4 * NR + 1 <= NM ? 1 : 0;  // first group that carries a conversion
-        constexpr int LPG = (LPS + NM - 1) / NM;  // global loads per group in step 0
-        const uint8_t *cur = smem + (kt & 3) * STAGE;
-        const uint8_t *nxt = smem + ((kt + 1) & 3) * STAGE;
-        u32x4 rawn[2];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const bool pre = t < 3 || MORE;  // is there a next step
-            const uint8_t *src = t < 3 ? cur + xa[(t + 1) & 3] : nxt + xa[0];
-            // code bytes of the next step
-            uint32_t d0 = t == 3 ? rawn[0][0] : (t + 1 < 2 ? raw[0][2 * (t + 1)] : raw[1][2 * (t + 1 - 2)]);
-            uint32_t d1 = t == 3 ? rawn[0][1] : (t + 1 < 2 ? raw[0][2 * (t + 1) + 1] : raw[1][2 * (t + 1 - 2) + 1]);
-            // pin the conversions of this step to this step (the optimizer would otherwise collect
-            // them across the loop back-edge)
-            if (pre) asm volatile("" : "+v"(d0), "+v"(d1));
-            u32x4 xfn[MB];
-            u32x4 wfn[NR];
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int j = q / NR, i = q % NR;
-                acc[i][j] = mfma32(wf[i], xf[j], acc[i][j]);
-                if (pre && q < MB) xfn[q] = *reinterpret_cast<const u32x4 *>(src + q * 4096);
-                if (pre && q >= CQ && q - CQ < 4 * NR) {
-                    uint32_t piece = convert_piece((q - CQ) / 4, (q - CQ) % 4, d0, d1);
-                    asm volatile("" : "+v"(piece));  // keeps the conversion inside this group
-                    wfn[(q - CQ) / 4][(q - CQ) % 4] = piece;
-                }
-                if (MORE && t == 2 && q >= NM - 2) rawn[q - (NM - 2)] = *reinterpret_cast<const u32x4 *>(nxt + (q == NM - 2 ? qa0 : qa1));
-                if (MORE && t == 0) {
-#pragma unroll
-                    for (int u = 0; u < LPG; ++u) {
-                        const int ld = (NM - 1 - q) * LPG + u;  // the last groups carry the loads
-                        if (ld < LPS) issue_one(kt + 3, ld);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (pre) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) wf[i] = wfn[i];
-#pragma unroll
-                for (int j = 0; j < MB; ++j) xf[j] = xfn[j];
-            }
-        }
-        if (MORE) {
-            raw[0] = rawn[0];
-            raw[1] = rawn[1];
-        }
-    };
-
-    for (int kt = 0; kt + 1 < nkt; ++kt) {
-        // Stage kt + 1 must be resident for the operand prefetch at the end of this iteration; the
-        // loads of stage kt + 2 may stay in flight.  After the barrier every wave is done with
-        // stage kt - 1, whose buffer stage kt + 3 reuses.
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
-        __syncthreads();
-        tile(std::true_type{}, kt);
-    }
-    tile(std::false_type{}, nkt - 1);
-    wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
+    float no_rowsum[MB];
+    fwd_main_loop<NR, HAS8, EP, MB, false>(a, smem, m0, n0, 0, (a.K + BKT - 1) / BKT, a.K, acc, no_rowsum, 0u);
 
     // ---- epilogue ---------------------------------------------------------------------------
     // accumulator v = 4 g + e of a lane holds row (channel) 8 g + 4 h + e, column (token) l32.
@@ -1393,7 +1088,6 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(DwArgs a) {
 // ============================================================================================
 // host side
 // ============================================================================================
-static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct BwdWorkspace {
     size_t cvec, as[3], gt, xt, qt, dwp, total;
@@ -1454,17 +1148,27 @@ static mq_status launch_fwd_mb(FwdArgs a, hipStream_t st, int64_t *blocks) {
 // (32 per MFMA, plus about 180 cycles per 64-wide k stage and bit-width that do not shrink with the tile:
 // conversions and the stage barrier - fitted on the 9B gate shape, where 160 tokens run 2.5-4 % faster than
 // 128 although both fill their rounds; prologue and epilogue constants measured on the Gemma-2-2B shapes).
+int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb) {
+    const int hi = fwd_mb(nr);
+    int64_t best = 0;
+    for (int h = hi; h >= hi - 1; --h) {
+        const int64_t tiles = cdiv(M, 32 * h) * cdiv(N, FWD_BN);
+        const int64_t rounds = cdiv(tiles, 256);
+        const int64_t per_tile = cdiv(K, BKT) * (nr * h * 128 + 180 * nr) + 3000 + 890 * nr * h;
+        if (h == hi || rounds * per_tile < best) {
+            best = rounds * per_tile;
+            if (mb) *mb = h;
+        }
+    }
+    return best;
+}
+
 template <int NR, bool HAS8, bool EP, bool LOSS>
 static mq_status launch_fwd(const FwdArgs &a, hipStream_t st, int64_t *blocks) {
     constexpr int HI = fwd_mb(NR), LO = HI - 1;
-    auto cost = [&](int mb) {
-        const int64_t tiles = cdiv(a.M, 32 * mb) * cdiv(a.N, FWD_BN);
-        const int64_t rounds = cdiv(tiles, 256);
-        const int64_t per_tile = cdiv(a.K, BKT) * (NR * mb * 128 + 180 * NR) + 3000 + 890 * NR * mb;
-        return rounds * per_tile;
-    };
-    return cost(LO) < cost(HI) ? launch_fwd_mb<NR, HAS8, EP, LO, LOSS>(a, st, blocks)
-                               : launch_fwd_mb<NR, HAS8, EP, HI, LOSS>(a, st, blocks);
+    int mb = HI;
+    fwd_tiled_cost(a.M, a.N, a.K, NR, &mb);
+    return mb == LO ? launch_fwd_mb<NR, HAS8, EP, LO, LOSS>(a, st, blocks) : launch_fwd_mb<NR, HAS8, EP, HI, LOSS>(a, st, blocks);
 }
 
 template <int NR, bool HAS8, bool LOSS>
@@ -1481,8 +1185,22 @@ static mq_status launch_fwd_any(const FwdArgs &a, int nr, bool has8, bool ep, hi
     return has8 ? launch_fwd_ep<3, true, LOSS>(a, ep, st, blocks) : launch_fwd_ep<3, false, LOSS>(a, ep, st, blocks);
 }
 
-// workgroups of the forward kernel at its smallest token tile (128 tokens): bound for the partial sums
-static int64_t fwd_max_blocks(int64_t M, int64_t N) { return cdiv(M, 128) * cdiv(N, FWD_BN); }
+// Workspace of the forward: the tiled kernel's row sums at offset 0, the objective's partial sums (a bound over both
+// forms: the tiled kernel at its smallest token tile, 128 tokens, or the finishing kernel of the split form) and the
+// losses in slot order, and what the split form keeps.
+struct FwdWorkspace {
+    size_t loss, slots, rs_part, part, total;
+};
+static FwdWorkspace fwd_layout(int64_t M, int64_t N, const FwdSplitPlan &plan, bool loss) {
+    FwdWorkspace w;
+    w.loss = align256((size_t)M * 4);
+    const int64_t blocks = std::max<int64_t>(cdiv(M, 128) * cdiv(N, FWD_BN), plan.mb ? plan.loss_blocks : 0);
+    w.slots = w.loss + (loss ? (size_t)blocks * 16 : 0);
+    w.rs_part = align256(w.slots + 256);
+    w.part = w.rs_part + (plan.mb ? align256(plan.rs_bytes) : 0);
+    w.total = plan.mb ? w.part + plan.part_bytes : w.slots + 256;
+    return w;
+}
 
 template <int NRS, bool HAS8, bool EP>
 static mq_status launch_dx_one(const DxArgs &d, hipStream_t st) {
@@ -1510,8 +1228,8 @@ extern "C" size_t mq_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, in
     if (op == MQ_OP_GEMV)  // M = B, nr = bits per code
         return M < 1 || M > 16 || N < 0 || K < 1 || nr < 1 || nr > 8 ? 0 : std::max<size_t>(256, gemv_split_workspace_bytes(M, N, K, nr));
     if (M < 0 || N < 0 || K < 0 || nr < 1 || nr > 3) return 0;
-    if (op == MQ_OP_LINEAR_FWD) return align256((size_t)M * 4) + 256;
-    if (op == MQ_OP_LINEAR_FWD_L2) return align256((size_t)M * 4) + (size_t)fwd_max_blocks(M, N) * 16 + 256;
+    if (op == MQ_OP_LINEAR_FWD || op == MQ_OP_LINEAR_FWD_L2)
+        return fwd_layout(M, N, fwd_split_plan(M, N, K, nr), op == MQ_OP_LINEAR_FWD_L2).total;
     if (op == MQ_OP_LINEAR_BWD) return bwd_layout(M, N, K, nr).total + 256;
     if (op == MQ_OP_FFN_DECODE) return ffn_workspace_bytes(M, N, K);
     if (op == MQ_OP_L2_LOSS) return loss_workspace_bytes(M, N);
@@ -1536,7 +1254,8 @@ struct FwdLoss {
 static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha, const float *zero, int64_t M,
                          int64_t N, int64_t K, const int *rs, int nr, uint32_t flags, uint16_t *const *Y,
                          const FwdLoss *loss, void *ws, size_t ws_bytes, void *hip_stream,
-                         bool check_only = false, uint16_t *const *gated_out = nullptr, int gate = 0) {
+                         bool check_only = false, uint16_t *const *gated_out = nullptr, int gate = 0,
+                         bool tiled_only = false) {
     if (M < 0 || N < 0 || K < 1) return MQ_ERR_SHAPE;
     if (M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > (1 << 22)) return MQ_ERR_SHAPE;
     if (cdiv(M, 128) * cdiv(N, FWD_BN) > 0x7FFFFFFF) return MQ_ERR_SHAPE;  // tiles of one launch
@@ -1573,9 +1292,11 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         if (loss->bias && !aligned16(loss->bias)) return MQ_ERR_ALIGN;
     }
     if (!aligned16(X) || !aligned16(Q) || !aligned16(alpha) || !aligned16(zero)) return MQ_ERR_ALIGN;
-    const int op = loss ? MQ_OP_LINEAR_FWD_L2 : MQ_OP_LINEAR_FWD;
     if (check_only) return MQ_OK;  // every argument but the workspace is fine
-    if (!ws || ws_bytes < mq_workspace_bytes(op, M, N, K, nr) || !aligned16(ws)) return MQ_ERR_WORKSPACE;
+    const FwdSplitPlan plan = tiled_only ? FwdSplitPlan{} : fwd_split_plan(M, N, K, nr);
+    const FwdWorkspace lay = fwd_layout(M, N, plan, loss != nullptr);
+    if (!ws || ws_bytes < lay.total || !aligned16(ws)) return MQ_ERR_WORKSPACE;
+    uint8_t *base = static_cast<uint8_t *>(ws);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
     FwdArgs a{};
@@ -1614,7 +1335,7 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         a.T = loss->target;
         a.bias = loss->bias;
         a.mix = loss->mix ? 1 : 0;
-        a.partial = reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + align256((size_t)M * 4));
+        a.partial = reinterpret_cast<float *>(base + lay.loss);
         for (int i = 0; i < nr; ++i) {
             const int sl = slot_of[i];
             a.dY[sl] = loss->dY[i];
@@ -1624,15 +1345,19 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         }
     }
 
-    rowsum_kernel<<<dim3((unsigned)cdiv(M, 4)), dim3(256), 0, st>>>(X, (int)M, (int)K, static_cast<float *>(ws));
     const bool ep = flags & MQ_FLAG_EXTRA_PRECISION;
     int64_t blocks = 0;
-    if (!loss) return launch_fwd_any<false>(a, nr, has8, ep, st, &blocks);
-    s = launch_fwd_any<true>(a, nr, has8, ep, st, &blocks);
-    if (s != MQ_OK) return s;
+    if (plan.mb) {
+        s = launch_fwd_split(a, plan, nr, has8, ep, loss != nullptr, reinterpret_cast<float *>(base + lay.part),
+                             reinterpret_cast<float *>(base + lay.rs_part), st, &blocks);
+    } else {
+        rowsum_kernel<<<dim3((unsigned)cdiv(M, 4)), dim3(256), 0, st>>>(X, (int)M, (int)K, static_cast<float *>(ws));
+        s = loss ? launch_fwd_any<true>(a, nr, has8, ep, st, &blocks) : launch_fwd_any<false>(a, nr, has8, ep, st, &blocks);
+    }
+    if (s != MQ_OK || !loss) return s;
     // the kernel's sums are in slot order: where that is not the caller's order (an r = 8 that is
     // not first) they are finished into the tail of the workspace and permuted
-    float *slot_losses = a.partial + (size_t)fwd_max_blocks(M, N) * 4;
+    float *slot_losses = reinterpret_cast<float *>(base + lay.slots);
     bool same = true;
     for (int i = 0; i < nr; ++i) same = same && slot_of[i] == i;
     s = launch_loss_finish(a.partial, blocks, nr, (float)(1.0 / mn), same ? loss->losses : slot_losses, st);
@@ -1697,8 +1422,6 @@ extern "C" mq_status mq_linear_fwd_multi_noalloc(const uint16_t *X, const uint8_
                                                  int nr, uint32_t flags, uint16_t *const *Y, void *hip_stream) {
     using namespace mq;
     if (M > kNoAllocMaxTokens) return MQ_ERR_SHAPE;  // more tokens than the built-in scratch holds
-    const size_t need = M >= 0 && nr >= 1 && nr <= 3 ? mq_workspace_bytes(MQ_OP_LINEAR_FWD, M, N, K, nr) : 0;
-    if (need > sizeof(float) * (kNoAllocMaxTokens + 64)) return MQ_ERR_SHAPE;
     // the arguments are checked before the device is touched; an empty call launches nothing and needs no scratch
     mq_status s = fwd_run(X, Q, alpha, zero, M, N, K, rs, nr, flags, Y, nullptr, nullptr, 0, hip_stream, true);
     if (s != MQ_OK || M == 0 || N == 0) return s;
@@ -1706,7 +1429,7 @@ extern "C" mq_status mq_linear_fwd_multi_noalloc(const uint16_t *X, const uint8_
     s = noalloc_scratch(&ws);
     if (s != MQ_OK) return s;
     return fwd_run(X, Q, alpha, zero, M, N, K, rs, nr, flags, Y, nullptr, ws, sizeof(float) * (kNoAllocMaxTokens + 64),
-                   hip_stream);
+                   hip_stream, false, nullptr, 0, true);
 }
 
 extern "C" mq_status mq_linear_fwd_multi_l2(const uint16_t *X, const uint8_t *Q, const float *alpha,

@@ -1,0 +1,295 @@
+// The fused forward for few tokens: K split over workgroups.
+//
+// A prompt or a calibration sample of M tokens gives the tiled forward kernel ceil(M / 160) * N / 128 workgroups: 32 of
+// the 256 compute units for 77 tokens through a 4096 x 4096 layer, each walking all of K alone (35 us for 17 MB of codes).
+// Here a workgroup takes one token tile of 32 .. 128 tokens, 128 channels and one range of K, runs the same main loop,
+// and leaves its fp32 accumulators in the workspace in the order its lanes hold them (every store and load is a whole
+// 1 KB line group); a second kernel adds the ranges in a fixed order and applies the forward's epilogue (and, with the
+// objective or the gated unit, theirs).  The per-token sums of X that the epilogue needs come out of the tiles that pass
+// through LDS anyway (block j of a tile is summed by the workgroups of channel tile j mod tiles_n), so the row-sum
+// pre-pass and its launch disappear.
+#include <algorithm>
+
+#include "mq_linear.h"
+
+namespace mq {
+
+struct FwdSplitArgs {
+    FwdArgs f;
+    float *part;     // [split][tile][bit-width][token block][g][256] four channels of one token each
+    float *rs_part;  // [split][tiles_m * 32 MB] sums of X over the split's range of K
+    int splits;
+};
+
+template <int NR, bool HAS8, bool EP, int MB>
+__global__ __launch_bounds__(256) void fwd_split_kernel(FwdSplitArgs s) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    const FwdArgs &a = s.f;
+    constexpr int BM = 32 * MB;
+    const int tiles = a.tiles_m * a.tiles_n;
+    // Neighbouring ids, which share an XCD's L2, are token tiles of one channel tile (the same codes), then channel tiles
+    // of one K range (the same columns of X).
+    const int lid = (int)xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const int split = lid / tiles, tile = lid % tiles;
+    const int tn = tile / a.tiles_m, tm = tile % a.tiles_m;
+    const int m0 = tm * BM, n0 = tn * FWD_BN;
+    const int nkt = (a.K + BKT - 1) / BKT;
+    const int kt0 = (int)((int64_t)nkt * split / s.splits), kt1 = (int)((int64_t)nkt * (split + 1) / s.splits);
+    uint32_t rs_mask = 0;
+    float rsum[MB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+        rsum[j] = 0.f;
+        if (j % a.tiles_n == tn) rs_mask |= 1u << j;
+    }
+    f32x16 acc[NR][MB];
+    fwd_main_loop<NR, HAS8, EP, MB, true>(a, smem, m0, n0, kt0, kt1 - kt0, min(a.K, kt1 * BKT), acc, rsum, rs_mask);
+
+#pragma unroll
+    for (int j = 0; j < MB; ++j)
+        if (rs_mask & (1u << j)) {
+            float v = rsum[j];
+            v += __shfl_xor(v, 1, 64);
+            v += __shfl_xor(v, 2, 64);
+            v += __shfl_xor(v, 4, 64);
+            if ((threadIdx.x & 7) == 0) s.rs_part[(size_t)split * a.tiles_m * BM + m0 + j * 32 + (threadIdx.x >> 3)] = v;
+        }
+    f32x4 *dst = reinterpret_cast<f32x4 *>(s.part) + ((size_t)split * tiles + tile) * (NR * MB * 4 * 256) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                dst[((i * MB + j) * 4 + g) * 256] =
+                    f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+}
+
+// Adds the K ranges and finishes the outputs.  Workgroup = (tile, token block, 32 channels): wave g takes accumulator rows
+// 8 g + 4 h .. + 3, so the four waves write 64 contiguous bytes of 32 tokens.  The arithmetic per output is that of the
+// tiled forward kernel's epilogue.
+template <int NR, bool LOSS>
+__global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, int mb) {
+    __shared__ float red[4][4];
+    const FwdArgs &a = s.f;
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int h = lane >> 5, l32 = lane & 31;
+    const int w = blockIdx.x & 3, j = (int)(blockIdx.x >> 2) % mb, tile = (int)(blockIdx.x >> 2) / mb;
+    const int tiles = a.tiles_m * a.tiles_n;
+    const int tn = tile / a.tiles_m, tm = tile % a.tiles_m;
+    const int m = tm * 32 * mb + j * 32 + l32, n = tn * FWD_BN + w * 32 + 8 * g + 4 * h;
+    const bool ok = m < a.M && n < a.N;
+
+    const size_t rs_step = (size_t)a.tiles_m * 32 * mb, step = (size_t)tiles * NR * mb * 1024;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(s.part) + (((size_t)tile * NR * mb + j) * 4 + g) * 256 + w * 64 + lane;
+    f32x4 sum[NR];
+    float rs = 0.f;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < s.splits; p0 += 4) {  // the loads of four ranges are in flight together
+        f32x4 v[4][NR];
+        float r[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const bool live = p0 + p < s.splits;
+            r[p] = live ? s.rs_part[(p0 + p) * rs_step + m] : 0.f;
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+                v[p][i] = live ? __builtin_nontemporal_load(src + (p0 + p) * step + (size_t)i * mb * 1024) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            rs += r[p];
+#pragma unroll
+            for (int i = 0; i < NR; ++i) sum[i] += v[p][i];
+        }
+    }
+
+    u32x2 y[NR];
+    float err[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) err[i] = 0.f;
+    if (ok) {
+        const f32x4 al = *reinterpret_cast<const f32x4 *>(a.alpha + n), ze = *reinterpret_cast<const f32x4 *>(a.zero + n);
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (LOSS)
+            if (a.bias) bias = *reinterpret_cast<const f32x4 *>(a.bias + n);
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const bool is8 = a.r[i] == 8;
+            const float mult = is8 ? 1.0f : (float)(1 << (8 - a.r[i]));
+            const float offset = is8 ? 0.0f : 128.0f * mult;
+            float o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float t = (offset + ze[e]) * rs;
+                const float inner = __builtin_fmaf(mult, sum[i][e], -t);
+                o[e] = LOSS ? __builtin_fmaf(al[e], inner, bias[e]) : al[e] * inner;
+            }
+            y[i] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+        }
+        const size_t at = (size_t)m * a.N + n;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            if (a.Y[i]) *reinterpret_cast<u32x2 *>(a.Y[i] + at) = y[i];
+            if constexpr (!LOSS)
+                if (a.gate) {
+                    auto gated = [&](uint32_t pair) {
+                        const float gt = bf16_lo(pair), up = bf16_hi(pair);
+                        return (a.gate == 2 ? silu(gt) : gelu_tanh(gt)) * up;
+                    };
+                    *reinterpret_cast<uint32_t *>(a.A[i] + (size_t)m * (a.N >> 1) + (n >> 1)) = pack_bf16x2(gated(y[i].x), gated(y[i].y));
+                }
+        }
+        if constexpr (LOSS) {
+            u32x2 t = {0u, 0u};
+            if (a.T) t = *reinterpret_cast<const u32x2 *>(a.T + at);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                u32x2 ref = t;
+                const bool taught = a.teacher[i] >= 0;
+#pragma unroll
+                for (int u = 0; u < NR; ++u)
+                    if (a.teacher[i] == u) ref = y[u];
+                u32x2 o;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float y0 = bf16_lo(y[i][c]), y1 = bf16_hi(y[i][c]);
+                    float d0 = y0 - bf16_lo(ref[c]), d1 = y1 - bf16_hi(ref[c]);
+                    if (a.mix && taught) {  // teacher and ground truth, weighted equally
+                        const float e0 = y0 - bf16_lo(t[c]), e1 = y1 - bf16_hi(t[c]);
+                        err[i] += 0.5f * (d0 * d0 + d1 * d1 + e0 * e0 + e1 * e1);
+                        d0 = 0.5f * (d0 + e0);
+                        d1 = 0.5f * (d1 + e1);
+                    } else {
+                        err[i] = __builtin_fmaf(d1, d1, __builtin_fmaf(d0, d0, err[i]));
+                    }
+                    o[c] = pack_bf16x2(a.coef[i] * d0, a.coef[i] * d1);
+                }
+                *reinterpret_cast<u32x2 *>(a.dY[i] + at) = o;
+            }
+        }
+    }
+    if constexpr (LOSS) {  // workgroup sums in a fixed order
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            float v = err[i];
+#pragma unroll
+            for (int msk = 1; msk < 64; msk <<= 1) v += __shfl_xor(v, msk, 64);
+            if (lane == 0) red[g][i] = v;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4)
+            a.partial[(size_t)blockIdx.x * 4 + threadIdx.x] =
+                (int)threadIdx.x < NR ? red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x] : 0.f;
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------------
+namespace {
+
+constexpr int split_lds(int mb) { return FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE); }
+
+template <int NR, bool HAS8, bool EP, int MB>
+mq_status launch_split_mb(const FwdSplitArgs &s, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_split_kernel<NR, HAS8, EP, MB>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, split_lds(MB));
+    if (attr != hipSuccess) return MQ_ERR_DEVICE;
+    fwd_split_kernel<NR, HAS8, EP, MB><<<dim3(s.f.tiles_m * s.f.tiles_n * s.splits), dim3(256), split_lds(MB), st>>>(s);
+    return launch_status();
+}
+
+template <int NR, bool HAS8, bool EP>
+mq_status launch_split(const FwdSplitArgs &s, int mb, hipStream_t st) {
+    switch (mb) {
+        case 1: return launch_split_mb<NR, HAS8, EP, 1>(s, st);
+        case 2: return launch_split_mb<NR, HAS8, EP, 2>(s, st);
+        case 3: return launch_split_mb<NR, HAS8, EP, 3>(s, st);
+        default: return launch_split_mb<NR, HAS8, EP, 4>(s, st);
+    }
+}
+
+template <int NR>
+mq_status launch_split_nr(const FwdSplitArgs &s, int mb, bool has8, bool ep, hipStream_t st) {
+    if constexpr (NR == 1) ep = ep && !has8;  // the code of r = 8 is never rounded up past the byte
+    if (has8) {
+        if constexpr (NR > 1)
+            if (ep) return launch_split<NR, true, true>(s, mb, st);
+        return launch_split<NR, true, false>(s, mb, st);
+    }
+    return ep ? launch_split<NR, false, true>(s, mb, st) : launch_split<NR, false, false>(s, mb, st);
+}
+
+template <int NR>
+mq_status launch_finish(const FwdSplitArgs &s, int mb, bool loss, hipStream_t st, int64_t *blocks) {
+    *blocks = (int64_t)s.f.tiles_m * s.f.tiles_n * mb * 4;
+    if (loss)
+        fwd_split_finish_kernel<NR, true><<<dim3((unsigned)*blocks), dim3(256), 0, st>>>(s, mb);
+    else
+        fwd_split_finish_kernel<NR, false><<<dim3((unsigned)*blocks), dim3(256), 0, st>>>(s, mb);
+    return launch_status();
+}
+
+}  // namespace
+
+// Which form, and how it is cut: the least modelled time in ns over one to four token blocks per workgroup and up to 16
+// ranges of at least five 64-wide stages, against the tiled kernel.  Per stage a compute unit needs 128 cycles per
+// matrix product row (32 x 64 x 32) and bit-width, 172 per bit-width for the conversions and 50 for the barrier, for each of
+// the workgroups it holds (80 KB of LDS and 256 registers each where two fit), but never less than the 1000 cycles a stage
+// takes to arrive; all workgroups together cannot read codes faster than 2900 or tiles of X faster than 4100 bytes per
+// cycle; a workgroup starts and ends in 4200 cycles; launches and the finishing kernel cost 8500 cycles, 1800 bytes of
+// accumulators take a cycle to be written and read back.  The constants are a fit to 2200 timed combinations (10 layers of
+// 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths): the choice is 1.5 % slower than the best of them
+// on average.  Measured, tiled -> chosen: 4096 x 4096, 77 tokens, int4 37.6 -> 15.7 us; 4096 x 14336 117 -> 26 us;
+// 2304 x 9216 at r = 8/4/2, 203 tokens 125 -> 44 us; level with the tiled kernel at 600 (14336 rows: 130) tokens and more.
+FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
+    FwdSplitPlan best{0, 0, 0, 0, 0};
+    if (M < 1 || N < 1 || M > 2048) return best;
+    const int64_t tiles_n = cdiv(N, FWD_BN), nkt = cdiv(K, BKT);
+    double best_cost = 0.47 * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + 4600.0;  // with its row-sum pre-pass
+    for (int mb = 1; mb <= 4; ++mb) {
+        const int64_t tiles_m = cdiv(M, 32 * mb), tiles = tiles_m * tiles_n;
+        if (mb > 1 && tiles_m == cdiv(M, 32 * (mb - 1))) continue;
+        const int resident = std::max(1, std::min(163840 / split_lds(mb), 512 / (16 * nr * mb + 110)));
+        const double busy = nr * mb * 128.0 + 172.0 * nr + 50.0;
+        for (int splits = 1; splits <= 16; ++splits) {
+            const int64_t stages = cdiv(nkt, splits);
+            if (splits > 1 && stages < 5) break;
+            if (splits == 1 && M > 64) continue;
+            const size_t part = (size_t)splits * tiles * nr * mb * 16384;
+            if (part > ((size_t)96 << 20)) break;
+            const int64_t per_cu = cdiv(tiles * splits, 256), full = per_cu / resident, rest = per_cu % resident;
+            double loop = full * std::max(resident * busy, 1000.0) + (rest ? std::max(rest * busy, 1000.0) : 0.0);
+            loop = loop * stages + (full + (rest ? 1 : 0)) * 4200.0;
+            loop = std::max(loop, std::max((double)N * K / 2900.0, (double)tiles * splits * stages * mb * 4096.0 / 4100.0));
+            const double cost = 0.51 * (loop + 8500.0 + part / 1800.0 + 217.0 * splits * nr);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best.mb = mb;
+                best.splits = splits;
+                best.part_bytes = part;
+                best.rs_bytes = (size_t)splits * tiles_m * 32 * mb * 4;
+                best.loss_blocks = tiles * mb * 4;
+            }
+        }
+    }
+    return best;
+}
+
+mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part, float *rs_part,
+                           hipStream_t st, int64_t *blocks) {
+    FwdSplitArgs s;
+    s.f = f;
+    s.f.tiles_m = (int)cdiv(f.M, 32 * plan.mb);
+    s.f.tiles_n = (int)cdiv(f.N, FWD_BN);
+    s.part = part;
+    s.rs_part = rs_part;
+    s.splits = plan.splits;
+    mq_status e = nr == 1 ? launch_split_nr<1>(s, plan.mb, has8, ep, st) : nr == 2 ? launch_split_nr<2>(s, plan.mb, has8, ep, st)
+                                                                                    : launch_split_nr<3>(s, plan.mb, has8, ep, st);
+    if (e != MQ_OK) return e;
+    return nr == 1 ? launch_finish<1>(s, plan.mb, loss, st, blocks) : nr == 2 ? launch_finish<2>(s, plan.mb, loss, st, blocks)
+                                                                               : launch_finish<3>(s, plan.mb, loss, st, blocks);
+}
+
+}  // namespace mq
