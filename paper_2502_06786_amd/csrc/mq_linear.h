@@ -366,4 +366,28 @@ FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr);
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part,
                            float *rs_part, hipStream_t st, int64_t *blocks);
 
+// ============================================================================================
+// backward dX (mq_linear_dx.hip)
+// ============================================================================================
+struct DxArgs {
+    const uint16_t *As[3];  // [M, N] bf16, slot order (the r = 8 slot first when HAS8)
+    const uint8_t *QT;      // [K, N] u8
+    const float *cvec;      // [nsplit][M]: partial sums of c[m] over column ranges
+    int nsplit;
+    uint16_t *dX;           // [M, K] bf16
+    int M, N, K;
+    int r[3];               // bit-width per slot
+    int tiles_m, tiles_k;
+    int splits;             // ranges of n per tile
+    float *part;            // splits > 1: fp32 accumulators, [split][tile][k block][token block][g][256] quads
+};
+
+// How dX cuts its work; splits == 1: no partial sums.
+struct DxPlan {
+    int mb, splits;     // 32-token blocks per workgroup, ranges of n
+    size_t part_bytes;  // fp32 accumulators of all ranges
+};
+DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr);
+mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st);
+
 }  // namespace mq

@@ -1,0 +1,472 @@
+// dX of the straight-through backward, on the bf16 matrix cores: the tiled kernel, and the same kernel with the contraction
+// cut into ranges for the sizes whose tiles leave compute units idle.
+#include <algorithm>
+
+#include "mq_linear.h"
+
+namespace mq {
+
+// ============================================================================================
+// backward dX: dX[m, k] = sum_i sum_n As_i[m, n] * V_i[n, k] - c[m], V_i = the bf16 operand of slot i
+// Rows of the matrix-core product are k (from the transposed codes QT[K, N]), columns are tokens,
+// the contraction runs over n and, within each n tile, over the bit-widths.
+// ============================================================================================
+constexpr int DX_MB = 5;                        // most 32-token blocks per wave
+constexpr int DX_RB = 2;                        // 32-row blocks of k per wave
+constexpr int DX_BK = 4 * 32 * DX_RB;           // k rows per workgroup (4 waves)
+constexpr int DX_Q_TILE = DX_BK * 64;
+constexpr int DX_OS = DX_BK * 2 + 8;            // row stride of the output staging tile
+constexpr int dx_lds(int mb) {                  // four stages; the staging tile of the epilogue is smaller
+    return 4 * (mb * 4096 + DX_Q_TILE);
+}
+static_assert(dx_lds(DX_MB) >= 32 * DX_MB * DX_OS && dx_lds(1) >= 32 * DX_OS, "the staging tile has to fit");
+
+// Same pipeline as the forward kernel (one wave per SIMD, four LDS stages, one small fenced group
+// of operand work per MFMA), with the roles changed: a stage is one 64-wide tile of n for ONE
+// bit-width, i.e. the gradient operand As_slot[tokens, n tile] and the transposed codes
+// QT[k rows, n tile]; the NRS bit-widths of an n tile follow each other and all accumulate into the
+// same accumulators.  Wave w owns k rows [64 w, 64 w + 64) for all 32 MB tokens of the tile.  The
+// stage loop is unrolled over the bit-widths so that the kind of code conversion is a compile-time
+// property of each copy of the stage body.
+//
+// a.splits > 1: workgroup (range, tile) contracts one range of n tiles and leaves its fp32 accumulators in a.part in the
+// order its lanes hold them (each store a whole 1 KB per wave); dx_finish_kernel adds the ranges.
+template <int NRS, bool HAS8, bool EP, int MB>
+__global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    constexpr int RB = DX_RB;
+    constexpr int BM = 32 * MB;
+    constexpr int A_TILE = BM * 128;
+    constexpr int STAGE = A_TILE + DX_Q_TILE;
+    constexpr int QL = DX_BK / 64;       // direct-to-LDS loads per wave and stage for the codes (16 rows each)
+    constexpr int LPS = MB + QL;         // loads per wave and stage
+    constexpr int NM = RB * MB;          // MFMAs per 16-wide step
+    constexpr int CQ = 4 * RB + 1 <= NM ? 1 : 0;             // first MFMA of a step that carries a conversion
+    constexpr int PPG = (4 * RB + NM - CQ - 1) / (NM - CQ);  // conversions per MFMA (1 from MB = 5 on)
+    constexpr int LPG = (LPS + NM - 1) / NM;                 // global loads per MFMA of step 0
+    constexpr int RPG = (2 * RB + NM - 1) / NM;              // code reads per MFMA of step 2
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, l32 = lane & 31;
+
+    const int tiles = a.tiles_m * a.tiles_k;
+    const uint32_t wid = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const int split = (int)wid / tiles;
+    const uint32_t lid = wid % (uint32_t)tiles;
+    const int nnt_all = (a.N + BKT - 1) / BKT;
+    const int nt0 = (int)((int64_t)nnt_all * split / a.splits), nt1 = (int)((int64_t)nnt_all * (split + 1) / a.splits);
+    const int n_end = min(a.N, nt1 * BKT);
+    constexpr int GROUP = 4;
+    const int width = GROUP * a.tiles_k;
+    const int first_m = (int)(lid / width) * GROUP;
+    const int gsz = min(a.tiles_m - first_m, GROUP);
+    const int tm = first_m + (int)(lid % width) % gsz;
+    const int tk = (int)(lid % width) / gsz;
+    const int m0 = tm * BM, k0 = tk * DX_BK;
+
+    __amdgpu_buffer_rsrc_t rA[NRS];
+#pragma unroll
+    for (int i = 0; i < NRS; ++i) rA[i] = make_rsrc(a.As[i] + (size_t)m0 * a.N, (uint64_t)(a.M - m0) * a.N * 2);
+    const __amdgpu_buffer_rsrc_t rQ = make_rsrc(a.QT + (size_t)k0 * a.N, (uint64_t)(a.K - k0) * a.N);
+
+    uint32_t aoff0, qoff0;
+    int acol, qcol;
+    bf16_tile_lane<4>(wave, lane, 0, (uint32_t)a.N * 2u, aoff0, acol);
+    u8_tile_lane<4>(wave, lane, 0, (uint32_t)a.N, qoff0, qcol);
+    const uint32_t astep = 32u * (uint32_t)a.N * 2u, qstep = 64u * (uint32_t)a.N;
+
+    // load i of stage (n tile nt, bit-width slot) into LDS buffer `buf`; out-of-range requests
+    // (a tile past the range) are answered with zeros, so the loads in flight are the same every stage
+    auto issue_one = [&](int nt, auto slot_tag, int buf, int i) {
+        constexpr int SLOT = decltype(slot_tag)::value;
+        const int n0 = nt * BKT;
+        uint8_t *as = smem + buf * STAGE;
+        if (i < MB) {
+            const uint32_t ab = (n0 + acol < n_end) ? aoff0 + (uint32_t)n0 * 2u : kOOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA[SLOT], (lds_ptr)(as + (wave + i * 4) * 1024), 16,
+                                                     ab + (uint32_t)i * astep, 0, 0, 0);
+        } else {
+            // The code bytes of an n tile are fetched with its first bit-width only: the other bit-widths
+            // of the tile slice the same bytes, which the lanes then still hold in registers.  Their
+            // requests go out of range (no traffic) so that every stage has the same number of loads.
+            const uint32_t qb = (SLOT == 0 && n0 + qcol < n_end) ? qoff0 + (uint32_t)n0 : kOOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rQ, (lds_ptr)(as + A_TILE + (wave + (i - MB) * 4) * 1024), 16,
+                                                     qb + (uint32_t)(i - MB) * qstep, 0, 0, 0);
+        }
+    };
+
+    // LDS fragment addresses (byte offsets inside a stage)
+    uint32_t qa[RB][2];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int kl = wave * (32 * RB) + rb * 32 + l32;
+        qa[rb][0] = A_TILE + kl * 64 + ((h ^ ((kl >> 2) & 3)) << 4);
+        qa[rb][1] = A_TILE + kl * 64 + (((h + 2) ^ ((kl >> 2) & 3)) << 4);
+    }
+    uint32_t xa[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int cx = 2 * h + 4 * (t >> 1) + (t & 1);
+        xa[t] = l32 * 128 + ((cx ^ ((l32 >> 1) & 7)) << 4);
+    }
+
+    SliceParam sp[NRS];
+#pragma unroll
+    for (int i = 0; i < NRS; ++i) sp[i] = slice_param<EP>(a.r[i]);
+
+    // dword w (two consecutive n) of the code operand of bit-width SLOT from 8 code bytes (d0, d1)
+    auto convert_piece = [&](auto slot_tag, int w, uint32_t d0, uint32_t d1) -> uint32_t {
+        constexpr int SLOT = decltype(slot_tag)::value;
+        const uint32_t d = w < 2 ? d0 : d1;
+        if constexpr (HAS8 && SLOT == 0) {
+            const float lo = (w & 1) ? (float)((d >> 16) & 0xFFu) : (float)(d & 0xFFu);
+            const float hi = (w & 1) ? (float)(d >> 24) : (float)((d >> 8) & 0xFFu);
+            return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+        } else if constexpr (EP) {
+            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x0C030C02u : 0x0C010C00u);
+            return (((placed + sp[SLOT].half2) >> sp[SLOT].sh) & 0x00FF00FFu) | kMagic128;
+        } else {
+            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x030C020Cu : 0x010C000Cu);
+            u16x2 t = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, placed),
+                                                    __builtin_bit_cast(u16x2, sp[SLOT].half2));
+            const unsigned short s16 = (unsigned short)sp[SLOT].sh;
+            t = t >> u16x2{s16, s16};
+            return __builtin_bit_cast(uint32_t, t) | kMagic128;
+        }
+    };
+
+    f32x16 acc[RB][MB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[rb][j][v] = 0.f;
+
+    // prologue: stages 0, 1, 2 (n tile nt0 + st / NRS, bit-width st % NRS)
+    {
+        auto issue_stage = [&](auto st_tag) {
+            constexpr int ST = decltype(st_tag)::value;
+#pragma unroll
+            for (int i = 0; i < LPS; ++i) issue_one(nt0 + ST / NRS, std::integral_constant<int, ST % NRS>{}, ST & 3, i);
+        };
+        issue_stage(std::integral_constant<int, 0>{});
+        issue_stage(std::integral_constant<int, 1>{});
+        issue_stage(std::integral_constant<int, 2>{});
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPS) : "memory");
+    __syncthreads();
+
+    u32x4 xf[MB];         // gradient operands of the current step
+    u32x4 raw[RB][2];     // 32 code bytes per k row of this lane: four steps of one stage
+    u32x4 wf[RB];         // code operands of the current step
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        raw[rb][0] = *reinterpret_cast<const u32x4 *>(smem + qa[rb][0]);
+        raw[rb][1] = *reinterpret_cast<const u32x4 *>(smem + qa[rb][1]);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) wf[rb][w] = convert_piece(std::integral_constant<int, 0>{}, w, raw[rb][0][0], raw[rb][0][1]);
+    }
+#pragma unroll
+    for (int j = 0; j < MB; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + j * 4096);
+
+    // One stage: four 16-wide steps.  st = index of this stage, nt3 / the slot of stage st + 3 are
+    // what the loads issued in step 0 fetch.
+    auto tile = [&](auto slot_tag, auto more_tag, int st, int nt) {
+        constexpr int SLOT = decltype(slot_tag)::value;
+        constexpr bool MORE = decltype(more_tag)::value;
+        constexpr int NEXT = (SLOT + 1) % NRS;
+        const uint8_t *cur = smem + (st & 3) * STAGE;
+        const uint8_t *nxt = smem + ((st + 1) & 3) * STAGE;
+        u32x4 rawn[RB][2];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bool pre = t < 3 || MORE;
+            const uint8_t *src = t < 3 ? cur + xa[(t + 1) & 3] : nxt + xa[0];
+            uint32_t d0[RB], d1[RB];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                d0[rb] = t == 3 ? rawn[rb][0][0] : (t + 1 < 2 ? raw[rb][0][2 * (t + 1)] : raw[rb][1][2 * (t + 1 - 2)]);
+                d1[rb] = t == 3 ? rawn[rb][0][1] : (t + 1 < 2 ? raw[rb][0][2 * (t + 1) + 1] : raw[rb][1][2 * (t + 1 - 2) + 1]);
+                if (pre) asm volatile("" : "+v"(d0[rb]), "+v"(d1[rb]));  // pins the conversions to this step
+            }
+            u32x4 xfn[MB];
+            u32x4 wfn[RB];
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+                const int j = q / RB, rb = q % RB;
+                acc[rb][j] = mfma32(wf[rb], xf[j], acc[rb][j]);
+                if (pre && q < MB) xfn[q] = *reinterpret_cast<const u32x4 *>(src + q * 4096);
+                if (pre && q >= CQ) {
+#pragma unroll
+                    for (int u = 0; u < PPG; ++u) {
+                        const int pc = (q - CQ) * PPG + u, prb = pc / 4, pw = pc % 4;
+                        if (pc < 4 * RB) {
+                            uint32_t piece = t < 3 ? convert_piece(std::integral_constant<int, SLOT>{}, pw, d0[prb], d1[prb])
+                                                   : convert_piece(std::integral_constant<int, NEXT>{}, pw, d0[prb], d1[prb]);
+                            asm volatile("" : "+v"(piece));  // keeps the conversion inside this group
+                            wfn[prb][pw] = piece;
+                        }
+                    }
+                }
+                if (MORE && t == 2) {
+#pragma unroll
+                    for (int u = 0; u < RPG; ++u) {
+                        const int e = (q - NM) * RPG + RPG * ((2 * RB + RPG - 1) / RPG) + u;  // the last groups carry the reads
+                        if (e >= 0 && e < 2 * RB) {
+                            if constexpr (NEXT == 0)  // a new n tile: its code bytes
+                                rawn[e / 2][e % 2] = *reinterpret_cast<const u32x4 *>(nxt + qa[e / 2][e % 2]);
+                            else                      // the next bit-width of this n tile: the bytes at hand
+                                rawn[e / 2][e % 2] = raw[e / 2][e % 2];
+                        }
+                    }
+                }
+                if (MORE && t == 0) {
+#pragma unroll
+                    for (int u = 0; u < LPG; ++u) {
+                        const int ld = (NM - 1 - q) * LPG + u;
+                        if (ld < LPS) issue_one(nt + (SLOT + 3) / NRS, std::integral_constant<int, (SLOT + 3) % NRS>{}, (st + 3) & 3, ld);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (pre) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) wf[rb] = wfn[rb];
+#pragma unroll
+                for (int j = 0; j < MB; ++j) xf[j] = xfn[j];
+            }
+        }
+        if (MORE) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                raw[rb][0] = rawn[rb][0];
+                raw[rb][1] = rawn[rb][1];
+            }
+        }
+    };
+    auto stage = [&](auto slot_tag, auto more_tag, int st, int nt) {
+        // stage st + 1 must be resident (operand prefetch at the end of this stage); the loads of
+        // stage st + 2 may stay in flight; after the barrier the buffer of stage st - 1 is free
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
+        __syncthreads();
+        tile(slot_tag, more_tag, st, nt);
+    };
+
+    int st = 0;
+    for (int nt = nt0; nt + 1 < nt1; ++nt) {
+        stage(std::integral_constant<int, 0>{}, std::true_type{}, st++, nt);
+        if constexpr (NRS > 1) stage(std::integral_constant<int, 1>{}, std::true_type{}, st++, nt);
+        if constexpr (NRS > 2) stage(std::integral_constant<int, 2>{}, std::true_type{}, st++, nt);
+    }
+    {
+        const int nt = nt1 - 1;
+        if constexpr (NRS == 1) {
+            stage(std::integral_constant<int, 0>{}, std::false_type{}, st++, nt);
+        } else if constexpr (NRS == 2) {
+            stage(std::integral_constant<int, 0>{}, std::true_type{}, st++, nt);
+            stage(std::integral_constant<int, 1>{}, std::false_type{}, st++, nt);
+        } else {
+            stage(std::integral_constant<int, 0>{}, std::true_type{}, st++, nt);
+            stage(std::integral_constant<int, 1>{}, std::true_type{}, st++, nt);
+            stage(std::integral_constant<int, 2>{}, std::false_type{}, st++, nt);
+        }
+    }
+    wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
+
+    if (a.splits > 1) {
+        f32x4 *dst = reinterpret_cast<f32x4 *>(a.part) + ((size_t)split * tiles + lid) * (RB * MB * 4 * 256) + threadIdx.x;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    dst[((rb * MB + j) * 4 + g) * 256] =
+                        f32x4{acc[rb][j][4 * g], acc[rb][j][4 * g + 1], acc[rb][j][4 * g + 2], acc[rb][j][4 * g + 3]};
+        return;
+    }
+
+    // ---- epilogue: rows of the product are k, columns tokens; dX = acc - c[m] --------------------
+    // assembled in LDS as [token][k] bf16 (rows padded by 8 bytes) and stored as whole 512-byte rows
+    __syncthreads();
+    // c[m] = sum over the column ranges of the prep kernel, in their order.  The partial sums of all the
+    // lane's tokens are requested four ranges at a time (20 loads in flight: one memory round trip per
+    // group instead of one per value, which with nothing else to run cost more than the stores).
+    float cs[MB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) cs[j] = 0.f;
+    for (int sp0 = 0; sp0 < a.nsplit; sp0 += 4) {
+        float part[4][MB];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < MB; ++j) {
+                const int m = m0 + j * 32 + l32;
+                part[u][j] = (sp0 + u < a.nsplit && m < a.M) ? a.cvec[(size_t)(sp0 + u) * a.M + m] : 0.f;
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < MB; ++j) cs[j] += part[u][j];
+    }
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+        const float c = cs[j];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int kloc = wave * (32 * RB) + rb * 32 + 8 * g + 4 * h;
+                const u32x2 o = {pack_bf16x2(acc[rb][j][4 * g] - c, acc[rb][j][4 * g + 1] - c),
+                                 pack_bf16x2(acc[rb][j][4 * g + 2] - c, acc[rb][j][4 * g + 3] - c)};
+                *reinterpret_cast<u32x2 *>(smem + (j * 32 + l32) * DX_OS + kloc * 2) = o;
+            }
+    }
+    __syncthreads();
+    constexpr int CPR = DX_BK / 8;  // 16-byte chunks per row
+#pragma unroll
+    for (int it = 0; it < BM * CPR / 256; ++it) {
+        const int c = it * 256 + threadIdx.x;
+        const int row = c / CPR, ch = c % CPR;
+        const int m = m0 + row, k = k0 + ch * 8;
+        if (m < a.M && k < a.K) {
+            const uint8_t *src = smem + row * DX_OS + ch * 16;
+            const u32x2 lo = *reinterpret_cast<const u32x2 *>(src);
+            const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + 8);
+            __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y},
+                                        reinterpret_cast<u32x4 *>(a.dX + (size_t)m * a.K + k));
+        }
+    }
+#else
+    (void)a;
+#endif
+}
+
+// Adds the ranges of the contraction in their order and finishes dX.  Workgroup = (tile, token block, 32-row block of k of
+// one wave): its wave g takes accumulator rows 8 g + 4 h .. + 3, so the four waves write 64 contiguous bytes of 32 tokens.
+__global__ __launch_bounds__(256) void dx_finish_kernel(DxArgs a, int mb) {
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int h = lane >> 5, l32 = lane & 31;
+    const int w = blockIdx.x & 3, rb = (blockIdx.x >> 2) % DX_RB, rest = (int)(blockIdx.x >> 2) / DX_RB;
+    const int j = rest % mb, tile = rest / mb;
+    const int tiles = a.tiles_m * a.tiles_k;
+    constexpr int GROUP = 4;   // tile order of dx_kernel
+    const int width = GROUP * a.tiles_k;
+    const int first_m = tile / width * GROUP;
+    const int gsz = min(a.tiles_m - first_m, GROUP);
+    const int tm = first_m + tile % width % gsz, tk = tile % width / gsz;
+    const int m = tm * 32 * mb + j * 32 + l32, k = tk * DX_BK + w * 32 * DX_RB + rb * 32 + 8 * g + 4 * h;
+    if (m >= a.M || k >= a.K) return;
+
+    const size_t step = (size_t)tiles * DX_RB * mb * 1024;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(a.part) + (((size_t)tile * DX_RB * mb + rb * mb + j) * 4 + g) * 256 + w * 64 + lane;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < a.splits; p0 += 4) {  // the loads of four ranges are in flight together
+        f32x4 v[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            v[p] = p0 + p < a.splits ? __builtin_nontemporal_load(src + (p0 + p) * step) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) sum += v[p];
+    }
+    float c = 0.f;
+    for (int s0 = 0; s0 < a.nsplit; s0 += 4) {
+        float v[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) v[p] = s0 + p < a.nsplit ? a.cvec[(size_t)(s0 + p) * a.M + m] : 0.f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) c += v[p];
+    }
+    *reinterpret_cast<u32x2 *>(a.dX + (size_t)m * a.K + k) = u32x2{pack_bf16x2(sum[0] - c, sum[1] - c), pack_bf16x2(sum[2] - c, sum[3] - c)};
+}
+
+// ---- host side ------------------------------------------------------------------------------------
+namespace {
+
+template <int NRS, bool HAS8, bool EP, int MB>
+mq_status launch_dx_mb(const DxArgs &d, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(dx_kernel<NRS, HAS8, EP, MB>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, dx_lds(MB));
+    if (attr != hipSuccess) return MQ_ERR_DEVICE;
+    dx_kernel<NRS, HAS8, EP, MB><<<dim3(d.tiles_m * d.tiles_k * d.splits), dim3(256), dx_lds(MB), st>>>(d);
+    return launch_status();
+}
+
+template <int NRS, bool HAS8, bool EP>
+mq_status launch_dx_one(const DxArgs &d, int mb, hipStream_t st) {
+    switch (mb) {
+        case 1: return launch_dx_mb<NRS, HAS8, EP, 1>(d, st);
+        case 2: return launch_dx_mb<NRS, HAS8, EP, 2>(d, st);
+        case 3: return launch_dx_mb<NRS, HAS8, EP, 3>(d, st);
+        case 4: return launch_dx_mb<NRS, HAS8, EP, 4>(d, st);
+        default: return launch_dx_mb<NRS, HAS8, EP, 5>(d, st);
+    }
+}
+
+template <int NRS>
+mq_status launch_dx_nrs(const DxArgs &d, int mb, bool has8, bool ep, hipStream_t st) {
+    if constexpr (NRS == 1) ep = ep && !has8;  // the code of r = 8 is never rounded up past the byte
+    if (has8) {
+        if constexpr (NRS > 1)
+            if (ep) return launch_dx_one<NRS, true, true>(d, mb, st);
+        return launch_dx_one<NRS, true, false>(d, mb, st);
+    }
+    return ep ? launch_dx_one<NRS, false, true>(d, mb, st) : launch_dx_one<NRS, false, false>(d, mb, st);
+}
+
+}  // namespace
+
+// Tile height and ranges: the least modelled time (cycles) over one to five token blocks per workgroup and up to 16 ranges of
+// n.  160 tokens x 256 k tiles alone leave most compute units idle up to about 2000 tokens (16 tokens through 9216 x 2304 are
+// nine workgroups that walk 432 stages each: 263 us), and a full partial round of low tiles often beats the same round of
+// high ones.  A stage (one n tile, one bit-width) takes 256 cycles per token block for its products and 520 for conversions
+// and the barrier, for each of the workgroups that a compute unit holds (two where the stages of 32 tokens fit twice into its
+// LDS), but never less than the 1055 + 140 per token block it takes to arrive; all workgroups together do not get gradients
+// faster than 3650 or codes faster than 6480 bytes per cycle; a tile's epilogue costs 900 per token block, the finishing
+// launch 4100 and 310 per range, and 1940 bytes of accumulators go out and come back per cycle.  The constants are a fit to
+// 3100 timed combinations (8 layers of 256 x 256 to 14336 x 4096, 16 to 4096 tokens, one and three bit-widths): the choice
+// is 0.4 % slower than the best of them on average, 9 % at worst.  dX with its preparation, 160-token tiles -> chosen, at
+// r = 8/4/2: 9216 x 2304, 16 tokens 263 -> 54 us, 400 tokens 342 -> 96 us, 2000 tokens 371 -> 274 us; 3600 x 3600, 400
+// tokens 160 -> 73 us, 4096 tokens 388 -> 354 us; 256 x 256, 16 tokens 15.6 (32-token tile) -> 13.9 us; the same at
+// 4096 tokens through 9216 x 2304 (499 us).
+DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
+    DxPlan best{DX_MB, 1, 0};
+    double best_cost = 0;
+    const int64_t tiles_k = cdiv(K, DX_BK), nnt = cdiv(N, BKT);
+    for (int mb = DX_MB; mb >= 1; --mb) {
+        const int64_t tiles = cdiv(M, 32 * mb) * tiles_k;
+        if (mb > 1 && cdiv(M, 32 * mb) == cdiv(M, 32 * (mb - 1))) continue;  // a lower tile covers as much
+        const int resident = 2 * dx_lds(mb) <= 163840 ? 2 : 1;
+        const double busy = mb * 256.0 + 520.0, arrive = mb * 140.0 + 1055.0;
+        for (int splits = 1; splits <= std::min<int64_t>(16, nnt); ++splits) {
+            const size_t part = splits > 1 ? (size_t)splits * tiles * mb * DX_RB * 16384 : 0;
+            if (splits > 1 && (part > ((size_t)96 << 20) || tiles * splits > 1100)) break;
+            const int64_t per_cu = cdiv(tiles * splits, 256), full = per_cu / resident, rest = per_cu % resident;
+            const int64_t n_stages = cdiv(nnt, splits), stages = n_stages * nr;
+            double cost = full * std::max(resident * busy, arrive) + (rest ? std::max(rest * busy, arrive) : 0.0);
+            cost = cost * stages + per_cu * mb * 900.0;
+            cost = std::max(cost, (double)tiles * splits * (stages * mb * (4096.0 / 3650.0) + n_stages * (16384.0 / 6480.0)));
+            if (splits > 1) cost += 4100.0 + 310.0 * splits + part / 1940.0;
+            if (best_cost == 0 || cost < best_cost) {
+                best_cost = cost;
+                best = DxPlan{mb, splits, part};
+            }
+        }
+    }
+    return best;
+}
+
+mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st) {
+    d.tiles_m = (int)cdiv(d.M, 32 * plan.mb);
+    d.tiles_k = (int)cdiv(d.K, DX_BK);
+    d.splits = plan.splits;
+    const mq_status s = nr == 1 ? launch_dx_nrs<1>(d, plan.mb, has8, ep, st) : nr == 2 ? launch_dx_nrs<2>(d, plan.mb, has8, ep, st)
+                                                                                        : launch_dx_nrs<3>(d, plan.mb, has8, ep, st);
+    if (s != MQ_OK || plan.splits == 1) return s;
+    dx_finish_kernel<<<dim3((unsigned)(d.tiles_m * d.tiles_k * plan.mb * DX_RB * 4)), dim3(256), 0, st>>>(d, plan.mb);
+    return launch_status();
+}
+
+}  // namespace mq
