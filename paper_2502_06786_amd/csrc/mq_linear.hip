@@ -370,6 +370,13 @@ struct PrepArgs {
     int nr, M, N;
     int ldm;             // M rounded up to a multiple of 8
     int cols_per_split;  // multiple of 64
+    int strips, nsplit;  // token strips, column ranges
+    // the transposed copies that the same launch makes (null: not wanted): the codes for dX, the input for dW
+    const uint8_t *Q;
+    uint8_t *QT;         // [K, N]
+    const uint16_t *X;
+    uint16_t *XT;        // [M / 32][K][32]; tokens M .. ldm - 1 are zeros
+    int K;
 };
 
 constexpr int PREP_ROWS = 32;
@@ -380,11 +387,10 @@ constexpr int PREP_MAX_SPLIT = 16;
 // line per gradient tensor.  The summed gradient tile is turned through LDS and leaves as 64-byte
 // row segments of GT.
 template <bool GATED>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
-    __shared__ uint16_t tile[64][PREP_ROWS + 2];
+__device__ __forceinline__ void prep_gradients(const PrepArgs &a, int strip, int split, uint16_t (*tile)[PREP_ROWS + 2]) {
     const int t = threadIdx.x, r = t >> 3, ch = t & 7;
-    const int m0 = blockIdx.x * PREP_ROWS, m = m0 + r;
-    const int nbeg = blockIdx.y * a.cols_per_split, nend = min(nbeg + a.cols_per_split, a.N);
+    const int m0 = strip * PREP_ROWS, m = m0 + r;
+    const int nbeg = split * a.cols_per_split, nend = min(nbeg + a.cols_per_split, a.N);
     const bool want_as = a.As[0] != nullptr;
     float c = 0.f;
     for (int n0 = nbeg; n0 < nend; n0 += 64) {
@@ -443,7 +449,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
             const int nn = t >> 2, part = t & 3;  // 64 rows of GT, four 16-byte pieces each
             if (n0 + nn < a.N && m0 + part * 8 < a.M) {  // (a piece that straddles M ends with zeros)
                 const uint32_t *src = reinterpret_cast<const uint32_t *>(&tile[nn][part * 8]);
-                *reinterpret_cast<u32x4 *>(a.GT + ((size_t)blockIdx.x * a.N + n0 + nn) * 32 + part * 8) =
+                *reinterpret_cast<u32x4 *>(a.GT + ((size_t)strip * a.N + n0 + nn) * 32 + part * 8) =
                     u32x4{src[0], src[1], src[2], src[3]};
             }
         }
@@ -452,47 +458,106 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
         c += __shfl_xor(c, 1, 64);
         c += __shfl_xor(c, 2, 64);
         c += __shfl_xor(c, 4, 64);
-        if (ch == 0 && m < a.M) a.cpart[(size_t)blockIdx.y * a.M + m] = c;
+        if (ch == 0 && m < a.M) a.cpart[(size_t)split * a.M + m] = c;
     }
 }
 
-// out[c, r] = in[r, c] for a [rows, cols] matrix of 1- or 2-byte elements; cols is a multiple of 16
-// bytes' worth of elements, the rows of out are ld_out elements apart (rows rounded up to such a
-// multiple) and end with zeros.  64 x (64 bytes) tiles, 16-byte global accesses on both sides, the
-// turn happens in LDS.
-// BLOCKED (2-byte elements): out is [rows / 32][cols][32] instead, i.e. element (c, r) sits at ((r / 32) cols + c) 32 + r % 32
-// (the operand layout of dw_kernel).
-template <typename T, bool BLOCKED = false>
-__global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ in, T *__restrict__ out, int rows,
-                                                        int cols, int ld_out) {
-    constexpr int E = 16 / sizeof(T);  // elements per 16 bytes
-    constexpr int TC = 4 * E;          // tile columns (64 bytes)
-    constexpr int S = 64 + 4 / sizeof(T);  // padded row of the turned tile (a multiple of 4 bytes)
-    __shared__ T tile[TC][S];
-    const int t = threadIdx.x;
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * TC;
+// Transposed copies.  Whole 128-byte lines are read, 16 bytes per lane; the elements of neighbouring rows are first put side
+// by side in registers, so that the LDS tile is written in dwords (a byte or a 16-bit value at a time, the LDS writes were
+// what took the time), and leave as 16-byte pieces.
+
+// 128 x 128 codes: QT[k][n] = Q[n][k].  Thread (g, ch) turns rows 4 g .. 4 g + 3, columns 16 ch .. 16 ch + 15.  The tile holds
+// 128 rows of 128 bytes, 144 bytes apart; the 16-byte pieces of row c are at positions piece ^ (c / 16), which spreads a wave's
+// dword writes over the banks.
+constexpr int QT_STRIDE = 36;  // dwords
+__device__ __forceinline__ void transpose_codes(const PrepArgs &a, int tn, int tk, uint32_t *tile) {
+    const int t = threadIdx.x, n0 = tn * 128, k0 = tk * 128;
     {
-        const int r = t >> 2, chunk = t & 3;
-        if (c0 + chunk * E < cols) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (r0 + r < rows) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(in + (size_t)(r0 + r) * cols + c0 + chunk * E));
-            T e[E];
-            __builtin_memcpy(e, &v, 16);
+        const int g = t >> 3, ch = t & 7;
+        u32x4 v[4];
 #pragma unroll
-            for (int j = 0; j < E; ++j) tile[chunk * E + j][r] = e[j];
+        for (int i = 0; i < 4; ++i) {
+            const int n = n0 + 4 * g + i, k = k0 + 16 * ch;  // (N, K are multiples of 16)
+            v[i] = n < a.N && k < a.K ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.Q + (size_t)n * a.K + k)) : u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            // bytes of four rows -> dwords of four columns
+            const uint32_t lo01 = __builtin_amdgcn_perm(v[1][w], v[0][w], 0x05010400u), hi01 = __builtin_amdgcn_perm(v[1][w], v[0][w], 0x07030602u);
+            const uint32_t lo23 = __builtin_amdgcn_perm(v[3][w], v[2][w], 0x05010400u), hi23 = __builtin_amdgcn_perm(v[3][w], v[2][w], 0x07030602u);
+            const uint32_t col[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                                     __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                tile[(16 * ch + 4 * w + j) * QT_STRIDE + (((g >> 2) ^ ch) << 2) + (g & 3)] = col[j];
         }
     }
     __syncthreads();
+    const int piece = t & 7;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = (t >> 3) + 32 * i, k = k0 + c, n = n0 + 16 * piece;
+        if (k < a.K && n < a.N)
+            *reinterpret_cast<u32x4 *>(a.QT + (size_t)k * a.N + n) =
+                *reinterpret_cast<const u32x4 *>(tile + c * QT_STRIDE + ((piece ^ (c >> 4)) << 2));
+    }
+}
+
+// 64 tokens x 64 columns of X into the token blocks of dw_kernel's operand: element (m, k) goes to
+// ((m / 32) K + k) 32 + m % 32.  Thread (g, ch) turns tokens 2 g, 2 g + 1 of columns 8 ch .. 8 ch + 7.  A column of a token
+// block is 16 dwords, 20 apart, with 8 more after every eight columns: a wave's dword writes touch every bank once.
+__device__ __forceinline__ int xt_at(int block, int col) { return block * (8 * 168) + (col >> 3) * 168 + (col & 7) * 20; }
+constexpr int XT_TILE = 2 * 8 * 168;  // dwords
+__device__ __forceinline__ void transpose_input(const PrepArgs &a, int tm, int tk, uint32_t *tile) {
+    const int t = threadIdx.x, m0 = tm * 64, k0 = tk * 64;
     {
-        constexpr int PIECES = 64 / E;  // 16-byte pieces per row of the turned tile
-        const int c = t / PIECES, piece = t % PIECES;
-        if (c < TC && c0 + c < cols && r0 + piece * E < rows) {
-            const uint32_t *src = reinterpret_cast<const uint32_t *>(&tile[c][piece * E]);
-            const int r = r0 + piece * E;
-            const size_t at = BLOCKED ? ((size_t)(r >> 5) * cols + c0 + c) * 32 + (r & 31) : (size_t)(c0 + c) * ld_out + r;
-            *reinterpret_cast<u32x4 *>(out + at) = u32x4{src[0], src[1], src[2], src[3]};
+        const int g = t >> 3, ch = t & 7;
+        u32x4 v[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int m = m0 + 2 * g + i, k = k0 + 8 * ch;
+            v[i] = m < a.M && k < a.K ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.X + (size_t)m * a.K + k)) : u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            tile[xt_at(g >> 4, 8 * ch + 2 * w) + (g & 15)] = __builtin_amdgcn_perm(v[1][w], v[0][w], 0x05040100u);
+            tile[xt_at(g >> 4, 8 * ch + 2 * w + 1) + (g & 15)] = __builtin_amdgcn_perm(v[1][w], v[0][w], 0x07060302u);
         }
     }
+    __syncthreads();
+    const int piece = t & 3, k = k0 + (t >> 2);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int m = m0 + 32 * b + 8 * piece;
+        if (k < a.K && m < a.M)  // (a piece that straddles M ends with zeros)
+            *reinterpret_cast<u32x4 *>(a.XT + ((size_t)(m >> 5) * a.K + k) * 32 + (m & 31)) =
+                *reinterpret_cast<const u32x4 *>(tile + xt_at(b, t >> 2) + 4 * piece);
+    }
+}
+
+// The whole preparation of a backward in one launch: the first strips x nsplit workgroups take the gradients, then come the
+// tiles of Q and of X that have to be turned.  (As three launches in a row, each a few microseconds for a small layer and
+// each with a tail in which most compute units wait: 16 x 256 x 256 10.8 us, 400 x 3600 x 3600 28 us.)
+template <bool GATED>
+__global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
+    __shared__ __attribute__((aligned(16))) uint32_t smem[128 * QT_STRIDE];
+    static_assert(XT_TILE <= 128 * QT_STRIDE && 64 * (PREP_ROWS + 2) * 2 <= 128 * QT_STRIDE * 4, "tiles share the LDS");
+    int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int gradients = a.strips * a.nsplit;
+    if (b < gradients) {
+        prep_gradients<GATED>(a, b % a.strips, b / a.strips, reinterpret_cast<uint16_t(*)[PREP_ROWS + 2]>(smem));
+        return;
+    }
+    b -= gradients;
+    const int qk = (a.K + 127) >> 7, codes = a.QT ? qk * ((a.N + 127) >> 7) : 0;
+    if (b < codes) {
+        transpose_codes(a, b / qk, b % qk, smem);
+        return;
+    }
+    b -= codes;
+    const int xk = (a.K + 63) >> 6, inputs = a.XT ? xk * ((a.M + 63) >> 6) : 0;
+    if (b >= inputs) return;
+    transpose_input(a, b / xk, b % xk, smem);
 }
 
 // ============================================================================================
@@ -798,10 +863,12 @@ static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr) {
     o += align256(m32 * N * 2);
     w.qt = o;
     o += align256((size_t)N * K);
-    // dX is done before dW begins: the partial sums of the one lie where the other keeps its operand and its partial tiles
-    w.xt = w.dxp = o;
-    w.dwp = w.xt + align256(m32 * K * 2);
-    w.total = std::max(w.dwp + align256(dw_plan(M, N, K).part_bytes), w.dxp + align256(dx_plan(M, N, K, nr).part_bytes));
+    w.xt = o;
+    o += align256(m32 * K * 2);
+    // dX is done before dW begins: their partial sums share their place
+    w.dxp = w.dwp = o;
+    o += align256(std::max(dw_plan(M, N, K).part_bytes, dx_plan(M, N, K, nr).part_bytes));
+    w.total = o;
     return w;
 }
 
@@ -1192,16 +1259,23 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.cols_per_split = (int)(cdiv(cdiv(N, nsplit), 64) * 64);
     nsplit = (int)cdiv(N, p.cols_per_split);
     p.silu = (flags & MQ_FLAG_FFN_SILU) ? 1 : 0;
+    p.strips = (int)strips;
+    p.nsplit = nsplit;
+    p.K = (int)K;
+    p.Q = Q;
+    p.QT = dX ? base + lay.qt : nullptr;
+    p.X = X;
+    p.XT = dW ? reinterpret_cast<uint16_t *>(base + lay.xt) : nullptr;
+    const int64_t blocks = strips * nsplit + (dX ? cdiv(N, 128) * cdiv(K, 128) : 0) + (dW ? cdiv(M, 64) * cdiv(K, 64) : 0);
+    if (blocks > 0x7F000000) return MQ_ERR_SHAPE;
+    const int64_t gx = std::min<int64_t>(blocks, 1 << 20);
+    const dim3 grid((unsigned)gx, (unsigned)cdiv(blocks, gx));
     if (gated)
-        bwd_prep_kernel<true><<<dim3((unsigned)strips, (unsigned)nsplit), dim3(256), 0, st>>>(p);
+        bwd_prep_kernel<true><<<grid, dim3(256), 0, st>>>(p);
     else
-        bwd_prep_kernel<false><<<dim3((unsigned)strips, (unsigned)nsplit), dim3(256), 0, st>>>(p);
+        bwd_prep_kernel<false><<<grid, dim3(256), 0, st>>>(p);
 
     if (dX) {
-        uint8_t *QT = base + lay.qt;
-        transpose_kernel<uint8_t><<<dim3((unsigned)cdiv(K, 64), (unsigned)cdiv(N, 64)), dim3(256), 0, st>>>(
-            Q, QT, (int)N, (int)K, (int)N);
-
         // slot order of the kernel: the r = 8 bit-width (if any) first
         DxArgs d;
         int order[3] = {0, 0, 0}, has8 = 0, pos = 0;
@@ -1217,7 +1291,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
             d.As[i] = p.As[j];
             d.r[i] = rs[j];
         }
-        d.QT = QT;
+        d.QT = p.QT;
         d.cvec = p.cpart;
         d.nsplit = nsplit;
         d.dX = dX;
@@ -1229,12 +1303,9 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         if (ds != MQ_OK) return ds;
     }
     if (dW) {
-        uint16_t *XT = reinterpret_cast<uint16_t *>(base + lay.xt);
-        transpose_kernel<uint16_t, true><<<dim3((unsigned)cdiv(K, 32), (unsigned)cdiv(M, 64)), dim3(256), 0, st>>>(
-            X, XT, (int)M, (int)K, p.ldm);
         DwArgs w;
         w.GT = p.GT;
-        w.XT = XT;
+        w.XT = p.XT;
         w.dW = dW;
         w.M = (int)M;
         w.N = (int)N;
