@@ -48,9 +48,13 @@ size_t ffn_workspace_bytes(int64_t B, int64_t F, int64_t d);
 // workspace of mq_matquant_l2_loss (mq_loss.hip)
 size_t loss_workspace_bytes(int64_t M, int64_t N);
 // workspace of mq_linear_bwd_clip (mq_clip.hip)
-size_t clip_workspace_bytes(int64_t M, int64_t N, int64_t K);
+size_t clip_workspace_bytes(int64_t M, int64_t N, int64_t K, int nr);
 // workspace of mq_affine_bwd (mq_affine.hip)
 size_t affine_workspace_bytes(int64_t M, int64_t N, int64_t K);
+// G[i] [N, K] = lambda_i dY_i^T X for nr gradients against one X (mq_linear.hip)
+size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr);
+mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lambda, int64_t M, int64_t N, int64_t K, int nr,
+                  float *G, uint8_t *ws, hipStream_t st);
 // losses[i] = inv_mn * sum over the workgroups of partial[workgroup][i] (rows of 4 floats), in a
 // fixed order; one small launch on `st` (mq_loss.hip)
 mq_status launch_loss_finish(const float *partial, int64_t blocks, int nr, float inv_mn, float *losses,

@@ -371,6 +371,9 @@ struct PrepArgs {
     int ldm;             // M rounded up to a multiple of 8
     int cols_per_split;  // multiple of 64
     int strips, nsplit;  // token strips, column ranges
+    // > 0: no sum; gradient i alone, times lam[i], goes to GT + i * gt_step (As and cpart are null, `each` times as many workgroups)
+    int each;
+    int64_t gt_step;
     // the transposed copies that the same launch makes (null: not wanted): the codes for dX, the input for dW
     const uint8_t *Q;
     uint8_t *QT;         // [K, N]
@@ -544,11 +547,19 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
     static_assert(XT_TILE <= 128 * QT_STRIDE && 64 * (PREP_ROWS + 2) * 2 <= 128 * QT_STRIDE * 4, "tiles share the LDS");
     int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     const int gradients = a.strips * a.nsplit;
-    if (b < gradients) {
+    if (b < gradients * max(a.each, 1)) {
+        if (a.each) {
+            const int i = b / gradients;
+            a.dY[0] = i == 0 ? a.dY[0] : i == 1 ? a.dY[1] : a.dY[2];
+            a.lam[0] = i == 0 ? a.lam[0] : i == 1 ? a.lam[1] : a.lam[2];
+            a.GT += i * a.gt_step;
+            a.nr = 1;
+            b %= gradients;
+        }
         prep_gradients<GATED>(a, b % a.strips, b / a.strips, reinterpret_cast<uint16_t(*)[PREP_ROWS + 2]>(smem));
         return;
     }
-    b -= gradients;
+    b -= gradients * max(a.each, 1);
     const int qk = (a.K + 127) >> 7, codes = a.QT ? qk * ((a.N + 127) >> 7) : 0;
     if (b < codes) {
         transpose_codes(a, b / qk, b % qk, smem);
@@ -578,42 +589,68 @@ struct DwArgs {
     int tiles_n, tiles_k;
     int whole;           // work items [0, whole) are whole tiles; the others are token ranges of the remaining tiles
     int parts;           // token ranges per remaining tile
+    int64_t gt_step;     // several gradients against the same X: tile t belongs to gradient t / (tiles_n tiles_k), whose
+                         // operand is that many times gt_step elements after GT and whose result N K after dW
 };
 
-constexpr int DW_RB = 4;                   // 32-row blocks of n per wave
-constexpr int DW_MB = 4;                   // 32-column blocks of k per wave
-constexpr int DW_BN = 2 * 32 * DW_RB;      // rows of n per workgroup (2 x 2 waves)
-constexpr int DW_BK = 2 * 32 * DW_MB;      // columns of k per workgroup
-constexpr int DW_BM = 32;                  // contraction elements (tokens) per stage: 64-byte rows
-constexpr int DW_A_TILE = DW_BN * 64, DW_B_TILE = DW_BK * 64;
-constexpr int DW_STAGE = DW_A_TILE + DW_B_TILE;
-constexpr int DW_NST = 5;                  // LDS stages
-constexpr int DW_LDS = DW_NST * DW_STAGE;
-constexpr int DW_CUS = 256;                // compute units a round of workgroups fills
+constexpr int DW_BM = 32;                            // contraction elements (tokens) per stage: 64-byte rows
+constexpr int DW_NST = 5;                            // LDS stages
+constexpr int dw_side(int hb) { return 64 * hb; }    // rows of n and columns of k per workgroup: 2 x 2 waves of hb 32-blocks
+constexpr int dw_lds(int hb) { return DW_NST * 2 * dw_side(hb) * 64; }
+constexpr int DW_CUS = 256;                          // compute units a round of workgroups fills
 
-// How the tiles of dW are dealt to workgroups.  Whole rounds of 256 tiles run one tile per workgroup; the tiles of a
-// last partial round (at most half a round) are cut along the tokens into `parts` ranges each, so that the round
-// still occupies every compute unit for 1 / parts of a tile's time; the ranges leave fp32 partial tiles in the
-// workspace and dw_reduce_kernel adds them in a fixed order.
+// How the tiles of dW (of `batch` gradients together) are dealt to workgroups.  Two sizes of tile: 256 x 256 (hb = 4) has the
+// smaller operand traffic per product, 128 x 128 (hb = 2) four times as many tiles, two of which fit a compute unit.  Whole
+// rounds of 256 x 256 tiles run one tile per workgroup; the tiles of a last partial round (at most half a round) are cut
+// along the tokens into `parts` ranges each, so that the round still occupies every compute unit for 1 / parts of a tile's
+// time.  Where the tiles do not fill one round all of them may be cut.  The ranges leave fp32 partial tiles in the workspace
+// and dw_reduce_kernel adds them in a fixed order.
+//
+// The choice is the least modelled time (cycles): a 32-token stage takes 1045 per 256-tile; of 128-tiles, 742 for two on a
+// compute unit, 437 for one; a tile ends in 10700 (2100); a cut costs 1300, 2230 per range and a cycle per 4780 bytes of
+// partial tiles written and read back.  The constants are a fit to 900 timed combinations (10 layers of 256 x 256 to
+// 14336 x 4096, 16 to 8192 tokens); the choice is 0.3 % slower than the best of them on average, 10 % at worst.  dW with its
+// preparation, 256-tiles -> chosen: 256 x 256, 16 tokens 12.5 -> 8.7 us, 4096 tokens 84 -> 24 us; 2000 x 1008, 400 tokens 23
+// -> 14 us; 2304 x 2304, 2000 tokens 60 -> 45 us; 6400 x 1104, 4096 tokens 117 -> 93 us; 2304 x 9216, 1200 tokens 90 -> 80 us,
+// 4096 tokens the same (201 us).
 struct DwPlan {
-    int tiles_n, tiles_k, whole, rest, parts;
+    int hb, tiles_n, tiles_k, whole, rest, parts;
     size_t part_bytes;
 };
-static DwPlan dw_plan(int64_t M, int64_t N, int64_t K) {
-    DwPlan p;
-    p.tiles_n = (int)cdiv(N, DW_BN);
-    p.tiles_k = (int)cdiv(K, DW_BK);
-    const int64_t tiles = (int64_t)p.tiles_n * p.tiles_k;
+static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
+    DwPlan best{};
+    double best_cost = 0;
     const int64_t stages = cdiv(M, DW_BM);
-    int rest = (int)(tiles % DW_CUS);
-    int parts = rest > 0 ? DW_CUS / rest : 1;
-    parts = (int)std::min<int64_t>(parts, std::max<int64_t>(1, stages / 8));   // at least eight stages per range
-    if (tiles < DW_CUS || parts < 2) rest = 0, parts = 1;
-    p.whole = (int)(tiles - rest);
-    p.rest = rest;
-    p.parts = parts;
-    p.part_bytes = (size_t)rest * parts * DW_BN * DW_BK * 4;
-    return p;
+    const int64_t max_parts = std::max<int64_t>(1, stages / 8);  // at least eight stages per range
+    for (int hb = 4; hb >= 2; hb -= 2) {
+        const int side = dw_side(hb);
+        const int64_t tiles_n = cdiv(N, side), tiles_k = cdiv(K, side), tiles = tiles_n * tiles_k * batch;
+        auto rounds = [&](int64_t items, int64_t st) {
+            const int64_t per_cu = cdiv(items, DW_CUS);
+            if (hb == 4) return per_cu * (1045.0 * st + 10700.0);
+            return (per_cu / 2 * 742.0 + per_cu % 2 * 437.0) * st + per_cu * 2100.0;
+        };
+        auto consider = [&](int64_t rest, int64_t parts) {
+            const size_t bytes = (size_t)rest * parts * side * side * 4;
+            double cost = rounds(tiles - rest, stages);
+            if (rest > 0) cost += rounds(rest * parts, cdiv(stages, parts)) + 1300.0 + 2230.0 * parts + 2.0 * bytes / 4780.0;
+            if (best_cost == 0 || cost < best_cost) {
+                best_cost = cost;
+                best = DwPlan{hb, (int)tiles_n, (int)tiles_k, (int)(tiles - rest), (int)rest, (int)parts, bytes};
+            }
+        };
+        const int64_t over = tiles % DW_CUS;
+        if (tiles < DW_CUS) {
+            for (int64_t parts = 2; parts <= std::min<int64_t>(8, max_parts); ++parts)
+                if ((size_t)tiles * parts * side * side * 4 <= ((size_t)96 << 20)) consider(tiles, parts);
+        } else if (hb == 4 && over > 0) {
+            const int64_t parts = std::min<int64_t>(DW_CUS / over, max_parts);
+            if (parts >= 2) consider(over, parts);
+        }
+        // a last partial round of 256-tiles that can be cut is cut: whole tiles there cost a full round
+        if (!(hb == 4 && best.rest > 0 && best.whole > 0)) consider(0, 1);
+    }
+    return best;
 }
 
 // Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, one small fenced group of
@@ -622,10 +659,13 @@ static DwPlan dw_plan(int64_t M, int64_t N, int64_t K) {
 // (all 256 accumulator registers), 8 operand reads per 16 MFMAs - the square wave tile is what keeps the LDS traffic
 // (32 KB read + 16 KB written per 16-token step and compute unit, 94 bytes per clock at the matrix-core rate) under
 // the 128 bytes per clock the LDS delivers.  Stages are 32 tokens deep (64-byte rows); five of them fill the LDS.
+template <int HB>
 __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    constexpr int RB = DW_RB, MB = DW_MB, NM = RB * MB;
+    constexpr int RB = HB, MB = HB, NM = RB * MB;
+    constexpr int DW_BN = dw_side(HB), DW_BK = dw_side(HB);
+    constexpr int DW_A_TILE = DW_BN * 64, DW_STAGE = DW_A_TILE + DW_BK * 64;
     constexpr int AL = DW_BN / 64, BL = DW_BK / 64;  // direct-to-LDS loads per wave and stage (16 rows each)
     constexpr int LPS = AL + BL;
     static_assert(RB + MB <= NM && LPS <= NM, "not enough MFMAs to hide the operand work");
@@ -638,7 +678,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     const int nmt_all = (a.M + DW_BM - 1) / DW_BM;
     uint32_t lid;
     int mt0 = 0, mt1 = nmt_all;
-    float *dst = a.dW;
+    float *dst = nullptr;
     bool to_part = false;
     if ((int)blockIdx.x < a.whole) {
         lid = xcd_contiguous_id(blockIdx.x, (uint32_t)a.whole);
@@ -650,6 +690,11 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         dst = a.part + (size_t)idx * (DW_BN * DW_BK);
         to_part = true;
     }
+    const uint32_t tiles = (uint32_t)(a.tiles_n * a.tiles_k);
+    const uint32_t grad = lid / tiles;
+    lid %= tiles;
+    const uint16_t *GT = a.GT + grad * a.gt_step;
+    if (!to_part) dst = a.dW + (size_t)grad * a.N * a.K;
     constexpr int GROUP = 4;
     const int width = GROUP * a.tiles_k;
     const int first_n = (int)(lid / width) * GROUP;
@@ -672,7 +717,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         uint8_t *base = smem + buf * DW_STAGE;
         const uint32_t o = (mm + colb / 2 < a.M) ? off0 : kOOB;
         if (i < AL) {
-            const __amdgpu_buffer_rsrc_t rG = make_rsrc(a.GT + ((size_t)mt * a.N + n0) * 32, (uint64_t)(a.N - n0) * 64);
+            const __amdgpu_buffer_rsrc_t rG = make_rsrc(GT + ((size_t)mt * a.N + n0) * 32, (uint64_t)(a.N - n0) * 64);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rG, (lds_ptr)(base + (wave + i * 4) * 1024), 16,
                                                      o + (uint32_t)i * rstep, 0, 0, 0);
         } else {
@@ -687,8 +732,8 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const uint32_t chunk = (uint32_t)((2 * t + h) ^ ((l32 >> 2) & 3)) << 4;
-        ab[t] = (uint32_t)(wn * 128 + l32) * 64u + chunk;
-        bb[t] = (uint32_t)DW_A_TILE + (uint32_t)(wk * 128 + l32) * 64u + chunk;
+        ab[t] = (uint32_t)(wn * 32 * RB + l32) * 64u + chunk;
+        bb[t] = (uint32_t)DW_A_TILE + (uint32_t)(wk * 32 * MB + l32) * 64u + chunk;
     }
 
     f32x16 acc[RB][MB];
@@ -773,13 +818,13 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         constexpr bool ACCUMULATE = decltype(accumulate_tag)::value;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int r0 = wn * 128 + rb * 32;                      // first row of the block inside the tile
+            const int r0 = wn * 32 * RB + rb * 32;                      // first row of the block inside the tile
             const int64_t left = ((int64_t)rows - r0) * ld - (to_part ? 0 : k0);  // elements to the end of the destination
             const __amdgpu_buffer_rsrc_t rW = make_rsrc(origin + (int64_t)r0 * ld, left > 0 ? (uint64_t)left * 4u : 0u);
             uint32_t voff[MB];
 #pragma unroll
             for (int j = 0; j < MB; ++j) {
-                const int c = wk * 128 + j * 32 + l32;
+                const int c = wk * 32 * MB + j * 32 + l32;
                 voff[j] = c < cols ? ((uint32_t)(4 * h) * (uint32_t)ld + (uint32_t)c) * 4u : kOOB;
             }
 #pragma unroll
@@ -814,28 +859,33 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 #endif
 }
 
-// dW tile (+)= the partial tiles of its token ranges, added in the order of the ranges.  One workgroup per 16 rows of
-// a split tile, a thread per four columns.
+// dW tile (+)= the partial tiles of its token ranges, added in the order of the ranges.  A thread takes four rows of four
+// columns, a workgroup 64 / HB rows of a split tile.
+template <int HB>
 __global__ __launch_bounds__(256) void dw_reduce_kernel(DwArgs a) {
-    const int t = blockIdx.x / (DW_BN / 16), r16 = blockIdx.x % (DW_BN / 16);   // split tile, 16-row block
-    const uint32_t lid = (uint32_t)(a.whole + t);
+    constexpr int SIDE = dw_side(HB), ROWS = 64 / HB, TPR = SIDE / 4;
+    const int t = blockIdx.x / (SIDE / ROWS), rblock = blockIdx.x % (SIDE / ROWS);   // split tile, row block
+    uint32_t lid = (uint32_t)(a.whole + t);
+    const uint32_t tiles = (uint32_t)(a.tiles_n * a.tiles_k);
+    float *dW = a.dW + (size_t)(lid / tiles) * a.N * a.K;
+    lid %= tiles;
     constexpr int GROUP = 4;
     const int width = GROUP * a.tiles_k;
     const int first_n = (int)(lid / width) * GROUP;
     const int gsz = min(a.tiles_n - first_n, GROUP);
     const int tn = first_n + (int)(lid % width) % gsz;
     const int tk = (int)(lid % width) / gsz;
-    const int row = r16 * 16 + (threadIdx.x >> 6) * 4, col = (threadIdx.x & 63) * 4;
-    const int k = tk * DW_BK + col;
+    const int row = rblock * ROWS + (threadIdx.x / TPR) * 4, col = (threadIdx.x % TPR) * 4;
+    const int k = tk * SIDE + col;
     if (k >= a.K) return;   // (K is a multiple of 8: four columns are inside or outside together)
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
-        const int n = tn * DW_BN + row + rr;
+        const int n = tn * SIDE + row + rr;
         if (n >= a.N) return;
-        const float *src = a.part + (size_t)t * a.parts * (DW_BN * DW_BK) + (size_t)(row + rr) * DW_BK + col;
+        const float *src = a.part + (size_t)t * a.parts * (SIDE * SIDE) + (size_t)(row + rr) * SIDE + col;
         f32x4 sum = *reinterpret_cast<const f32x4 *>(src);
-        for (int p = 1; p < a.parts; ++p) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)p * (DW_BN * DW_BK));
-        f32x4 *out = reinterpret_cast<f32x4 *>(a.dW + (size_t)n * a.K + k);
+        for (int p = 1; p < a.parts; ++p) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)p * (SIDE * SIDE));
+        f32x4 *out = reinterpret_cast<f32x4 *>(dW + (size_t)n * a.K + k);
         if (a.accumulate) sum += *out;
         *out = sum;
     }
@@ -867,7 +917,7 @@ static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr) {
     o += align256(m32 * K * 2);
     // dX is done before dW begins: their partial sums share their place
     w.dxp = w.dwp = o;
-    o += align256(std::max(dw_plan(M, N, K).part_bytes, dx_plan(M, N, K, nr).part_bytes));
+    o += align256(std::max(dw_plan(M, N, K, 1).part_bytes, dx_plan(M, N, K, nr).part_bytes));
     w.total = o;
     return w;
 }
@@ -887,6 +937,22 @@ template <typename Kern>
 static bool allow_lds(Kern kern, int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                bytes) == hipSuccess;
+}
+
+template <int HB>
+static mq_status launch_dw_side(const DwArgs &w, const DwPlan &plan, hipStream_t st) {
+    if (!allow_lds(dw_kernel<HB>, dw_lds(HB))) return MQ_ERR_DEVICE;
+    dw_kernel<HB><<<dim3(plan.whole + plan.rest * plan.parts), dim3(256), dw_lds(HB), st>>>(w);
+    if (plan.rest > 0) dw_reduce_kernel<HB><<<dim3(plan.rest * HB * HB), dim3(256), 0, st>>>(w);
+    return launch_status();
+}
+
+static mq_status launch_dw(DwArgs w, const DwPlan &plan, hipStream_t st) {
+    w.tiles_n = plan.tiles_n;
+    w.tiles_k = plan.tiles_k;
+    w.whole = plan.whole;
+    w.parts = plan.parts;
+    return plan.hb == 2 ? launch_dw_side<2>(w, plan, st) : launch_dw_side<4>(w, plan, st);
 }
 
 template <int NR, bool HAS8, bool EP, int MB, bool LOSS>
@@ -971,7 +1037,7 @@ extern "C" size_t mq_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, in
     if (op == MQ_OP_LINEAR_BWD) return bwd_layout(M, N, K, nr).total + 256;
     if (op == MQ_OP_FFN_DECODE) return ffn_workspace_bytes(M, N, K);
     if (op == MQ_OP_L2_LOSS) return loss_workspace_bytes(M, N);
-    if (op == MQ_OP_LINEAR_BWD_CLIP) return clip_workspace_bytes(M, N, K);
+    if (op == MQ_OP_LINEAR_BWD_CLIP) return clip_workspace_bytes(M, N, K, nr);
     if (op == MQ_OP_AFFINE_BWD) return affine_workspace_bytes(M, N, K);
     return 0;
 }
@@ -1181,6 +1247,76 @@ extern "C" mq_status mq_linear_fwd_multi_l2(const uint16_t *X, const uint8_t *Q,
 }
 
 namespace mq {
+// fills in the cut of the gradients and launches the preparation
+static mq_status launch_prep(PrepArgs &p, bool gated, hipStream_t st) {
+    // column ranges so that about a thousand workgroups exist; c[m] is summed over them in the dX epilogue
+    const int64_t M = p.M, N = p.N, K = p.K, strips = cdiv(M, PREP_ROWS);
+    const int nsplit = (int)std::min<int64_t>(std::min<int64_t>(PREP_MAX_SPLIT, cdiv(N, 64)), std::max<int64_t>(1, cdiv(1024, strips)));
+    p.cols_per_split = (int)(cdiv(cdiv(N, nsplit), 64) * 64);
+    p.strips = (int)strips;
+    p.nsplit = (int)cdiv(N, p.cols_per_split);
+    const int64_t blocks = strips * p.nsplit * std::max(p.each, 1) + (p.QT ? cdiv(N, 128) * cdiv(K, 128) : 0) + (p.XT ? cdiv(M, 64) * cdiv(K, 64) : 0);
+    if (blocks > 0x7F000000) return MQ_ERR_SHAPE;
+    const int64_t gx = std::min<int64_t>(blocks, 1 << 20);
+    const dim3 grid((unsigned)gx, (unsigned)cdiv(blocks, gx));
+    if (gated)
+        bwd_prep_kernel<true><<<grid, dim3(256), 0, st>>>(p);
+    else
+        bwd_prep_kernel<false><<<grid, dim3(256), 0, st>>>(p);
+    return launch_status();
+}
+
+// Workspace of dw_each: the transposed gradients, X, and the partial tiles
+struct EachWorkspace {
+    size_t gt_step, xt, dwp, total;  // gt_step in bytes
+};
+static EachWorkspace each_layout(int64_t M, int64_t N, int64_t K, int nr) {
+    EachWorkspace w;
+    const size_t m32 = ((size_t)M + 31) & ~(size_t)31;
+    w.gt_step = align256(m32 * N * 2);
+    w.xt = w.gt_step * nr;
+    w.dwp = w.xt + align256(m32 * K * 2);
+    w.total = w.dwp + align256(dw_plan(M, N, K, nr).part_bytes);
+    return w;
+}
+
+size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr) { return each_layout(M, N, K, nr).total; }
+
+// (no argument checks: the caller has made those of mq_linear_bwd)
+mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lambda, int64_t M, int64_t N, int64_t K, int nr,
+                  float *G, uint8_t *ws, hipStream_t st) {
+    const EachWorkspace lay = each_layout(M, N, K, nr);
+    PrepArgs p{};
+    for (int i = 0; i < nr; ++i) {
+        p.dY[i] = dY[i];
+        p.lam[i] = lambda ? lambda[i] : 1.0f;
+    }
+    for (int i = 0; i < 3; ++i) p.mult[i] = 1.0f;
+    p.GT = reinterpret_cast<uint16_t *>(ws);
+    p.gt_step = (int64_t)(lay.gt_step / 2);
+    p.each = p.nr = nr;
+    p.M = (int)M;
+    p.N = (int)N;
+    p.K = (int)K;
+    p.ldm = (int)((M + 7) & ~(int64_t)7);
+    p.X = X;
+    p.XT = reinterpret_cast<uint16_t *>(ws + lay.xt);
+    mq_status s = launch_prep(p, false, st);
+    if (s != MQ_OK) return s;
+    DwArgs w;
+    w.GT = p.GT;
+    w.gt_step = p.gt_step;
+    w.XT = p.XT;
+    w.dW = G;
+    w.part = reinterpret_cast<float *>(ws + lay.dwp);
+    w.M = (int)M;
+    w.N = (int)N;
+    w.K = (int)K;
+    w.ldm = p.ldm;
+    w.accumulate = 0;
+    return launch_dw(w, dw_plan(M, N, K, nr), st);
+}
+
 // gated: the output gradients come from GU and dA (see PrepArgs) instead of dY
 static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const float *alpha, const float *zero,
                          const uint16_t *const *dY, const uint16_t *const *GU, const uint16_t *const *dA,
@@ -1253,27 +1389,16 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.M = (int)M;
     p.N = (int)N;
     p.ldm = (int)((M + 7) & ~(int64_t)7);
-    // column ranges so that about a thousand workgroups exist; c[m] is summed over them in the dX epilogue
-    const int64_t strips = cdiv(M, PREP_ROWS);
-    int nsplit = (int)std::min<int64_t>(std::min<int64_t>(PREP_MAX_SPLIT, cdiv(N, 64)), std::max<int64_t>(1, cdiv(1024, strips)));
-    p.cols_per_split = (int)(cdiv(cdiv(N, nsplit), 64) * 64);
-    nsplit = (int)cdiv(N, p.cols_per_split);
     p.silu = (flags & MQ_FLAG_FFN_SILU) ? 1 : 0;
-    p.strips = (int)strips;
-    p.nsplit = nsplit;
     p.K = (int)K;
     p.Q = Q;
     p.QT = dX ? base + lay.qt : nullptr;
     p.X = X;
     p.XT = dW ? reinterpret_cast<uint16_t *>(base + lay.xt) : nullptr;
-    const int64_t blocks = strips * nsplit + (dX ? cdiv(N, 128) * cdiv(K, 128) : 0) + (dW ? cdiv(M, 64) * cdiv(K, 64) : 0);
-    if (blocks > 0x7F000000) return MQ_ERR_SHAPE;
-    const int64_t gx = std::min<int64_t>(blocks, 1 << 20);
-    const dim3 grid((unsigned)gx, (unsigned)cdiv(blocks, gx));
-    if (gated)
-        bwd_prep_kernel<true><<<grid, dim3(256), 0, st>>>(p);
-    else
-        bwd_prep_kernel<false><<<grid, dim3(256), 0, st>>>(p);
+    p.each = 0;
+    p.gt_step = 0;
+    s = launch_prep(p, gated, st);
+    if (s != MQ_OK) return s;
 
     if (dX) {
         // slot order of the kernel: the r = 8 bit-width (if any) first
@@ -1293,7 +1418,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         }
         d.QT = p.QT;
         d.cvec = p.cpart;
-        d.nsplit = nsplit;
+        d.nsplit = p.nsplit;
         d.dX = dX;
         d.M = (int)M;
         d.N = (int)N;
@@ -1307,20 +1432,15 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         w.GT = p.GT;
         w.XT = p.XT;
         w.dW = dW;
+        w.part = reinterpret_cast<float *>(base + lay.dwp);
         w.M = (int)M;
         w.N = (int)N;
         w.K = (int)K;
         w.ldm = p.ldm;
         w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
-        const DwPlan plan = dw_plan(M, N, K);
-        w.tiles_n = plan.tiles_n;
-        w.tiles_k = plan.tiles_k;
-        w.whole = plan.whole;
-        w.parts = plan.parts;
-        w.part = reinterpret_cast<float *>(base + lay.dwp);
-        if (!allow_lds(dw_kernel, DW_LDS)) return MQ_ERR_DEVICE;
-        dw_kernel<<<dim3(plan.whole + plan.rest * plan.parts), dim3(256), DW_LDS, st>>>(w);
-        if (plan.rest > 0) dw_reduce_kernel<<<dim3(plan.rest * (DW_BN / 16)), dim3(256), 0, st>>>(w);
+        w.gt_step = 0;
+        const mq_status ws_ = launch_dw(w, dw_plan(M, N, K, 1), st);
+        if (ws_ != MQ_OK) return ws_;
     }
     return launch_status();
 }
