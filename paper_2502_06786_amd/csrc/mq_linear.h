@@ -355,19 +355,19 @@ constexpr int fwd_mb(int nr) { return nr == 3 ? 5 : 6; }
 // modelled cost (matrix-core cycles) of the tiled forward kernel at its better tile height, which goes to *mb unless null
 int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb);
 
-// How the forward for few tokens cuts its work (mq_linear_split.hip); mb == 0: the tiled kernel is the better one.
+// How the forward for few tokens cuts its work (mq_linear_split.hip); mb == 0: whole contractions are the better choice.
 struct FwdSplitPlan {
     int mb, splits;       // 32-token blocks per workgroup, K ranges
     size_t part_bytes;    // fp32 accumulators of all ranges
     size_t rs_bytes;      // per-token sums of X per range
     int64_t loss_blocks;  // workgroups of the finishing kernel (rows of FwdArgs::partial)
 };
-FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr);
+FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss);
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part,
                            float *rs_part, hipStream_t st, int64_t *blocks);
 
 // ============================================================================================
-// backward dX (mq_linear_dx.hip)
+// backward dX, forward at one bit-width (mq_linear_wide.hip)
 // ============================================================================================
 struct DxArgs {
     const uint16_t *As[3];  // [M, N] bf16, slot order (the r = 8 slot first when HAS8)
@@ -388,6 +388,10 @@ struct DxPlan {
     size_t part_bytes;  // fp32 accumulators of all ranges
 };
 DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr);
+// The forward at one bit-width (plain or gated) with 32 mb x 256 tiles, 3 <= mb <= 6.  fwd_wide_mb: the better mb, or 0 where
+// the tiles of fwd_kernel are faster; *ns = modelled time of the choice.
+int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns);
+mq_status launch_fwd_wide(const FwdArgs &f, int mb, bool has8, bool ep, hipStream_t st);
 mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st);
 
 }  // namespace mq

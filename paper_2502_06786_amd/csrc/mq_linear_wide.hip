@@ -1,5 +1,5 @@
-// dX of the straight-through backward, on the bf16 matrix cores: the tiled kernel, and the same kernel with the contraction
-// cut into ranges for the sizes whose tiles leave compute units idle.
+// The products whose tiles are 256 code rows wide: dX of the straight-through backward, with its contraction cut into ranges
+// for the sizes whose tiles leave compute units idle, and the forward at one bit-width.
 #include <algorithm>
 
 #include "mq_linear.h"
@@ -29,15 +29,10 @@ static_assert(dx_lds(DX_MB) >= 32 * DX_MB * DX_OS && dx_lds(1) >= 32 * DX_OS, "t
 // stage loop is unrolled over the bit-widths so that the kind of code conversion is a compile-time
 // property of each copy of the stage body.
 //
-// a.splits > 1: workgroup (range, tile) contracts one range of n tiles and leaves its fp32 accumulators in a.part in the
-// order its lanes hold them (each store a whole 1 KB per wave); dx_finish_kernel adds the ranges.
 template <int NRS, bool HAS8, bool EP, int MB>
-__global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
-#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+__device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, int m0, int k0, int nt0, int nt1, f32x16 (&acc)[DX_RB][MB]) {
     constexpr int RB = DX_RB;
-    constexpr int BM = 32 * MB;
-    constexpr int A_TILE = BM * 128;
+    constexpr int A_TILE = MB * 4096;
     constexpr int STAGE = A_TILE + DX_Q_TILE;
     constexpr int QL = DX_BK / 64;       // direct-to-LDS loads per wave and stage for the codes (16 rows each)
     constexpr int LPS = MB + QL;         // loads per wave and stage
@@ -50,20 +45,7 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, l32 = lane & 31;
 
-    const int tiles = a.tiles_m * a.tiles_k;
-    const uint32_t wid = xcd_contiguous_id(blockIdx.x, gridDim.x);
-    const int split = (int)wid / tiles;
-    const uint32_t lid = wid % (uint32_t)tiles;
-    const int nnt_all = (a.N + BKT - 1) / BKT;
-    const int nt0 = (int)((int64_t)nnt_all * split / a.splits), nt1 = (int)((int64_t)nnt_all * (split + 1) / a.splits);
     const int n_end = min(a.N, nt1 * BKT);
-    constexpr int GROUP = 4;
-    const int width = GROUP * a.tiles_k;
-    const int first_m = (int)(lid / width) * GROUP;
-    const int gsz = min(a.tiles_m - first_m, GROUP);
-    const int tm = first_m + (int)(lid % width) % gsz;
-    const int tk = (int)(lid % width) / gsz;
-    const int m0 = tm * BM, k0 = tk * DX_BK;
 
     __amdgpu_buffer_rsrc_t rA[NRS];
 #pragma unroll
@@ -136,7 +118,6 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
         }
     };
 
-    f32x16 acc[RB][MB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -274,6 +255,35 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
         }
     }
     wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
+}
+
+// a.splits > 1: workgroup (range, tile) contracts one range of n tiles and leaves its fp32 accumulators in a.part in the
+// order its lanes hold them (each store a whole 1 KB per wave); dx_finish_kernel adds the ranges.
+template <int NRS, bool HAS8, bool EP, int MB>
+__global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    constexpr int RB = DX_RB, BM = 32 * MB;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, l32 = lane & 31;
+
+    const int tiles = a.tiles_m * a.tiles_k;
+    const uint32_t wid = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const int split = (int)wid / tiles;
+    const uint32_t lid = wid % (uint32_t)tiles;
+    const int nnt_all = (a.N + BKT - 1) / BKT;
+    const int nt0 = (int)((int64_t)nnt_all * split / a.splits), nt1 = (int)((int64_t)nnt_all * (split + 1) / a.splits);
+    constexpr int GROUP = 4;
+    const int width = GROUP * a.tiles_k;
+    const int first_m = (int)(lid / width) * GROUP;
+    const int gsz = min(a.tiles_m - first_m, GROUP);
+    const int tm = first_m + (int)(lid % width) % gsz;
+    const int tk = (int)(lid % width) / gsz;
+    const int m0 = tm * BM, k0 = tk * DX_BK;
+
+    f32x16 acc[RB][MB];
+    wide_main_loop<NRS, HAS8, EP, MB>(a, smem, m0, k0, nt0, nt1, acc);
 
     if (a.splits > 1) {
         f32x4 *dst = reinterpret_cast<f32x4 *>(a.part) + ((size_t)split * tiles + lid) * (RB * MB * 4 * 256) + threadIdx.x;
@@ -382,8 +392,128 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(DxArgs a, int mb) {
     *reinterpret_cast<u32x2 *>(a.dX + (size_t)m * a.K + k) = u32x2{pack_bf16x2(sum[0] - c, sum[1] - c), pack_bf16x2(sum[2] - c, sum[3] - c)};
 }
 
+// ============================================================================================
+// forward at one bit-width
+// ============================================================================================
+// The main loop of dX with other names: Y[m, n] = sum over k of X[m, k] * code[n, k], one bit-width.  With a single bit-width a
+// wave of the forward kernel (32 channels) reads one activation operand from LDS per product, 128 bytes per clock and compute
+// unit at the matrix-core rate, which is all the LDS delivers; 64 channels per wave halve that.  The order of every sum and the
+// arithmetic of the epilogue are those of fwd_kernel.
+struct FwdWideArgs {
+    DxArgs d;  // As[0] = X [M, K], QT = Q [N, K]; d.N is the contraction length K, d.K the channels N
+    const float *alpha, *zero, *rowsum;
+    uint16_t *Y, *A;  // A: see FwdArgs; either may be null
+    int gate;
+};
+
+template <bool HAS8, bool EP, int MB>
+__global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    const DxArgs &a = w.d;
+    constexpr int RB = DX_RB, BM = 32 * MB;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, l32 = lane & 31;
+
+    const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    constexpr int GROUP = 4;
+    const int width = GROUP * a.tiles_k;
+    const int first_m = (int)(lid / width) * GROUP;
+    const int gsz = min(a.tiles_m - first_m, GROUP);
+    const int tm = first_m + (int)(lid % width) % gsz;
+    const int tn = (int)(lid % width) / gsz;
+    const int m0 = tm * BM, n0 = tn * DX_BK, N = a.K;
+
+    f32x16 acc[RB][MB];
+    wide_main_loop<1, HAS8, EP, MB>(a, smem, m0, n0, 0, (a.N + BKT - 1) / BKT, acc);
+
+    __syncthreads();  // every wave is done with the operand stages
+    float rs[MB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+        const int m = m0 + j * 32 + l32;
+        rs[j] = m < a.M ? w.rowsum[m] : 0.f;
+    }
+    f32x4 al[RB][4], ze[RB][4];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int n = n0 + wave * (32 * RB) + rb * 32 + 8 * g + 4 * h;
+            al[rb][g] = ze[rb][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (n < N) {
+                al[rb][g] = *reinterpret_cast<const f32x4 *>(w.alpha + n);
+                ze[rb][g] = *reinterpret_cast<const f32x4 *>(w.zero + n);
+            }
+        }
+    const float mult = HAS8 ? 1.0f : (float)(1 << (8 - a.r[0])), offset = HAS8 ? 0.0f : 128.0f * mult;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int nloc = wave * (32 * RB) + rb * 32 + 8 * g + 4 * h;
+#pragma unroll
+            for (int j = 0; j < MB; ++j) {
+                float y[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float t = (offset + ze[rb][g][e]) * rs[j], v = acc[rb][j][4 * g + e];
+                    y[e] = al[rb][g][e] * (HAS8 ? v - t : __builtin_fmaf(mult, v, -t));
+                }
+                const u32x2 o = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+                *reinterpret_cast<u32x2 *>(smem + (j * 32 + l32) * DX_OS + nloc * 2) = o;
+            }
+        }
+    __syncthreads();
+    constexpr int CPR = DX_BK / 8;  // 16-byte chunks per row
+#pragma unroll
+    for (int it = 0; it < BM * CPR / 256; ++it) {
+        const int c = it * 256 + threadIdx.x;
+        const int row = c / CPR, ch = c % CPR;
+        const int m = m0 + row, n = n0 + ch * 8;
+        if (m < a.M && n < N) {
+            const uint8_t *src = smem + row * DX_OS + ch * 16;
+            const u32x2 lo = *reinterpret_cast<const u32x2 *>(src);
+            const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + 8);
+            if (w.Y)
+                __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y}, reinterpret_cast<u32x4 *>(w.Y + (size_t)m * N + n));
+            if (w.gate) {
+                auto gated = [&](uint32_t pair) {
+                    const float g = bf16_lo(pair), u = bf16_hi(pair);
+                    return (w.gate == 2 ? silu(g) : gelu_tanh(g)) * u;
+                };
+                const u32x2 o = {pack_bf16x2(gated(lo.x), gated(lo.y)), pack_bf16x2(gated(hi.x), gated(hi.y))};
+                __builtin_nontemporal_store(o, reinterpret_cast<u32x2 *>(w.A + (size_t)m * (N >> 1) + (n >> 1)));
+            }
+        }
+    }
+#else
+    (void)w;
+#endif
+}
+
 // ---- host side ------------------------------------------------------------------------------------
 namespace {
+
+template <bool HAS8, bool EP, int MB>
+mq_status launch_fwd_wide_mb(const FwdWideArgs &w, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_wide_kernel<HAS8, EP, MB>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, dx_lds(MB));
+    if (attr != hipSuccess) return MQ_ERR_DEVICE;
+    fwd_wide_kernel<HAS8, EP, MB><<<dim3(w.d.tiles_m * w.d.tiles_k), dim3(256), dx_lds(MB), st>>>(w);
+    return launch_status();
+}
+
+template <bool HAS8, bool EP>
+mq_status launch_fwd_wide_one(const FwdWideArgs &w, int mb, hipStream_t st) {
+    switch (mb) {
+        case 3: return launch_fwd_wide_mb<HAS8, EP, 3>(w, st);
+        case 4: return launch_fwd_wide_mb<HAS8, EP, 4>(w, st);
+        case 5: return launch_fwd_wide_mb<HAS8, EP, 5>(w, st);
+        default: return launch_fwd_wide_mb<HAS8, EP, 6>(w, st);
+    }
+}
 
 template <int NRS, bool HAS8, bool EP, int MB>
 mq_status launch_dx_mb(const DxArgs &d, hipStream_t st) {
@@ -456,6 +586,48 @@ DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
         }
     }
     return best;
+}
+
+// Which tile the forward at one bit-width takes where K is not split: rounds of workgroups times the time of a tile, in ns, a fit
+// to 650 timed combinations (10 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens).  Wide tiles are half as many, so
+// they lose while the narrow ones still fit one round (3600 x 3600, 1000 tokens 45 against 54 us) and win from the second
+// round on; the choice among the five forms is at most 2 % slower than the best of them.  int4, narrow -> chosen: 14336 x 4096,
+// 2011 tokens 256 -> 221 us, 4096 tokens 501 -> 425 us; 2304 x 9216, 4096 tokens 199 -> 168 us; 3600 x 3600, 1600 tokens 82
+// -> 59 us; 2000 x 1008, 4096 tokens 34 -> 28.5 us.
+int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns) {
+    double best = 0.678 * (double)fwd_tiled_cost(M, N, K, 1, nullptr);
+    int choice = 0;
+    for (int mb = 3; mb <= 6; ++mb) {
+        const int64_t rounds = cdiv(cdiv(M, 32 * mb) * cdiv(N, DX_BK), 256);
+        const double t = (double)rounds * ((double)cdiv(K, BKT) * (94.0 * mb + 402.0) + 3870.0 + 824.0 * mb);
+        if (t < best) {
+            best = t;
+            choice = mb;
+        }
+    }
+    if (ns) *ns = best;
+    return choice;
+}
+
+mq_status launch_fwd_wide(const FwdArgs &f, int mb, bool has8, bool ep, hipStream_t st) {
+    FwdWideArgs w{};
+    w.d.As[0] = f.X;
+    w.d.QT = f.Q;
+    w.d.M = f.M;
+    w.d.N = f.K;
+    w.d.K = f.N;
+    w.d.r[0] = f.r[0];
+    w.d.tiles_m = (int)cdiv(f.M, 32 * mb);
+    w.d.tiles_k = (int)cdiv(f.N, DX_BK);
+    w.d.splits = 1;
+    w.alpha = f.alpha;
+    w.zero = f.zero;
+    w.rowsum = f.rowsum;
+    w.Y = f.Y[0];
+    w.A = f.A[0];
+    w.gate = f.gate;
+    if (has8) return launch_fwd_wide_one<true, false>(w, mb, st);  // the code of r = 8 is never rounded up past the byte
+    return ep ? launch_fwd_wide_one<false, true>(w, mb, st) : launch_fwd_wide_one<false, false>(w, mb, st);
 }
 
 mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st) {
