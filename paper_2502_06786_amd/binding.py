@@ -8,6 +8,7 @@ there is no CPU fallback: if libmq.so is missing the import fails.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -115,8 +116,12 @@ def status_string(status: int) -> str:
     return _lib.mq_status_string(int(status)).decode()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# A decode call is a few microseconds of GPU work, so what the host does per call counts: the stream handle is asked for
+# directly (torch.cuda.current_stream() builds a Stream object around it), pointers are passed as integers, and the sizes of
+# workspaces and the small host arrays are remembered by value.
+def _stream() -> int:
+    """Handle of the current device's current stream."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t, dtype=None):
@@ -126,9 +131,9 @@ def _ptr(t, dtype=None):
         raise ValueError("tensor must live on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise ValueError(f"expected {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _check(status: int, what: str):
@@ -149,6 +154,7 @@ class Overflow:
         return _Overflow(self.row_ptr.data_ptr(), self.col_idx.data_ptr(), self.capacity, self.nnz.data_ptr())
 
 
+@functools.lru_cache(maxsize=1024)
 def mq_workspace_bytes(op: int, M: int, N: int, K: int, nr: int) -> int:
     return int(_lib.mq_workspace_bytes(op, M, N, K, nr))
 
@@ -162,7 +168,7 @@ def mq_quantize_int8(W, gamma=None, beta=None, Q=None, alpha=None, zero=None):
     Q = torch.empty(N, K, dtype=torch.uint8, device=W.device) if Q is None else Q
     alpha = torch.empty(N, dtype=torch.float32, device=W.device) if alpha is None else alpha
     zero = torch.empty(N, dtype=torch.float32, device=W.device) if zero is None else zero
-    st = _lib.mq_quantize_int8(ctypes.c_void_p(W.data_ptr()), N, K, ldw, _ptr(gamma, torch.float32),
+    st = _lib.mq_quantize_int8(W.data_ptr(), N, K, ldw, _ptr(gamma, torch.float32),
                                _ptr(beta, torch.float32), _ptr(Q, torch.uint8), _ptr(alpha, torch.float32),
                                _ptr(zero, torch.float32), _stream())
     _check(st, "mq_quantize_int8")
@@ -237,12 +243,18 @@ def mq_slice_multi(Q, rs, out=None, ovf_r: int | None = None, ovf: Overflow | No
     return (out, ovf) if ovf_r is not None else out
 
 
+@functools.lru_cache(maxsize=256)
+def _int_array_of(vals):
+    return (ctypes.c_int * len(vals))(*vals)
+
+
 def _int_array(vals):
-    return (ctypes.c_int * len(vals))(*[int(v) for v in vals])
+    """Host int array for a call; the library only reads it."""
+    return _int_array_of(tuple([int(v) for v in vals]))
 
 
 def _ptr_array(tensors, dtype):
-    return (ctypes.c_void_p * len(tensors))(*[t.data_ptr() if _ptr(t, dtype) else None for t in tensors])
+    return (ctypes.c_void_p * len(tensors))(*[_ptr(t, dtype) for t in tensors])
 
 
 def mq_linear_fwd_multi(X, Q, alpha, zero, rs, extra_precision: bool = False, Y=None, ws=None):
@@ -492,7 +504,7 @@ def mq_linear_bwd_clip(W, X, Q, alpha, zero, dY, lambdas, rs, gamma=None, beta=N
     flags = MQ_FLAG_EXTRA_PRECISION if extra_precision else 0
     if W.dtype != torch.float32 or not W.is_cuda:
         raise ValueError("W must be a float32 tensor on the GPU")
-    st = _lib.mq_linear_bwd_clip(ctypes.c_void_p(W.data_ptr()), W.stride(0), _ptr(X, torch.bfloat16), _ptr(Q, torch.uint8),
+    st = _lib.mq_linear_bwd_clip(W.data_ptr(), W.stride(0), _ptr(X, torch.bfloat16), _ptr(Q, torch.uint8),
                                  _ptr(alpha, torch.float32), _ptr(zero, torch.float32), _ptr(gamma, torch.float32),
                                  _ptr(beta, torch.float32), _ptr_array(dY, torch.bfloat16), lam, M, N, K, _int_array(rs), nr,
                                  flags, _ptr(out[0]), _ptr(out[1]), _ptr(out[2]) if want_dalpha_dzero else None,
@@ -508,7 +520,7 @@ def mq_affine_weight(W, s=None, delta=None, b=None, want_Ws: bool = True, want_c
         raise ValueError("W must be a float32 GPU tensor with unit column stride")
     Ws = torch.empty(N, K, dtype=torch.float32, device=W.device) if want_Ws else None
     c = torch.empty(N, dtype=torch.float32, device=W.device) if want_c else None
-    st = _lib.mq_affine_weight(ctypes.c_void_p(W.data_ptr()), N, K, W.stride(0), _ptr(s, torch.float32),
+    st = _lib.mq_affine_weight(W.data_ptr(), N, K, W.stride(0), _ptr(s, torch.float32),
                                _ptr(delta, torch.float32), _ptr(b, torch.float32), _ptr(Ws), _ptr(c), _stream())
     _check(st, "mq_affine_weight")
     return Ws, c
@@ -538,7 +550,7 @@ def mq_affine_bwd(X, dXt, W, dWs, dY, lambdas, s=None, delta=None, ws=None):
     lam = (ctypes.c_float * nr)(*lambdas) if lambdas is not None else None
     if W.dtype != torch.float32 or W.stride(1) != 1:
         raise ValueError("W must be float32 with unit column stride")
-    st = _lib.mq_affine_bwd(_ptr(X, torch.bfloat16), _ptr(dXt, torch.bfloat16), ctypes.c_void_p(W.data_ptr()), W.stride(0),
+    st = _lib.mq_affine_bwd(_ptr(X, torch.bfloat16), _ptr(dXt, torch.bfloat16), W.data_ptr(), W.stride(0),
                             _ptr(dWs, torch.float32), _ptr_array(dY, torch.bfloat16), lam, nr, M, N, K,
                             _ptr(s, torch.float32), _ptr(delta, torch.float32), _ptr(out[0]), _ptr(out[1]), _ptr(out[2]),
                             _ptr(ws), ws.numel(), _stream())

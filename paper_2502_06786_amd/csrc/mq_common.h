@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/mq.h"
 
 namespace mq {
@@ -42,6 +44,48 @@ inline mq_status launch_status() { return hipGetLastError() == hipSuccess ? MQ_O
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Lets `kern` use `bytes` of dynamic LDS on the current device.  The attribute is set once per kernel, size and device.
+template <auto Kern>
+bool allow_lds(int bytes) {
+    static std::atomic<int> allowed[64];  // per device: the largest size granted so far
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return false;
+    if (dev < 64 && allowed[dev].load(std::memory_order_acquire) >= bytes) return true;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(Kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
+        return false;
+    if (dev < 64) {
+        int old = allowed[dev].load(std::memory_order_relaxed);
+        while (old < bytes && !allowed[dev].compare_exchange_weak(old, bytes, std::memory_order_release)) {
+        }
+    }
+    return true;
+}
+
+// The last few plans of a thread by their sizes: a plan is the best of up to a hundred modelled cuts, and a call asks for
+// the same one several times (workspace size, check, launch).  `make(key...)` is a pure function of the key.
+template <typename Plan, typename Make, typename... Key>
+Plan remembered(Make make, Key... key) {
+    constexpr int kSlots = 16;
+    struct Slot {
+        int64_t key[sizeof...(Key)];
+        bool used;
+        Plan plan;
+    };
+    static thread_local Slot slots[kSlots];
+    const int64_t k[] = {static_cast<int64_t>(key)...};
+    uint64_t h = 0;
+    for (int64_t v : k) h = (h ^ (uint64_t)v) * 0x9E3779B97F4A7C15ull;
+    Slot &s = slots[h >> 60];
+    bool same = s.used;
+    for (size_t i = 0; i < sizeof...(Key); ++i) same = same && s.key[i] == k[i];
+    if (!same) {
+        s.plan = make(key...);
+        for (size_t i = 0; i < sizeof...(Key); ++i) s.key[i] = k[i];
+        s.used = true;
+    }
+    return s.plan;
+}
 
 // workspace of mq_ffn_mixnmatch (mq_ffn.hip)
 size_t ffn_workspace_bytes(int64_t B, int64_t F, int64_t d);

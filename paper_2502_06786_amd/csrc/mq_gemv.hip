@@ -622,14 +622,9 @@ static mq_status launch_gemv(const GemvArgs &a, int nw, int ks, hipStream_t st) 
     const int capacity = 256 * per_cu;
     const int rounds = (ngroups + capacity - 1) / capacity;
     const int grid = (ngroups + rounds - 1) / rounds;
-    auto go = [&](auto kern) -> mq_status {
-        if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return MQ_ERR_DEVICE;
-        kern<<<dim3(grid), dim3(64 * nw), lds, st>>>(a, bp, CB, ks, ngroups, (int)x_off, single);
-        return launch_status();
-    };
-    return go(gemv_kernel<R, RG, D>);
+    if (lds > 65536 && !allow_lds<gemv_kernel<R, RG, D>>((int)lds)) return MQ_ERR_DEVICE;
+    gemv_kernel<R, RG, D><<<dim3(grid), dim3(64 * nw), lds, st>>>(a, bp, CB, ks, ngroups, (int)x_off, single);
+    return launch_status();
 }
 
 }  // namespace mq

@@ -358,9 +358,7 @@ struct QuadPlan {
 template <int R, int NL, int S>
 mq_status launch_quad(const GemvArgs &a, const QuadPlan &p, hipStream_t st) {
     auto kern = gemv_quad_kernel<R, NL, S>;
-    if (p.lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds) != hipSuccess)
-        return MQ_ERR_DEVICE;
+    if (p.lds > 65536 && !allow_lds<gemv_quad_kernel<R, NL, S>>((int)p.lds)) return MQ_ERR_DEVICE;
     kern<<<dim3(p.grid), dim3(64 * p.ks * p.rw), p.lds, st>>>(a, p.ks, p.rw, p.ch, p.nsl);
     return launch_status();
 }

@@ -390,9 +390,7 @@ struct RegPlan {
 template <int R, int NL, int S, int MAXT>
 mq_status launch_reg(const GemvArgs &a, const RegPlan &p, hipStream_t st) {
     auto kern = gemv_reg_kernel<R, NL, S, MAXT, false>;
-    if (p.lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)p.lds) != hipSuccess)
-        return MQ_ERR_DEVICE;
+    if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, MAXT, false>>((int)p.lds)) return MQ_ERR_DEVICE;
     kern<<<dim3(p.grid), dim3(64 * p.ks), p.lds, st>>>(a, p.ks, 1, p.ch, p.nsl, nullptr, nullptr);
     return launch_status();
 }
@@ -401,9 +399,7 @@ mq_status launch_reg(const GemvArgs &a, const RegPlan &p, hipStream_t st) {
 template <int R, int NL, int S>
 mq_status launch_reg_split(const GemvArgs &a, const RegPlan &p, int groups, void *ws, hipStream_t st) {
     auto kern = gemv_reg_kernel<R, NL, S, 256, true>;
-    if (p.lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)p.lds) != hipSuccess)
-        return MQ_ERR_DEVICE;
+    if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, 256, true>>((int)p.lds)) return MQ_ERR_DEVICE;
     const int nrb = (a.N + 15) / 16;
     f32x4 *pdot = static_cast<f32x4 *>(ws);
     float *psum = reinterpret_cast<float *>(pdot + (size_t)groups * nrb * 64);

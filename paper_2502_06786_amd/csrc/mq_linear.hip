@@ -617,7 +617,7 @@ struct DwPlan {
     int hb, tiles_n, tiles_k, whole, rest, parts;
     size_t part_bytes;
 };
-static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
+static DwPlan make_dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
     DwPlan best{};
     double best_cost = 0;
     const int64_t stages = cdiv(M, DW_BM);
@@ -652,6 +652,8 @@ static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
     }
     return best;
 }
+
+static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) { return remembered<DwPlan>(make_dw_plan, M, N, K, batch); }
 
 // Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, one small fenced group of
 // operand work per MFMA), without any code conversion: both operands are bf16 rows with the contraction index
@@ -933,15 +935,9 @@ static mq_status check_rs(const int *rs, int nr) {
     return MQ_OK;
 }
 
-template <typename Kern>
-static bool allow_lds(Kern kern, int bytes) {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               bytes) == hipSuccess;
-}
-
 template <int HB>
 static mq_status launch_dw_side(const DwArgs &w, const DwPlan &plan, hipStream_t st) {
-    if (!allow_lds(dw_kernel<HB>, dw_lds(HB))) return MQ_ERR_DEVICE;
+    if (!allow_lds<dw_kernel<HB>>(dw_lds(HB))) return MQ_ERR_DEVICE;
     dw_kernel<HB><<<dim3(plan.whole + plan.rest * plan.parts), dim3(256), dw_lds(HB), st>>>(w);
     if (plan.rest > 0) dw_reduce_kernel<HB><<<dim3(plan.rest * HB * HB), dim3(256), 0, st>>>(w);
     return launch_status();
@@ -960,7 +956,7 @@ static mq_status launch_fwd_mb(FwdArgs a, hipStream_t st, int64_t *blocks) {
     a.tiles_m = (int)cdiv(a.M, 32 * MB);
     a.tiles_n = (int)cdiv(a.N, FWD_BN);
     *blocks = (int64_t)a.tiles_m * a.tiles_n;
-    if (!allow_lds(fwd_kernel<NR, HAS8, EP, MB, LOSS>, fwd_lds(MB, NR))) return MQ_ERR_DEVICE;
+    if (!allow_lds<fwd_kernel<NR, HAS8, EP, MB, LOSS>>(fwd_lds(MB, NR))) return MQ_ERR_DEVICE;
     fwd_kernel<NR, HAS8, EP, MB, LOSS><<<dim3(a.tiles_m * a.tiles_n), dim3(256), fwd_lds(MB, NR), st>>>(a);
     return launch_status();
 }

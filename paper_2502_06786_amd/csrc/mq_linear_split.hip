@@ -192,9 +192,7 @@ constexpr int split_lds(int mb) { return FWD_STAGES * (mb * 32 * 128 + FWD_Q_TIL
 
 template <int NR, bool HAS8, bool EP, int MB>
 mq_status launch_split_mb(const FwdSplitArgs &s, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_split_kernel<NR, HAS8, EP, MB>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, split_lds(MB));
-    if (attr != hipSuccess) return MQ_ERR_DEVICE;
+    if (!allow_lds<fwd_split_kernel<NR, HAS8, EP, MB>>(split_lds(MB))) return MQ_ERR_DEVICE;
     fwd_split_kernel<NR, HAS8, EP, MB><<<dim3(s.f.tiles_m * s.f.tiles_n * s.splits), dim3(256), split_lds(MB), st>>>(s);
     return launch_status();
 }
@@ -242,7 +240,7 @@ mq_status launch_finish(const FwdSplitArgs &s, int mb, bool loss, hipStream_t st
 // 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths): the choice is 1.5 % slower than the best of them
 // on average.  Measured, tiled -> chosen: 4096 x 4096, 77 tokens, int4 37.6 -> 15.7 us; 4096 x 14336 117 -> 26 us;
 // 2304 x 9216 at r = 8/4/2, 203 tokens 125 -> 44 us; level with the tiled kernel at 600 (14336 rows: 130) tokens and more.
-FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss) {
+static FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss) {
     FwdSplitPlan best{0, 0, 0, 0, 0};
     if (M < 1 || N < 1 || M > 2048) return best;
     const int64_t tiles_n = cdiv(N, FWD_BN), nkt = cdiv(K, BKT);
@@ -276,6 +274,10 @@ FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss) 
         }
     }
     return best;
+}
+
+FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss) {
+    return remembered<FwdSplitPlan>(make_split_plan, M, N, K, nr, loss);
 }
 
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part, float *rs_part,

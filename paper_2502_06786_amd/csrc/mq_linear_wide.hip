@@ -498,9 +498,7 @@ namespace {
 
 template <bool HAS8, bool EP, int MB>
 mq_status launch_fwd_wide_mb(const FwdWideArgs &w, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_wide_kernel<HAS8, EP, MB>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, dx_lds(MB));
-    if (attr != hipSuccess) return MQ_ERR_DEVICE;
+    if (!allow_lds<fwd_wide_kernel<HAS8, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
     fwd_wide_kernel<HAS8, EP, MB><<<dim3(w.d.tiles_m * w.d.tiles_k), dim3(256), dx_lds(MB), st>>>(w);
     return launch_status();
 }
@@ -517,9 +515,7 @@ mq_status launch_fwd_wide_one(const FwdWideArgs &w, int mb, hipStream_t st) {
 
 template <int NRS, bool HAS8, bool EP, int MB>
 mq_status launch_dx_mb(const DxArgs &d, hipStream_t st) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(dx_kernel<NRS, HAS8, EP, MB>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, dx_lds(MB));
-    if (attr != hipSuccess) return MQ_ERR_DEVICE;
+    if (!allow_lds<dx_kernel<NRS, HAS8, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
     dx_kernel<NRS, HAS8, EP, MB><<<dim3(d.tiles_m * d.tiles_k * d.splits), dim3(256), dx_lds(MB), st>>>(d);
     return launch_status();
 }
@@ -561,7 +557,7 @@ mq_status launch_dx_nrs(const DxArgs &d, int mb, bool has8, bool ep, hipStream_t
 // r = 8/4/2: 9216 x 2304, 16 tokens 263 -> 54 us, 400 tokens 342 -> 96 us, 2000 tokens 371 -> 274 us; 3600 x 3600, 400
 // tokens 160 -> 73 us, 4096 tokens 388 -> 354 us; 256 x 256, 16 tokens 15.6 (32-token tile) -> 13.9 us; the same at
 // 4096 tokens through 9216 x 2304 (499 us).
-DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
+static DxPlan make_dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
     DxPlan best{DX_MB, 1, 0};
     double best_cost = 0;
     const int64_t tiles_k = cdiv(K, DX_BK), nnt = cdiv(N, BKT);
@@ -587,6 +583,8 @@ DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
     }
     return best;
 }
+
+DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr) { return remembered<DxPlan>(make_dx_plan, M, N, K, nr); }
 
 // Which tile the forward at one bit-width takes where K is not split: rounds of workgroups times the time of a tile, in ns, a fit
 // to 650 timed combinations (10 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens).  Wide tiles are half as many, so
