@@ -19,6 +19,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)rec, 0x00020000);
 }
 
+// All but this wave's newest N global loads have landed and all but its newest L LDS reads are done, then the workgroup
+// meets: after it the tiles of the other waves are in LDS too, and the buffer of the previous stage may be filled again (the L
+// newest reads of a wave are those of the stage that follows; LDS reads are done in their order).  Not __syncthreads(), whose
+// fence waits for every load in flight, direct-to-LDS loads being writes to LDS: wherever the compiler saw loads before a
+// barrier (all prologues, two of the three stages of a channel tile in dX) the two stages that should have stayed on their
+// way were drained.  14336 x 3584, 8192 tokens, r = 8/4/2: dX 2122 -> 2052 us, forward with the objective 2103 -> 2076 us.
+template <int N, int L>
+__device__ __forceinline__ void stage_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)\n\ts_barrier" ::"n"(N), "n"(L) : "memory");
+}
+
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ f32x16 mfma32(const u32x4 &a, const u32x4 &b, const f32x16 &c) {
@@ -241,8 +252,7 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     issue(1);
     issue(2);
     // stage 0 must have landed before the first operand fetch; stages 1 and 2 may stay in flight
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPS) : "memory");
-    __syncthreads();
+    stage_barrier<2 * LPS, 0>();
 
     u32x4 xf[MB];      // activation operands of the current k step (refilled as soon as they are consumed)
     u32x4 raw[2];      // 32 code bytes of this lane's channel: four k steps of one stage
@@ -341,8 +351,7 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
         // Stage kt + 1 must be resident for the operand prefetch at the end of this iteration; the
         // loads of stage kt + 2 may stay in flight.  After the barrier every wave is done with
         // stage kt - 1, whose buffer stage kt + 3 reuses.
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
-        __syncthreads();
+        stage_barrier<LPS, MB>();
         tile(std::true_type{}, kt);
     }
     tile(std::false_type{}, nkt - 1);

@@ -751,8 +751,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     for (int st = 0; st < DW_NST - 1; ++st)
 #pragma unroll
         for (int i = 0; i < LPS; ++i) issue_one(mt0 + st, st, i);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DW_NST - 2) * LPS) : "memory");
-    __syncthreads();
+    stage_barrier<(DW_NST - 2) * LPS, 0>();
 
     u32x4 af[RB], bf[MB];
 #pragma unroll
@@ -797,8 +796,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         // stage mt + 1 must be resident (operand prefetch at the end of this stage); the loads of
         // stages mt + 2 and mt + 3 may stay in flight; after the barrier the buffer of stage mt - 1
         // is free for stage mt + 4
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DW_NST - 3) * LPS) : "memory");
-        __syncthreads();
+        stage_barrier<(DW_NST - 3) * LPS, RB + MB>();
         tile(std::true_type{}, mt0 + mt, cb);
         cb = cb + 1 == DW_NST ? 0 : cb + 1;
     }

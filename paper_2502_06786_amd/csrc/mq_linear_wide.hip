@@ -136,8 +136,7 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
         issue_stage(std::integral_constant<int, 1>{});
         issue_stage(std::integral_constant<int, 2>{});
     }
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPS) : "memory");
-    __syncthreads();
+    stage_barrier<2 * LPS, 0>();
 
     u32x4 xf[MB];         // gradient operands of the current step
     u32x4 raw[RB][2];     // 32 code bytes per k row of this lane: four steps of one stage
@@ -230,8 +229,7 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
     auto stage = [&](auto slot_tag, auto more_tag, int st, int nt) {
         // stage st + 1 must be resident (operand prefetch at the end of this stage); the loads of
         // stage st + 2 may stay in flight; after the barrier the buffer of stage st - 1 is free
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
-        __syncthreads();
+        stage_barrier<LPS, MB>();
         tile(slot_tag, more_tag, st, nt);
     };
 
