@@ -36,19 +36,23 @@ __device__ __forceinline__ float gelu_tanh(float v) {
     return v * sigmoid_fast(2.0f * t);
 }
 __device__ __forceinline__ float silu(float v) { return v * sigmoid_fast(v); }
-// derivative of the gate activation (GELU in its tanh form, or SiLU)
-__device__ __forceinline__ float act_grad(float g, bool use_silu) {
+// the two gradients of a (gate, up) pair of the gated unit a = act(g) u, rounded to bf16 as a pair (dg, du).  The activation
+// and its derivative come from one sigmoid: the passes over the gradients are bound by this arithmetic (its exponential and
+// division above all), not by HBM.
+__device__ __forceinline__ uint32_t gated_pair_grad(float g, float u, float da, bool use_silu) {
+    float act, grad;
     if (use_silu) {
         const float sig = sigmoid_fast(g);
-        return sig * (1.0f + g * (1.0f - sig));
+        act = g * sig;
+        grad = sig * (1.0f + g * (1.0f - sig));
+    } else {
+        // 0.5 g (1 + tanh(t)) = g sigmoid(2 t),  t = c (g + 0.044715 g^3)
+        const float c = 0.7978845608028654f;
+        const float sig = sigmoid_fast(2.0f * c * (g + 0.044715f * g * g * g)), th = 2.0f * sig - 1.0f;
+        act = g * sig;
+        grad = 0.5f * (1.0f + th) + 0.5f * g * (1.0f - th * th) * c * (1.0f + 3.0f * 0.044715f * g * g);
     }
-    const float c = 0.7978845608028654f;
-    const float th = 2.0f * sigmoid_fast(2.0f * c * (g + 0.044715f * g * g * g)) - 1.0f;  // tanh
-    return 0.5f * (1.0f + th) + 0.5f * g * (1.0f - th * th) * c * (1.0f + 3.0f * 0.044715f * g * g);
-}
-// the two gradients of a (gate, up) pair of the gated unit a = act(g) u, rounded to bf16 as a pair (dg, du)
-__device__ __forceinline__ uint32_t gated_pair_grad(float g, float u, float da, bool use_silu) {
-    return pack_bf16x2(da * u * act_grad(g, use_silu), da * (use_silu ? silu(g) : gelu_tanh(g)));
+    return pack_bf16x2(da * u * grad, da * act);
 }
 __device__ __forceinline__ float bf16_rounded(float v) { return __uint_as_float(float_to_bf16_bits(v) << 16); }
 // one gated output from the (gate, up) pair of products

@@ -396,8 +396,33 @@ __device__ __forceinline__ void prep_gradients(const PrepArgs &a, int strip, int
     const int nbeg = split * a.cols_per_split, nend = min(nbeg + a.cols_per_split, a.N);
     const bool want_as = a.As[0] != nullptr;
     float c = 0.f;
+    // what a tile reads; the loads of the next one are in flight while a tile is worked on and turned
+    struct Raw {
+        u32x4 v[3];
+        u32x2 da[GATED ? 3 : 1];
+    };
+    auto load = [&](int n) {
+        Raw x;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            x.v[i] = u32x4{0u, 0u, 0u, 0u};
+            if constexpr (GATED) x.da[i] = u32x2{0u, 0u};
+            if (i < a.nr && m < a.M && n < a.N) {
+                if constexpr (GATED) {
+                    x.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.GU[i] + (size_t)m * a.N + n));
+                    x.da[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(a.dA[i] + (size_t)m * (a.N >> 1) + (n >> 1)));
+                } else {
+                    x.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.dY[i] + (size_t)m * a.N + n));
+                }
+            }
+        }
+        return x;
+    };
+    Raw next = load(nbeg + ch * 8);
     for (int n0 = nbeg; n0 < nend; n0 += 64) {
         const int n = n0 + ch * 8;
+        const Raw raw = next;
+        if (n0 + 64 < nend) next = load(n + 64);
         float g[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) g[j] = 0.f;
@@ -413,16 +438,14 @@ __device__ __forceinline__ void prep_gradients(const PrepArgs &a, int strip, int
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 if (i >= a.nr) break;
+                dy[i] = raw.v[i];
                 if constexpr (GATED) {
                     // the gradient of the gated unit, pair by pair, rounded to bf16 like mq_gated_unit_bwd does
-                    const u32x4 gu = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.GU[i] + (size_t)m * a.N + n));
-                    const u32x2 da = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(a.dA[i] + (size_t)m * (a.N >> 1) + (n >> 1)));
+                    const u32x2 da = raw.da[i];
 #pragma unroll
                     for (int w = 0; w < 4; ++w)
-                        dy[i][w] = gated_pair_grad(bf16_lo(gu[w]), bf16_hi(gu[w]), (w & 1) ? bf16_hi(da[w >> 1]) : bf16_lo(da[w >> 1]),
-                                                   a.silu != 0);
-                } else {
-                    dy[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.dY[i] + (size_t)m * a.N + n));
+                        dy[i][w] = gated_pair_grad(bf16_lo(raw.v[i][w]), bf16_hi(raw.v[i][w]),
+                                                   (w & 1) ? bf16_hi(da[w >> 1]) : bf16_lo(da[w >> 1]), a.silu != 0);
                 }
             }
 #pragma unroll
