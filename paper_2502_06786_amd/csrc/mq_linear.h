@@ -361,7 +361,9 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
 // 32-token blocks per workgroup of the tiled forward kernel: the accumulators (16 NR MB registers) must leave room for
 // the operands
 constexpr int fwd_mb(int nr) { return nr == 3 ? 5 : 6; }
-// modelled cost (matrix-core cycles) of the tiled forward kernel at its better tile height, which goes to *mb unless null
+// modelled cost (matrix-core cycles) of the tiled forward kernel at its best tile height, which goes to *mb unless null, and
+// the ns of such a cycle
+constexpr double kFwdCycleNs = 0.47;
 int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb);
 
 // How the forward for few tokens cuts its work (mq_linear_split.hip); mb == 0: whole contractions are the better choice.

@@ -43,8 +43,11 @@ constexpr int fwd_lds(int mb, int nr) {
 // of the next 16-wide k step are fetched into registers behind the MFMAs of the current one, also
 // across the stage boundary) and stages kt + 2, kt + 3 are in flight, so a load has two full
 // iterations to arrive.
+//
+// With three bit-widths and two or three token blocks, two workgroups fit a compute unit (at most 80 KB of LDS and 256
+// registers each): one converts, stages and stores its outputs while the other multiplies.
 template <int NR, bool HAS8, bool EP, int MB, bool LOSS>
-__global__ __launch_bounds__(256) void fwd_kernel(FwdArgs a) {
+__global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     constexpr int BM = 32 * MB;
     const int lane = threadIdx.x & 63;
@@ -988,8 +991,29 @@ static mq_status launch_fwd_mb(FwdArgs a, hipStream_t st, int64_t *blocks) {
 // (32 per MFMA, plus about 180 cycles per 64-wide k stage and bit-width that do not shrink with the tile:
 // conversions and the stage barrier - fitted on the 9B gate shape, where 160 tokens run 2.5-4 % faster than
 // 128 although both fill their rounds; prologue and epilogue constants measured on the Gemma-2-2B shapes).
+//
+// Three bit-widths have the low tiles with two workgroups per compute unit as well, and a cost of their own, a fit to 640 timed
+// combinations (8 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens, plain and with the objective), in ns: a 64-wide
+// stage takes 294 + 159 per token block, for two workgroups together 409 + 367 per block.  The choice, with the form that cuts
+// K, is 0.6 % slower than the best of them on average, 13 % at worst (before: 6.5 %, 75 %).  r = 8/4/2 with the objective:
+// 2000 x 1008, 700 tokens 35.8 -> 23.6 us; 3600 x 3600, 1400 tokens 140 -> 112 us; 12000 x 912, 2011 tokens 167 -> 145 us;
+// 9216 x 2304, 2800 tokens 334 -> 311 us; the high tiles stay for 14336 x 4096, 2011 tokens (568 us).
 int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb) {
     const int hi = fwd_mb(nr);
+    if (nr == 3) {
+        const double stages = (double)cdiv(K, BKT);
+        double best_ns = 0;
+        for (int h = hi; h >= 2; --h) {
+            const int64_t per_cu = cdiv(cdiv(M, 32 * h) * cdiv(N, FWD_BN), 256);
+            const double ends = 871.0 + 1907.0 * h, alone = stages * (294.0 + 159.0 * h) + ends;
+            const double ns = h > 3 ? per_cu * alone : per_cu / 2 * (stages * (409.0 + 367.0 * h) + 1.4 * ends) + per_cu % 2 * alone;
+            if (h == hi || ns < best_ns) {
+                best_ns = ns;
+                if (mb) *mb = h;
+            }
+        }
+        return (int64_t)(best_ns / kFwdCycleNs);
+    }
     int64_t best = 0;
     for (int h = hi; h >= hi - 1; --h) {
         const int64_t tiles = cdiv(M, 32 * h) * cdiv(N, FWD_BN);
@@ -1008,6 +1032,10 @@ static mq_status launch_fwd(const FwdArgs &a, hipStream_t st, int64_t *blocks) {
     constexpr int HI = fwd_mb(NR), LO = HI - 1;
     int mb = HI;
     fwd_tiled_cost(a.M, a.N, a.K, NR, &mb);
+    if constexpr (NR == 3) {
+        if (mb == 2) return launch_fwd_mb<NR, HAS8, EP, 2, LOSS>(a, st, blocks);
+        if (mb == 3) return launch_fwd_mb<NR, HAS8, EP, 3, LOSS>(a, st, blocks);
+    }
     return mb == LO ? launch_fwd_mb<NR, HAS8, EP, LO, LOSS>(a, st, blocks) : launch_fwd_mb<NR, HAS8, EP, HI, LOSS>(a, st, blocks);
 }
 
@@ -1026,7 +1054,7 @@ static mq_status launch_fwd_any(const FwdArgs &a, int nr, bool has8, bool ep, hi
 }
 
 // Workspace of the forward: the tiled kernel's row sums at offset 0, the objective's partial sums (a bound over both
-// forms: the tiled kernel at its smallest token tile, 128 tokens, or the finishing kernel of the split form) and the
+// forms: the tiled kernel at its smallest token tile, 64 tokens, or the finishing kernel of the split form) and the
 // losses in slot order, and what the split form keeps.
 struct FwdWorkspace {
     size_t loss, slots, rs_part, part, total;
@@ -1034,7 +1062,7 @@ struct FwdWorkspace {
 static FwdWorkspace fwd_layout(int64_t M, int64_t N, const FwdSplitPlan &plan, bool loss) {
     FwdWorkspace w;
     w.loss = align256((size_t)M * 4);
-    const int64_t blocks = std::max<int64_t>(cdiv(M, 128) * cdiv(N, FWD_BN), plan.mb ? plan.loss_blocks : 0);
+    const int64_t blocks = std::max<int64_t>(cdiv(M, 64) * cdiv(N, FWD_BN), plan.mb ? plan.loss_blocks : 0);
     w.slots = w.loss + (loss ? (size_t)blocks * 16 : 0);
     w.rs_part = align256(w.slots + 256);
     w.part = w.rs_part + (plan.mb ? align256(plan.rs_bytes) : 0);
@@ -1079,7 +1107,7 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
                          bool tiled_only = false) {
     if (M < 0 || N < 0 || K < 1) return MQ_ERR_SHAPE;
     if (M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > (1 << 22)) return MQ_ERR_SHAPE;
-    if (cdiv(M, 128) * cdiv(N, FWD_BN) > 0x7FFFFFFF) return MQ_ERR_SHAPE;  // tiles of one launch
+    if (cdiv(M, 128) * cdiv(N, FWD_BN) > 0x7FFFFFFF) return MQ_ERR_SHAPE;  // tiles of one launch (lower tiles are taken for small problems only)
     mq_status s = check_rs(rs, nr);
     if (s != MQ_OK) return s;
     if (K % 16 != 0 || N % 8 != 0) return MQ_ERR_ALIGN;

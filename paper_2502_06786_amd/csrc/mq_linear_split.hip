@@ -244,7 +244,8 @@ static FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr, boo
     FwdSplitPlan best{0, 0, 0, 0, 0};
     if (M < 1 || N < 1 || M > 2048) return best;
     const int64_t tiles_n = cdiv(N, FWD_BN), nkt = cdiv(K, BKT);
-    double best_cost = 0.47 * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + 4600.0;  // with its row-sum pre-pass
+    // with its row-sum pre-pass (for three bit-widths less the margin by which the fits of the two forms are apart)
+    double best_cost = kFwdCycleNs * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + (nr == 3 ? (double)M * K / 2000.0 - 500.0 : 4600.0);
     double wide;
     if (nr == 1 && !loss && fwd_wide_mb(M, N, K, &wide)) best_cost = std::min(best_cost, wide + 4600.0);
     for (int mb = 1; mb <= 4; ++mb) {
