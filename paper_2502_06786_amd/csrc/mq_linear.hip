@@ -340,10 +340,14 @@ __global__ __launch_bounds__(256) void rowsum_kernel(const uint16_t *__restrict_
     if (m >= M) return;
     const u32x4 *row = reinterpret_cast<const u32x4 *>(X + (size_t)m * K);
     float s = 0.f;
-    for (int c = lane; c < K / 8; c += 64) {
-        const u32x4 v = row[c];
+    for (int c0 = lane; c0 < K / 8; c0 += 256) {  // four loads in flight; the sum runs in the order of the chunks
+        u32x4 v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s += __uint_as_float(v[i] << 16) + __uint_as_float(v[i] & 0xFFFF0000u);
+        for (int u = 0; u < 4; ++u) v[u] = c0 + 64 * u < K / 8 ? row[c0 + 64 * u] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s += __uint_as_float(v[u][i] << 16) + __uint_as_float(v[u][i] & 0xFFFF0000u);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
