@@ -151,7 +151,9 @@ extern "C" mq_status mq_linear_bwd_clip(const float *W, int64_t ldw, const uint1
     for (int i = 0; i < nr && M > 0; ++i)
         if (!dY[i]) return MQ_ERR_NULL;
     if (!aligned16(W) || !aligned16(Q)) return MQ_ERR_ALIGN;
-    if (!ws || ws_bytes < clip_workspace_bytes(M, N, K, nr) || !aligned16(ws)) return MQ_ERR_WORKSPACE;
+    // (a workspace that was made for more tokens may be too small for the partial tiles of fewer: dw_each then cuts nothing)
+    const size_t g_bytes = align256((size_t)N * K * 4 * nr);
+    if (!ws || ws_bytes < g_bytes + dw_each_bytes(M, N, K, nr, true) + 512 || !aligned16(ws)) return MQ_ERR_WORKSPACE;
     if (M > 0) {
         if (!aligned16(X)) return MQ_ERR_ALIGN;
         for (int i = 0; i < nr; ++i)
@@ -166,7 +168,7 @@ extern "C" mq_status mq_linear_bwd_clip(const float *W, int64_t ldw, const uint1
         return launch_status();
     }
     // G_r = lambda_r dY_r^T X for all bit-widths, through the dW path of the backward
-    mq_status s = dw_each(X, dY, lambda, M, N, K, nr, G, base + align256((size_t)N * K * 4 * nr), st);
+    mq_status s = dw_each(X, dY, lambda, M, N, K, nr, G, base + g_bytes, ws_bytes - g_bytes - 256, st);
     if (s != MQ_OK) return s;
     ClipArgs a{};
     a.W = W;

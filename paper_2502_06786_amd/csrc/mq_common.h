@@ -95,10 +95,11 @@ size_t loss_workspace_bytes(int64_t M, int64_t N);
 size_t clip_workspace_bytes(int64_t M, int64_t N, int64_t K, int nr);
 // workspace of mq_affine_bwd (mq_affine.hip)
 size_t affine_workspace_bytes(int64_t M, int64_t N, int64_t K);
-// G[i] [N, K] = lambda_i dY_i^T X for nr gradients against one X (mq_linear.hip)
-size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr);
+// G[i] [N, K] = lambda_i dY_i^T X for nr gradients against one X (mq_linear.hip).  dw_each_bytes: the workspace it can use, or
+// the least that it works with.
+size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr, bool least = false);
 mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lambda, int64_t M, int64_t N, int64_t K, int nr,
-                  float *G, uint8_t *ws, hipStream_t st);
+                  float *G, uint8_t *ws, size_t ws_bytes, hipStream_t st);
 // losses[i] = inv_mn * sum over the workgroups of partial[workgroup][i] (rows of 4 floats), in a
 // fixed order; one small launch on `st` (mq_loss.hip)
 mq_status launch_loss_finish(const float *partial, int64_t blocks, int nr, float inv_mn, float *losses,

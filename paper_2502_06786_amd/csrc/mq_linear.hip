@@ -685,6 +685,12 @@ static DwPlan make_dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
 
 static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) { return remembered<DwPlan>(make_dw_plan, M, N, K, batch); }
 
+// The cut that needs no workspace.
+static DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
+    const int tiles_n = (int)cdiv(N, dw_side(4)), tiles_k = (int)cdiv(K, dw_side(4));
+    return DwPlan{4, tiles_n, tiles_k, tiles_n * tiles_k * batch, 0, 1, 0};
+}
+
 // Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, one small fenced group of
 // operand work per MFMA), without any code conversion: both operands are bf16 rows with the contraction index
 // (tokens) contiguous.  The four waves form a 2 x 2 grid over the 256 x 256 tile, 128 x 128 each: 16 accumulators
@@ -929,7 +935,7 @@ struct BwdWorkspace {
     size_t cvec, as[3], gt, xt, qt, dwp, dxp, total;
 };
 
-static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr) {
+static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr, const DxPlan &dx, const DwPlan &dw) {
     BwdWorkspace w;
     size_t o = 0;
     w.cvec = o;
@@ -947,9 +953,12 @@ static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr) {
     o += align256(m32 * K * 2);
     // dX is done before dW begins: their partial sums share their place
     w.dxp = w.dwp = o;
-    o += align256(std::max(dw_plan(M, N, K, 1).part_bytes, dx_plan(M, N, K, nr).part_bytes));
+    o += align256(std::max(dw.part_bytes, dx.part_bytes));
     w.total = o;
     return w;
+}
+static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr) {
+    return bwd_layout(M, N, K, nr, dx_plan(M, N, K, nr), dw_plan(M, N, K, 1));
 }
 
 static mq_status check_rs(const int *rs, int nr) {
@@ -1146,8 +1155,13 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
     }
     if (!aligned16(X) || !aligned16(Q) || !aligned16(alpha) || !aligned16(zero)) return MQ_ERR_ALIGN;
     if (check_only) return MQ_OK;  // every argument but the workspace is fine
-    const FwdSplitPlan plan = tiled_only ? FwdSplitPlan{} : fwd_split_plan(M, N, K, nr, loss != nullptr);
-    const FwdWorkspace lay = fwd_layout(M, N, plan, loss != nullptr);
+    FwdSplitPlan plan = tiled_only ? FwdSplitPlan{} : fwd_split_plan(M, N, K, nr, loss != nullptr);
+    FwdWorkspace lay = fwd_layout(M, N, plan, loss != nullptr);
+    if (plan.mb && ws_bytes < lay.total) {
+        // a workspace that was made for more tokens, where K is not cut, still serves fewer
+        plan = FwdSplitPlan{};
+        lay = fwd_layout(M, N, plan, loss != nullptr);
+    }
     if (!ws || ws_bytes < lay.total || !aligned16(ws)) return MQ_ERR_WORKSPACE;
     uint8_t *base = static_cast<uint8_t *>(ws);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1321,22 +1335,26 @@ static mq_status launch_prep(PrepArgs &p, bool gated, hipStream_t st) {
 struct EachWorkspace {
     size_t gt_step, xt, dwp, total;  // gt_step in bytes
 };
-static EachWorkspace each_layout(int64_t M, int64_t N, int64_t K, int nr) {
+static EachWorkspace each_layout(int64_t M, int64_t N, int64_t K, int nr, const DwPlan &dw) {
     EachWorkspace w;
     const size_t m32 = ((size_t)M + 31) & ~(size_t)31;
     w.gt_step = align256(m32 * N * 2);
     w.xt = w.gt_step * nr;
     w.dwp = w.xt + align256(m32 * K * 2);
-    w.total = w.dwp + align256(dw_plan(M, N, K, nr).part_bytes);
+    w.total = w.dwp + align256(dw.part_bytes);
     return w;
 }
 
-size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr) { return each_layout(M, N, K, nr).total; }
+size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr, bool least) {
+    return each_layout(M, N, K, nr, least ? dw_plan_whole(N, K, nr) : dw_plan(M, N, K, nr)).total;
+}
 
 // (no argument checks: the caller has made those of mq_linear_bwd)
 mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lambda, int64_t M, int64_t N, int64_t K, int nr,
-                  float *G, uint8_t *ws, hipStream_t st) {
-    const EachWorkspace lay = each_layout(M, N, K, nr);
+                  float *G, uint8_t *ws, size_t ws_bytes, hipStream_t st) {
+    DwPlan cut = dw_plan(M, N, K, nr);
+    if (ws_bytes < each_layout(M, N, K, nr, cut).total) cut = dw_plan_whole(N, K, nr);
+    const EachWorkspace lay = each_layout(M, N, K, nr, cut);
     PrepArgs p{};
     for (int i = 0; i < nr; ++i) {
         p.dY[i] = dY[i];
@@ -1365,7 +1383,7 @@ mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lam
     w.K = (int)K;
     w.ldm = p.ldm;
     w.accumulate = 0;
-    return launch_dw(w, dw_plan(M, N, K, nr), st);
+    return launch_dw(w, cut, st);
 }
 
 // gated: the output gradients come from GU and dA (see PrepArgs) instead of dY
@@ -1413,10 +1431,20 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     if ((dX && !aligned16(dX)) || (dW && !aligned16(dW)) || (X && !aligned16(X)) || (Q && !aligned16(Q)) ||
         (alpha && !aligned16(alpha)) || (zero && !aligned16(zero)))
         return MQ_ERR_ALIGN;
-    if (!ws || ws_bytes < mq_workspace_bytes(MQ_OP_LINEAR_BWD, M, N, K, nr) || !aligned16(ws))
-        return MQ_ERR_WORKSPACE;
+    // (a workspace that was made for more tokens may be too small for the partial sums of fewer: then nothing is cut)
+    DxPlan dx_cut = dx_plan(M, N, K, nr);
+    DwPlan dw_cut = dw_plan(M, N, K, 1);
+    BwdWorkspace lay = bwd_layout(M, N, K, nr, dx_cut, dw_cut);
+    if (ws_bytes < lay.total + 256) {
+        if (dx_cut.part_bytes) dx_cut = DxPlan{5, 1, 0};
+        lay = bwd_layout(M, N, K, nr, dx_cut, dw_cut);
+    }
+    if (ws_bytes < lay.total + 256) {
+        if (dw_cut.part_bytes) dw_cut = dw_plan_whole(N, K, 1);
+        lay = bwd_layout(M, N, K, nr, dx_cut, dw_cut);
+    }
+    if (!ws || ws_bytes < lay.total + 256 || !aligned16(ws)) return MQ_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const BwdWorkspace lay = bwd_layout(M, N, K, nr);
     uint8_t *base = static_cast<uint8_t *>(ws);
     const bool ep = flags & MQ_FLAG_EXTRA_PRECISION;
 
@@ -1475,7 +1503,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         d.N = (int)N;
         d.K = (int)K;
         d.part = reinterpret_cast<float *>(base + lay.dxp);
-        const mq_status ds = launch_dx(d, dx_plan(M, N, K, nr), nr, has8 != 0, ep, st);
+        const mq_status ds = launch_dx(d, dx_cut, nr, has8 != 0, ep, st);
         if (ds != MQ_OK) return ds;
     }
     if (dW) {
@@ -1490,8 +1518,8 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         w.ldm = p.ldm;
         w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
         w.gt_step = 0;
-        const mq_status ws_ = launch_dw(w, dw_plan(M, N, K, 1), st);
-        if (ws_ != MQ_OK) return ws_;
+        const mq_status dws = launch_dw(w, dw_cut, st);
+        if (dws != MQ_OK) return dws;
     }
     return launch_status();
 }
