@@ -2,7 +2,7 @@
 //
 // Forward (MatQuant objective, section 3.2: the same input goes through the layer once per
 // bit-width): ONE pass over X and the int8 codes.  A workgroup (256 threads, one wave per SIMD) owns
-// 128 output channels x 32 MB tokens (MB = 4 or 5); four LDS stages of a [32 MB x 64] bf16 tile of X
+// 128 output channels x 32 MB tokens (MB = 2 .. 6); four LDS stages of a [32 MB x 64] bf16 tile of X
 // and a [128 x 64] tile of int8 codes are filled by direct global->LDS loads, every wave turns the
 // codes of its 32 channels into one bf16 operand per requested bit-width in registers and issues
 // 32x32x16 MFMAs into one accumulator set per bit-width.
@@ -16,7 +16,7 @@
 //
 // Epilogue: Y = alpha_n * (2^s * acc - (2^s * 128 + z_n) * sum_k X[m,k]).
 //
-// Backward (identity STE): dX reuses the same in-register slicing on a transposed copy of the
+// Backward (identity STE): dX (mq_linear_wide.hip) reuses the in-register slicing on a transposed copy of the
 // codes, with one pre-scaled gradient operand per bit-width accumulated into a single accumulator;
 // dW is a plain bf16 GEMM of the lambda-weighted gradient sum against X.
 #include <algorithm>
