@@ -129,6 +129,9 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
             y[i] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
         }
         const size_t at = (size_t)m * a.N + n;
+        u32x2 t = {0u, 0u};  // read before an output is written: a caller may let one take the target's place
+        if constexpr (LOSS)
+            if (a.T) t = *reinterpret_cast<const u32x2 *>(a.T + at);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (a.Y[i]) *reinterpret_cast<u32x2 *>(a.Y[i] + at) = y[i];
@@ -142,8 +145,6 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
                 }
         }
         if constexpr (LOSS) {
-            u32x2 t = {0u, 0u};
-            if (a.T) t = *reinterpret_cast<const u32x2 *>(a.T + at);
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
                 u32x2 ref = t;

@@ -80,3 +80,19 @@ def test_split_forward_exact(mq):
         s = 8 - r
         code = ((q + ((1 << s) >> 1)) >> s).clamp(max=(1 << r) - 1) << s
         assert torch.equal(y.float().cpu(), code[:, hot].t().float()), r
+
+
+@pytest.mark.parametrize("rs,mix", [((4,), False), ((8, 4, 2), False), ((8, 4, 2), True)])
+def test_output_in_the_place_of_the_target(mq, rs, mix):
+    """An output may be stored over the target: every element of the target is read before its place is written."""
+    M, N, K = 77, 528, 4096
+    Q, a, z = mq.mq_quantize_int8(_randn(1, N, K, scale=0.02).cuda())
+    X, T = _randn(2, M, K).to(torch.bfloat16).cuda(), _randn(3, M, N).to(torch.bfloat16).cuda()
+    teacher = [-1] + [0] * (len(rs) - 1)
+    want_l, want = mq.mq_linear_fwd_multi_l2(X, Q, a, z, rs, T, teacher, None, mix)
+    Y = mq.mq_linear_fwd_multi(X, Q, a, z, rs)
+    over = T.clone()
+    losses, dY = mq.mq_linear_fwd_multi_l2(X, Q, a, z, rs, over, teacher, None, mix, Y=[over] + [None] * (len(rs) - 1))
+    assert torch.equal(over, Y[0]) and torch.equal(losses, want_l)
+    for i in range(len(rs)):
+        assert torch.equal(dY[i], want[i]), rs[i]
