@@ -373,7 +373,7 @@ struct FwdSplitPlan {
     size_t rs_bytes;      // per-token sums of X per range
     int64_t loss_blocks;  // workgroups of the finishing kernel (rows of FwdArgs::partial)
 };
-FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss);
+FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr);
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part,
                            float *rs_part, hipStream_t st, int64_t *blocks);
 

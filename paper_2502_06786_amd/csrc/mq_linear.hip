@@ -1091,7 +1091,7 @@ extern "C" size_t mq_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, in
         return M < 1 || M > 16 || N < 0 || K < 1 || nr < 1 || nr > 8 ? 0 : std::max<size_t>(256, gemv_split_workspace_bytes(M, N, K, nr));
     if (M < 0 || N < 0 || K < 0 || nr < 1 || nr > 3) return 0;
     if (op == MQ_OP_LINEAR_FWD || op == MQ_OP_LINEAR_FWD_L2)
-        return fwd_layout(M, N, fwd_split_plan(M, N, K, nr, op == MQ_OP_LINEAR_FWD_L2), op == MQ_OP_LINEAR_FWD_L2).total;
+        return fwd_layout(M, N, fwd_split_plan(M, N, K, nr), op == MQ_OP_LINEAR_FWD_L2).total;
     if (op == MQ_OP_LINEAR_BWD) return bwd_layout(M, N, K, nr).total + 256;
     if (op == MQ_OP_FFN_DECODE) return ffn_workspace_bytes(M, N, K);
     if (op == MQ_OP_L2_LOSS) return loss_workspace_bytes(M, N);
@@ -1155,7 +1155,7 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
     }
     if (!aligned16(X) || !aligned16(Q) || !aligned16(alpha) || !aligned16(zero)) return MQ_ERR_ALIGN;
     if (check_only) return MQ_OK;  // every argument but the workspace is fine
-    FwdSplitPlan plan = tiled_only ? FwdSplitPlan{} : fwd_split_plan(M, N, K, nr, loss != nullptr);
+    FwdSplitPlan plan = tiled_only ? FwdSplitPlan{} : fwd_split_plan(M, N, K, nr);
     FwdWorkspace lay = fwd_layout(M, N, plan, loss != nullptr);
     if (plan.mb && ws_bytes < lay.total) {
         // a workspace that was made for more tokens, where K is not cut, still serves fewer

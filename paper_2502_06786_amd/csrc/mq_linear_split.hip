@@ -241,14 +241,18 @@ mq_status launch_finish(const FwdSplitArgs &s, int mb, bool loss, hipStream_t st
 // 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths): the choice is 1.5 % slower than the best of them
 // on average.  Measured, tiled -> chosen: 4096 x 4096, 77 tokens, int4 37.6 -> 15.7 us; 4096 x 14336 117 -> 26 us;
 // 2304 x 9216 at r = 8/4/2, 203 tokens 125 -> 44 us; level with the tiled kernel at 600 (14336 rows: 130) tokens and more.
-static FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss) {
+//
+// The objective does not enter the rule, although its calls have no wide tiles to fall back on: the sums of a call with the
+// objective have to run in the order of those of the call without.  It costs the former 4 % (at most 11 %) on the one size in
+// 450 of 896 .. 14336 squared and 17 .. 2048 tokens, at one bit-width, where the wide tiles beat the cut (by 8 %).
+static FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
     FwdSplitPlan best{0, 0, 0, 0, 0};
     if (M < 1 || N < 1 || M > 2048) return best;
     const int64_t tiles_n = cdiv(N, FWD_BN), nkt = cdiv(K, BKT);
     // with its row-sum pre-pass (for three bit-widths less the margin by which the fits of the two forms are apart)
     double best_cost = kFwdCycleNs * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + (nr == 3 ? (double)M * K / 2000.0 - 500.0 : 4600.0);
     double wide;
-    if (nr == 1 && !loss && fwd_wide_mb(M, N, K, &wide)) best_cost = std::min(best_cost, wide + 4600.0);
+    if (nr == 1 && fwd_wide_mb(M, N, K, &wide)) best_cost = std::min(best_cost, wide + 4600.0);
     for (int mb = 1; mb <= 4; ++mb) {
         const int64_t tiles_m = cdiv(M, 32 * mb), tiles = tiles_m * tiles_n;
         if (mb > 1 && tiles_m == cdiv(M, 32 * (mb - 1))) continue;
@@ -278,8 +282,8 @@ static FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr, boo
     return best;
 }
 
-FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr, bool loss) {
-    return remembered<FwdSplitPlan>(make_split_plan, M, N, K, nr, loss);
+FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
+    return remembered<FwdSplitPlan>(make_split_plan, M, N, K, nr);
 }
 
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part, float *rs_part,

@@ -96,3 +96,15 @@ def test_output_in_the_place_of_the_target(mq, rs, mix):
     assert torch.equal(over, Y[0]) and torch.equal(losses, want_l)
     for i in range(len(rs)):
         assert torch.equal(dY[i], want[i]), rs[i]
+
+
+@pytest.mark.parametrize("M,N,K", [(443, 11472, 4608), (416, 11008, 4096), (77, 4096, 4096)])
+def test_objective_at_one_bit_width(mq, M, N, K):
+    """The dY of the fused call are those of the two calls in sequence, bit for bit, also where the plain forward takes the
+    256-channel tiles that the objective does not have (the first two sizes)."""
+    Q, a, z = mq.mq_quantize_int8(_randn(M, N, K, scale=0.02).cuda())
+    X, T = _randn(2, M, K).to(torch.bfloat16).cuda(), _randn(3, M, N).to(torch.bfloat16).cuda()
+    Y = mq.mq_linear_fwd_multi(X, Q, a, z, (4,))
+    _, want = mq.mq_matquant_l2_loss(Y, T)
+    _, dY = mq.mq_linear_fwd_multi_l2(X, Q, a, z, (4,), T)
+    assert torch.equal(dY[0], want[0])
