@@ -324,7 +324,9 @@ mq_status mq_linear_fwd_multi_l2(const uint16_t *X, const uint8_t *Q, const floa
  *   dY, lambda, rs, nr  as for mq_linear_bwd
  *   dgamma, dbeta  [N] fp32 out;  dalpha, dzero  [N] fp32 out or NULL (the gradients with respect to
  *            alpha and z, before the chain rule)
- *   ws       workspace of at least mq_workspace_bytes(MQ_OP_LINEAR_BWD_CLIP, M, N, K, nr)
+ *   ws       workspace of at least mq_workspace_bytes(MQ_OP_LINEAR_BWD_CLIP, M, N, K, nr), most of it one fp32
+ *            matrix [N, K] per bit-width; that of one bit-width (nr = 1) is also accepted: the bit-widths
+ *            are then taken one after the other, which is slower
  * Alignment and size limits as for mq_linear_bwd.  N == 0 is a no-op; M == 0 writes zeros.
  */
 mq_status mq_linear_bwd_clip(const float *W, int64_t ldw, const uint16_t *X, const uint8_t *Q,

@@ -9,7 +9,8 @@
 // own dY_r^T X contraction (the matrix-core kernel of the backward over the tiles of all of them, into
 // scratch matrices), followed by one row reduction against the coefficients (HBM-bound: 4 + 1 + 4 nr bytes
 // per weight).  One preparation, one round-up of tiles and one pass over W and Q instead of one per bit-width:
-// 486 -> 344 us of kernel time for 1999 tokens through 2304 x 9216 at r = 8/4/2.
+// 486 -> 344 us of kernel time for 1999 tokens through 2304 x 9216 at r = 8/4/2.  A workspace with room for one scratch matrix
+// (that of a call with one bit-width) serves the bit-widths one after the other, their sums over a channel kept in fp64.
 #include <algorithm>
 
 #include "mq_common.h"
@@ -25,6 +26,8 @@ struct ClipArgs {
     const float *alpha, *zero;
     const float *gamma, *beta;  // [N] or null (= 1)
     float *dgamma, *dbeta, *dalpha, *dzero;
+    double *acc;          // [N][2]: d alpha, d z of the launches before this one
+    int first, last;      // of the launches of a call
     int64_t ldw;
     int N, K;
     int r[3], ep;
@@ -94,6 +97,15 @@ __global__ __launch_bounds__(256) void clip_reduce_kernel(ClipArgs a) {
     if (threadIdx.x != 0) return;
     da = red[0][0] + red[1][0] + red[2][0] + red[3][0];
     dz = red[0][1] + red[1][1] + red[2][1] + red[3][1];
+    if (!a.first) {
+        da += a.acc[2 * n];
+        dz += a.acc[2 * n + 1];
+    }
+    if (!a.last) {
+        a.acc[2 * n] = da;
+        a.acc[2 * n + 1] = dz;
+        return;
+    }
     const double lo = fmin(fmin(red[0][2], red[1][2]), fmin(red[2][2], red[3][2]));
     const double hi = fmax(fmax(red[0][3], red[1][3]), fmax(red[2][3], red[3][3]));
     // chain rule through alpha(gamma, beta) and z(beta, alpha), with beta min = -z alpha.  A row whose
@@ -152,8 +164,15 @@ extern "C" mq_status mq_linear_bwd_clip(const float *W, int64_t ldw, const uint1
         if (!dY[i]) return MQ_ERR_NULL;
     if (!aligned16(W) || !aligned16(Q)) return MQ_ERR_ALIGN;
     // (a workspace that was made for more tokens may be too small for the partial tiles of fewer: dw_each then cuts nothing)
-    const size_t g_bytes = align256((size_t)N * K * 4 * nr);
-    if (!ws || ws_bytes < g_bytes + dw_each_bytes(M, N, K, nr, true) + 512 || !aligned16(ws)) return MQ_ERR_WORKSPACE;
+    int at_once = nr;
+    size_t g_bytes = align256((size_t)N * K * 4 * nr), acc_bytes = 0;
+    if (nr > 1 && ws_bytes < g_bytes + dw_each_bytes(M, N, K, nr, true) + 512) {
+        at_once = 1;
+        g_bytes = align256((size_t)N * K * 4);
+        acc_bytes = align256((size_t)N * 2 * sizeof(double));  // (inside the room of one bit-width's backward, which holds N K codes)
+    }
+    const size_t used = g_bytes + acc_bytes;
+    if (!ws || ws_bytes < used + dw_each_bytes(M, N, K, at_once, true) + 512 || !aligned16(ws)) return MQ_ERR_WORKSPACE;
     if (M > 0) {
         if (!aligned16(X)) return MQ_ERR_ALIGN;
         for (int i = 0; i < nr; ++i)
@@ -167,9 +186,6 @@ extern "C" mq_status mq_linear_bwd_clip(const float *W, int64_t ldw, const uint1
         clip_zero_kernel<<<dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st>>>(dgamma, dbeta, dalpha, dzero, (int)N);
         return launch_status();
     }
-    // G_r = lambda_r dY_r^T X for all bit-widths, through the dW path of the backward
-    mq_status s = dw_each(X, dY, lambda, M, N, K, nr, G, base + g_bytes, ws_bytes - g_bytes - 256, st);
-    if (s != MQ_OK) return s;
     ClipArgs a{};
     a.W = W;
     a.Q = Q;
@@ -185,13 +201,22 @@ extern "C" mq_status mq_linear_bwd_clip(const float *W, int64_t ldw, const uint1
     a.ldw = ldw;
     a.N = (int)N;
     a.K = (int)K;
-    for (int i = 0; i < nr; ++i) a.r[i] = rs[i];
+    a.acc = reinterpret_cast<double *>(base + g_bytes);
     a.ep = (flags & MQ_FLAG_EXTRA_PRECISION) ? 1 : 0;
-    if (nr == 1)
-        clip_reduce_kernel<1><<<dim3((unsigned)N), dim3(256), 0, st>>>(a);
-    else if (nr == 2)
-        clip_reduce_kernel<2><<<dim3((unsigned)N), dim3(256), 0, st>>>(a);
-    else
-        clip_reduce_kernel<3><<<dim3((unsigned)N), dim3(256), 0, st>>>(a);
-    return launch_status();
+    for (int i0 = 0; i0 < nr; i0 += at_once) {
+        // G_r = lambda_r dY_r^T X for the bit-widths at hand, through the dW path of the backward
+        mq_status s = dw_each(X, dY + i0, lambda ? lambda + i0 : nullptr, M, N, K, at_once, G, base + used, ws_bytes - used - 256, st);
+        if (s != MQ_OK) return s;
+        for (int i = 0; i < at_once; ++i) a.r[i] = rs[i0 + i];
+        a.first = i0 == 0;
+        a.last = i0 + at_once == nr;
+        if (at_once == 1)
+            clip_reduce_kernel<1><<<dim3((unsigned)N), dim3(256), 0, st>>>(a);
+        else if (at_once == 2)
+            clip_reduce_kernel<2><<<dim3((unsigned)N), dim3(256), 0, st>>>(a);
+        else
+            clip_reduce_kernel<3><<<dim3((unsigned)N), dim3(256), 0, st>>>(a);
+        if ((s = launch_status()) != MQ_OK) return s;
+    }
+    return MQ_OK;
 }

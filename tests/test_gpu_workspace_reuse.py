@@ -52,3 +52,25 @@ def test_smaller_calls(mq, M, most):
         mq.mq_linear_bwd(X, Q, a, z, dY, None, rs, ws=short)
     with pytest.raises(mq.MqError):
         mq.mq_linear_bwd_clip(W, X, Q, a, z, dY, None, rs, ones, ones, ws=short)
+
+
+@pytest.mark.parametrize("rs", [(8, 4, 2), (3, 8)])
+def test_clip_gradients_with_one_matrix(mq, rs):
+    """The workspace of one bit-width serves several, one after the other."""
+    M, N, K = 300, 272, 1040
+    g = torch.Generator().manual_seed(5)
+    W = (torch.randn(N, K, generator=g) * 0.02).cuda()
+    X = torch.randn(M, K, generator=g).to(torch.bfloat16).cuda()
+    dY = [(torch.randn(M, N, generator=g) * 1e-3).to(torch.bfloat16).cuda() for _ in rs]
+    gamma, beta = torch.rand(N, generator=g).cuda() * 0.2 + 0.8, torch.rand(N, generator=g).cuda() * 0.2 + 0.8
+    Q, a, z = mq.mq_quantize_int8(W, gamma, beta)
+    args = W, X, Q, a, z, dY, [0.5 + 0.25 * i for i in range(len(rs))], rs, gamma, beta
+    want = mq.mq_linear_bwd_clip(*args, want_dalpha_dzero=True)
+    one = mq.mq_workspace_bytes(mq.MQ_OP_LINEAR_BWD_CLIP, M, N, K, 1)
+    assert one < mq.mq_workspace_bytes(mq.MQ_OP_LINEAR_BWD_CLIP, M, N, K, len(rs)) - N * K * 4 + 1
+    for bytes_ in (one, N * K * 4 + 2 * (N + K) * 320 + 16 * N + 1024):   # (the second: nothing is cut along the tokens)
+        got = mq.mq_linear_bwd_clip(*args, want_dalpha_dzero=True, ws=torch.empty(bytes_, dtype=torch.uint8, device="cuda"))
+        for x, y in zip(got, want):
+            _close(x, y, 1e-5)   # fp32 sums of M terms in another order
+    with pytest.raises(mq.MqError):
+        mq.mq_linear_bwd_clip(*args, ws=torch.empty(N * K * 4, dtype=torch.uint8, device="cuda"))
