@@ -4,9 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <atomic>
-
 #include "../../include/mq.h"
+#include "mq_lds.h"
 
 namespace mq {
 
@@ -45,21 +44,15 @@ inline mq_status launch_status() { return hipGetLastError() == hipSuccess ? MQ_O
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Lets `kern` use `bytes` of dynamic LDS on the current device.  The attribute is set once per kernel, size and device.
+// Lets `Kern` use `bytes` of dynamic LDS on the current device.  The runtime is asked once per kernel, size and device.
 template <auto Kern>
 bool allow_lds(int bytes) {
-    static std::atomic<int> allowed[64];  // per device: the largest size granted so far
+    static LdsGrants grants;
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return false;
-    if (dev < 64 && allowed[dev].load(std::memory_order_acquire) >= bytes) return true;
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(Kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
-        return false;
-    if (dev < 64) {
-        int old = allowed[dev].load(std::memory_order_relaxed);
-        while (old < bytes && !allowed[dev].compare_exchange_weak(old, bytes, std::memory_order_release)) {
-        }
-    }
-    return true;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    return grants.ensure(dev, bytes, [](int b) {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(Kern), hipFuncAttributeMaxDynamicSharedMemorySize, b) == hipSuccess;
+    });
 }
 
 // The last few plans of a thread by their sizes: a plan is the best of up to a hundred modelled cuts, and a call asks for

@@ -204,6 +204,13 @@ __global__ __launch_bounds__(1024) void ovf_sum_kernel(OvfArgs a) {
     }
 }
 
+template <int BP>
+mq_status launch_ovf_sum_bp(const OvfArgs &a, int grid, size_t lds, hipStream_t st) {
+    if (lds > 65536 && !allow_lds<ovf_sum_kernel<BP>>((int)lds)) return MQ_ERR_DEVICE;
+    ovf_sum_kernel<BP><<<dim3(grid), dim3(1024), lds, st>>>(a);
+    return launch_status();
+}
+
 }  // namespace
 
 // Enqueues the kernel above: y[b, n] <- ovf_sum_pack(sum of x[b, k] over the overflow columns of row n).  K <= 65536.
@@ -234,19 +241,12 @@ mq_status launch_overflow_sums(const uint16_t *x, const int32_t *row_ptr, const 
     grid = (int)cdiv(N, a.rows_per_wg);
     const size_t lds = xt_bytes + ((size_t)a.rows_per_wg + 1) * 4;
     if (lds > 160 * 1024) return MQ_ERR_SHAPE;  // (cannot happen: N < 2^31 rows over 256 workgroups would need K * B beyond the cap above)
-    auto go = [&](auto kern) -> mq_status {
-        if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds) != hipSuccess)
-            return MQ_ERR_DEVICE;
-        kern<<<dim3(grid), dim3(1024), lds, st>>>(a);
-        return launch_status();
-    };
     switch (bp) {
-        case 16: return go(ovf_sum_kernel<16>);
-        case 8: return go(ovf_sum_kernel<8>);
-        case 4: return go(ovf_sum_kernel<4>);
-        case 2: return go(ovf_sum_kernel<2>);
-        default: return go(ovf_sum_kernel<1>);
+        case 16: return launch_ovf_sum_bp<16>(a, grid, lds, st);
+        case 8: return launch_ovf_sum_bp<8>(a, grid, lds, st);
+        case 4: return launch_ovf_sum_bp<4>(a, grid, lds, st);
+        case 2: return launch_ovf_sum_bp<2>(a, grid, lds, st);
+        default: return launch_ovf_sum_bp<1>(a, grid, lds, st);
     }
 }
 
