@@ -6,6 +6,7 @@
 
 #include "../../include/mq.h"
 #include "mq_lds.h"
+#include "mq_plan.h"
 
 namespace mq {
 
@@ -40,9 +41,6 @@ __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 inline mq_status launch_status() { return hipGetLastError() == hipSuccess ? MQ_OK : MQ_ERR_DEVICE; }
-
-inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
-inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Lets `Kern` use `bytes` of dynamic LDS on the current device.  The runtime is asked once per kernel, size and device.
 template <auto Kern>

@@ -10,7 +10,6 @@ namespace mq {
 
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
-constexpr int BKT = 64;                  // contraction elements per LDS stage
 constexpr uint32_t kOOB = 0x80000000u;   // buffer offset beyond any descriptor built here
 constexpr uint32_t kMagic128 = 0x43004300u;
 
@@ -152,10 +151,6 @@ struct FwdArgs {
     uint16_t *A[3];
     int gate;
 };
-
-constexpr int FWD_BN = 128;
-constexpr int FWD_Q_TILE = FWD_BN * 64;
-constexpr int FWD_STAGES = 4;
 
 // The contraction of one workgroup: acc[i][j] = sum over k in [64 kt0, k_end) of code_i[channels of this wave][k] *
 // X[tokens m0 + 32 j ..][k], for all bit-widths i and token blocks j of the tile at (m0, n0).  Four waves; wave w owns
@@ -358,21 +353,7 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
 }
 
-// 32-token blocks per workgroup of the tiled forward kernel: the accumulators (16 NR MB registers) must leave room for
-// the operands
-constexpr int fwd_mb(int nr) { return nr == 3 ? 5 : 6; }
-// modelled cost (matrix-core cycles) of the tiled forward kernel at its best tile height, which goes to *mb unless null, and
-// the ns of such a cycle
-constexpr double kFwdCycleNs = 0.47;
-int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb);
-
-// How the forward for few tokens cuts its work (mq_linear_split.hip); mb == 0: whole contractions are the better choice.
-struct FwdSplitPlan {
-    int mb, splits;       // 32-token blocks per workgroup, K ranges
-    size_t part_bytes;    // fp32 accumulators of all ranges
-    size_t rs_bytes;      // per-token sums of X per range
-    int64_t loss_blocks;  // workgroups of the finishing kernel (rows of FwdArgs::partial)
-};
+// the forward for few tokens (mq_linear_split.hip): its cut, remembered, and its launches (plan.mb != 0)
 FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr);
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part,
                            float *rs_part, hipStream_t st, int64_t *blocks);
@@ -393,15 +374,8 @@ struct DxArgs {
     float *part;            // splits > 1: fp32 accumulators, [split][tile][k block][token block][g][256] quads
 };
 
-// How dX cuts its work; splits == 1: no partial sums.
-struct DxPlan {
-    int mb, splits;     // 32-token blocks per workgroup, ranges of n
-    size_t part_bytes;  // fp32 accumulators of all ranges
-};
 DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr);
-// The forward at one bit-width (plain or gated) with 32 mb x 256 tiles, 3 <= mb <= 6.  fwd_wide_mb: the better mb, or 0 where
-// the tiles of fwd_kernel are faster; *ns = modelled time of the choice.
-int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns);
+// the forward at one bit-width (plain or gated), mb as fwd_wide_mb has chosen it
 mq_status launch_fwd_wide(const FwdArgs &f, int mb, bool has8, bool ep, hipStream_t st);
 mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st);
 

@@ -623,73 +623,7 @@ struct DwArgs {
                          // operand is that many times gt_step elements after GT and whose result N K after dW
 };
 
-constexpr int DW_BM = 32;                            // contraction elements (tokens) per stage: 64-byte rows
-constexpr int DW_NST = 5;                            // LDS stages
-constexpr int dw_side(int hb) { return 64 * hb; }    // rows of n and columns of k per workgroup: 2 x 2 waves of hb 32-blocks
-constexpr int dw_lds(int hb) { return DW_NST * 2 * dw_side(hb) * 64; }
-constexpr int DW_CUS = 256;                          // compute units a round of workgroups fills
-
-// How the tiles of dW (of `batch` gradients together) are dealt to workgroups.  Two sizes of tile: 256 x 256 (hb = 4) has the
-// smaller operand traffic per product, 128 x 128 (hb = 2) four times as many tiles, two of which fit a compute unit.  Whole
-// rounds of 256 x 256 tiles run one tile per workgroup; the tiles of a last partial round (at most half a round) are cut
-// along the tokens into `parts` ranges each, so that the round still occupies every compute unit for 1 / parts of a tile's
-// time.  Where the tiles do not fill one round all of them may be cut.  The ranges leave fp32 partial tiles in the workspace
-// and dw_reduce_kernel adds them in a fixed order.
-//
-// The choice is the least modelled time (cycles): a 32-token stage takes 1045 per 256-tile; of 128-tiles, 742 for two on a
-// compute unit, 437 for one; a tile ends in 10700 (2100); a cut costs 1300, 2230 per range and a cycle per 4780 bytes of
-// partial tiles written and read back.  The constants are a fit to 900 timed combinations (10 layers of 256 x 256 to
-// 14336 x 4096, 16 to 8192 tokens); the choice is 0.3 % slower than the best of them on average, 10 % at worst.  dW with its
-// preparation, 256-tiles -> chosen: 256 x 256, 16 tokens 12.5 -> 8.7 us, 4096 tokens 84 -> 24 us; 2000 x 1008, 400 tokens 23
-// -> 14 us; 2304 x 2304, 2000 tokens 60 -> 45 us; 6400 x 1104, 4096 tokens 117 -> 93 us; 2304 x 9216, 1200 tokens 90 -> 80 us,
-// 4096 tokens the same (201 us).
-struct DwPlan {
-    int hb, tiles_n, tiles_k, whole, rest, parts;
-    size_t part_bytes;
-};
-static DwPlan make_dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
-    DwPlan best{};
-    double best_cost = 0;
-    const int64_t stages = cdiv(M, DW_BM);
-    const int64_t max_parts = std::max<int64_t>(1, stages / 8);  // at least eight stages per range
-    for (int hb = 4; hb >= 2; hb -= 2) {
-        const int side = dw_side(hb);
-        const int64_t tiles_n = cdiv(N, side), tiles_k = cdiv(K, side), tiles = tiles_n * tiles_k * batch;
-        auto rounds = [&](int64_t items, int64_t st) {
-            const int64_t per_cu = cdiv(items, DW_CUS);
-            if (hb == 4) return per_cu * (1045.0 * st + 10700.0);
-            return (per_cu / 2 * 742.0 + per_cu % 2 * 437.0) * st + per_cu * 2100.0;
-        };
-        auto consider = [&](int64_t rest, int64_t parts) {
-            const size_t bytes = (size_t)rest * parts * side * side * 4;
-            double cost = rounds(tiles - rest, stages);
-            if (rest > 0) cost += rounds(rest * parts, cdiv(stages, parts)) + 1300.0 + 2230.0 * parts + 2.0 * bytes / 4780.0;
-            if (best_cost == 0 || cost < best_cost) {
-                best_cost = cost;
-                best = DwPlan{hb, (int)tiles_n, (int)tiles_k, (int)(tiles - rest), (int)rest, (int)parts, bytes};
-            }
-        };
-        const int64_t over = tiles % DW_CUS;
-        if (tiles < DW_CUS) {
-            for (int64_t parts = 2; parts <= std::min<int64_t>(8, max_parts); ++parts)
-                if ((size_t)tiles * parts * side * side * 4 <= ((size_t)96 << 20)) consider(tiles, parts);
-        } else if (hb == 4 && over > 0) {
-            const int64_t parts = std::min<int64_t>(DW_CUS / over, max_parts);
-            if (parts >= 2) consider(over, parts);
-        }
-        // a last partial round of 256-tiles that can be cut is cut: whole tiles there cost a full round
-        if (!(hb == 4 && best.rest > 0 && best.whole > 0)) consider(0, 1);
-    }
-    return best;
-}
-
 static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) { return remembered<DwPlan>(make_dw_plan, M, N, K, batch); }
-
-// The cut that needs no workspace.
-static DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
-    const int tiles_n = (int)cdiv(N, dw_side(4)), tiles_k = (int)cdiv(K, dw_side(4));
-    return DwPlan{4, tiles_n, tiles_k, tiles_n * tiles_k * batch, 0, 1, 0};
-}
 
 // Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, one small fenced group of
 // operand work per MFMA), without any code conversion: both operands are bf16 rows with the contraction index
@@ -996,48 +930,6 @@ static mq_status launch_fwd_mb(FwdArgs a, hipStream_t st, int64_t *blocks) {
     if (!allow_lds<fwd_kernel<NR, HAS8, EP, MB, LOSS>>(fwd_lds(MB, NR))) return MQ_ERR_DEVICE;
     fwd_kernel<NR, HAS8, EP, MB, LOSS><<<dim3(a.tiles_m * a.tiles_n), dim3(256), fwd_lds(MB, NR), st>>>(a);
     return launch_status();
-}
-
-// Token-tile height: the tallest tile amortises the code conversion and the epilogue best, but the
-// number of tiles rarely divides evenly over the 256 compute units; one block less can save a whole
-// round of workgroups.  Cost of a choice = rounds x (main loop + epilogue) in matrix-core cycles
-// (32 per MFMA, plus about 180 cycles per 64-wide k stage and bit-width that do not shrink with the tile:
-// conversions and the stage barrier - fitted on the 9B gate shape, where 160 tokens run 2.5-4 % faster than
-// 128 although both fill their rounds; prologue and epilogue constants measured on the Gemma-2-2B shapes).
-//
-// Three bit-widths have the low tiles with two workgroups per compute unit as well, and a cost of their own, a fit to 640 timed
-// combinations (8 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens, plain and with the objective), in ns: a 64-wide
-// stage takes 294 + 159 per token block, for two workgroups together 409 + 367 per block.  The choice, with the form that cuts
-// K, is 0.6 % slower than the best of them on average, 13 % at worst (before: 6.5 %, 75 %).  r = 8/4/2 with the objective:
-// 2000 x 1008, 700 tokens 35.8 -> 23.6 us; 3600 x 3600, 1400 tokens 140 -> 112 us; 12000 x 912, 2011 tokens 167 -> 145 us;
-// 9216 x 2304, 2800 tokens 334 -> 311 us; the high tiles stay for 14336 x 4096, 2011 tokens (568 us).
-int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb) {
-    const int hi = fwd_mb(nr);
-    if (nr == 3) {
-        const double stages = (double)cdiv(K, BKT);
-        double best_ns = 0;
-        for (int h = hi; h >= 2; --h) {
-            const int64_t per_cu = cdiv(cdiv(M, 32 * h) * cdiv(N, FWD_BN), 256);
-            const double ends = 871.0 + 1907.0 * h, alone = stages * (294.0 + 159.0 * h) + ends;
-            const double ns = h > 3 ? per_cu * alone : per_cu / 2 * (stages * (409.0 + 367.0 * h) + 1.4 * ends) + per_cu % 2 * alone;
-            if (h == hi || ns < best_ns) {
-                best_ns = ns;
-                if (mb) *mb = h;
-            }
-        }
-        return (int64_t)(best_ns / kFwdCycleNs);
-    }
-    int64_t best = 0;
-    for (int h = hi; h >= hi - 1; --h) {
-        const int64_t tiles = cdiv(M, 32 * h) * cdiv(N, FWD_BN);
-        const int64_t rounds = cdiv(tiles, 256);
-        const int64_t per_tile = cdiv(K, BKT) * (nr * h * 128 + 180 * nr) + 3000 + 890 * nr * h;
-        if (h == hi || rounds * per_tile < best) {
-            best = rounds * per_tile;
-            if (mb) *mb = h;
-        }
-    }
-    return best;
 }
 
 template <int NR, bool HAS8, bool EP, bool LOSS>

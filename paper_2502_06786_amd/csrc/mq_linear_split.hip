@@ -189,8 +189,6 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
 // ---- host side ------------------------------------------------------------------------------------
 namespace {
 
-constexpr int split_lds(int mb) { return FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE); }
-
 template <int NR, bool HAS8, bool EP, int MB>
 mq_status launch_split_mb(const FwdSplitArgs &s, hipStream_t st) {
     if (!allow_lds<fwd_split_kernel<NR, HAS8, EP, MB>>(split_lds(MB))) return MQ_ERR_DEVICE;
@@ -230,57 +228,6 @@ mq_status launch_finish(const FwdSplitArgs &s, int mb, bool loss, hipStream_t st
 }
 
 }  // namespace
-
-// Which form, and how it is cut: the least modelled time in ns over one to four token blocks per workgroup and up to 16
-// ranges of at least five 64-wide stages, against the tiled kernel.  Per stage a compute unit needs 128 cycles per
-// matrix product row (32 x 64 x 32) and bit-width, 172 per bit-width for the conversions and 50 for the barrier, for each of
-// the workgroups it holds (80 KB of LDS and 256 registers each where two fit), but never less than the 1000 cycles a stage
-// takes to arrive; all workgroups together cannot read codes faster than 2900 or tiles of X faster than 4100 bytes per
-// cycle; a workgroup starts and ends in 4200 cycles; launches and the finishing kernel cost 8500 cycles, 1800 bytes of
-// accumulators take a cycle to be written and read back.  The constants are a fit to 2200 timed combinations (10 layers of
-// 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths): the choice is 1.5 % slower than the best of them
-// on average.  Measured, tiled -> chosen: 4096 x 4096, 77 tokens, int4 37.6 -> 15.7 us; 4096 x 14336 117 -> 26 us;
-// 2304 x 9216 at r = 8/4/2, 203 tokens 125 -> 44 us; level with the tiled kernel at 600 (14336 rows: 130) tokens and more.
-//
-// The objective does not enter the rule, although its calls have no wide tiles to fall back on: the sums of a call with the
-// objective have to run in the order of those of the call without.  It costs the former 4 % (at most 11 %) on the one size in
-// 450 of 896 .. 14336 squared and 17 .. 2048 tokens, at one bit-width, where the wide tiles beat the cut (by 8 %).
-static FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
-    FwdSplitPlan best{0, 0, 0, 0, 0};
-    if (M < 1 || N < 1 || M > 2048) return best;
-    const int64_t tiles_n = cdiv(N, FWD_BN), nkt = cdiv(K, BKT);
-    // with its row-sum pre-pass (for three bit-widths less the margin by which the fits of the two forms are apart)
-    double best_cost = kFwdCycleNs * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + (nr == 3 ? (double)M * K / 2000.0 - 500.0 : 4600.0);
-    double wide;
-    if (nr == 1 && fwd_wide_mb(M, N, K, &wide)) best_cost = std::min(best_cost, wide + 4600.0);
-    for (int mb = 1; mb <= 4; ++mb) {
-        const int64_t tiles_m = cdiv(M, 32 * mb), tiles = tiles_m * tiles_n;
-        if (mb > 1 && tiles_m == cdiv(M, 32 * (mb - 1))) continue;
-        const int resident = std::max(1, std::min(163840 / split_lds(mb), 512 / (16 * nr * mb + 110)));
-        const double busy = nr * mb * 128.0 + 172.0 * nr + 50.0;
-        for (int splits = 1; splits <= 16; ++splits) {
-            const int64_t stages = cdiv(nkt, splits);
-            if (splits > 1 && stages < 5) break;
-            if (splits == 1 && M > 64) continue;
-            const size_t part = (size_t)splits * tiles * nr * mb * 16384;
-            if (part > ((size_t)96 << 20)) break;
-            const int64_t per_cu = cdiv(tiles * splits, 256), full = per_cu / resident, rest = per_cu % resident;
-            double loop = full * std::max(resident * busy, 1000.0) + (rest ? std::max(rest * busy, 1000.0) : 0.0);
-            loop = loop * stages + (full + (rest ? 1 : 0)) * 4200.0;
-            loop = std::max(loop, std::max((double)N * K / 2900.0, (double)tiles * splits * stages * mb * 4096.0 / 4100.0));
-            const double cost = 0.51 * (loop + 8500.0 + part / 1800.0 + 217.0 * splits * nr);
-            if (cost < best_cost) {
-                best_cost = cost;
-                best.mb = mb;
-                best.splits = splits;
-                best.part_bytes = part;
-                best.rs_bytes = (size_t)splits * tiles_m * 32 * mb * 4;
-                best.loss_blocks = tiles * mb * 4;
-            }
-        }
-    }
-    return best;
-}
 
 FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
     return remembered<FwdSplitPlan>(make_split_plan, M, N, K, nr);

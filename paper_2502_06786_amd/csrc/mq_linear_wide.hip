@@ -11,14 +11,6 @@ namespace mq {
 // Rows of the matrix-core product are k (from the transposed codes QT[K, N]), columns are tokens,
 // the contraction runs over n and, within each n tile, over the bit-widths.
 // ============================================================================================
-constexpr int DX_MB = 5;                        // most 32-token blocks per wave
-constexpr int DX_RB = 2;                        // 32-row blocks of k per wave
-constexpr int DX_BK = 4 * 32 * DX_RB;           // k rows per workgroup (4 waves)
-constexpr int DX_Q_TILE = DX_BK * 64;
-constexpr int DX_OS = DX_BK * 2 + 8;            // row stride of the output staging tile
-constexpr int dx_lds(int mb) {                  // four stages; the staging tile of the epilogue is smaller
-    return 4 * (mb * 4096 + DX_Q_TILE);
-}
 static_assert(dx_lds(DX_MB) >= 32 * DX_MB * DX_OS && dx_lds(1) >= 32 * DX_OS, "the staging tile has to fit");
 
 // Same pipeline as the forward kernel (one wave per SIMD, four LDS stages, one small fenced group
@@ -542,68 +534,7 @@ mq_status launch_dx_nrs(const DxArgs &d, int mb, bool has8, bool ep, hipStream_t
 
 }  // namespace
 
-// Tile height and ranges: the least modelled time (cycles) over one to five token blocks per workgroup and up to 16 ranges of
-// n.  160 tokens x 256 k tiles alone leave most compute units idle up to about 2000 tokens (16 tokens through 9216 x 2304 are
-// nine workgroups that walk 432 stages each: 263 us), and a full partial round of low tiles often beats the same round of
-// high ones.  A stage (one n tile, one bit-width) takes 256 cycles per token block for its products and 520 for conversions
-// and the barrier, for each of the workgroups that a compute unit holds (two where the stages of 32 tokens fit twice into its
-// LDS), but never less than the 1055 + 140 per token block it takes to arrive; all workgroups together do not get gradients
-// faster than 3650 or codes faster than 6480 bytes per cycle; a tile's epilogue costs 900 per token block, the finishing
-// launch 4100 and 310 per range, and 1940 bytes of accumulators go out and come back per cycle.  The constants are a fit to
-// 3100 timed combinations (8 layers of 256 x 256 to 14336 x 4096, 16 to 4096 tokens, one and three bit-widths): the choice
-// is 0.4 % slower than the best of them on average, 9 % at worst.  dX with its preparation, 160-token tiles -> chosen, at
-// r = 8/4/2: 9216 x 2304, 16 tokens 263 -> 54 us, 400 tokens 342 -> 96 us, 2000 tokens 371 -> 274 us; 3600 x 3600, 400
-// tokens 160 -> 73 us, 4096 tokens 388 -> 354 us; 256 x 256, 16 tokens 15.6 (32-token tile) -> 13.9 us; the same at
-// 4096 tokens through 9216 x 2304 (499 us).
-static DxPlan make_dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
-    DxPlan best{DX_MB, 1, 0};
-    double best_cost = 0;
-    const int64_t tiles_k = cdiv(K, DX_BK), nnt = cdiv(N, BKT);
-    for (int mb = DX_MB; mb >= 1; --mb) {
-        const int64_t tiles = cdiv(M, 32 * mb) * tiles_k;
-        if (mb > 1 && cdiv(M, 32 * mb) == cdiv(M, 32 * (mb - 1))) continue;  // a lower tile covers as much
-        const int resident = 2 * dx_lds(mb) <= 163840 ? 2 : 1;
-        const double busy = mb * 256.0 + 520.0, arrive = mb * 140.0 + 1055.0;
-        for (int splits = 1; splits <= std::min<int64_t>(16, nnt); ++splits) {
-            const size_t part = splits > 1 ? (size_t)splits * tiles * mb * DX_RB * 16384 : 0;
-            if (splits > 1 && (part > ((size_t)96 << 20) || tiles * splits > 1100)) break;
-            const int64_t per_cu = cdiv(tiles * splits, 256), full = per_cu / resident, rest = per_cu % resident;
-            const int64_t n_stages = cdiv(nnt, splits), stages = n_stages * nr;
-            double cost = full * std::max(resident * busy, arrive) + (rest ? std::max(rest * busy, arrive) : 0.0);
-            cost = cost * stages + per_cu * mb * 900.0;
-            cost = std::max(cost, (double)tiles * splits * (stages * mb * (4096.0 / 3650.0) + n_stages * (16384.0 / 6480.0)));
-            if (splits > 1) cost += 4100.0 + 310.0 * splits + part / 1940.0;
-            if (best_cost == 0 || cost < best_cost) {
-                best_cost = cost;
-                best = DxPlan{mb, splits, part};
-            }
-        }
-    }
-    return best;
-}
-
 DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr) { return remembered<DxPlan>(make_dx_plan, M, N, K, nr); }
-
-// Which tile the forward at one bit-width takes where K is not split: rounds of workgroups times the time of a tile, in ns, a fit
-// to 650 timed combinations (10 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens).  Wide tiles are half as many, so
-// they lose while the narrow ones still fit one round (3600 x 3600, 1000 tokens 45 against 54 us) and win from the second
-// round on; the choice among the five forms is at most 2 % slower than the best of them.  int4, narrow -> chosen: 14336 x 4096,
-// 2011 tokens 256 -> 221 us, 4096 tokens 501 -> 425 us; 2304 x 9216, 4096 tokens 199 -> 168 us; 3600 x 3600, 1600 tokens 82
-// -> 59 us; 2000 x 1008, 4096 tokens 34 -> 28.5 us.
-int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns) {
-    double best = 0.678 * (double)fwd_tiled_cost(M, N, K, 1, nullptr);
-    int choice = 0;
-    for (int mb = 3; mb <= 6; ++mb) {
-        const int64_t rounds = cdiv(cdiv(M, 32 * mb) * cdiv(N, DX_BK), 256);
-        const double t = (double)rounds * ((double)cdiv(K, BKT) * (94.0 * mb + 402.0) + 3870.0 + 824.0 * mb);
-        if (t < best) {
-            best = t;
-            choice = mb;
-        }
-    }
-    if (ns) *ns = best;
-    return choice;
-}
 
 mq_status launch_fwd_wide(const FwdArgs &f, int mb, bool has8, bool ep, hipStream_t st) {
     FwdWideArgs w{};

@@ -1,0 +1,284 @@
+// How the calls of the linear layer are cut into tiles, ranges and rounds: rules on sizes, host arithmetic without HIP.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+namespace mq {
+
+inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+constexpr int BKT = 64;                  // contraction elements per LDS stage
+
+// ============================================================================================
+// forward
+// ============================================================================================
+constexpr int FWD_BN = 128;
+constexpr int FWD_Q_TILE = FWD_BN * 64;
+constexpr int FWD_STAGES = 4;
+
+// 32-token blocks per workgroup of the tiled forward kernel: the accumulators (16 NR MB registers) must leave room for
+// the operands
+constexpr int fwd_mb(int nr) { return nr == 3 ? 5 : 6; }
+constexpr double kFwdCycleNs = 0.47;  // ns per cycle of fwd_tiled_cost
+
+// Token-tile height: the tallest tile amortises the code conversion and the epilogue best, but the
+// number of tiles rarely divides evenly over the 256 compute units; one block less can save a whole
+// round of workgroups.  Cost of a choice = rounds x (main loop + epilogue) in matrix-core cycles
+// (32 per MFMA, plus about 180 cycles per 64-wide k stage and bit-width that do not shrink with the tile:
+// conversions and the stage barrier - fitted on the 9B gate shape, where 160 tokens run 2.5-4 % faster than
+// 128 although both fill their rounds; prologue and epilogue constants measured on the Gemma-2-2B shapes).
+//
+// Three bit-widths have the low tiles with two workgroups per compute unit as well, and a cost of their own, a fit to 640 timed
+// combinations (8 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens, plain and with the objective), in ns: a 64-wide
+// stage takes 294 + 159 per token block, for two workgroups together 409 + 367 per block.  The choice, with the form that cuts
+// K, is 0.6 % slower than the best of them on average, 13 % at worst (before: 6.5 %, 75 %).  r = 8/4/2 with the objective:
+// 2000 x 1008, 700 tokens 35.8 -> 23.6 us; 3600 x 3600, 1400 tokens 140 -> 112 us; 12000 x 912, 2011 tokens 167 -> 145 us;
+// 9216 x 2304, 2800 tokens 334 -> 311 us; the high tiles stay for 14336 x 4096, 2011 tokens (568 us).
+//
+// The result is the modelled cost (matrix-core cycles) at the best tile height, which goes to *mb unless null.
+inline int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb) {
+    const int hi = fwd_mb(nr);
+    if (nr == 3) {
+        const double stages = (double)cdiv(K, BKT);
+        double best_ns = 0;
+        for (int h = hi; h >= 2; --h) {
+            const int64_t per_cu = cdiv(cdiv(M, 32 * h) * cdiv(N, FWD_BN), 256);
+            const double ends = 871.0 + 1907.0 * h, alone = stages * (294.0 + 159.0 * h) + ends;
+            const double ns = h > 3 ? per_cu * alone : per_cu / 2 * (stages * (409.0 + 367.0 * h) + 1.4 * ends) + per_cu % 2 * alone;
+            if (h == hi || ns < best_ns) {
+                best_ns = ns;
+                if (mb) *mb = h;
+            }
+        }
+        return (int64_t)(best_ns / kFwdCycleNs);
+    }
+    int64_t best = 0;
+    for (int h = hi; h >= hi - 1; --h) {
+        const int64_t tiles = cdiv(M, 32 * h) * cdiv(N, FWD_BN);
+        const int64_t rounds = cdiv(tiles, 256);
+        const int64_t per_tile = cdiv(K, BKT) * (nr * h * 128 + 180 * nr) + 3000 + 890 * nr * h;
+        if (h == hi || rounds * per_tile < best) {
+            best = rounds * per_tile;
+            if (mb) *mb = h;
+        }
+    }
+    return best;
+}
+
+// ---- one bit-width, 256-channel tiles (mq_linear_wide.hip) ------------------------------------
+// The tiles are those of dX: DX_BK code rows, four waves of DX_RB blocks each.
+constexpr int DX_MB = 5;                        // most 32-token blocks per wave
+constexpr int DX_RB = 2;                        // 32-row blocks of k per wave
+constexpr int DX_BK = 4 * 32 * DX_RB;           // k rows per workgroup (4 waves)
+constexpr int DX_Q_TILE = DX_BK * 64;
+constexpr int DX_OS = DX_BK * 2 + 8;            // row stride of the output staging tile
+constexpr int dx_lds(int mb) {                  // four stages; the staging tile of the epilogue is smaller
+    return 4 * (mb * 4096 + DX_Q_TILE);
+}
+
+// Which tile the forward at one bit-width takes where K is not split: rounds of workgroups times the time of a tile, in ns, a fit
+// to 650 timed combinations (10 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens).  Wide tiles are half as many, so
+// they lose while the narrow ones still fit one round (3600 x 3600, 1000 tokens 45 against 54 us) and win from the second
+// round on; the choice among the five forms is at most 2 % slower than the best of them.  int4, narrow -> chosen: 14336 x 4096,
+// 2011 tokens 256 -> 221 us, 4096 tokens 501 -> 425 us; 2304 x 9216, 4096 tokens 199 -> 168 us; 3600 x 3600, 1600 tokens 82
+// -> 59 us; 2000 x 1008, 4096 tokens 34 -> 28.5 us.
+// The result is the height of the better wide tile in blocks of 32 tokens, or 0 where the tiles of fwd_kernel are faster; *ns,
+// unless null, the modelled time of the choice.
+inline int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns) {
+    double best = 0.678 * (double)fwd_tiled_cost(M, N, K, 1, nullptr);
+    int choice = 0;
+    for (int mb = 3; mb <= 6; ++mb) {
+        const int64_t rounds = cdiv(cdiv(M, 32 * mb) * cdiv(N, DX_BK), 256);
+        const double t = (double)rounds * ((double)cdiv(K, BKT) * (94.0 * mb + 402.0) + 3870.0 + 824.0 * mb);
+        if (t < best) {
+            best = t;
+            choice = mb;
+        }
+    }
+    if (ns) *ns = best;
+    return choice;
+}
+
+// ---- few tokens: K split over workgroups (mq_linear_split.hip) --------------------------------
+constexpr int split_lds(int mb) { return FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE); }
+
+// How the forward for few tokens cuts its work (mq_linear_split.hip); mb == 0: whole contractions are the better choice.
+struct FwdSplitPlan {
+    int mb, splits;       // 32-token blocks per workgroup, K ranges
+    size_t part_bytes;    // fp32 accumulators of all ranges
+    size_t rs_bytes;      // per-token sums of X per range
+    int64_t loss_blocks;  // workgroups of the finishing kernel (rows of FwdArgs::partial)
+};
+
+// Which form, and how it is cut: the least modelled time in ns over one to four token blocks per workgroup and up to 16
+// ranges of at least five 64-wide stages, against the tiled kernel.  Per stage a compute unit needs 128 cycles per
+// matrix product row (32 x 64 x 32) and bit-width, 172 per bit-width for the conversions and 50 for the barrier, for each of
+// the workgroups it holds (80 KB of LDS and 256 registers each where two fit), but never less than the 1000 cycles a stage
+// takes to arrive; all workgroups together cannot read codes faster than 2900 or tiles of X faster than 4100 bytes per
+// cycle; a workgroup starts and ends in 4200 cycles; launches and the finishing kernel cost 8500 cycles, 1800 bytes of
+// accumulators take a cycle to be written and read back.  The constants are a fit to 2200 timed combinations (10 layers of
+// 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths): the choice is 1.5 % slower than the best of them
+// on average.  Measured, tiled -> chosen: 4096 x 4096, 77 tokens, int4 37.6 -> 15.7 us; 4096 x 14336 117 -> 26 us;
+// 2304 x 9216 at r = 8/4/2, 203 tokens 125 -> 44 us; level with the tiled kernel at 600 (14336 rows: 130) tokens and more.
+//
+// The objective does not enter the rule, although its calls have no wide tiles to fall back on: the sums of a call with the
+// objective have to run in the order of those of the call without.  It costs the former 4 % (at most 11 %) on the one size in
+// 450 of 896 .. 14336 squared and 17 .. 2048 tokens, at one bit-width, where the wide tiles beat the cut (by 8 %).
+inline FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
+    FwdSplitPlan best{0, 0, 0, 0, 0};
+    if (M < 1 || N < 1 || M > 2048) return best;
+    const int64_t tiles_n = cdiv(N, FWD_BN), nkt = cdiv(K, BKT);
+    // with its row-sum pre-pass (for three bit-widths less the margin by which the fits of the two forms are apart)
+    double best_cost = kFwdCycleNs * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + (nr == 3 ? (double)M * K / 2000.0 - 500.0 : 4600.0);
+    double wide;
+    if (nr == 1 && fwd_wide_mb(M, N, K, &wide)) best_cost = std::min(best_cost, wide + 4600.0);
+    for (int mb = 1; mb <= 4; ++mb) {
+        const int64_t tiles_m = cdiv(M, 32 * mb), tiles = tiles_m * tiles_n;
+        if (mb > 1 && tiles_m == cdiv(M, 32 * (mb - 1))) continue;
+        const int resident = std::max(1, std::min(163840 / split_lds(mb), 512 / (16 * nr * mb + 110)));
+        const double busy = nr * mb * 128.0 + 172.0 * nr + 50.0;
+        for (int splits = 1; splits <= 16; ++splits) {
+            const int64_t stages = cdiv(nkt, splits);
+            if (splits > 1 && stages < 5) break;
+            if (splits == 1 && M > 64) continue;
+            const size_t part = (size_t)splits * tiles * nr * mb * 16384;
+            if (part > ((size_t)96 << 20)) break;
+            const int64_t per_cu = cdiv(tiles * splits, 256), full = per_cu / resident, rest = per_cu % resident;
+            double loop = full * std::max(resident * busy, 1000.0) + (rest ? std::max(rest * busy, 1000.0) : 0.0);
+            loop = loop * stages + (full + (rest ? 1 : 0)) * 4200.0;
+            loop = std::max(loop, std::max((double)N * K / 2900.0, (double)tiles * splits * stages * mb * 4096.0 / 4100.0));
+            const double cost = 0.51 * (loop + 8500.0 + part / 1800.0 + 217.0 * splits * nr);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best.mb = mb;
+                best.splits = splits;
+                best.part_bytes = part;
+                best.rs_bytes = (size_t)splits * tiles_m * 32 * mb * 4;
+                best.loss_blocks = tiles * mb * 4;
+            }
+        }
+    }
+    return best;
+}
+
+// ============================================================================================
+// backward dX (mq_linear_wide.hip)
+// ============================================================================================
+// How dX cuts its work; splits == 1: no partial sums.
+struct DxPlan {
+    int mb, splits;     // 32-token blocks per workgroup, ranges of n
+    size_t part_bytes;  // fp32 accumulators of all ranges
+};
+
+// Tile height and ranges: the least modelled time (cycles) over one to five token blocks per workgroup and up to 16 ranges of
+// n.  160 tokens x 256 k tiles alone leave most compute units idle up to about 2000 tokens (16 tokens through 9216 x 2304 are
+// nine workgroups that walk 432 stages each: 263 us), and a full partial round of low tiles often beats the same round of
+// high ones.  A stage (one n tile, one bit-width) takes 256 cycles per token block for its products and 520 for conversions
+// and the barrier, for each of the workgroups that a compute unit holds (two where the stages of 32 tokens fit twice into its
+// LDS), but never less than the 1055 + 140 per token block it takes to arrive; all workgroups together do not get gradients
+// faster than 3650 or codes faster than 6480 bytes per cycle; a tile's epilogue costs 900 per token block, the finishing
+// launch 4100 and 310 per range, and 1940 bytes of accumulators go out and come back per cycle.  The constants are a fit to
+// 3100 timed combinations (8 layers of 256 x 256 to 14336 x 4096, 16 to 4096 tokens, one and three bit-widths): the choice
+// is 0.4 % slower than the best of them on average, 9 % at worst.  dX with its preparation, 160-token tiles -> chosen, at
+// r = 8/4/2: 9216 x 2304, 16 tokens 263 -> 54 us, 400 tokens 342 -> 96 us, 2000 tokens 371 -> 274 us; 3600 x 3600, 400
+// tokens 160 -> 73 us, 4096 tokens 388 -> 354 us; 256 x 256, 16 tokens 15.6 (32-token tile) -> 13.9 us; the same at
+// 4096 tokens through 9216 x 2304 (499 us).
+inline DxPlan make_dx_plan(int64_t M, int64_t N, int64_t K, int nr) {
+    DxPlan best{DX_MB, 1, 0};
+    double best_cost = 0;
+    const int64_t tiles_k = cdiv(K, DX_BK), nnt = cdiv(N, BKT);
+    for (int mb = DX_MB; mb >= 1; --mb) {
+        const int64_t tiles = cdiv(M, 32 * mb) * tiles_k;
+        if (mb > 1 && cdiv(M, 32 * mb) == cdiv(M, 32 * (mb - 1))) continue;  // a lower tile covers as much
+        const int resident = 2 * dx_lds(mb) <= 163840 ? 2 : 1;
+        const double busy = mb * 256.0 + 520.0, arrive = mb * 140.0 + 1055.0;
+        for (int splits = 1; splits <= std::min<int64_t>(16, nnt); ++splits) {
+            const size_t part = splits > 1 ? (size_t)splits * tiles * mb * DX_RB * 16384 : 0;
+            if (splits > 1 && (part > ((size_t)96 << 20) || tiles * splits > 1100)) break;
+            const int64_t per_cu = cdiv(tiles * splits, 256), full = per_cu / resident, rest = per_cu % resident;
+            const int64_t n_stages = cdiv(nnt, splits), stages = n_stages * nr;
+            double cost = full * std::max(resident * busy, arrive) + (rest ? std::max(rest * busy, arrive) : 0.0);
+            cost = cost * stages + per_cu * mb * 900.0;
+            cost = std::max(cost, (double)tiles * splits * (stages * mb * (4096.0 / 3650.0) + n_stages * (16384.0 / 6480.0)));
+            if (splits > 1) cost += 4100.0 + 310.0 * splits + part / 1940.0;
+            if (best_cost == 0 || cost < best_cost) {
+                best_cost = cost;
+                best = DxPlan{mb, splits, part};
+            }
+        }
+    }
+    return best;
+}
+
+// ============================================================================================
+// backward dW (mq_linear.hip)
+// ============================================================================================
+constexpr int DW_BM = 32;                            // contraction elements (tokens) per stage: 64-byte rows
+constexpr int DW_NST = 5;                            // LDS stages
+constexpr int dw_side(int hb) { return 64 * hb; }    // rows of n and columns of k per workgroup: 2 x 2 waves of hb 32-blocks
+constexpr int dw_lds(int hb) { return DW_NST * 2 * dw_side(hb) * 64; }
+constexpr int DW_CUS = 256;                          // compute units a round of workgroups fills
+
+// How the tiles of dW (of `batch` gradients together) are dealt to workgroups.  Two sizes of tile: 256 x 256 (hb = 4) has the
+// smaller operand traffic per product, 128 x 128 (hb = 2) four times as many tiles, two of which fit a compute unit.  Whole
+// rounds of 256 x 256 tiles run one tile per workgroup; the tiles of a last partial round (at most half a round) are cut
+// along the tokens into `parts` ranges each, so that the round still occupies every compute unit for 1 / parts of a tile's
+// time.  Where the tiles do not fill one round all of them may be cut.  The ranges leave fp32 partial tiles in the workspace
+// and dw_reduce_kernel adds them in a fixed order.
+//
+// The choice is the least modelled time (cycles): a 32-token stage takes 1045 per 256-tile; of 128-tiles, 742 for two on a
+// compute unit, 437 for one; a tile ends in 10700 (2100); a cut costs 1300, 2230 per range and a cycle per 4780 bytes of
+// partial tiles written and read back.  The constants are a fit to 900 timed combinations (10 layers of 256 x 256 to
+// 14336 x 4096, 16 to 8192 tokens); the choice is 0.3 % slower than the best of them on average, 10 % at worst.  dW with its
+// preparation, 256-tiles -> chosen: 256 x 256, 16 tokens 12.5 -> 8.7 us, 4096 tokens 84 -> 24 us; 2000 x 1008, 400 tokens 23
+// -> 14 us; 2304 x 2304, 2000 tokens 60 -> 45 us; 6400 x 1104, 4096 tokens 117 -> 93 us; 2304 x 9216, 1200 tokens 90 -> 80 us,
+// 4096 tokens the same (201 us).
+struct DwPlan {
+    int hb, tiles_n, tiles_k, whole, rest, parts;
+    size_t part_bytes;
+};
+inline DwPlan make_dw_plan(int64_t M, int64_t N, int64_t K, int batch) {
+    DwPlan best{};
+    double best_cost = 0;
+    const int64_t stages = cdiv(M, DW_BM);
+    const int64_t max_parts = std::max<int64_t>(1, stages / 8);  // at least eight stages per range
+    for (int hb = 4; hb >= 2; hb -= 2) {
+        const int side = dw_side(hb);
+        const int64_t tiles_n = cdiv(N, side), tiles_k = cdiv(K, side), tiles = tiles_n * tiles_k * batch;
+        auto rounds = [&](int64_t items, int64_t st) {
+            const int64_t per_cu = cdiv(items, DW_CUS);
+            if (hb == 4) return per_cu * (1045.0 * st + 10700.0);
+            return (per_cu / 2 * 742.0 + per_cu % 2 * 437.0) * st + per_cu * 2100.0;
+        };
+        auto consider = [&](int64_t rest, int64_t parts) {
+            const size_t bytes = (size_t)rest * parts * side * side * 4;
+            double cost = rounds(tiles - rest, stages);
+            if (rest > 0) cost += rounds(rest * parts, cdiv(stages, parts)) + 1300.0 + 2230.0 * parts + 2.0 * bytes / 4780.0;
+            if (best_cost == 0 || cost < best_cost) {
+                best_cost = cost;
+                best = DwPlan{hb, (int)tiles_n, (int)tiles_k, (int)(tiles - rest), (int)rest, (int)parts, bytes};
+            }
+        };
+        const int64_t over = tiles % DW_CUS;
+        if (tiles < DW_CUS) {
+            for (int64_t parts = 2; parts <= std::min<int64_t>(8, max_parts); ++parts)
+                if ((size_t)tiles * parts * side * side * 4 <= ((size_t)96 << 20)) consider(tiles, parts);
+        } else if (hb == 4 && over > 0) {
+            const int64_t parts = std::min<int64_t>(DW_CUS / over, max_parts);
+            if (parts >= 2) consider(over, parts);
+        }
+        // a last partial round of 256-tiles that can be cut is cut: whole tiles there cost a full round
+        if (!(hb == 4 && best.rest > 0 && best.whole > 0)) consider(0, 1);
+    }
+    return best;
+}
+
+// The cut that needs no workspace.
+inline DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
+    const int tiles_n = (int)cdiv(N, dw_side(4)), tiles_k = (int)cdiv(K, dw_side(4));
+    return DwPlan{4, tiles_n, tiles_k, tiles_n * tiles_k * batch, 0, 1, 0};
+}
+
+}  // namespace mq
