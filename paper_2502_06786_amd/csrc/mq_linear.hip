@@ -1012,7 +1012,7 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
                          bool tiled_only = false) {
     if (M < 0 || N < 0 || K < 1) return MQ_ERR_SHAPE;
     if (M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > (1 << 22)) return MQ_ERR_SHAPE;
-    if (cdiv(M, 128) * cdiv(N, FWD_BN) > 0x7FFFFFFF) return MQ_ERR_SHAPE;  // tiles of one launch (lower tiles are taken for small problems only)
+    if (cdiv(M, 128) * cdiv(N, FWD_BN) > 0x7FFFFFFF) return MQ_ERR_SHAPE;  // tiles of one launch (lower ones are taken only where theirs fit, too)
     mq_status s = check_rs(rs, nr);
     if (s != MQ_OK) return s;
     if (K % 16 != 0 || N % 8 != 0) return MQ_ERR_ALIGN;

@@ -44,7 +44,8 @@ inline int64_t fwd_tiled_cost(int64_t M, int64_t N, int64_t K, int nr, int *mb) 
         const double stages = (double)cdiv(K, BKT);
         double best_ns = 0;
         for (int h = hi; h >= 2; --h) {
-            const int64_t per_cu = cdiv(cdiv(M, 32 * h) * cdiv(N, FWD_BN), 256);
+            const int64_t tiles = cdiv(M, 32 * h) * cdiv(N, FWD_BN), per_cu = cdiv(tiles, 256);
+            if (tiles > 0x7FFFFFFF) continue;  // more than a launch takes (never at 128 tokens and more: fwd_run)
             const double ends = 871.0 + 1907.0 * h, alone = stages * (294.0 + 159.0 * h) + ends;
             const double ns = h > 3 ? per_cu * alone : per_cu / 2 * (stages * (409.0 + 367.0 * h) + 1.4 * ends) + per_cu % 2 * alone;
             if (h == hi || ns < best_ns) {

@@ -1,0 +1,70 @@
+"""The library's rules on sizes (csrc/mq_plan.h) for tests that have to know which form a call takes: built with the host
+compiler on first use, no GPU needed."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+from collections import namedtuple
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2502_06786_amd", "csrc")
+
+SOURCE = r'''
+#include "mq_plan.h"
+using namespace mq;
+extern "C" void plan_forward(int64_t M, int64_t N, int64_t K, int nr, int64_t *out) {
+    const FwdSplitPlan p = make_split_plan(M, N, K, nr);
+    int tiled = 0;
+    fwd_tiled_cost(M, N, K, nr, &tiled);
+    out[0] = p.mb, out[1] = p.splits, out[2] = nr == 1 ? fwd_wide_mb(M, N, K, nullptr) : 0, out[3] = tiled;
+}
+extern "C" void plan_dx(int64_t M, int64_t N, int64_t K, int nr, int64_t *out) {
+    const DxPlan p = make_dx_plan(M, N, K, nr);
+    out[0] = p.mb, out[1] = p.splits;
+}
+extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out) {
+    const DwPlan p = make_dw_plan(M, N, K, batch);
+    out[0] = p.hb, out[1] = p.whole, out[2] = p.rest, out[3] = p.parts;
+}
+'''
+
+# form: "split" (K cut into `ranges`), "wide" (256-channel tiles), "tiled"; blocks: tile height in blocks of 32 tokens
+Forward = namedtuple("Forward", "form blocks ranges")
+Dx = namedtuple("Dx", "blocks ranges")              # ranges: of channels
+Dw = namedtuple("Dw", "side whole cut ranges")      # tiles of side x side: run whole, cut into `ranges` of tokens each
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    folder = tempfile.mkdtemp(prefix="mq_plans_")
+    src, so = os.path.join(folder, "plans.cpp"), os.path.join(folder, "plans.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, src, "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw):
+        f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
+        f.restype = None
+    return lib
+
+
+def _ask(name, *sizes):
+    out = (ctypes.c_int64 * 4)()
+    getattr(_lib(), name)(*sizes, out)
+    return list(out)
+
+
+def forward(M, N, K, nr, objective=False):
+    mb, splits, wide, tiled = _ask("plan_forward", M, N, K, nr)
+    if mb:
+        return Forward("split", mb, splits)
+    return Forward("wide", wide, 1) if wide and not objective else Forward("tiled", tiled, 1)
+
+
+def dx(M, N, K, nr):
+    return Dx(*_ask("plan_dx", M, N, K, nr)[:2])
+
+
+def dw(M, N, K, gradients=1):
+    hb, whole, rest, parts = _ask("plan_dw", M, N, K, gradients)
+    return Dw(64 * hb, whole, rest, parts)
