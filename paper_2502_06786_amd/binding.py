@@ -154,7 +154,7 @@ class Overflow:
         return _Overflow(self.row_ptr.data_ptr(), self.col_idx.data_ptr(), self.capacity, self.nnz.data_ptr())
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)  # (typed: a float that equals a size is refused, as it is the first time)
 def mq_workspace_bytes(op: int, M: int, N: int, K: int, nr: int) -> int:
     return int(_lib.mq_workspace_bytes(op, M, N, K, nr))
 

@@ -1,7 +1,10 @@
 """What the library's host side remembers between calls, where it could be remembered wrongly: small programs around its host
 headers, built with the host compiler."""
+import ctypes
 import os
 import subprocess
+
+import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2502_06786_amd", "csrc")
 
@@ -56,3 +59,11 @@ int main() {
     return 0;
 }
 ''')
+
+
+def test_remembered_workspace_sizes_refuse_what_the_call_refuses():
+    """16.0 equals 16 and hashes alike, but it is no size."""
+    from paper_2502_06786_amd import binding
+    assert binding.mq_workspace_bytes(0, 16, 256, 256, 3) > 0
+    with pytest.raises(ctypes.ArgumentError):
+        binding.mq_workspace_bytes(0, 16.0, 256, 256, 3)
