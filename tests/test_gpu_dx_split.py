@@ -27,15 +27,26 @@ CASES = [
     # M, N, K, rs, extra precision
     (1, 64, 16, (4,), False),               # one stage, one token, a sixteenth of a k tile
     (16, 256, 256, (8, 4, 2), False),       # four ranges of one n tile
-    (31, 4112, 272, (2,), False),           # 16 ranges; n ends 16 into a stage
+    (31, 4112, 272, (2,), False),           # 13 ranges; n ends 16 into a stage
     (33, 1040, 528, (3, 8), True),
     (64, 2000, 1008, (8, 4, 2), True),
     (77, 9216, 240, (8,), False),
-    (96, 1616, 9216, (4,), True),           # three token blocks, few ranges
+    (96, 1616, 9216, (4,), True),           # three tiles of one block, few ranges
     (130, 3600, 3600, (8, 4, 2), False),    # five token blocks, the last with two rows
-    (250, 2304, 2320, (6, 2), False),       # four blocks
-    (400, 896, 3600, (4,), False),          # low tiles, no ranges
-    (1201, 2000, 1008, (8, 4, 2), False),   # several token tiles and ranges
+    (250, 2304, 2320, (6, 2), False),       # two blocks
+    (400, 896, 3600, (4,), False),          # tiles of one block, no ranges
+    (1201, 2000, 1008, (8, 4, 2), False),   # three blocks, several token tiles and ranges
+    # the other heights, with ranges and without, where n and k end inside their tiles
+    (131, 80, 13392, (3, 8), False),        # two, no ranges
+    (1206, 1184, 80, (8, 4, 2), True),      # two
+    (259, 80, 14448, (4,), False),          # three, no ranges
+    (65, 416, 11248, (4, 3, 2), False),     # three
+    (411, 80, 14032, (6, 2), True),         # four, no ranges
+    (2037, 4240, 80, (8, 4, 2), False),     # four
+    (2042, 7280, 80, (8, 3), True),         # four
+    (525, 80, 13248, (8,), False),          # five, no ranges
+    (298, 2160, 3104, (6, 2), False),       # five
+    (142, 2192, 11968, (2,), False),        # five
 ]
 
 

@@ -25,6 +25,7 @@ def _randn(seed, *shape, scale=1.0):
 
 CASES = [
     # M, N, K, rs, extra precision
+    # -- token tiles of one block of 32
     (1, 16, 640, (2,), False),             # one token, an eighth of a channel tile
     (31, 144, 1040, (4,), False),         # K ends 16 into a stage
     (33, 128, 2064, (8,), False),
@@ -34,6 +35,20 @@ CASES = [
     (130, 400, 1616, (8, 4, 2), False),   # two token tiles
     (203, 144, 9216, (2,), True),
     (600, 256, 2304, (6, 2), False),
+    # -- two blocks
+    (35, 12272, 784, (8,), False),
+    (1825, 16, 2720, (2,), False),        # one channel tile, which sums every token block of X itself
+    (35, 9280, 544, (4, 8), False),
+    (33, 8400, 1552, (8, 4, 2), True),
+    # -- three
+    (77, 4096, 4096, (4,), False),
+    (1218, 144, 2144, (2,), True),        # two channel tiles share three token blocks
+    (67, 6576, 528, (4, 2), True),
+    (66, 5664, 2192, (4, 3, 2), False),
+    # -- four (at two and three bit-widths)
+    (116, 8256, 528, (8, 2), False),
+    (2038, 16, 29568, (3, 2), True),
+    (218, 2704, 4368, (8, 4, 2), False),
 ]
 
 
@@ -66,9 +81,9 @@ def test_split_forward(mq, oracle, M, N, K, rs, ep):
         assert torch.equal(GU[i], Y[i]) and torch.equal(A[i], A0[i]), rs[i]
 
 
-def test_split_forward_exact(mq):
+@pytest.mark.parametrize("M,N,K", [(65, 136, 2048), (66, 5664, 2192), (218, 2704, 4368)])
+def test_split_forward_exact(mq, M, N, K):
     """alpha = 1, z = 0 and one-hot activations: every output is one slice value, no rounding anywhere."""
-    M, N, K = 65, 136, 2048
     g = torch.Generator().manual_seed(3)
     q = torch.randint(0, 256, (N, K), generator=g, dtype=torch.int32)
     hot = torch.randint(0, K, (M,), generator=g)

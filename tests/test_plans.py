@@ -1,7 +1,7 @@
 """Rules on sizes (no GPU): what the launches that follow from them rely on."""
 import pytest
 
-from tests import plans
+from tests import plans, test_gpu_dw_tiles, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide
 
 cdiv = lambda a, b: -(-a // b)
 
@@ -16,3 +16,35 @@ def test_tiles_of_a_forward_fit_one_launch(nr, K):
         p = plans.forward(M, N, K, nr)
         channels = 256 if p.form == "wide" else 128
         assert cdiv(M, 32 * p.blocks) * cdiv(N, channels) < 1 << 31, (M, N, p)
+
+
+# ---- the sizes of the GPU tests take the forms that they are there for -------------------------------------------------
+def test_split_forward_sizes():
+    seen = set()
+    for M, N, K, rs, _ in test_gpu_forward_split.CASES:
+        p = plans.forward(M, N, K, len(rs))
+        assert p.form == "split" and p.ranges > 1, (M, N, K, rs, p)
+        seen.add((len(rs), p.blocks))
+    assert seen == {(1, 1), (1, 2), (1, 3), (2, 1), (2, 2), (2, 3), (2, 4), (3, 1), (3, 2), (3, 3), (3, 4)}
+    # at one bit-width, where the plain forward takes the wide tiles, the objective takes the tiles of the same sums
+    assert [plans.forward(M, N, K, 1).form for M, N, K in ((443, 11472, 4608), (416, 11008, 4096), (77, 4096, 4096))] == ["wide", "wide", "split"]
+
+
+def test_tiled_forward_sizes():
+    assert {plans.forward(M, N, K, 3)[:2] for M, N, K, _, _ in test_gpu_forward_low_tiles.CASES} == {("tiled", 2), ("tiled", 3)}
+    assert {plans.forward(M, N, K, 1)[:2] for M, N, K, _, _ in test_gpu_forward_wide.CASES} == {("wide", b) for b in (3, 4, 5, 6)}
+
+
+def test_dx_sizes():
+    seen = {(p.blocks, p.ranges > 1) for p in (plans.dx(M, N, K, len(rs)) for M, N, K, rs, _ in test_gpu_dx_split.CASES)}
+    assert seen == {(b, cut) for b in (1, 2, 3, 4, 5) for cut in (False, True)}
+
+
+def test_dw_sizes():
+    form = lambda p: (p.side, p.whole > 0, p.cut > 0)
+    seen = {form(plans.dw(M, N, K)) for M, N, K, _ in test_gpu_dw_tiles.CASES}
+    assert seen == {(128, True, False), (128, False, True), (256, True, False), (256, False, True), (256, True, True)}
+    assert [form(plans.dw(M, N, K, len(rs))) for M, N, K, rs in test_gpu_dw_tiles.CLIP_CASES] == [
+        (128, False, True), (256, True, False), (256, False, True), (256, True, True)]
+    for M, N, K, rs in test_gpu_dw_tiles.CLIP_CASES:
+        assert N % plans.dw(M, N, K, len(rs)).side and K % plans.dw(M, N, K, len(rs)).side
