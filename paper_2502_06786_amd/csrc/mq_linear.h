@@ -65,48 +65,8 @@ __device__ __forceinline__ void u8_tile_lane(int wave, int lane, int inst, uint3
     col = c * 16;
 }
 
-// ---- code -> bf16 operand conversions ---------------------------------------------------------
-// Eight int8 codes (two dwords, k ascending) -> eight bf16 of the same value.
-__device__ __forceinline__ u32x4 codes_to_bf16_r8(uint32_t d0, uint32_t d1) {
-    auto two = [](float lo, float hi) {
-        return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-    };
-    return u32x4{two((float)(d0 & 0xFFu), (float)((d0 >> 8) & 0xFFu)),
-                 two((float)((d0 >> 16) & 0xFFu), (float)(d0 >> 24)),
-                 two((float)(d1 & 0xFFu), (float)((d1 >> 8) & 0xFFu)),
-                 two((float)((d1 >> 16) & 0xFFu), (float)(d1 >> 24))};
-}
-
-// Bytes of two dwords placed in 16-bit lanes, k ascending.  HIGH: byte << 8 (for the saturating
-// add), else byte in the low half.
-template <bool HIGH>
-__device__ __forceinline__ u32x4 place_bytes(uint32_t d0, uint32_t d1) {
-    constexpr uint32_t s01 = HIGH ? 0x010C000Cu : 0x0C010C00u;
-    constexpr uint32_t s23 = HIGH ? 0x030C020Cu : 0x0C030C02u;
-    return u32x4{__builtin_amdgcn_perm(0u, d0, s01), __builtin_amdgcn_perm(0u, d0, s23),
-                 __builtin_amdgcn_perm(0u, d1, s01), __builtin_amdgcn_perm(0u, d1, s23)};
-}
-
-// r-bit slice of section 3.2 as bf16(128 + code), from bytes placed by place_bytes<!EP>.
-// half2 = half in both 16-bit lanes (shifted left by 8 unless EP); sh = s (+ 8 unless EP).
-template <bool EP>
-__device__ __forceinline__ u32x4 sliced_to_bf16(const u32x4 &placed, uint32_t half2, uint32_t sh) {
-    u32x4 out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if constexpr (EP) {
-            out[i] = (((placed[i] + half2) >> sh) & 0x00FF00FFu) | kMagic128;
-        } else {
-            const uint32_t pv = placed[i];
-            u16x2 t = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, pv), __builtin_bit_cast(u16x2, half2));
-            const unsigned short s16 = (unsigned short)sh;
-            t = t >> u16x2{s16, s16};
-            out[i] = __builtin_bit_cast(uint32_t, t) | kMagic128;
-        }
-    }
-    return out;
-}
-
+// ---- code -> bf16 operand conversion -----------------------------------------------------------
+// r-bit slice of section 3.2 as bf16(128 + code): the kernels' convert_piece, two codes at a time.
 struct SliceParam {  // wave-uniform per bit-width
     uint32_t half2;  // half (<< 8 unless EP) in both 16-bit lanes
     uint32_t sh;     // shift that leaves the code

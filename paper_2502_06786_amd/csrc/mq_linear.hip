@@ -373,9 +373,8 @@ struct PrepArgs {
     float mult[3];       // 2^s_i
     float bias[3];       // 128 for sliced slots, 0 for the r = 8 slot
     float *cpart;        // [nsplit][M] partial sums of c over column ranges, or null
-    uint16_t *GT;        // [M / 32][N][32] (blocks of 32 tokens; see DwArgs) or null; tokens M .. ldm - 1 are written as zeros
+    uint16_t *GT;        // [M / 32][N][32] (blocks of 32 tokens; see DwArgs) or null; a piece of 8 tokens that straddles M ends with zeros
     int nr, M, N;
-    int ldm;             // M rounded up to a multiple of 8
     int cols_per_split;  // multiple of 64
     int strips, nsplit;  // token strips, column ranges
     // > 0: no sum; gradient i alone, times lam[i], goes to GT + i * gt_step (As and cpart are null, `each` times as many workgroups)
@@ -385,7 +384,7 @@ struct PrepArgs {
     const uint8_t *Q;
     uint8_t *QT;         // [K, N]
     const uint16_t *X;
-    uint16_t *XT;        // [M / 32][K][32]; tokens M .. ldm - 1 are zeros
+    uint16_t *XT;        // [M / 32][K][32], as GT
     int K;
 };
 
@@ -614,7 +613,6 @@ struct DwArgs {
     float *dW;           // [N, K]
     float *part;         // [split tiles][parts][256][256]: partial tiles of the split last round
     int M, N, K;
-    int ldm;             // M rounded up to a multiple of 8; tokens M .. ldm - 1 hold zeros
     int accumulate;
     int tiles_n, tiles_k;
     int whole;           // work items [0, whole) are whole tiles; the others are token ranges of the remaining tiles
@@ -1259,7 +1257,6 @@ mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lam
     p.M = (int)M;
     p.N = (int)N;
     p.K = (int)K;
-    p.ldm = (int)((M + 7) & ~(int64_t)7);
     p.X = X;
     p.XT = reinterpret_cast<uint16_t *>(ws + lay.xt);
     mq_status s = launch_prep(p, false, st);
@@ -1273,7 +1270,6 @@ mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lam
     w.M = (int)M;
     w.N = (int)N;
     w.K = (int)K;
-    w.ldm = p.ldm;
     w.accumulate = 0;
     return launch_dw(w, cut, st);
 }
@@ -1359,7 +1355,6 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.nr = nr;
     p.M = (int)M;
     p.N = (int)N;
-    p.ldm = (int)((M + 7) & ~(int64_t)7);
     p.silu = (flags & MQ_FLAG_FFN_SILU) ? 1 : 0;
     p.K = (int)K;
     p.Q = Q;
@@ -1407,7 +1402,6 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         w.M = (int)M;
         w.N = (int)N;
         w.K = (int)K;
-        w.ldm = p.ldm;
         w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
         w.gt_step = 0;
         const mq_status dws = launch_dw(w, dw_cut, st);

@@ -202,8 +202,9 @@ mq_status launch_split(const FwdSplitArgs &s, int mb, hipStream_t st) {
         case 1: return launch_split_mb<NR, HAS8, EP, 1>(s, st);
         case 2: return launch_split_mb<NR, HAS8, EP, 2>(s, st);
         case 3: return launch_split_mb<NR, HAS8, EP, 3>(s, st);
-        default: return launch_split_mb<NR, HAS8, EP, 4>(s, st);
     }
+    if constexpr (split_mb(NR) == 4) return launch_split_mb<NR, HAS8, EP, 4>(s, st);
+    return MQ_ERR_SHAPE;  // (make_split_plan stays within split_mb)
 }
 
 template <int NR>

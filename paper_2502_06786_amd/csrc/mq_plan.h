@@ -103,6 +103,9 @@ inline int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns) {
 }
 
 // ---- few tokens: K split over workgroups (mq_linear_split.hip) --------------------------------
+// most 32-token blocks per workgroup: at one bit-width two workgroups of three share a compute unit, one of four has it alone,
+// and no size was found for which the rule below would take it
+constexpr int split_mb(int nr) { return nr == 1 ? 3 : 4; }
 constexpr int split_lds(int mb) { return FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE); }
 
 // How the forward for few tokens cuts its work (mq_linear_split.hip); mb == 0: whole contractions are the better choice.
@@ -135,7 +138,7 @@ inline FwdSplitPlan make_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
     double best_cost = kFwdCycleNs * (double)fwd_tiled_cost(M, N, K, nr, nullptr) + (nr == 3 ? (double)M * K / 2000.0 - 500.0 : 4600.0);
     double wide;
     if (nr == 1 && fwd_wide_mb(M, N, K, &wide)) best_cost = std::min(best_cost, wide + 4600.0);
-    for (int mb = 1; mb <= 4; ++mb) {
+    for (int mb = 1; mb <= split_mb(nr); ++mb) {
         const int64_t tiles_m = cdiv(M, 32 * mb), tiles = tiles_m * tiles_n;
         if (mb > 1 && tiles_m == cdiv(M, 32 * (mb - 1))) continue;
         const int resident = std::max(1, std::min(163840 / split_lds(mb), 512 / (16 * nr * mb + 110)));
