@@ -24,8 +24,9 @@
  *     output is defined.
  *   - Device pointers must be 16-byte aligned and all matrices are dense
  *     (row stride = row length) except W, which has `ldw`.
- *   - Reentrant: no mutable global state.  Two calls may run concurrently on
- *     different streams when their buffers (workspace included) do not overlap.
+ *   - Reentrant: nothing is kept between calls that a result depends on.  Two
+ *     calls may run concurrently, from one or several host threads, on different
+ *     streams when their buffers (workspace included) do not overlap.
  */
 #ifndef MQ_H
 #define MQ_H
@@ -43,7 +44,8 @@ typedef enum {
     MQ_ERR_SHAPE = 2,     /* negative size, size beyond a documented limit                 */
     MQ_ERR_BITS = 3,      /* r outside the accepted set, duplicate r, nr out of range      */
     MQ_ERR_ALIGN = 4,     /* pointer not 16-byte aligned or a row length not a legal multiple */
-    MQ_ERR_WORKSPACE = 5, /* workspace NULL or smaller than mq_workspace_bytes()           */
+    MQ_ERR_WORKSPACE = 5, /* workspace NULL, not 16-byte aligned or too small: see
+                             mq_workspace_bytes()                                           */
     MQ_ERR_CAPACITY = 6,  /* mq_overflow.capacity negative.  A capacity that turns out too
                              small is not an error of the call: see mq_overflow.nnz          */
     MQ_ERR_DEVICE = 7     /* a HIP call failed (launch error)                              */
@@ -159,6 +161,9 @@ mq_status mq_slice_multi(const uint8_t *Q, int64_t N, int64_t K, const int *rs, 
  *   flags  MQ_FLAG_EXTRA_PRECISION: slices use the unclamped code
  *   Y      host array of nr device pointers, each [M, N] bf16 out
  *   ws     workspace of at least mq_workspace_bytes(MQ_OP_LINEAR_FWD, M, N, K, nr)
+ * The order of the fp32 sums over k is fixed by M, N, K and nr: up to 2048 tokens K may be cut into ranges that
+ * are summed apart (which needs more of the workspace), and an output may then differ in its last bit from that of
+ * the same r in a call with more or fewer bit-widths.
  * K must be a multiple of 16 and N a multiple of 8 (16-byte rows).  M is free.
  * M == 0 or N == 0 is a no-op.  Limits (MQ_ERR_SHAPE beyond): M, N below 2^31 - 256,
  * K <= 2^22, ceil(M / 128) * ceil(N / 128) below 2^31.
@@ -173,9 +178,9 @@ mq_status mq_linear_fwd_multi(const uint16_t *X, const uint8_t *Q, const float *
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and limits
  * as mq_linear_fwd_multi without `ws`; the per-token sums of X that the forward keeps between its
  * pre-pass and its epilogue live in a fixed device array inside the library (1 MiB, one copy per GPU,
- * held until the process ends).  No hipMalloc, hipFree or other allocating call is made.  (For few tokens
- * mq_linear_fwd_multi splits K over workgroups through its workspace; this form never does, so there the order of the
- * fp32 sums differs between the two.)
+ * held until the process ends).  No hipMalloc, hipFree or other allocating call is made.  (Where
+ * mq_linear_fwd_multi cuts K into ranges, this form does not: there the order of the fp32 sums differs
+ * between the two, and this one is slower.)
  *   - M <= 262144 tokens (MQ_ERR_SHAPE beyond: the built-in scratch holds one float per token).
  *   - Every call on one GPU uses that GPU's array: calls that overlap in time on the same GPU (two
  *     streams, two host threads) race and must be serialised by the caller.  Calls on different GPUs
@@ -460,8 +465,16 @@ mq_status mq_linear_bwd_gated(const uint16_t *X, const uint8_t *Q, const float *
                               int64_t M, int64_t F, int64_t K, const int *rs, int nr, uint32_t flags,
                               uint16_t *dX, float *dW, void *ws, size_t ws_bytes, void *hip_stream);
 
-/* Bytes of workspace `op` needs at these sizes (0 on invalid arguments).  MQ_OP_FFN_DECODE: M = B, N = F, K = d.
- * MQ_OP_GEMV: M = B, nr = r (bits per code). */
+/* Bytes of workspace for `op` at these sizes (0 on invalid arguments).  MQ_OP_FFN_DECODE: M = B, N = F, K = d.
+ * MQ_OP_GEMV: M = B, nr = r (bits per code).
+ *
+ * MQ_OP_LINEAR_FWD, MQ_OP_LINEAR_FWD_L2, MQ_OP_LINEAR_BWD, MQ_OP_LINEAR_BWD_CLIP: the bytes do not always grow with M.
+ * Where few tokens would leave most of the GPU idle, contractions are cut into ranges whose fp32 partial sums (at most
+ * 96 MiB) go through the workspace.  A workspace that was made for more tokens of the same layer is accepted although it may
+ * hold none: the contraction is then not cut, the call is slower (several times, for few tokens) and the order of its fp32
+ * sums another one.  Anything smaller than that form needs is refused with MQ_ERR_WORKSPACE before the first launch.  To
+ * have the fast form at every size, make one workspace for the largest of the bytes over the token counts in use.  Results
+ * that this header calls bit-identical between two calls are so when each has at least these bytes for its own sizes. */
 size_t mq_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, int nr);
 
 /* Static, human-readable name of a status code. */

@@ -364,3 +364,22 @@ def test_gemv_with_workspace_argument_checks(lib):
     assert f(p, p, p, p, None, 16, 64, 14330, 2, p, p, 1 << 30, None) == ALIGN
     assert f(None, p, p, p, None, 16, 64, 14336, 2, p, p, 1 << 30, None) == NULL
     assert f(p, p, p, p, None, 16, 0, 14336, 2, p, p, 1 << 30, None) == OK
+
+
+def test_small_workspaces_are_refused(lib):
+    """Nothing is launched on a workspace that does not hold what the forms without partial sums need (the row sums of X; the
+    operands of the backward; a scratch matrix), whatever the size that mq_workspace_bytes names."""
+    ci = ctypes.c_int
+    p = ctypes.c_void_p(4096)    # never dereferenced: every call below fails on the host
+    rs, three = (ci * 3)(8, 4, 2), (ctypes.c_void_p * 3)(4096, 4096, 4096)
+    M, N, K = 77, 528, 4096
+    assert lib.mq_workspace_bytes(0, M, N, K, 3) > 1 << 20                        # K is cut here
+    assert lib.mq_workspace_bytes(0, 4096, N, K, 3) < 1 << 20                     # and not here
+    fwd = lambda ws, b: lib.mq_linear_fwd_multi(p, p, p, p, M, N, K, rs, 3, 0, three, ws, b, None)
+    assert fwd(p, 4 * M) == WORKSPACE and fwd(None, 1 << 30) == WORKSPACE and fwd(ctypes.c_void_p(4104), 1 << 30) == WORKSPACE
+    l2 = lambda b: lib.mq_linear_fwd_multi_l2(p, p, p, p, M, N, K, rs, 3, 0, None, p, None, None, None, three, p, p, b, None)
+    assert l2(4 * M + 256) == WORKSPACE
+    bwd = lambda b: lib.mq_linear_bwd(p, p, p, p, three, None, M, N, K, rs, 3, 0, p, p, p, b, None)
+    assert bwd(3 * 2 * M * N + N * K) == WORKSPACE
+    clip = lambda b: lib.mq_linear_bwd_clip(p, K, p, p, p, p, None, None, three, None, M, N, K, rs, 3, 0, p, p, None, None, p, b, None)
+    assert clip(4 * N * K) == WORKSPACE

@@ -35,6 +35,11 @@ def test_tiled_forward_sizes():
     assert {plans.forward(M, N, K, 1)[:2] for M, N, K, _, _ in test_gpu_forward_wide.CASES} == {("wide", b) for b in (3, 4, 5, 6)}
 
 
+def test_noalloc_sizes():
+    # the comparison with the workspace form is bit for bit: K is not cut there
+    assert all(plans.forward(M, N, K, 3).form == "tiled" for M, N, K in ((600, 392, 464), (130, 136, 208)))
+
+
 def test_dx_sizes():
     seen = {(p.blocks, p.ranges > 1) for p in (plans.dx(M, N, K, len(rs)) for M, N, K, rs, _ in test_gpu_dx_split.CASES)}
     assert seen == {(b, cut) for b in (1, 2, 3, 4, 5) for cut in (False, True)}

@@ -1,6 +1,6 @@
 """The forward entry point that allocates nothing (built-in scratch) against mq_linear_fwd_multi, through the C ABI:
 two calls in a row, the second with a smaller input; outputs must be bit-identical to the workspace entry point's
-(the same kernels run on the same operands)."""
+(the same kernels run on the same operands: at these sizes the workspace form does not cut K into ranges)."""
 import ctypes
 
 import numpy as np
