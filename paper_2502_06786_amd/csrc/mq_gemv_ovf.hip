@@ -9,7 +9,7 @@
 // integer, e.g. for one-hot activations).
 //
 // The list is a CSR over output channels with ascending uint16 columns.  Sixteen neighbouring lanes own a row
-// at a time (rows are handed out inside a workgroup through an LDS counter, so uneven rows balance) and read its
+// at a time (the workgroup's rows are dealt to its groups of lanes round-robin) and read its
 // columns as 16-byte pieces, eight per lane, 256 contiguous bytes per step.  The activations sit in LDS
 // TRANSPOSED, xT[k][b] with the BP batch entries of a column next to each other, so that one entry costs one
 // LDS read of 2 BP bytes and BP additions, and no lane ever waits for another: the sixteen partial sums of a row

@@ -611,7 +611,7 @@ struct DwArgs {
     const uint16_t *GT;  // [M / 32][N][32]
     const uint16_t *XT;  // [M / 32][K][32]
     float *dW;           // [N, K]
-    float *part;         // [split tiles][parts][256][256]: partial tiles of the split last round
+    float *part;         // [split tiles][parts][side][side]: partial tiles of the tiles that are cut
     int M, N, K;
     int accumulate;
     int tiles_n, tiles_k;
@@ -625,10 +625,11 @@ static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) { return remem
 
 // Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, one small fenced group of
 // operand work per MFMA), without any code conversion: both operands are bf16 rows with the contraction index
-// (tokens) contiguous.  The four waves form a 2 x 2 grid over the 256 x 256 tile, 128 x 128 each: 16 accumulators
-// (all 256 accumulator registers), 8 operand reads per 16 MFMAs - the square wave tile is what keeps the LDS traffic
-// (32 KB read + 16 KB written per 16-token step and compute unit, 94 bytes per clock at the matrix-core rate) under
-// the 128 bytes per clock the LDS delivers.  Stages are 32 tokens deep (64-byte rows); five of them fill the LDS.
+// (tokens) contiguous.  The four waves form a 2 x 2 grid over the tile.  HB = 4, a 256 x 256 tile, 128 x 128 per wave: 16
+// accumulators (all 256 accumulator registers), 8 operand reads per 16 MFMAs - the square wave tile is what keeps the LDS
+// traffic (32 KB read + 16 KB written per 16-token step and compute unit, 94 bytes per clock at the matrix-core rate) under
+// the 128 bytes per clock the LDS delivers.  HB = 2, a 128 x 128 tile, 64 x 64 per wave: 4 accumulators, 4 reads per 4 MFMAs,
+// two workgroups to a compute unit.  Stages are 32 tokens deep (64-byte rows); five of them fill the LDS (HB = 2: half of it).
 template <int HB>
 __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
@@ -776,7 +777,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     // element of the wave's 32-row block and ends with the destination, so rows past N fall out of range and are
     // dropped by the memory unit; a column past K is sent out of range explicitly.  The row part of the
     // address (wave-uniform) travels in the scalar offset, the lane part in one register per k block.
-    // A token range of a split tile writes its whole 256 x 256 partial tile instead (row length 256, no edges).
+    // A token range of a cut tile writes its whole partial tile instead (row length = side of the tile, no edges).
     // When accumulating, the old values of four rows are requested together, one memory round trip per 16 values.
     const int ld = to_part ? DW_BK : a.K;              // row length of the destination
     const int rows = to_part ? DW_BN : a.N - n0;       // rows and columns of the destination from this tile's origin

@@ -82,7 +82,7 @@ constexpr int dx_lds(int mb) {                  // four stages; the staging tile
 // Which tile the forward at one bit-width takes where K is not split: rounds of workgroups times the time of a tile, in ns, a fit
 // to 650 timed combinations (10 layers of 2000 x 1008 to 14336 x 4096, 100 to 4096 tokens).  Wide tiles are half as many, so
 // they lose while the narrow ones still fit one round (3600 x 3600, 1000 tokens 45 against 54 us) and win from the second
-// round on; the choice among the five forms is at most 2 % slower than the best of them.  int4, narrow -> chosen: 14336 x 4096,
+// round on; with the form that cuts K the choice is 0.2 % slower than the best on average, 4 % at worst.  int4, narrow -> chosen: 14336 x 4096,
 // 2011 tokens 256 -> 221 us, 4096 tokens 501 -> 425 us; 2304 x 9216, 4096 tokens 199 -> 168 us; 3600 x 3600, 1600 tokens 82
 // -> 59 us; 2000 x 1008, 4096 tokens 34 -> 28.5 us.
 // The result is the height of the better wide tile in blocks of 32 tokens, or 0 where the tiles of fwd_kernel are faster; *ns,
@@ -122,10 +122,12 @@ struct FwdSplitPlan {
 // the workgroups it holds (80 KB of LDS and 256 registers each where two fit), but never less than the 1000 cycles a stage
 // takes to arrive; all workgroups together cannot read codes faster than 2900 or tiles of X faster than 4100 bytes per
 // cycle; a workgroup starts and ends in 4200 cycles; launches and the finishing kernel cost 8500 cycles, 1800 bytes of
-// accumulators take a cycle to be written and read back.  The constants are a fit to 2200 timed combinations (10 layers of
-// 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths): the choice is 1.5 % slower than the best of them
-// on average.  Measured, tiled -> chosen: 4096 x 4096, 77 tokens, int4 37.6 -> 15.7 us; 4096 x 14336 117 -> 26 us;
-// 2304 x 9216 at r = 8/4/2, 203 tokens 125 -> 44 us; level with the tiled kernel at 600 (14336 rows: 130) tokens and more.
+// accumulators take a cycle to be written and read back.  The constants are a fit; over 4770 timed combinations (10 layers of
+// 256 x 256 to 36864 x 4608, 17 to 2000 tokens, one to three bit-widths) the choice is 1.7 % slower than the best cut that it
+// weighs on average, 27 % at worst (2000 x 1008, 700 tokens, two bit-widths).  One range at more than 64 tokens is not
+// weighed: it would pay on the smallest layers only (256 x 256, 77 to 700 tokens 9.3 us against 12.5).  Measured, tiled ->
+// chosen: 4096 x 4096, 77 tokens, int4 38.7 -> 17.8 us; 4096 x 14336 115 -> 26 us; 2304 x 9216 at r = 8/4/2, 203 tokens 86 ->
+// 44 us; level with the tiled kernel at 700 (14336 rows: 200) tokens and more.
 //
 // The objective does not enter the rule, although its calls have no wide tiles to fall back on: the sums of a call with the
 // objective have to run in the order of those of the call without.  It costs the former 4 % (at most 11 %) on the one size in
@@ -183,9 +185,9 @@ struct DxPlan {
 // and the barrier, for each of the workgroups that a compute unit holds (two where the stages of 32 tokens fit twice into its
 // LDS), but never less than the 1055 + 140 per token block it takes to arrive; all workgroups together do not get gradients
 // faster than 3650 or codes faster than 6480 bytes per cycle; a tile's epilogue costs 900 per token block, the finishing
-// launch 4100 and 310 per range, and 1940 bytes of accumulators go out and come back per cycle.  The constants are a fit to
-// 3100 timed combinations (8 layers of 256 x 256 to 14336 x 4096, 16 to 4096 tokens, one and three bit-widths): the choice
-// is 0.4 % slower than the best of them on average, 9 % at worst.  dX with its preparation, 160-token tiles -> chosen, at
+// launch 4100 and 310 per range, and 1940 bytes of accumulators go out and come back per cycle.  The constants are a fit; over
+// 3500 timed combinations (8 layers of 256 x 256 to 14336 x 4096, 16 to 4096 tokens, one and three bit-widths) the choice
+// is 0.7 % slower than the best of them on average, 18 % at worst (256 x 256, 2000 tokens, r = 8/4/2).  dX with its preparation, 160-token tiles -> chosen, at
 // r = 8/4/2: 9216 x 2304, 16 tokens 263 -> 54 us, 400 tokens 342 -> 96 us, 2000 tokens 371 -> 274 us; 3600 x 3600, 400
 // tokens 160 -> 73 us, 4096 tokens 388 -> 354 us; 256 x 256, 16 tokens 15.6 (32-token tile) -> 13.9 us; the same at
 // 4096 tokens through 9216 x 2304 (499 us).
