@@ -3,6 +3,7 @@
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "mq_gemv.h"
 
@@ -31,11 +32,37 @@ __device__ __forceinline__ void stage_barrier() {
 
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ f32x16 mfma32(const u32x4 &a, const u32x4 &b, const f32x16 &c) {
-    Frag8 fa, fb;
-    fa.u = a;
-    fb.u = b;
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.b, fb.b, c, 0, 0, 0);
+// f(integral_constant 0), ..., f(integral_constant N - 1): the schedules below are written out at compile time
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_each(std::make_integer_sequence<int, N>{}, f);
+}
+
+// acc += A B on the 16x16x32 product, in place in the accumulator file.  The large kernels are bound by the power that the chip
+// draws, and of the two bf16 shapes this one does more work for it: a loop of products alone, operands from LDS, one wave per
+// SIMD, runs at 1.93 PFLOP/s on N(0, 1) values (32x32x16: 1.71), at 2.28 with small codes as A (1.76; codes as B: 2.07), which is
+// why codes are A everywhere.  14336 x 3584, 8192 tokens, r = 8/4/2: forward with the objective 2050 -> 1900 us, dX 2000 -> 1790,
+// dW 685 -> 625 (the clock rises from 1.72 to 2.0 GHz).  In assembly because the register allocator, given the
+// builtin, does not keep 240 and more accumulator registers in place: it moved them about with hundreds of copies per stage.
+// The compiler does not see a matrix product here, so the waits it would place are ours: an operand written by a vector
+// instruction (not one read from LDS) is used two instructions later at the earliest, and an accumulator is read or copied eight
+// cycles after its product at the earliest, which mfma16_settle() behind the last product of a stage sees to (the matrix core is
+// still busy then).
+// FILE_A: the accumulator file or (where two workgroups share a compute unit and it holds 128 registers) the vector file.
+template <bool FILE_A = true>
+__device__ __forceinline__ void mfma16_acc(f32x4 &acc, const u32x4 &a, const u32x4 &b) {
+    if constexpr (FILE_A)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma16_settle() {
+    asm volatile("s_nop 7");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // ---- LDS tiles ------------------------------------------------------------------------------
@@ -66,7 +93,7 @@ __device__ __forceinline__ void u8_tile_lane(int wave, int lane, int inst, uint3
 }
 
 // ---- code -> bf16 operand conversion -----------------------------------------------------------
-// r-bit slice of section 3.2 as bf16(128 + code): the kernels' convert_piece, two codes at a time.
+// r-bit slice of section 3.2 as bf16(128 + code), two codes at a time.
 struct SliceParam {  // wave-uniform per bit-width
     uint32_t half2;  // half (<< 8 unless EP) in both 16-bit lanes
     uint32_t sh;     // shift that leaves the code
@@ -84,6 +111,109 @@ __device__ __forceinline__ SliceParam slice_param(int r) {
         p.sh = s + 8;
     }
     return p;
+}
+
+// Four codes (one dword) -> two dwords of bf16 pairs, in four steps of two independent instructions each, so that a step fits
+// behind a matrix product without waiting for the one before it (a wave issues a dependent vector instruction only every eight
+// cycles, and a 16x16x32 product takes sixteen).  t carries the values between the steps; the empty asm keeps a step where it is.
+template <bool IS8, bool EP, int STEP>
+__device__ __forceinline__ void convert_step(uint32_t d, const SliceParam &p, uint32_t (&t)[4], uint32_t &lo, uint32_t &hi) {
+    if constexpr (IS8) {  // int8 -> fp32 -> bf16 (exact, codes <= 255)
+        if constexpr (STEP < 2) {
+            t[2 * STEP] = __float_as_uint((float)((d >> (16 * STEP)) & 0xFFu));
+            t[2 * STEP + 1] = __float_as_uint((float)((d >> (16 * STEP + 8)) & 0xFFu));
+            asm volatile("" : "+v"(t[2 * STEP]), "+v"(t[2 * STEP + 1]));
+        } else if constexpr (STEP == 2) {
+            lo = __builtin_amdgcn_perm(t[1], t[0], 0x07060302u);
+            hi = __builtin_amdgcn_perm(t[3], t[2], 0x07060302u);
+            asm volatile("" : "+v"(lo), "+v"(hi));
+        }
+    } else {
+        if constexpr (STEP == 0) {
+            t[0] = __builtin_amdgcn_perm(0u, d, EP ? 0x0C010C00u : 0x010C000Cu);
+            t[1] = __builtin_amdgcn_perm(0u, d, EP ? 0x0C030C02u : 0x030C020Cu);
+        } else if constexpr (STEP == 1) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                t[c] = EP ? t[c] + p.half2
+                          : __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, t[c]),
+                                                                                       __builtin_bit_cast(u16x2, p.half2)));
+        } else if constexpr (STEP == 2) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const unsigned short s16 = (unsigned short)p.sh;
+                t[c] = EP ? t[c] >> p.sh : __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, t[c]) >> u16x2{s16, s16});
+            }
+        } else {
+            lo = (EP ? t[0] & 0x00FF00FFu : t[0]) | kMagic128;
+            hi = (EP ? t[1] & 0x00FF00FFu : t[1]) | kMagic128;
+            asm volatile("" : "+v"(lo), "+v"(hi));
+        }
+
+    }
+}
+// What stands between the products of one 32-wide step, laid out at compile time.  A product takes the matrix core sixteen cycles
+// and a wave issues an instruction every four, so up to three instructions fit behind each without cost, and a fourth one that
+// another product could have had idles the matrix core.
+//   NM products, GROUP of them per block of 16 tokens (BLOCKS blocks); PAIRS dwords of codes to convert for the next step, those
+//   at multiples of PERIOD by the route of r = 8 if HAS8 (three conversion steps instead of four); STEP 0 or 1 of the stage;
+//   LOADS global loads and CODES reads of the next stage's code bytes: in LONG stages the former over both steps and the latter
+//   early in step 0; in short ones, in which loads are waited for, the former in step 0, and the latter once the bytes of this stage
+//   are used up, which saves copying them;
+//   IN_PLACE: the operands of a token block are read at its last product, otherwise at the first BLOCKS products.
+template <int NM, int GROUP, int BLOCKS, int PAIRS, int PERIOD, bool HAS8, int STEP, int LOADS, bool LONG, int CODES, bool IN_PLACE>
+struct StepSchedule {
+    int conv[NM + 1] = {};                // conversion steps before product q
+    int load[NM + 1] = {}, code[NM + 1] = {};
+    int pair[4 * PAIRS] = {}, step[4 * PAIRS] = {}, at[4 * PAIRS] = {};   // the conversion steps in their order
+    int width = 1;                        // pairs converted side by side
+    int first_load = 0;                   // loads of the steps before
+
+    constexpr StepSchedule() {
+        int uses[NM] = {};
+        for (int q = 0; q < NM; ++q) {
+            load[q + 1] = load[q];
+            code[q + 1] = code[q];
+            for (int l = 0; l < LOADS; ++l) {
+                const int block = l * (LONG ? 2 : 1) * BLOCKS / LOADS;
+                if (block / BLOCKS == STEP && block % BLOCKS * GROUP + 1 == q) ++load[q + 1], uses[q] += 3;
+                if (q == 0 && block / BLOCKS < STEP) ++first_load;
+            }
+            for (int e = 0; STEP == 0 && e < CODES; ++e)
+                if ((LONG ? e * GROUP + GROUP / 2 : NM - 2 - CODES + e) == q) ++code[q + 1], ++uses[q];
+            if (IN_PLACE ? q % GROUP == GROUP - 1 : q < BLOCKS) uses[q] += 2;
+        }
+        int total = 0;
+        for (int e = 0; e < PAIRS; ++e) total += HAS8 && e % PERIOD == 0 ? 3 : 4;
+        // room for conversion steps behind each product, at the least number of instructions per product for which they all fit;
+        // they are dealt out in proportion to it.  The last two products stay free (mfma16_acc).
+        int room[NM] = {}, rooms = 0, seen = 0, most = 1;
+        for (int budget = 3; rooms < total; ++budget) {
+            rooms = 0;
+            for (int q = 0; q < NM; ++q) rooms += room[q] = q < NM - 2 && uses[q] < budget ? (budget - uses[q]) / 2 : 0;
+        }
+        for (int q = 0; q < NM; ++q) {
+            seen += room[q];
+            conv[q + 1] = total * seen / rooms;
+            if (conv[q + 1] - conv[q] > most) most = conv[q + 1] - conv[q];
+        }
+        while (width < PAIRS && (width < most || PAIRS % width != 0)) ++width;
+        int n = 0;
+        for (int g = 0; g < PAIRS; g += width)
+            for (int s = 0; s < 4; ++s)
+                for (int w = 0; w < width; ++w)
+                    if (s < 3 || !(HAS8 && (g + w) % PERIOD == 0)) pair[n] = g + w, step[n] = s, at[n++] = w;
+    }
+};
+// all four steps at once (prologues)
+template <bool IS8, bool EP>
+__device__ __forceinline__ u32x4 convert_eight(uint32_t d0, uint32_t d1, const SliceParam &p) {
+    uint32_t o[4], t[4];
+    static_for<8>([&](auto c_tag) {
+        constexpr int c = decltype(c_tag)::value, half = c / 4;
+        convert_step<IS8, EP, c % 4>(half ? d1 : d0, p, t, o[2 * half], o[2 * half + 1]);
+    });
+    return u32x4{o[0], o[1], o[2], o[3]};
 }
 
 // ============================================================================================
@@ -112,20 +242,25 @@ struct FwdArgs {
     int gate;
 };
 
-// The contraction of one workgroup: acc[i][j] = sum over k in [64 kt0, k_end) of code_i[channels of this wave][k] *
-// X[tokens m0 + 32 j ..][k], for all bit-widths i and token blocks j of the tile at (m0, n0).  Four waves; wave w owns
-// channels [32 w, 32 w + 32) of the tile for all its tokens.  ROWSUM: also rsum[j] += this thread's share (chunk t % 8 of
+// Where an accumulator lives: with three bit-widths and 96 tokens two workgroups share a compute unit, each with 128 accumulator
+// registers, and four of the 36 blocks go to the vector file.
+constexpr bool fwd_acc_in_file_a(int nr, int mb, int i, int tb) { return !(nr == 3 && mb == 3 && tb == 5 && i > 0); }
+
+// The contraction of one workgroup: acc[i][rb][tb] = sum over k in [64 kt0, k_end) of code_i[channels 16 rb .. of this wave][k] *
+// X[tokens m0 + 16 tb ..][k], for all bit-widths i and token blocks tb of the tile at (m0, n0).  Four waves; wave w owns
+// channels [32 w, 32 w + 32) of the tile for all its tokens; lane (l16, g4) ends up with channels 4 g4 .. 4 g4 + 3 of token l16 of
+// a block.  ROWSUM: also rsum[j] += this thread's share (chunk t % 8 of
 // row t / 8) of sum_k X for the token blocks in rs_mask.
 template <int NR, bool HAS8, bool EP, int MB, bool ROWSUM>
 __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, int m0, int n0, int kt0, int nkt, int k_end,
-                                              f32x16 (&acc)[NR][MB], float (&rsum)[MB], uint32_t rs_mask) {
+                                              f32x4 (&acc)[NR][2][2 * MB], float (&rsum)[MB], uint32_t rs_mask) {
     constexpr int BM = 32 * MB;
     constexpr int X_TILE = BM * 128;
     constexpr int STAGE = X_TILE + FWD_Q_TILE;
     constexpr int LPS = MB + 2;  // direct-to-LDS loads per wave and stage
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int h = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
 
     const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.X + (size_t)m0 * a.K, (uint64_t)(a.M - m0) * a.K * 2);
     const __amdgpu_buffer_rsrc_t rQ = make_rsrc(a.Q + (size_t)n0 * a.K, (uint64_t)(a.N - n0) * a.K);
@@ -160,48 +295,24 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
         for (int i = 0; i < MB + 2; ++i) issue_one(kt, i);
     };
 
-    // LDS fragment addresses (byte offsets inside a stage)
-    const int nl = wave * 32 + l32;
-    const uint32_t qa0 = X_TILE + nl * 64 + ((h ^ ((nl >> 2) & 3)) << 4);
-    const uint32_t qa1 = X_TILE + nl * 64 + (((h + 2) ^ ((nl >> 2) & 3)) << 4);
-    uint32_t xa[4];
+    // LDS fragment addresses (byte offsets inside a stage).  The order of the contraction inside a stage is free as long as both
+    // operands follow it: a lane reads the sixteen code bytes 16 g4 .. of a row at once and uses eight of them per 32-wide step.
+    const int nl = wave * 32 + l16;
+    const uint32_t qa = X_TILE + nl * 64 + ((g4 ^ ((nl >> 2) & 3)) << 4);   // + 1024 per block of 16 channels
+    uint32_t xa[2];                                                         // + 2048 per block of 16 tokens
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int cx = 2 * h + 4 * (t >> 1) + (t & 1);
-        xa[t] = l32 * 128 + ((cx ^ ((l32 >> 1) & 7)) << 4);
-    }
+    for (int t = 0; t < 2; ++t) xa[t] = l16 * 128 + (((2 * g4 + t) ^ ((l16 >> 1) & 7)) << 4);
 
     SliceParam sp[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) sp[i] = slice_param<EP>(a.r[i]);
 
-    // Dword w (two consecutive k) of the code operand of slot i, from the 8 code bytes (d0, d1).
-    auto convert_piece = [&](int i, int w, uint32_t d0, uint32_t d1) -> uint32_t {
-        const uint32_t d = w < 2 ? d0 : d1;
-        if (HAS8 && i == 0) {
-            const float lo = (w & 1) ? (float)((d >> 16) & 0xFFu) : (float)(d & 0xFFu);
-            const float hi = (w & 1) ? (float)(d >> 24) : (float)((d >> 8) & 0xFFu);
-            return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-        }
-        if constexpr (EP) {
-            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x0C030C02u : 0x0C010C00u);
-            return (((placed + sp[i].half2) >> sp[i].sh) & 0x00FF00FFu) | kMagic128;
-        } else {
-            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x030C020Cu : 0x010C000Cu);
-            u16x2 t = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, placed),
-                                                    __builtin_bit_cast(u16x2, sp[i].half2));
-            const unsigned short s16 = (unsigned short)sp[i].sh;
-            t = t >> u16x2{s16, s16};
-            return __builtin_bit_cast(uint32_t, t) | kMagic128;
-        }
-    };
-
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll
-        for (int j = 0; j < MB; ++j)
+        for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int tb = 0; tb < 2 * MB; ++tb) acc[i][rb][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     issue(0);
     issue(1);
@@ -209,31 +320,32 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     // stage 0 must have landed before the first operand fetch; stages 1 and 2 may stay in flight
     stage_barrier<2 * LPS, 0>();
 
-    u32x4 xf[MB];      // activation operands of the current k step (refilled as soon as they are consumed)
-    u32x4 raw[2];      // 32 code bytes of this lane's channel: four k steps of one stage
-    u32x4 wf[NR];      // code operands of the current k step
-    raw[0] = *reinterpret_cast<const u32x4 *>(smem + qa0);
-    raw[1] = *reinterpret_cast<const u32x4 *>(smem + qa1);
+    // Activation operands.  A block of tokens is done with after 2 NR products, and where the next block of the same step keeps
+    // the matrix core busy for long enough its register is refilled for the next step right there; the smallest tiles have a
+    // second set, which is requested from the first product on.
+    constexpr int XS = (NR == 1 || MB <= 2) ? 2 : 1;
+    u32x4 xf[XS][2 * MB];
+    u32x4 raw[2];          // the sixteen code bytes of this lane's two channels: both steps of one stage
+    u32x4 wf[2][NR][2];    // code operands of the two steps of a stage
 #pragma unroll
-    for (int j = 0; j < MB; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + j * 4096);
+    for (int rb = 0; rb < 2; ++rb) raw[rb] = *reinterpret_cast<const u32x4 *>(smem + qa + rb * 1024);
+#pragma unroll
+    for (int tb = 0; tb < 2 * MB; ++tb) xf[0][tb] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + tb * 2048);
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) wf[i][w] = convert_piece(i, w, raw[0][0], raw[0][1]);
+        for (int rb = 0; rb < 2; ++rb)
+            wf[0][i][rb] = HAS8 && i == 0 ? convert_eight<true, EP>(raw[rb][0], raw[rb][1], sp[i])
+                                          : convert_eight<false, EP>(raw[rb][0], raw[rb][1], sp[i]);
 
-    // One stage of 64 k: four 16-wide steps of NR * MB MFMAs.  A wave issues in order, so whatever
+    // One stage of 64 k: two 32-wide steps of 4 NR MB MFMAs.  A wave issues in order, so whatever
     // is queued behind an MFMA that waits for the matrix pipe waits with it; the other work of a
-    // step is therefore cut into one small group per MFMA, fenced so that the compiler keeps it
-    // there:  group q < MB requests operand block q of step t + 1 from LDS (it then has the rest
-    // of the step to arrive), groups 1 .. 4 NR each produce one dword of the next code operands,
-    // the last groups of step 0 issue the global loads of stage kt + 3, and step 2 fetches the
-    // code bytes of the next stage.  MORE (compile time): there is a next stage.
-    auto tile = [&](auto more_tag, int kt) {
-        constexpr bool MORE = decltype(more_tag)::value;
-        constexpr int NM = NR * MB;
-        constexpr int CQ = 4 * NR + 1 <= NM ? 1 : 0;                // first group that carries a conversion
-        constexpr int PPG = (4 * NR + NM - CQ - 1) / (NM - CQ);     // conversions per group (1 from MB = 4 on)
-        constexpr int LPG = (LPS + NM - 1) / NM;  // global loads per group in step 0
+    // step is therefore cut into small pieces (StepSchedule), fenced so that the compiler keeps them between the MFMAs: the
+    // conversions of the next step's code operands, the reads of its activation operands, the global loads of stage kt + 3, in
+    // step 0 the code bytes of the next stage.  (After the last stage that is a stage of zeros,
+    // which nobody multiplies: a copy of the code for the last stage made the compiler move accumulators between the two.)
+    auto tile = [&](int kt) {
+        constexpr int NM = 4 * NR * MB;
         const uint8_t *cur = smem + (kt & 3) * STAGE;
         const uint8_t *nxt = smem + ((kt + 1) & 3) * STAGE;
         u32x4 rawn[2];
@@ -247,69 +359,49 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
                     for (int w = 0; w < 4; ++w) rsum[j] += bf16_lo(v[w]) + bf16_hi(v[w]);
                 }
         }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const bool pre = t < 3 || MORE;  // is there a next step
-            const uint8_t *src = t < 3 ? cur + xa[(t + 1) & 3] : nxt + xa[0];
-            // code bytes of the next step
-            uint32_t d0 = t == 3 ? rawn[0][0] : (t + 1 < 2 ? raw[0][2 * (t + 1)] : raw[1][2 * (t + 1 - 2)]);
-            uint32_t d1 = t == 3 ? rawn[0][1] : (t + 1 < 2 ? raw[0][2 * (t + 1) + 1] : raw[1][2 * (t + 1 - 2) + 1]);
-            // pin the conversions of this step to this step (the optimizer would otherwise collect
-            // them across the loop back-edge)
-            if (pre) asm volatile("" : "+v"(d0), "+v"(d1));
-            u32x4 xfn[MB];
-            u32x4 wfn[NR];
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int j = q / NR, i = q % NR;
-                acc[i][j] = mfma32(wf[i], xf[j], acc[i][j]);
-                if (pre && q < MB) xfn[q] = *reinterpret_cast<const u32x4 *>(src + q * 4096);
-                if (pre && q >= CQ) {
-#pragma unroll
-                    for (int u = 0; u < PPG; ++u) {
-                        const int pc = (q - CQ) * PPG + u;
-                        if (pc < 4 * NR) {
-                            uint32_t piece = convert_piece(pc / 4, pc % 4, d0, d1);
-                            asm volatile("" : "+v"(piece));  // keeps the conversion inside this group
-                            wfn[pc / 4][pc % 4] = piece;
-                        }
+        static_for<2>([&](auto t_tag) {
+            constexpr int t = decltype(t_tag)::value;
+            constexpr StepSchedule<NM, 2 * NR, 2 * MB, 4 * NR, NR, HAS8, t, LPS, NR * MB >= 12, 2, XS == 1> plan;
+            const uint8_t *src = t == 0 ? cur + xa[1] : nxt + xa[0];
+            uint32_t tmp[plan.width][4];
+            static_for<NM>([&](auto q_tag) {
+                constexpr int q = decltype(q_tag)::value, tb = q / (2 * NR), i = q % (2 * NR) / 2, rb = q % 2;
+                mfma16_acc<fwd_acc_in_file_a(NR, MB, i, tb)>(acc[i][rb][tb], wf[t][i][rb], xf[t % XS][tb]);
+                if constexpr (XS == 2 && q < 2 * MB) xf[1 - t % XS][q] = *reinterpret_cast<const u32x4 *>(src + q * 2048);
+                if constexpr (XS == 1 && q % (2 * NR) == 2 * NR - 1) xf[0][tb] = *reinterpret_cast<const u32x4 *>(src + tb * 2048);
+                static_for<plan.code[q + 1] - plan.code[q]>([&](auto u_tag) {
+                    constexpr int e = plan.code[q] + decltype(u_tag)::value;
+                    rawn[e] = *reinterpret_cast<const u32x4 *>(nxt + qa + e * 1024);
+                });
+                static_for<plan.conv[q + 1] - plan.conv[q]>([&](auto u_tag) {
+                    constexpr int c = plan.conv[q] + decltype(u_tag)::value, pair = plan.pair[c], step = plan.step[c];
+                    constexpr int ci = pair % NR, crb = pair / NR / 2, half = pair / NR % 2;
+                    u32x4 &out = wf[1 - t][ci][crb];
+                    uint32_t lo = out[2 * half], hi = out[2 * half + 1];
+                    convert_step<HAS8 && ci == 0, EP, step>(t == 0 ? raw[crb][2 + half] : rawn[crb][half], sp[ci], tmp[plan.at[c]], lo, hi);
+                    if constexpr (step == (HAS8 && ci == 0 ? 2 : 3)) {
+                        out[2 * half] = lo;
+                        out[2 * half + 1] = hi;
                     }
-                }
-                if (MORE && t == 2) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-                        if (q == (NM > 2 ? NM - 2 + u : NM - 1)) rawn[u] = *reinterpret_cast<const u32x4 *>(nxt + (u ? qa1 : qa0));
-                }
-                if (MORE && t == 0) {
-#pragma unroll
-                    for (int u = 0; u < LPG; ++u) {
-                        const int ld = (NM - 1 - q) * LPG + u;  // the last groups carry the loads
-                        if (ld < LPS) issue_one(kt + 3, ld);
-                    }
-                }
+                });
+                static_for<plan.load[q + 1] - plan.load[q]>([&](auto u_tag) {
+                    issue_one(kt + 3, plan.first_load + plan.load[q] + decltype(u_tag)::value);
+                });
                 __builtin_amdgcn_sched_barrier(0);
-            }
-            if (pre) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) wf[i] = wfn[i];
-#pragma unroll
-                for (int j = 0; j < MB; ++j) xf[j] = xfn[j];
-            }
-        }
-        if (MORE) {
-            raw[0] = rawn[0];
-            raw[1] = rawn[1];
-        }
+            });
+        });
+        mfma16_settle();
+        raw[0] = rawn[0];
+        raw[1] = rawn[1];
     };
 
-    for (int kt = 0; kt + 1 < nkt; ++kt) {
-        // Stage kt + 1 must be resident for the operand prefetch at the end of this iteration; the
+    for (int kt = 0; kt < nkt; ++kt) {
+        // Stage kt + 1 must be resident for the operand prefetch of this iteration; the
         // loads of stage kt + 2 may stay in flight.  After the barrier every wave is done with
         // stage kt - 1, whose buffer stage kt + 3 reuses.
-        stage_barrier<LPS, MB>();
-        tile(std::true_type{}, kt);
+        stage_barrier<LPS, 2 * MB>();
+        tile(kt);
     }
-    tile(std::false_type{}, nkt - 1);
     wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
 }
 
@@ -331,7 +423,7 @@ struct DxArgs {
     int r[3];               // bit-width per slot
     int tiles_m, tiles_k;
     int splits;             // ranges of n per tile
-    float *part;            // splits > 1: fp32 accumulators, [split][tile][k block][token block][g][256] quads
+    float *part;            // splits > 1: fp32 accumulators, [split][tile][block of 16 k][block of 16 tokens][256] quads
 };
 
 DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr);

@@ -5,7 +5,7 @@
 // 128 output channels x 32 MB tokens (MB = 2 .. 6); four LDS stages of a [32 MB x 64] bf16 tile of X
 // and a [128 x 64] tile of int8 codes are filled by direct global->LDS loads, every wave turns the
 // codes of its 32 channels into one bf16 operand per requested bit-width in registers and issues
-// 32x32x16 MFMAs into one accumulator set per bit-width.
+// 16x16x32 MFMAs into one accumulator set per bit-width.
 //
 //   r = 8     : int8 -> fp32 -> bf16 (exact, codes <= 255).
 //   r < 8     : the slicing operator of section 3.2 on 16-bit lanes.  The byte is placed in the high
@@ -30,8 +30,10 @@ namespace mq {
 // ============================================================================================
 // forward
 // ============================================================================================
+// row stride of the staging tile of the epilogue: the 8-byte writes of sixteen tokens and the 16-byte read-back spread over all banks
+constexpr int FWD_OS = FWD_BN * 2 + 16;
 constexpr int fwd_lds(int mb, int nr) {
-    const int stages = FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE), staging = nr * mb * 32 * (FWD_BN * 2 + 8);
+    const int stages = FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE), staging = nr * mb * 32 * FWD_OS;
     return stages > staging ? stages : staging;
 }
 
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
     constexpr int BM = 32 * MB;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int h = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
 
     // What the epilogue needs from the kernel arguments is fetched now, into scalar registers that stay
     // live through the main loop: read where it is used, each costs a scalar-memory round trip with
@@ -91,36 +93,35 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
     const int tn = (int)(lid % width) / gsz;
     const int m0 = tm * BM, n0 = tn * FWD_BN;
 
-    f32x16 acc[NR][MB];
+    f32x4 acc[NR][2][2 * MB];
     float no_rowsum[MB];
     fwd_main_loop<NR, HAS8, EP, MB, false>(a, smem, m0, n0, 0, (a.K + BKT - 1) / BKT, a.K, acc, no_rowsum, 0u);
 
     // ---- epilogue ---------------------------------------------------------------------------
-    // accumulator v = 4 g + e of a lane holds row (channel) 8 g + 4 h + e, column (token) l32.
-    // A lane therefore owns only 4 consecutive channels of a token; the tile is first assembled in
-    // LDS ([token][channel] bf16, rows padded by 8 bytes so that both the 8-byte writes and the
-    // read-back are bank-conflict free) and then stored as whole 256-byte rows.
-    constexpr int OS = FWD_BN * 2 + 8;  // staging row stride in bytes
+    // a lane holds channels 4 g4 .. 4 g4 + 3 of token l16 per 16 x 16 block.
+    // It therefore owns only 4 consecutive channels of a token; the tile is first assembled in
+    // LDS ([token][channel] bf16, FWD_OS) and then stored as whole 256-byte rows.
+    constexpr int OS = FWD_OS;          // staging row stride in bytes
     constexpr int OT = BM * OS;         // one bit-width
     __syncthreads();                    // every wave is done with the operand stages
-    float rs[MB];
+    float rs[2 * MB];
 #pragma unroll
-    for (int j = 0; j < MB; ++j) {
-        const int m = m0 + j * 32 + l32;
-        rs[j] = m < a.M ? k_rowsum[m] : 0.f;
+    for (int tb = 0; tb < 2 * MB; ++tb) {
+        const int m = m0 + tb * 16 + l16;
+        rs[tb] = m < a.M ? k_rowsum[m] : 0.f;
     }
-    f32x4 alv[4], zev[4], bv[LOSS ? 4 : 1];
+    f32x4 alv[2], zev[2], bv[LOSS ? 2 : 1];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int nloc = wave * 32 + 8 * g + 4 * h;
-        alv[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-        zev[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (LOSS) bv[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < 2; ++rb) {
+        const int nloc = wave * 32 + rb * 16 + 4 * g4;
+        alv[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        zev[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (LOSS) bv[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (n0 + nloc < a.N) {
-            alv[g] = *reinterpret_cast<const f32x4 *>(k_alpha + n0 + nloc);
-            zev[g] = *reinterpret_cast<const f32x4 *>(k_zero + n0 + nloc);
+            alv[rb] = *reinterpret_cast<const f32x4 *>(k_alpha + n0 + nloc);
+            zev[rb] = *reinterpret_cast<const f32x4 *>(k_zero + n0 + nloc);
             if constexpr (LOSS)
-                if (k_bias) bv[g] = *reinterpret_cast<const f32x4 *>(k_bias + n0 + nloc);
+                if (k_bias) bv[rb] = *reinterpret_cast<const f32x4 *>(k_bias + n0 + nloc);
         }
     }
     // LOSS: the lane's chunks of the target are requested now, behind the parameter loads, and
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
     // without spills); the others are requested after the staging and arrive while the first ones
     // are consumed.
     constexpr int CHUNKS = BM * 16 / 256;
-    constexpr int EARLY = NR * MB > 12 ? 2 : (NR * MB == 12 ? CHUNKS / 2 : CHUNKS);
+    constexpr int EARLY = NR * MB > 12 || (NR == 3 && MB == 3) ? 2 : (NR * MB == 12 ? CHUNKS / 2 : CHUNKS);
     u32x4 tpre[LOSS ? CHUNKS : 1];
     auto request_target = [&](int it) {
         const int c = it * 256 + threadIdx.x;
@@ -143,9 +144,9 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
         for (int it = 0; it < EARLY; ++it) request_target(it);
     }
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int nloc = wave * 32 + 8 * g + 4 * h;
-        const f32x4 al = alv[g], ze = zev[g];
+    for (int rb = 0; rb < 2; ++rb) {
+        const int nloc = wave * 32 + rb * 16 + 4 * g4;
+        const f32x4 al = alv[rb], ze = zev[rb];
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             const bool is8 = HAS8 && i == 0;
@@ -155,17 +156,17 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) bz[e] = bias + ze[e];
 #pragma unroll
-            for (int j = 0; j < MB; ++j) {
+            for (int tb = 0; tb < 2 * MB; ++tb) {
                 float y[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     // (mult is a power of two, so the fused form rounds exactly like mult * acc - t)
-                    const float t = bz[e] * rs[j];
-                    const float inner = is8 ? acc[i][j][4 * g + e] - t : __builtin_fmaf(mult, acc[i][j][4 * g + e], -t);
-                    y[e] = LOSS ? __builtin_fmaf(al[e], inner, bv[g][e]) : al[e] * inner;
+                    const float t = bz[e] * rs[tb], v = acc[i][rb][tb][e];
+                    const float inner = is8 ? v - t : __builtin_fmaf(mult, v, -t);
+                    y[e] = LOSS ? __builtin_fmaf(al[e], inner, bv[rb][e]) : al[e] * inner;
                 }
                 const u32x2 o = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
-                *reinterpret_cast<u32x2 *>(smem + i * OT + (j * 32 + l32) * OS + nloc * 2) = o;
+                *reinterpret_cast<u32x2 *>(smem + i * OT + (tb * 16 + l16) * OS + nloc * 2) = o;
             }
         }
     }
@@ -184,11 +185,8 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
                 const int m = m0 + row, n = n0 + ch * 8;
                 if (m < a.M && n < a.N) {
                     const uint8_t *src = smem + i * OT + row * OS + ch * 16;
-                    const u32x2 lo = *reinterpret_cast<const u32x2 *>(src);
-                    const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + 8);
-                    if (k_Y[i])
-                        __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y},
-                                                    reinterpret_cast<u32x4 *>(k_Y[i] + (size_t)m * a.N + n));
+                    const u32x4 y = *reinterpret_cast<const u32x4 *>(src);
+                    if (k_Y[i]) __builtin_nontemporal_store(y, reinterpret_cast<u32x4 *>(k_Y[i] + (size_t)m * a.N + n));
                     if (k_gate) {
                         // the gated unit on the rounded outputs, pair by pair (the arithmetic of mq_gated_unit_fwd)
                         const bool use_silu = k_gate == 2;
@@ -196,7 +194,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
                             const float g = bf16_lo(pair), u = bf16_hi(pair);
                             return (use_silu ? silu(g) : gelu_tanh(g)) * u;
                         };
-                        const u32x2 o = {pack_bf16x2(gated(lo.x), gated(lo.y)), pack_bf16x2(gated(hi.x), gated(hi.y))};
+                        const u32x2 o = {pack_bf16x2(gated(y[0]), gated(y[1])), pack_bf16x2(gated(y[2]), gated(y[3]))};
                         __builtin_nontemporal_store(o, reinterpret_cast<u32x2 *>(k_A[i] + (size_t)m * (a.N >> 1) + (n >> 1)));
                     }
                 }
@@ -249,10 +247,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
             auto staged = [&](int it, u32x4 (&dst)[NR]) {
 #pragma unroll
                 for (int i = 0; i < NR; ++i) {
-                    const uint8_t *src = smem + i * OT + (crow + 16 * it) * OS + cch * 16;
-                    const u32x2 lo = *reinterpret_cast<const u32x2 *>(src);
-                    const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + 8);
-                    dst[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    dst[i] = *reinterpret_cast<const u32x4 *>(smem + i * OT + (crow + 16 * it) * OS + cch * 16);
                 }
             };
             u32x4 ynext[NR];
@@ -623,27 +618,27 @@ struct DwArgs {
 
 static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) { return remembered<DwPlan>(make_dw_plan, M, N, K, batch); }
 
-// Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, one small fenced group of
-// operand work per MFMA), without any code conversion: both operands are bf16 rows with the contraction index
-// (tokens) contiguous.  The four waves form a 2 x 2 grid over the tile.  HB = 4, a 256 x 256 tile, 128 x 128 per wave: 16
-// accumulators (all 256 accumulator registers), 8 operand reads per 16 MFMAs - the square wave tile is what keeps the LDS
-// traffic (32 KB read + 16 KB written per 16-token step and compute unit, 94 bytes per clock at the matrix-core rate) under
-// the 128 bytes per clock the LDS delivers.  HB = 2, a 128 x 128 tile, 64 x 64 per wave: 4 accumulators, 4 reads per 4 MFMAs,
-// two workgroups to a compute unit.  Stages are 32 tokens deep (64-byte rows); five of them fill the LDS (HB = 2: half of it).
+// Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, operand work fenced in between the
+// MFMAs), without any code conversion: both operands are bf16 rows with the contraction index (tokens) contiguous.  The four
+// waves form a 2 x 2 grid over the tile.  HB = 4, a 256 x 256 tile, 128 x 128 per wave: 64 accumulators of 16 x 16 (all 256
+// accumulator registers), 16 operand reads per 64 MFMAs - the square wave tile is what keeps the LDS traffic (32 KB read + 16 KB
+// written per 16 tokens and compute unit, 94 bytes per clock at the matrix-core rate) under the 128 bytes per clock the LDS
+// delivers.  HB = 2, a 128 x 128 tile, 64 x 64 per wave: 16 accumulators, 8 reads per 16 MFMAs, two workgroups to a compute
+// unit.  Stages are one 32-token step deep (64-byte rows); five of them fill the LDS (HB = 2: half of it).
 template <int HB>
 __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    constexpr int RB = HB, MB = HB, NM = RB * MB;
+    constexpr int RB = 2 * HB, NM = RB * RB;         // 16-row blocks of either operand per wave, MFMAs per stage
     constexpr int DW_BN = dw_side(HB), DW_BK = dw_side(HB);
     constexpr int DW_A_TILE = DW_BN * 64, DW_STAGE = DW_A_TILE + DW_BK * 64;
     constexpr int AL = DW_BN / 64, BL = DW_BK / 64;  // direct-to-LDS loads per wave and stage (16 rows each)
     constexpr int LPS = AL + BL;
-    static_assert(RB + MB <= NM && LPS <= NM, "not enough MFMAs to hide the operand work");
+    static_assert(LPS <= NM / 2, "not enough MFMAs to hide the loads");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave >> 1, wk = wave & 1;
-    const int h = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
 
     // work item -> tile and token range
     const int nmt_all = (a.M + DW_BM - 1) / DW_BM;
@@ -679,144 +674,135 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     u8_tile_lane<4>(wave, lane, 0, 64u, off0, colb);
     const uint32_t rstep = 64u * 64u;  // 64 rows further down
 
-    // load i of the stage of token block mt into LDS buffer `buf`.  The descriptor of a stage starts at the tile's
-    // first row inside that block and ends with the block, so rows past N (K) are out of range; a block or a piece
-    // past M is requested at an out-of-range offset.  Both are answered with zeros without touching memory, so the
-    // loads in flight are the same every stage.
+    // Load i of the stage of token block mt into LDS buffer `buf`.  The descriptors of a stage start at the tile's
+    // first row inside that block and end with the block, so rows past N (K) are out of range; a block or a piece
+    // past M or the range is requested at an out-of-range offset.  Both are answered with zeros without touching memory, so the
+    // loads in flight are the same every stage.  Stages are requested in their order: the bases walk along.
+    const int m_end = min(a.M, mt1 * DW_BM);
+    const uint16_t *g_base = GT + ((size_t)mt0 * a.N + n0) * 32, *x_base = a.XT + ((size_t)mt0 * a.K + k0) * 32;
+    const size_t g_block = (size_t)a.N * 32, x_block = (size_t)a.K * 32;
+    const uint64_t g_bytes = (uint64_t)(a.N - n0) * 64, x_bytes = (uint64_t)(a.K - k0) * 64;
     auto issue_one = [&](int mt, int buf, int i) {
-        const int mm = mt * DW_BM;
         uint8_t *base = smem + buf * DW_STAGE;
-        const uint32_t o = (mm + colb / 2 < a.M) ? off0 : kOOB;
-        if (i < AL) {
-            const __amdgpu_buffer_rsrc_t rG = make_rsrc(GT + ((size_t)mt * a.N + n0) * 32, (uint64_t)(a.N - n0) * 64);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rG, (lds_ptr)(base + (wave + i * 4) * 1024), 16,
+        const uint32_t o = (mt * DW_BM + colb / 2 < m_end) ? off0 : kOOB;
+        if (i < AL)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(g_base, g_bytes), (lds_ptr)(base + (wave + i * 4) * 1024), 16,
                                                      o + (uint32_t)i * rstep, 0, 0, 0);
-        } else {
-            const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.XT + ((size_t)mt * a.K + k0) * 32, (uint64_t)(a.K - k0) * 64);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rX, (lds_ptr)(base + DW_A_TILE + (wave + (i - AL) * 4) * 1024), 16,
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(x_base, x_bytes), (lds_ptr)(base + DW_A_TILE + (wave + (i - AL) * 4) * 1024), 16,
                                                      o + (uint32_t)(i - AL) * rstep, 0, 0, 0);
+        if (i == LPS - 1) {
+            g_base += g_block;
+            x_base += x_block;
         }
     };
 
-    // LDS fragment offsets inside a stage for the two 16-token steps of a stage
-    uint32_t ab[2], bb[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const uint32_t chunk = (uint32_t)((2 * t + h) ^ ((l32 >> 2) & 3)) << 4;
-        ab[t] = (uint32_t)(wn * 32 * RB + l32) * 64u + chunk;
-        bb[t] = (uint32_t)DW_A_TILE + (uint32_t)(wk * 32 * MB + l32) * 64u + chunk;
-    }
+    // LDS fragment offsets inside a stage: lane (l16, g4) takes tokens 8 g4 .. 8 g4 + 7 of row l16 of a block of 16
+    const uint32_t chunk = (uint32_t)(g4 ^ ((l16 >> 2) & 3)) << 4;
+    const uint32_t gb = (uint32_t)(wn * 16 * RB + l16) * 64u + chunk;
+    const uint32_t xb = (uint32_t)DW_A_TILE + (uint32_t)(wk * 16 * RB + l16) * 64u + chunk;
 
-    f32x16 acc[RB][MB];
+    f32x4 acc[RB][RB];   // [block of n][block of k]: rows 4 g4 .. 4 g4 + 3, column l16 of the block
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[rb][j][v] = 0.f;
+        for (int j = 0; j < RB; ++j) acc[rb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int nmt = mt1 - mt0;   // >= 1 (the host plans at least eight stages per range)
 #pragma unroll
     for (int st = 0; st < DW_NST - 1; ++st)
 #pragma unroll
         for (int i = 0; i < LPS; ++i) issue_one(mt0 + st, st, i);
     stage_barrier<(DW_NST - 2) * LPS, 0>();
 
-    u32x4 af[RB], bf[MB];
+    // The products of a stage come in two halves, over the first and over the second half of the columns' blocks.  Every operand
+    // has one register: the second half of the columns is read in the first half of the stage, the first half of the columns and
+    // each block of rows, as soon as it is done with, are read for the next stage in the second half.
+    u32x4 gf[RB], xf[RB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) af[rb] = *reinterpret_cast<const u32x4 *>(smem + ab[0] + rb * 2048);
+    for (int rb = 0; rb < RB; ++rb) gf[rb] = *reinterpret_cast<const u32x4 *>(smem + gb + rb * 1024);
 #pragma unroll
-    for (int j = 0; j < MB; ++j) bf[j] = *reinterpret_cast<const u32x4 *>(smem + bb[0] + j * 2048);
+    for (int j = 0; j < RB / 2; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xb + j * 1024);
 
-    // one stage: two 16-token steps; cb = LDS buffer of this stage
-    auto tile = [&](auto more_tag, int mt, int cb) {
-        constexpr bool MORE = decltype(more_tag)::value;
+    // one stage; cb = LDS buffer of this stage
+    auto tile = [&](int mt, int cb) {
         const int nb = cb + 1 == DW_NST ? 0 : cb + 1;   // buffer of the next stage
         const int ib = cb == 0 ? DW_NST - 1 : cb - 1;   // buffer of stage mt + NST - 1 (= the one of stage mt - 1)
-        const uint8_t *cur = smem + cb * DW_STAGE;
-        const uint8_t *nxt = smem + nb * DW_STAGE;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const bool pre = t == 0 || MORE;
-            const uint8_t *src = t == 0 ? cur : nxt;
-            const int tn_ = t == 0 ? 1 : 0;
-            u32x4 afn[RB], bfn[MB];
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int rb = q % RB, j = q / RB;
-                acc[rb][j] = mfma32(af[rb], bf[j], acc[rb][j]);
-                if (pre && q < RB) afn[q] = *reinterpret_cast<const u32x4 *>(src + ab[tn_] + q * 2048);
-                if (pre && q >= RB && q < RB + MB)
-                    bfn[q - RB] = *reinterpret_cast<const u32x4 *>(src + bb[tn_] + (q - RB) * 2048);
-                if (MORE && t == 0 && q >= NM - LPS) issue_one(mt + DW_NST - 1, ib, q - (NM - LPS));
-                __builtin_amdgcn_sched_barrier(0);
+        const uint8_t *cur = smem + cb * DW_STAGE, *nxt = smem + nb * DW_STAGE;
+        static_for<NM>([&](auto q_tag) {
+            constexpr int q = decltype(q_tag)::value, H = NM / 2, HJ = RB / 2;
+            constexpr int half = q / H, rb = q % H / HJ, j = half * HJ + q % HJ;
+            mfma16_acc<HB == 4>(acc[rb][j], gf[rb], xf[j]);
+            if constexpr (half == 0) {
+                if constexpr (q < HJ) xf[HJ + q] = *reinterpret_cast<const u32x4 *>(cur + xb + (HJ + q) * 1024);
+                constexpr int L0 = LPS * q / H, L1 = LPS * (q + 1) / H;
+                if constexpr (L1 > L0) issue_one(mt + DW_NST - 1, ib, L0);
+            } else {
+                if constexpr (q - H < HJ) xf[q - H] = *reinterpret_cast<const u32x4 *>(nxt + xb + (q - H) * 1024);
+                if constexpr (q % HJ == HJ - 1) gf[rb] = *reinterpret_cast<const u32x4 *>(nxt + gb + rb * 1024);
             }
-            if (pre) {
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) af[rb] = afn[rb];
-#pragma unroll
-                for (int j = 0; j < MB; ++j) bf[j] = bfn[j];
-            }
-        }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        mfma16_settle();
     };
 
-    int cb = 0;
-    for (int mt = 0; mt + 1 < nmt; ++mt) {
-        // stage mt + 1 must be resident (operand prefetch at the end of this stage); the loads of
-        // stages mt + 2 and mt + 3 may stay in flight; after the barrier the buffer of stage mt - 1
-        // is free for stage mt + 4
-        stage_barrier<(DW_NST - 3) * LPS, RB + MB>();
-        tile(std::true_type{}, mt0 + mt, cb);
+    for (int mt = mt0, cb = 0; mt < mt1; ++mt) {
+        // Stage mt + 1 must be resident (operands read for it inside this stage); the loads of stages mt + 2 and mt + 3 may stay
+        // in flight; after the barrier the buffer of stage mt - 1, all of whose operands have been multiplied, is free for stage
+        // mt + 4.
+        stage_barrier<(DW_NST - 3) * LPS, RB + RB / 2>();
+        tile(mt, cb);
         cb = cb + 1 == DW_NST ? 0 : cb + 1;
     }
-    tile(std::false_type{}, mt0 + nmt - 1, cb);
     wait_vm0();  // loads of stages that nobody consumes must have landed before the workgroup ends
 
-    // Rows of the product are n, columns k: a store instruction writes 32 consecutive k (one 128-byte line)
-    // of two rows.  Branch-free: every store goes through a buffer descriptor that starts at the first
-    // element of the wave's 32-row block and ends with the destination, so rows past N fall out of range and are
+    // Two neighbouring column blocks exchange half of their lanes, after which a store instruction writes 32 consecutive k (one
+    // 128-byte line) of two rows (lines left to two instructions of 64 bytes per row: 9216 x 2304, 16 tokens 17.2 -> 21.7 us).
+    // Branch-free: every store goes through a buffer descriptor that starts at the first
+    // element of the wave's 16-row block and ends with the destination, so rows past N fall out of range and are
     // dropped by the memory unit; a column past K is sent out of range explicitly.  The row part of the
-    // address (wave-uniform) travels in the scalar offset, the lane part in one register per k block.
+    // address (wave-uniform) travels in the scalar offset, the lane part in one register per pair of blocks.
     // A token range of a cut tile writes its whole partial tile instead (row length = side of the tile, no edges).
-    // When accumulating, the old values of four rows are requested together, one memory round trip per 16 values.
+    // When accumulating, the old values of a row block are requested together, one memory round trip for all of them.
     const int ld = to_part ? DW_BK : a.K;              // row length of the destination
     const int rows = to_part ? DW_BN : a.N - n0;       // rows and columns of the destination from this tile's origin
     const int cols = to_part ? DW_BK : a.K - k0;
     float *origin = to_part ? dst : dst + (int64_t)n0 * a.K + k0;
+    uint32_t voff[RB / 2];
+#pragma unroll
+    for (int jp = 0; jp < RB / 2; ++jp) {
+        const int c = wk * 16 * RB + jp * 32 + (lane & 31);
+        voff[jp] = c < cols ? ((uint32_t)(8 * (lane >> 5)) * (uint32_t)ld + (uint32_t)c) * 4u : kOOB;
+    }
     auto store_tile = [&](auto accumulate_tag) {
         constexpr bool ACCUMULATE = decltype(accumulate_tag)::value;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int r0 = wn * 32 * RB + rb * 32;                      // first row of the block inside the tile
+            const int r0 = wn * 16 * RB + rb * 16;                      // first row of the block inside the tile
             const int64_t left = ((int64_t)rows - r0) * ld - (to_part ? 0 : k0);  // elements to the end of the destination
             const __amdgpu_buffer_rsrc_t rW = make_rsrc(origin + (int64_t)r0 * ld, left > 0 ? (uint64_t)left * 4u : 0u);
-            uint32_t voff[MB];
+            uint32_t old[ACCUMULATE ? 8 : 1][RB / 2];
+            if constexpr (ACCUMULATE) {
 #pragma unroll
-            for (int j = 0; j < MB; ++j) {
-                const int c = wk * 32 * MB + j * 32 + l32;
-                voff[j] = c < cols ? ((uint32_t)(4 * h) * (uint32_t)ld + (uint32_t)c) * 4u : kOOB;
+                for (int row = 0; row < 8; ++row)
+#pragma unroll
+                    for (int jp = 0; jp < RB / 2; ++jp)
+                        old[row][jp] = __builtin_amdgcn_raw_buffer_load_b32(rW, voff[jp], (uint32_t)row * (uint32_t)ld * 4u, 0);
             }
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                uint32_t old[ACCUMULATE ? 4 : 1][MB];
-                if constexpr (ACCUMULATE) {  // the values of four rows are requested together
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                for (int jp = 0; jp < RB / 2; ++jp) {
+                    // rows (0 and 8) + e in the first result, (4 and 12) + e in the second
+                    const auto two = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rb][2 * jp][e]), __float_as_uint(acc[rb][2 * jp + 1][e]),
+                                                                      false, false);
 #pragma unroll
-                        for (int j = 0; j < MB; ++j)
-                            old[e][j] = __builtin_amdgcn_raw_buffer_load_b32(rW, voff[j], (uint32_t)(8 * g + e) * (uint32_t)ld * 4u, 0);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t row = (uint32_t)(8 * g + e) * (uint32_t)ld * 4u;
-#pragma unroll
-                    for (int j = 0; j < MB; ++j) {
-                        float v = acc[rb][j][4 * g + e];
-                        if constexpr (ACCUMULATE) v = __uint_as_float(old[e][j]) + v;
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rW, voff[j], row, 0);
+                    for (int u = 0; u < 2; ++u) {
+                        const int row = 4 * u + e;
+                        float v = __uint_as_float(two[u]);
+                        if constexpr (ACCUMULATE) v = __uint_as_float(old[row][jp]) + v;
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rW, voff[jp], (uint32_t)row * (uint32_t)ld * 4u, 0);
                     }
                 }
-            }
         }
     };
     if (a.accumulate && !to_part)

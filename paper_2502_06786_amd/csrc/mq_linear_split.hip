@@ -16,13 +16,13 @@ namespace mq {
 
 struct FwdSplitArgs {
     FwdArgs f;
-    float *part;     // [split][tile][bit-width][token block][g][256] four channels of one token each
+    float *part;     // [split][tile][bit-width][block of 16 channels][block of 16 tokens][256] four channels of one token each
     float *rs_part;  // [split][tiles_m * 32 MB] sums of X over the split's range of K
     int splits;
 };
 
 template <int NR, bool HAS8, bool EP, int MB>
-__global__ __launch_bounds__(256) void fwd_split_kernel(FwdSplitArgs s) {
+__global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(FwdSplitArgs s) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const FwdArgs &a = s.f;
     constexpr int BM = 32 * MB;
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void fwd_split_kernel(FwdSplitArgs s) {
         rsum[j] = 0.f;
         if (j % a.tiles_n == tn) rs_mask |= 1u << j;
     }
-    f32x16 acc[NR][MB];
+    f32x4 acc[NR][2][2 * MB];
     fwd_main_loop<NR, HAS8, EP, MB, true>(a, smem, m0, n0, kt0, kt1 - kt0, min(a.K, kt1 * BKT), acc, rsum, rs_mask);
 
 #pragma unroll
@@ -58,30 +58,28 @@ __global__ __launch_bounds__(256) void fwd_split_kernel(FwdSplitArgs s) {
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll
-        for (int j = 0; j < MB; ++j)
+        for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                dst[((i * MB + j) * 4 + g) * 256] =
-                    f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+            for (int tb = 0; tb < 2 * MB; ++tb) dst[((i * 2 + rb) * 2 * MB + tb) * 256] = acc[i][rb][tb];
 }
 
-// Adds the K ranges and finishes the outputs.  Workgroup = (tile, token block, 32 channels): wave g takes accumulator rows
-// 8 g + 4 h .. + 3, so the four waves write 64 contiguous bytes of 32 tokens.  The arithmetic per output is that of the
+// Adds the K ranges and finishes the outputs.  Workgroup = (tile, 32 tokens, 32 channels): its waves take the four 16 x 16
+// blocks and write 64 contiguous bytes of 32 tokens.  The arithmetic per output is that of the
 // tiled forward kernel's epilogue.
 template <int NR, bool LOSS>
 __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, int mb) {
     __shared__ float red[4][4];
     const FwdArgs &a = s.f;
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int h = lane >> 5, l32 = lane & 31;
-    const int w = blockIdx.x & 3, j = (int)(blockIdx.x >> 2) % mb, tile = (int)(blockIdx.x >> 2) / mb;
+    const int g4 = lane >> 4, l16 = lane & 15, rb = g & 1;
+    const int w = blockIdx.x & 3, tb = (int)(blockIdx.x >> 2) % mb * 2 + (g >> 1), tile = (int)(blockIdx.x >> 2) / mb;
     const int tiles = a.tiles_m * a.tiles_n;
     const int tn = tile / a.tiles_m, tm = tile % a.tiles_m;
-    const int m = tm * 32 * mb + j * 32 + l32, n = tn * FWD_BN + w * 32 + 8 * g + 4 * h;
+    const int m = tm * 32 * mb + tb * 16 + l16, n = tn * FWD_BN + w * 32 + rb * 16 + 4 * g4;
     const bool ok = m < a.M && n < a.N;
 
     const size_t rs_step = (size_t)a.tiles_m * 32 * mb, step = (size_t)tiles * NR * mb * 1024;
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(s.part) + (((size_t)tile * NR * mb + j) * 4 + g) * 256 + w * 64 + lane;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(s.part) + (((size_t)tile * NR * 2 + rb) * 2 * mb + tb) * 256 + w * 64 + lane;
     f32x4 sum[NR];
     float rs = 0.f;
 #pragma unroll

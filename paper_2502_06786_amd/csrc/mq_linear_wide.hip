@@ -22,20 +22,16 @@ static_assert(dx_lds(DX_MB) >= 32 * DX_MB * DX_OS && dx_lds(1) >= 32 * DX_OS, "t
 // property of each copy of the stage body.
 //
 template <int NRS, bool HAS8, bool EP, int MB>
-__device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, int m0, int k0, int nt0, int nt1, f32x16 (&acc)[DX_RB][MB]) {
-    constexpr int RB = DX_RB;
+__device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, int m0, int k0, int nt0, int nt1, f32x4 (&acc)[2 * DX_RB][2 * MB]) {
+    constexpr int RB = 2 * DX_RB;        // 16-row blocks per wave
     constexpr int A_TILE = MB * 4096;
     constexpr int STAGE = A_TILE + DX_Q_TILE;
     constexpr int QL = DX_BK / 64;       // direct-to-LDS loads per wave and stage for the codes (16 rows each)
     constexpr int LPS = MB + QL;         // loads per wave and stage
-    constexpr int NM = RB * MB;          // MFMAs per 16-wide step
-    constexpr int CQ = 4 * RB + 1 <= NM ? 1 : 0;             // first MFMA of a step that carries a conversion
-    constexpr int PPG = (4 * RB + NM - CQ - 1) / (NM - CQ);  // conversions per MFMA (1 from MB = 5 on)
-    constexpr int LPG = (LPS + NM - 1) / NM;                 // global loads per MFMA of step 0
-    constexpr int RPG = (2 * RB + NM - 1) / NM;              // code reads per MFMA of step 2
+    constexpr int NM = 2 * MB * RB;      // MFMAs per 32-wide step
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int h = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
 
     const int n_end = min(a.N, nt1 * BKT);
 
@@ -70,52 +66,21 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
         }
     };
 
-    // LDS fragment addresses (byte offsets inside a stage)
-    uint32_t qa[RB][2];
+    // LDS fragment addresses (byte offsets inside a stage); the order of the contraction is that of fwd_main_loop
+    const int kl = wave * (16 * RB) + l16;
+    const uint32_t qa = A_TILE + kl * 64 + ((g4 ^ ((kl >> 2) & 3)) << 4);   // + 1024 per block of 16 rows
+    uint32_t xa[2];                                                         // + 2048 per block of 16 tokens
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const int kl = wave * (32 * RB) + rb * 32 + l32;
-        qa[rb][0] = A_TILE + kl * 64 + ((h ^ ((kl >> 2) & 3)) << 4);
-        qa[rb][1] = A_TILE + kl * 64 + (((h + 2) ^ ((kl >> 2) & 3)) << 4);
-    }
-    uint32_t xa[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int cx = 2 * h + 4 * (t >> 1) + (t & 1);
-        xa[t] = l32 * 128 + ((cx ^ ((l32 >> 1) & 7)) << 4);
-    }
+    for (int t = 0; t < 2; ++t) xa[t] = l16 * 128 + (((2 * g4 + t) ^ ((l16 >> 1) & 7)) << 4);
 
     SliceParam sp[NRS];
 #pragma unroll
     for (int i = 0; i < NRS; ++i) sp[i] = slice_param<EP>(a.r[i]);
 
-    // dword w (two consecutive n) of the code operand of bit-width SLOT from 8 code bytes (d0, d1)
-    auto convert_piece = [&](auto slot_tag, int w, uint32_t d0, uint32_t d1) -> uint32_t {
-        constexpr int SLOT = decltype(slot_tag)::value;
-        const uint32_t d = w < 2 ? d0 : d1;
-        if constexpr (HAS8 && SLOT == 0) {
-            const float lo = (w & 1) ? (float)((d >> 16) & 0xFFu) : (float)(d & 0xFFu);
-            const float hi = (w & 1) ? (float)(d >> 24) : (float)((d >> 8) & 0xFFu);
-            return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-        } else if constexpr (EP) {
-            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x0C030C02u : 0x0C010C00u);
-            return (((placed + sp[SLOT].half2) >> sp[SLOT].sh) & 0x00FF00FFu) | kMagic128;
-        } else {
-            const uint32_t placed = __builtin_amdgcn_perm(0u, d, (w & 1) ? 0x030C020Cu : 0x010C000Cu);
-            u16x2 t = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, placed),
-                                                    __builtin_bit_cast(u16x2, sp[SLOT].half2));
-            const unsigned short s16 = (unsigned short)sp[SLOT].sh;
-            t = t >> u16x2{s16, s16};
-            return __builtin_bit_cast(uint32_t, t) | kMagic128;
-        }
-    };
-
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[rb][j][v] = 0.f;
+        for (int tb = 0; tb < 2 * MB; ++tb) acc[rb][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // prologue: stages 0, 1, 2 (n tile nt0 + st / NRS, bit-width st % NRS)
     {
@@ -130,119 +95,78 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
     }
     stage_barrier<2 * LPS, 0>();
 
-    u32x4 xf[MB];         // gradient operands of the current step
-    u32x4 raw[RB][2];     // 32 code bytes per k row of this lane: four steps of one stage
-    u32x4 wf[RB];         // code operands of the current step
+    constexpr int XS = MB <= 2 ? 2 : 1;   // sets of gradient operands (see fwd_main_loop)
+    u32x4 xf[XS][2 * MB];
+    u32x4 raw[RB];        // the sixteen code bytes of this lane's rows: both steps of one stage
+    u32x4 wf[2][RB];      // code operands of the two steps of a stage
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        raw[rb][0] = *reinterpret_cast<const u32x4 *>(smem + qa[rb][0]);
-        raw[rb][1] = *reinterpret_cast<const u32x4 *>(smem + qa[rb][1]);
+    for (int rb = 0; rb < RB; ++rb) raw[rb] = *reinterpret_cast<const u32x4 *>(smem + qa + rb * 1024);
 #pragma unroll
-        for (int w = 0; w < 4; ++w) wf[rb][w] = convert_piece(std::integral_constant<int, 0>{}, w, raw[rb][0][0], raw[rb][0][1]);
-    }
+    for (int tb = 0; tb < 2 * MB; ++tb) xf[0][tb] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + tb * 2048);
 #pragma unroll
-    for (int j = 0; j < MB; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + j * 4096);
+    for (int rb = 0; rb < RB; ++rb) wf[0][rb] = convert_eight<HAS8, EP>(raw[rb][0], raw[rb][1], sp[0]);
 
-    // One stage: four 16-wide steps.  st = index of this stage, nt3 / the slot of stage st + 3 are
-    // what the loads issued in step 0 fetch.
-    auto tile = [&](auto slot_tag, auto more_tag, int st, int nt) {
+    // One stage: two 32-wide steps, the other work in between the MFMAs as in fwd_main_loop.  st = index of this stage; the loads
+    // issued in step 0 fetch stage st + 3.
+    auto tile = [&](auto slot_tag, int st, int nt) {
         constexpr int SLOT = decltype(slot_tag)::value;
-        constexpr bool MORE = decltype(more_tag)::value;
         constexpr int NEXT = (SLOT + 1) % NRS;
         const uint8_t *cur = smem + (st & 3) * STAGE;
         const uint8_t *nxt = smem + ((st + 1) & 3) * STAGE;
-        u32x4 rawn[RB][2];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const bool pre = t < 3 || MORE;
-            const uint8_t *src = t < 3 ? cur + xa[(t + 1) & 3] : nxt + xa[0];
-            uint32_t d0[RB], d1[RB];
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                d0[rb] = t == 3 ? rawn[rb][0][0] : (t + 1 < 2 ? raw[rb][0][2 * (t + 1)] : raw[rb][1][2 * (t + 1 - 2)]);
-                d1[rb] = t == 3 ? rawn[rb][0][1] : (t + 1 < 2 ? raw[rb][0][2 * (t + 1) + 1] : raw[rb][1][2 * (t + 1 - 2) + 1]);
-                if (pre) asm volatile("" : "+v"(d0[rb]), "+v"(d1[rb]));  // pins the conversions to this step
-            }
-            u32x4 xfn[MB];
-            u32x4 wfn[RB];
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int j = q / RB, rb = q % RB;
-                acc[rb][j] = mfma32(wf[rb], xf[j], acc[rb][j]);
-                if (pre && q < MB) xfn[q] = *reinterpret_cast<const u32x4 *>(src + q * 4096);
-                if (pre && q >= CQ) {
-#pragma unroll
-                    for (int u = 0; u < PPG; ++u) {
-                        const int pc = (q - CQ) * PPG + u, prb = pc / 4, pw = pc % 4;
-                        if (pc < 4 * RB) {
-                            uint32_t piece = t < 3 ? convert_piece(std::integral_constant<int, SLOT>{}, pw, d0[prb], d1[prb])
-                                                   : convert_piece(std::integral_constant<int, NEXT>{}, pw, d0[prb], d1[prb]);
-                            asm volatile("" : "+v"(piece));  // keeps the conversion inside this group
-                            wfn[prb][pw] = piece;
-                        }
+        u32x4 rawn[RB];
+        static_for<2>([&](auto t_tag) {
+            constexpr int t = decltype(t_tag)::value;
+            constexpr int CSLOT = t == 0 ? SLOT : NEXT;       // bit-width of the operands that are converted
+            constexpr bool IS8 = HAS8 && CSLOT == 0;
+            // (the code bytes of a new n tile are read; those of its other bit-widths are at hand)
+            constexpr StepSchedule<NM, RB, 2 * MB, 2 * RB, 1, IS8, t, LPS, NRS == 3 && MB >= 4, NEXT == 0 ? RB : 0, XS == 1> plan;
+            const uint8_t *src = t == 0 ? cur + xa[1] : nxt + xa[0];
+            uint32_t tmp[plan.width][4];
+            static_for<NM>([&](auto q_tag) {
+                constexpr int q = decltype(q_tag)::value, tb = q / RB, rb = q % RB;
+                mfma16_acc(acc[rb][tb], wf[t][rb], xf[t % XS][tb]);
+                if constexpr (XS == 2 && q < 2 * MB) xf[1 - t % XS][q] = *reinterpret_cast<const u32x4 *>(src + q * 2048);
+                if constexpr (XS == 1 && rb == RB - 1) xf[0][tb] = *reinterpret_cast<const u32x4 *>(src + tb * 2048);
+                static_for<plan.code[q + 1] - plan.code[q]>([&](auto u_tag) {
+                    constexpr int e = plan.code[q] + decltype(u_tag)::value;
+                    rawn[e] = *reinterpret_cast<const u32x4 *>(nxt + qa + e * 1024);
+                });
+                static_for<plan.conv[q + 1] - plan.conv[q]>([&](auto u_tag) {
+                    constexpr int c = plan.conv[q] + decltype(u_tag)::value, crb = plan.pair[c] / 2, half = plan.pair[c] % 2;
+                    u32x4 &out = wf[1 - t][crb];
+                    uint32_t lo = out[2 * half], hi = out[2 * half + 1];
+                    convert_step<IS8, EP, plan.step[c]>(t == 0 ? raw[crb][2 + half] : NEXT == 0 ? rawn[crb][half] : raw[crb][half], sp[CSLOT],
+                                                        tmp[plan.at[c]], lo, hi);
+                    if constexpr (plan.step[c] == (IS8 ? 2 : 3)) {
+                        out[2 * half] = lo;
+                        out[2 * half + 1] = hi;
                     }
-                }
-                if (MORE && t == 2) {
-#pragma unroll
-                    for (int u = 0; u < RPG; ++u) {
-                        const int e = (q - NM) * RPG + RPG * ((2 * RB + RPG - 1) / RPG) + u;  // the last groups carry the reads
-                        if (e >= 0 && e < 2 * RB) {
-                            if constexpr (NEXT == 0)  // a new n tile: its code bytes
-                                rawn[e / 2][e % 2] = *reinterpret_cast<const u32x4 *>(nxt + qa[e / 2][e % 2]);
-                            else                      // the next bit-width of this n tile: the bytes at hand
-                                rawn[e / 2][e % 2] = raw[e / 2][e % 2];
-                        }
-                    }
-                }
-                if (MORE && t == 0) {
-#pragma unroll
-                    for (int u = 0; u < LPG; ++u) {
-                        const int ld = (NM - 1 - q) * LPG + u;
-                        if (ld < LPS) issue_one(nt + (SLOT + 3) / NRS, std::integral_constant<int, (SLOT + 3) % NRS>{}, (st + 3) & 3, ld);
-                    }
-                }
+                });
+                static_for<plan.load[q + 1] - plan.load[q]>([&](auto u_tag) {
+                    issue_one(nt + (SLOT + 3) / NRS, std::integral_constant<int, (SLOT + 3) % NRS>{}, (st + 3) & 3,
+                              plan.first_load + plan.load[q] + decltype(u_tag)::value);
+                });
                 __builtin_amdgcn_sched_barrier(0);
-            }
-            if (pre) {
+            });
+        });
+        mfma16_settle();
+        if constexpr (NEXT == 0) {
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) wf[rb] = wfn[rb];
-#pragma unroll
-                for (int j = 0; j < MB; ++j) xf[j] = xfn[j];
-            }
-        }
-        if (MORE) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                raw[rb][0] = rawn[rb][0];
-                raw[rb][1] = rawn[rb][1];
-            }
+            for (int rb = 0; rb < RB; ++rb) raw[rb] = rawn[rb];
         }
     };
-    auto stage = [&](auto slot_tag, auto more_tag, int st, int nt) {
-        // stage st + 1 must be resident (operand prefetch at the end of this stage); the loads of
+    auto stage = [&](auto slot_tag, int st, int nt) {
+        // stage st + 1 must be resident (operand prefetch inside this stage); the loads of
         // stage st + 2 may stay in flight; after the barrier the buffer of stage st - 1 is free
-        stage_barrier<LPS, MB>();
-        tile(slot_tag, more_tag, st, nt);
+        stage_barrier<LPS, 2 * MB>();
+        tile(slot_tag, st, nt);
     };
 
     int st = 0;
-    for (int nt = nt0; nt + 1 < nt1; ++nt) {
-        stage(std::integral_constant<int, 0>{}, std::true_type{}, st++, nt);
-        if constexpr (NRS > 1) stage(std::integral_constant<int, 1>{}, std::true_type{}, st++, nt);
-        if constexpr (NRS > 2) stage(std::integral_constant<int, 2>{}, std::true_type{}, st++, nt);
-    }
-    {
-        const int nt = nt1 - 1;
-        if constexpr (NRS == 1) {
-            stage(std::integral_constant<int, 0>{}, std::false_type{}, st++, nt);
-        } else if constexpr (NRS == 2) {
-            stage(std::integral_constant<int, 0>{}, std::true_type{}, st++, nt);
-            stage(std::integral_constant<int, 1>{}, std::false_type{}, st++, nt);
-        } else {
-            stage(std::integral_constant<int, 0>{}, std::true_type{}, st++, nt);
-            stage(std::integral_constant<int, 1>{}, std::true_type{}, st++, nt);
-            stage(std::integral_constant<int, 2>{}, std::false_type{}, st++, nt);
-        }
+    for (int nt = nt0; nt < nt1; ++nt) {
+        stage(std::integral_constant<int, 0>{}, st++, nt);
+        if constexpr (NRS > 1) stage(std::integral_constant<int, 1>{}, st++, nt);
+        if constexpr (NRS > 2) stage(std::integral_constant<int, 2>{}, st++, nt);
     }
     wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
 }
@@ -253,10 +177,10 @@ template <int NRS, bool HAS8, bool EP, int MB>
 __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    constexpr int RB = DX_RB, BM = 32 * MB;
+    constexpr int RB = 2 * DX_RB, BM = 32 * MB;  // 16-row blocks per wave
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int h = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
 
     const int tiles = a.tiles_m * a.tiles_k;
     const uint32_t wid = xcd_contiguous_id(blockIdx.x, gridDim.x);
@@ -272,19 +196,15 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
     const int tk = (int)(lid % width) / gsz;
     const int m0 = tm * BM, k0 = tk * DX_BK;
 
-    f32x16 acc[RB][MB];
+    f32x4 acc[RB][2 * MB];
     wide_main_loop<NRS, HAS8, EP, MB>(a, smem, m0, k0, nt0, nt1, acc);
 
     if (a.splits > 1) {
-        f32x4 *dst = reinterpret_cast<f32x4 *>(a.part) + ((size_t)split * tiles + lid) * (RB * MB * 4 * 256) + threadIdx.x;
+        f32x4 *dst = reinterpret_cast<f32x4 *>(a.part) + ((size_t)split * tiles + lid) * (RB * 2 * MB * 256) + threadIdx.x;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int j = 0; j < MB; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    dst[((rb * MB + j) * 4 + g) * 256] =
-                        f32x4{acc[rb][j][4 * g], acc[rb][j][4 * g + 1], acc[rb][j][4 * g + 2], acc[rb][j][4 * g + 3]};
+            for (int tb = 0; tb < 2 * MB; ++tb) dst[(rb * 2 * MB + tb) * 256] = acc[rb][tb];
         return;
     }
 
@@ -292,37 +212,35 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
     // assembled in LDS as [token][k] bf16 (rows padded by 8 bytes) and stored as whole 512-byte rows
     __syncthreads();
     // c[m] = sum over the column ranges of the prep kernel, in their order.  The partial sums of all the
-    // lane's tokens are requested four ranges at a time (20 loads in flight: one memory round trip per
+    // lane's tokens are requested four ranges at a time (one memory round trip per
     // group instead of one per value, which with nothing else to run cost more than the stores).
-    float cs[MB];
+    float cs[2 * MB];
 #pragma unroll
-    for (int j = 0; j < MB; ++j) cs[j] = 0.f;
+    for (int tb = 0; tb < 2 * MB; ++tb) cs[tb] = 0.f;
     for (int sp0 = 0; sp0 < a.nsplit; sp0 += 4) {
-        float part[4][MB];
+        float part[4][2 * MB];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int j = 0; j < MB; ++j) {
-                const int m = m0 + j * 32 + l32;
-                part[u][j] = (sp0 + u < a.nsplit && m < a.M) ? a.cvec[(size_t)(sp0 + u) * a.M + m] : 0.f;
+            for (int tb = 0; tb < 2 * MB; ++tb) {
+                const int m = m0 + tb * 16 + l16;
+                part[u][tb] = (sp0 + u < a.nsplit && m < a.M) ? a.cvec[(size_t)(sp0 + u) * a.M + m] : 0.f;
             }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int j = 0; j < MB; ++j) cs[j] += part[u][j];
+            for (int tb = 0; tb < 2 * MB; ++tb) cs[tb] += part[u][tb];
     }
 #pragma unroll
-    for (int j = 0; j < MB; ++j) {
-        const float c = cs[j];
+    for (int tb = 0; tb < 2 * MB; ++tb) {
+        const float c = cs[tb];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int kloc = wave * (32 * RB) + rb * 32 + 8 * g + 4 * h;
-                const u32x2 o = {pack_bf16x2(acc[rb][j][4 * g] - c, acc[rb][j][4 * g + 1] - c),
-                                 pack_bf16x2(acc[rb][j][4 * g + 2] - c, acc[rb][j][4 * g + 3] - c)};
-                *reinterpret_cast<u32x2 *>(smem + (j * 32 + l32) * DX_OS + kloc * 2) = o;
-            }
+        for (int rb = 0; rb < RB; ++rb) {
+            const int kloc = wave * (16 * RB) + rb * 16 + 4 * g4;
+            const f32x4 v = acc[rb][tb];
+            *reinterpret_cast<u32x2 *>(smem + (tb * 16 + l16) * DX_OS + kloc * 2) =
+                u32x2{pack_bf16x2(v[0] - c, v[1] - c), pack_bf16x2(v[2] - c, v[3] - c)};
+        }
     }
     __syncthreads();
     constexpr int CPR = DX_BK / 8;  // 16-byte chunks per row
@@ -333,10 +251,7 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
         const int m = m0 + row, k = k0 + ch * 8;
         if (m < a.M && k < a.K) {
             const uint8_t *src = smem + row * DX_OS + ch * 16;
-            const u32x2 lo = *reinterpret_cast<const u32x2 *>(src);
-            const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + 8);
-            __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y},
-                                        reinterpret_cast<u32x4 *>(a.dX + (size_t)m * a.K + k));
+            __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(src), reinterpret_cast<u32x4 *>(a.dX + (size_t)m * a.K + k));
         }
     }
 #else
@@ -344,24 +259,24 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
 #endif
 }
 
-// Adds the ranges of the contraction in their order and finishes dX.  Workgroup = (tile, token block, 32-row block of k of
-// one wave): its wave g takes accumulator rows 8 g + 4 h .. + 3, so the four waves write 64 contiguous bytes of 32 tokens.
+// Adds the ranges of the contraction in their order and finishes dX.  Workgroup = (tile, 32 tokens, 32 rows of k of
+// one wave of dx_kernel): its four waves take the four 16 x 16 blocks and write 64 contiguous bytes of 32 tokens.
 __global__ __launch_bounds__(256) void dx_finish_kernel(DxArgs a, int mb) {
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int h = lane >> 5, l32 = lane & 31;
-    const int w = blockIdx.x & 3, rb = (blockIdx.x >> 2) % DX_RB, rest = (int)(blockIdx.x >> 2) / DX_RB;
-    const int j = rest % mb, tile = rest / mb;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g4 = lane >> 4, l16 = lane & 15;
+    const int w = blockIdx.x & 3, rest = (int)(blockIdx.x >> 2) / DX_RB;
+    const int rb = (int)(blockIdx.x >> 2) % DX_RB * 2 + (wave & 1), tb = rest % mb * 2 + (wave >> 1), tile = rest / mb;
     const int tiles = a.tiles_m * a.tiles_k;
     constexpr int GROUP = 4;   // tile order of dx_kernel
     const int width = GROUP * a.tiles_k;
     const int first_m = tile / width * GROUP;
     const int gsz = min(a.tiles_m - first_m, GROUP);
     const int tm = first_m + tile % width % gsz, tk = tile % width / gsz;
-    const int m = tm * 32 * mb + j * 32 + l32, k = tk * DX_BK + w * 32 * DX_RB + rb * 32 + 8 * g + 4 * h;
+    const int m = tm * 32 * mb + tb * 16 + l16, k = tk * DX_BK + w * 32 * DX_RB + rb * 16 + 4 * g4;
     if (m >= a.M || k >= a.K) return;
 
     const size_t step = (size_t)tiles * DX_RB * mb * 1024;
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(a.part) + (((size_t)tile * DX_RB * mb + rb * mb + j) * 4 + g) * 256 + w * 64 + lane;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(a.part) + (((size_t)tile * 2 * DX_RB + rb) * 2 * mb + tb) * 256 + w * 64 + lane;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
     for (int p0 = 0; p0 < a.splits; p0 += 4) {  // the loads of four ranges are in flight together
         f32x4 v[4];
@@ -401,10 +316,10 @@ __global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const DxArgs &a = w.d;
-    constexpr int RB = DX_RB, BM = 32 * MB;
+    constexpr int RB = 2 * DX_RB, BM = 32 * MB;  // 16-row blocks per wave
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int h = lane >> 5, l32 = lane & 31;
+    const int g4 = lane >> 4, l16 = lane & 15;
 
     const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
     constexpr int GROUP = 4;
@@ -415,46 +330,42 @@ __global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
     const int tn = (int)(lid % width) / gsz;
     const int m0 = tm * BM, n0 = tn * DX_BK, N = a.K;
 
-    f32x16 acc[RB][MB];
+    f32x4 acc[RB][2 * MB];
     wide_main_loop<1, HAS8, EP, MB>(a, smem, m0, n0, 0, (a.N + BKT - 1) / BKT, acc);
 
     __syncthreads();  // every wave is done with the operand stages
-    float rs[MB];
+    float rs[2 * MB];
 #pragma unroll
-    for (int j = 0; j < MB; ++j) {
-        const int m = m0 + j * 32 + l32;
-        rs[j] = m < a.M ? w.rowsum[m] : 0.f;
+    for (int tb = 0; tb < 2 * MB; ++tb) {
+        const int m = m0 + tb * 16 + l16;
+        rs[tb] = m < a.M ? w.rowsum[m] : 0.f;
     }
-    f32x4 al[RB][4], ze[RB][4];
+    f32x4 al[RB], ze[RB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = n0 + wave * (32 * RB) + rb * 32 + 8 * g + 4 * h;
-            al[rb][g] = ze[rb][g] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (n < N) {
-                al[rb][g] = *reinterpret_cast<const f32x4 *>(w.alpha + n);
-                ze[rb][g] = *reinterpret_cast<const f32x4 *>(w.zero + n);
-            }
+    for (int rb = 0; rb < RB; ++rb) {
+        const int n = n0 + wave * (16 * RB) + rb * 16 + 4 * g4;
+        al[rb] = ze[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (n < N) {
+            al[rb] = *reinterpret_cast<const f32x4 *>(w.alpha + n);
+            ze[rb] = *reinterpret_cast<const f32x4 *>(w.zero + n);
         }
+    }
     const float mult = HAS8 ? 1.0f : (float)(1 << (8 - a.r[0])), offset = HAS8 ? 0.0f : 128.0f * mult;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int rb = 0; rb < RB; ++rb) {
+        const int nloc = wave * (16 * RB) + rb * 16 + 4 * g4;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int nloc = wave * (32 * RB) + rb * 32 + 8 * g + 4 * h;
+        for (int tb = 0; tb < 2 * MB; ++tb) {
+            float y[4];
 #pragma unroll
-            for (int j = 0; j < MB; ++j) {
-                float y[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float t = (offset + ze[rb][g][e]) * rs[j], v = acc[rb][j][4 * g + e];
-                    y[e] = al[rb][g][e] * (HAS8 ? v - t : __builtin_fmaf(mult, v, -t));
-                }
-                const u32x2 o = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
-                *reinterpret_cast<u32x2 *>(smem + (j * 32 + l32) * DX_OS + nloc * 2) = o;
+            for (int e = 0; e < 4; ++e) {
+                const float t = (offset + ze[rb][e]) * rs[tb], v = acc[rb][tb][e];
+                y[e] = al[rb][e] * (HAS8 ? v - t : __builtin_fmaf(mult, v, -t));
             }
+            const u32x2 o = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+            *reinterpret_cast<u32x2 *>(smem + (tb * 16 + l16) * DX_OS + nloc * 2) = o;
         }
+    }
     __syncthreads();
     constexpr int CPR = DX_BK / 8;  // 16-byte chunks per row
 #pragma unroll
@@ -464,16 +375,15 @@ __global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
         const int m = m0 + row, n = n0 + ch * 8;
         if (m < a.M && n < N) {
             const uint8_t *src = smem + row * DX_OS + ch * 16;
-            const u32x2 lo = *reinterpret_cast<const u32x2 *>(src);
-            const u32x2 hi = *reinterpret_cast<const u32x2 *>(src + 8);
+            const u32x4 y = *reinterpret_cast<const u32x4 *>(src);
             if (w.Y)
-                __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y}, reinterpret_cast<u32x4 *>(w.Y + (size_t)m * N + n));
+                __builtin_nontemporal_store(y, reinterpret_cast<u32x4 *>(w.Y + (size_t)m * N + n));
             if (w.gate) {
                 auto gated = [&](uint32_t pair) {
                     const float g = bf16_lo(pair), u = bf16_hi(pair);
                     return (w.gate == 2 ? silu(g) : gelu_tanh(g)) * u;
                 };
-                const u32x2 o = {pack_bf16x2(gated(lo.x), gated(lo.y)), pack_bf16x2(gated(hi.x), gated(hi.y))};
+                const u32x2 o = {pack_bf16x2(gated(y[0]), gated(y[1])), pack_bf16x2(gated(y[2]), gated(y[3]))};
                 __builtin_nontemporal_store(o, reinterpret_cast<u32x2 *>(w.A + (size_t)m * (N >> 1) + (n >> 1)));
             }
         }

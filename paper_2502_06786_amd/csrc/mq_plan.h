@@ -74,7 +74,7 @@ constexpr int DX_MB = 5;                        // most 32-token blocks per wave
 constexpr int DX_RB = 2;                        // 32-row blocks of k per wave
 constexpr int DX_BK = 4 * 32 * DX_RB;           // k rows per workgroup (4 waves)
 constexpr int DX_Q_TILE = DX_BK * 64;
-constexpr int DX_OS = DX_BK * 2 + 8;            // row stride of the output staging tile
+constexpr int DX_OS = DX_BK * 2 + 16;           // row stride of the output staging tile
 constexpr int dx_lds(int mb) {                  // four stages; the staging tile of the epilogue is smaller
     return 4 * (mb * 4096 + DX_Q_TILE);
 }
