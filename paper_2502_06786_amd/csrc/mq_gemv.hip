@@ -246,8 +246,10 @@ __device__ __forceinline__ void gemv_segment(const u32x4 (&wt)[RG], const uint8_
 // loop is over.  single != 0: all of x is staged once per workgroup and stays (area A then is as
 // large as the reduction data); single == 0: x is restaged (in one or more chunks) for every group
 // of row blocks and the reduction data may run over it.
-template <int R, int RG, int D>
-__global__ __launch_bounds__(1024) void gemv_kernel(GemvArgs a, int bp, int CB, int KS, int ngroups, int x_off,
+// THREADS bounds the workgroup: 512 wherever eight waves are launched, which leaves the compiler 256 registers.  Bounded by 1024,
+// with 128, two row groups at int2 and int3 spilled inside the main loop (14336 x 4096 int2, B = 4: 9.8 -> 8.75 us).
+template <int R, int RG, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void gemv_kernel(GemvArgs a, int bp, int CB, int KS, int ngroups, int x_off,
                                                     int single_flag) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int lane = threadIdx.x & 63;
@@ -622,9 +624,15 @@ static mq_status launch_gemv(const GemvArgs &a, int nw, int ks, hipStream_t st) 
     const int capacity = 256 * per_cu;
     const int rounds = (ngroups + capacity - 1) / capacity;
     const int grid = (ngroups + rounds - 1) / rounds;
-    if (lds > 65536 && !allow_lds<gemv_kernel<R, RG, D>>((int)lds)) return MQ_ERR_DEVICE;
-    gemv_kernel<R, RG, D><<<dim3(grid), dim3(64 * nw), lds, st>>>(a, bp, CB, ks, ngroups, (int)x_off, single);
-    return launch_status();
+    auto launch = [&](auto threads_tag) {
+        constexpr int THREADS = decltype(threads_tag)::value;
+        if (lds > 65536 && !allow_lds<gemv_kernel<R, RG, D, THREADS>>((int)lds)) return MQ_ERR_DEVICE;
+        gemv_kernel<R, RG, D, THREADS><<<dim3(grid), dim3(64 * nw), lds, st>>>(a, bp, CB, ks, ngroups, (int)x_off, single);
+        return launch_status();
+    };
+    if constexpr (RG == 1)  // (K is cut into sixteen only where the rows are few)
+        if (nw > 8) return launch(std::integral_constant<int, 1024>{});
+    return launch(std::integral_constant<int, 512>{});
 }
 
 }  // namespace mq

@@ -150,33 +150,36 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
     };
     const bool has_b = i < a.B;
     const uint16_t *xrow = a.x + (size_t)(has_b ? i : 0) * a.K;
-    auto load_x = [&](int slice) {
+    constexpr int XPD = OPL / 8;   // 16-byte pieces of activations per weight dword
+    // the pieces of a slice as they lie in memory
+    auto request_x = [&](int slice) {
+#pragma unroll
+        for (int ln = 0; ln < NL; ++ln)
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                const int bytew = (slice * NL + ln) * 128 + (g + 4 * (d >> 2)) * 16 + 4 * (d & 3);  // of the dword, in the packed row
+                const u32x4 *q = reinterpret_cast<const u32x4 *>(xrow + (has_b && bytew < a.KB ? bytew * CPB : 0));
+#pragma unroll
+                for (int p = 0; p < XPD; ++p) xr[ln][d * XPD + p] = q[p];
+            }
+    };
+    // the same in the order of the unpacked codes, zeros past the batch and the row; adds to the sums
+    auto arrange_x = [&](int slice) {
 #pragma unroll
         for (int ln = 0; ln < NL; ++ln) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int byte0 = (slice * NL + ln) * 128 + (g + 4 * h) * 16;   // first byte of the piece in the packed row
+            for (int d = 0; d < 8; ++d) {
+                const int bytew = (slice * NL + ln) * 128 + (g + 4 * (d >> 2)) * 16 + 4 * (d & 3);
+                const bool valid = has_b && bytew < a.KB;
+                u32x4 x0 = xr[ln][d * XPD];
+                if (!valid) x0 = u32x4{0u, 0u, 0u, 0u};
                 if constexpr (R == 2) {
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const int bytew = byte0 + 4 * w;
-                        const bool valid = has_b && bytew < a.KB;
-                        const u32x4 *q = reinterpret_cast<const u32x4 *>(xrow + (valid ? bytew * CPB : 0));
-                        u32x4 x0 = q[0], x1 = q[1];
-                        if (!valid) x0 = x1 = u32x4{0u, 0u, 0u, 0u};
-                        xr[ln][(h * 4 + w) * 2] = u32x4{pair_lo(x0.x, x1.x), pair_hi(x0.x, x1.x), pair_lo(x0.y, x1.y), pair_hi(x0.y, x1.y)};
-                        xr[ln][(h * 4 + w) * 2 + 1] = u32x4{pair_lo(x0.z, x1.z), pair_hi(x0.z, x1.z), pair_lo(x0.w, x1.w), pair_hi(x0.w, x1.w)};
-                    }
-                } else if constexpr (R == 4) {
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const int bytew = byte0 + 4 * w;
-                        const bool valid = has_b && bytew < a.KB;
-                        const u32x4 *q = reinterpret_cast<const u32x4 *>(xrow + (valid ? bytew * CPB : 0));
-                        u32x4 x0 = q[0];
-                        if (!valid) x0 = u32x4{0u, 0u, 0u, 0u};
-                        xr[ln][h * 4 + w] = u32x4{pair_lo(x0.x, x0.z), pair_hi(x0.x, x0.z), pair_lo(x0.y, x0.w), pair_hi(x0.y, x0.w)};
-                    }
+                    u32x4 x1 = xr[ln][d * XPD + 1];
+                    if (!valid) x1 = u32x4{0u, 0u, 0u, 0u};
+                    xr[ln][d * 2] = u32x4{pair_lo(x0.x, x1.x), pair_hi(x0.x, x1.x), pair_lo(x0.y, x1.y), pair_hi(x0.y, x1.y)};
+                    xr[ln][d * 2 + 1] = u32x4{pair_lo(x0.z, x1.z), pair_hi(x0.z, x1.z), pair_lo(x0.w, x1.w), pair_hi(x0.w, x1.w)};
+                } else {
+                    xr[ln][d] = u32x4{pair_lo(x0.x, x0.z), pair_hi(x0.x, x0.z), pair_lo(x0.y, x0.w), pair_hi(x0.y, x0.w)};
                 }
             }
 #pragma unroll
@@ -211,10 +214,14 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
         }
     }
 
-    if (nr > 0 && nv > 0) load_x(SB + ks);
+    // The activations are requested before the first weights, and waited for behind them.
+    const bool works = nr > 0 && nv > 0;
+    if (works) request_x(SB + ks);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int st = 0; st < S; ++st) issue_next();
-
+    __builtin_amdgcn_sched_barrier(0);
+    if (works) arrange_x(SB + ks);
 
     // ---- main loop -------------------------------------------------------------------------------------
     static_assert(S >= 2 && S <= 16, "ring depth");
@@ -288,7 +295,10 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
                         sums[((ks + KS * rcur) * 16 + lane) * 2 + 1] = R == 2 ? s2 : 128.f * s1;
                     }
                     s1 = s2 = 0.f;
-                    if (++rcur < nr) load_x(SB + ks + KS * rcur);
+                    if (++rcur < nr) {
+                        request_x(SB + ks + KS * rcur);
+                        arrange_x(SB + ks + KS * rcur);
+                    }
                 }
             }
         }
@@ -410,6 +420,11 @@ mq_status launch_reg_split(const GemvArgs &a, const RegPlan &p, int groups, void
     return launch_status();
 }
 
+// Ring depth of the split form: with four waves to a compute unit three int4 tiles each are not enough in flight (4096 x 14336, B = 16:
+// 16.0 us with three, 14.9 with six, 14.8 with eight; 4608 x 36864: 31.2, 28.7, 28.8); an int2 tile takes twice as long to work on
+// (13.7, 14.0, 14.1; 9.3, 9.4, 9.4 on 2304 x 9216 at B = 8).
+constexpr int split_depth(int r) { return r == 4 ? 6 : 3; }
+
 // Split plan: workgroups of four waves (four slices), every wave visiting p.ch row blocks; about one workgroup per
 // compute unit (measured best on 4096 x 14336 and 4608 x 36864 at B = 8 and 16: 13 us against 25, 25 against 94; two
 // to four per compute unit cost 10-35 % more, their activation loads grow with the number of workgroups).
@@ -424,7 +439,7 @@ bool split_plan(const GemvArgs &a, int r, RegPlan *p, int *groups) {
     p->ks = std::min(4, p->nsl);
     *groups = (p->nsl + p->ks - 1) / p->ks;
     if (*groups < 4 || a.N > 8192) return false;
-    p->depth = 3;
+    p->depth = split_depth(r);
     const int row_groups = std::max(1, 256 / *groups);
     p->ch = (nrb + row_groups - 1) / row_groups;
     p->grid = (nrb + p->ch - 1) / p->ch;
@@ -495,9 +510,9 @@ mq_status launch_gemv_reg_split(const GemvArgs &a, int r, void *ws, size_t ws_by
     if (!split_plan(a, r, &p, &groups)) return MQ_OK;
     if (!ws || ws_bytes < gemv_split_workspace_bytes(a.B, a.N, a.K, r) || !aligned16(ws)) return MQ_ERR_WORKSPACE;
     *handled = true;
-    if (r == 2) return launch_reg_split<2, 1, 3>(a, p, groups, ws, st);
-    if (p.nl == 2) return launch_reg_split<4, 2, 3>(a, p, groups, ws, st);
-    return launch_reg_split<4, 1, 3>(a, p, groups, ws, st);
+    if (r == 2) return launch_reg_split<2, 1, split_depth(2)>(a, p, groups, ws, st);
+    if (p.nl == 2) return launch_reg_split<4, 2, split_depth(4)>(a, p, groups, ws, st);
+    return launch_reg_split<4, 1, split_depth(4)>(a, p, groups, ws, st);
 }
 
 }  // namespace mq
