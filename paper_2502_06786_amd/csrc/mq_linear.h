@@ -73,6 +73,13 @@ __device__ __forceinline__ void mfma16_settle() {
 // groups of a 256-byte window; both swizzles do that (measured: same rate as a contiguous read).  A direct-to-LDS load writes lane l of a wave at base + 16 l, so the swizzle is
 // applied by choosing which global chunk each lane fetches.
 
+// The operands of the 16x16x32 product are read with sixteen rows across the lanes and four chunks of them across the groups of
+// sixteen lanes, and those served together are lanes 0-3, 12-15, 20-23, 24-27 (4-11, 16-19, 28-31; the upper half likewise): rows
+// 0-3 and 12-15 of one group, 4-11 of its neighbour.  The chunks of neighbouring groups therefore have to differ in the right
+// bits: with chunk g for group g every read met a conflict (half of the cycles the LDS was busy).  Which elements of the
+// contraction a group takes is free as long as both operands agree.
+__device__ __forceinline__ int group_chunk(int g4) { return (0x9C >> (2 * g4)) & 3; }  // 0, 3, 1, 2
+
 // Per-lane byte offset (row * ld_bytes + chunk * 16) of instruction `inst` of this wave for a bf16
 // tile, and the element column of the chunk (for the tail predicate).
 template <int NWAVES>
@@ -296,12 +303,13 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     };
 
     // LDS fragment addresses (byte offsets inside a stage).  The order of the contraction inside a stage is free as long as both
-    // operands follow it: a lane reads the sixteen code bytes 16 g4 .. of a row at once and uses eight of them per 32-wide step.
+    // operands follow it: a lane reads the sixteen code bytes 16 gc .. of a row at once and uses eight of them per 32-wide step.
     const int nl = wave * 32 + l16;
-    const uint32_t qa = X_TILE + nl * 64 + ((g4 ^ ((nl >> 2) & 3)) << 4);   // + 1024 per block of 16 channels
+    const int gc = group_chunk(g4);
+    const uint32_t qa = X_TILE + nl * 64 + ((gc ^ ((nl >> 2) & 3)) << 4);   // + 1024 per block of 16 channels
     uint32_t xa[2];                                                         // + 2048 per block of 16 tokens
 #pragma unroll
-    for (int t = 0; t < 2; ++t) xa[t] = l16 * 128 + (((2 * g4 + t) ^ ((l16 >> 1) & 7)) << 4);
+    for (int t = 0; t < 2; ++t) xa[t] = l16 * 128 + (((2 * gc + t) ^ ((l16 >> 1) & 7)) << 4);
 
     SliceParam sp[NR];
 #pragma unroll

@@ -697,8 +697,8 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         }
     };
 
-    // LDS fragment offsets inside a stage: lane (l16, g4) takes tokens 8 g4 .. 8 g4 + 7 of row l16 of a block of 16
-    const uint32_t chunk = (uint32_t)(g4 ^ ((l16 >> 2) & 3)) << 4;
+    // LDS fragment offsets inside a stage: lane (l16, g4) takes eight tokens of row l16 of a block of 16
+    const uint32_t chunk = (uint32_t)(group_chunk(g4) ^ ((l16 >> 2) & 3)) << 4;
     const uint32_t gb = (uint32_t)(wn * 16 * RB + l16) * 64u + chunk;
     const uint32_t xb = (uint32_t)DW_A_TILE + (uint32_t)(wk * 16 * RB + l16) * 64u + chunk;
 

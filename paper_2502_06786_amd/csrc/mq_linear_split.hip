@@ -60,7 +60,8 @@ __global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(Fw
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-            for (int tb = 0; tb < 2 * MB; ++tb) dst[((i * 2 + rb) * 2 * MB + tb) * 256] = acc[i][rb][tb];
+            for (int tb = 0; tb < 2 * MB; ++tb)
+                if (m0 + 16 * tb < a.M) dst[((i * 2 + rb) * 2 * MB + tb) * 256] = acc[i][rb][tb];
 }
 
 // Adds the K ranges and finishes the outputs.  Workgroup = (tile, 32 tokens, 32 channels): its waves take the four 16 x 16
@@ -84,12 +85,13 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
     float rs = 0.f;
 #pragma unroll
     for (int i = 0; i < NR; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < s.splits; p0 += 4) {  // the loads of four ranges are in flight together
+    const int splits = tm * 32 * mb + tb * 16 < a.M ? s.splits : 0;  // (a block past the tokens has not been stored)
+    for (int p0 = 0; p0 < splits; p0 += 4) {  // the loads of four ranges are in flight together
         f32x4 v[4][NR];
         float r[4];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            const bool live = p0 + p < s.splits;
+            const bool live = p0 + p < splits;
             r[p] = live ? s.rs_part[(p0 + p) * rs_step + m] : 0.f;
 #pragma unroll
             for (int i = 0; i < NR; ++i)

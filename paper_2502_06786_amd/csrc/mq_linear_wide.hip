@@ -68,10 +68,11 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
 
     // LDS fragment addresses (byte offsets inside a stage); the order of the contraction is that of fwd_main_loop
     const int kl = wave * (16 * RB) + l16;
-    const uint32_t qa = A_TILE + kl * 64 + ((g4 ^ ((kl >> 2) & 3)) << 4);   // + 1024 per block of 16 rows
+    const int gc = group_chunk(g4);
+    const uint32_t qa = A_TILE + kl * 64 + ((gc ^ ((kl >> 2) & 3)) << 4);   // + 1024 per block of 16 rows
     uint32_t xa[2];                                                         // + 2048 per block of 16 tokens
 #pragma unroll
-    for (int t = 0; t < 2; ++t) xa[t] = l16 * 128 + (((2 * g4 + t) ^ ((l16 >> 1) & 7)) << 4);
+    for (int t = 0; t < 2; ++t) xa[t] = l16 * 128 + (((2 * gc + t) ^ ((l16 >> 1) & 7)) << 4);
 
     SliceParam sp[NRS];
 #pragma unroll
@@ -204,7 +205,8 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int tb = 0; tb < 2 * MB; ++tb) dst[(rb * 2 * MB + tb) * 256] = acc[rb][tb];
+            for (int tb = 0; tb < 2 * MB; ++tb)
+                if (m0 + 16 * tb < a.M) dst[(rb * 2 * MB + tb) * 256] = acc[rb][tb];  // (dx_finish_kernel reads no other)
         return;
     }
 
