@@ -25,6 +25,13 @@ struct GemvArgs {
     const uint16_t *res;  // [B, N] bf16, kPostResidual only
 };
 
+// The overflow list of the extra-precision slice, for the kernel that forms its sums in the same launch.
+struct GemvList {
+    const int32_t *row_ptr;   // [N + 1]
+    const uint16_t *col_idx;  // [cap]
+    int cap;
+};
+
 enum { kPostNone = 0, kPostResidual = 1, kPostGelu = 2, kPostSilu = 3 };
 
 // 1 / (1 + exp(-t)) with the hardware exponential and reciprocal (about 1e-6 relative: far below the bf16 rounding
@@ -88,8 +95,9 @@ mq_status launch_overflow_sums(const uint16_t *x, const int32_t *row_ptr, const 
                                int64_t B, int64_t N, int64_t K, uint16_t *y, hipStream_t st);
 
 // Small-batch kernel (B <= 4, r = 4 or 2): activations live in registers.
-// Returns MQ_OK with *handled = false when the shape is outside what it covers.
-mq_status launch_gemv_quad(const GemvArgs &a, int r, hipStream_t st, bool *handled);
+// Returns MQ_OK with *handled = false when the shape is outside what it covers.  list: form the sums over it as well (a.add_y is
+// not looked at then), or null.
+mq_status launch_gemv_quad(const GemvArgs &a, int r, const GemvList *list, hipStream_t st, bool *handled);
 
 // Batches of 5 .. 16 on tall int4 / int2 planes (no residual epilogue restriction): activations in registers as
 // 16x16x32 matrix-core operands.  Same convention for *handled.

@@ -246,8 +246,8 @@ __device__ __forceinline__ void gemv_segment(const u32x4 (&wt)[RG], const uint8_
 // loop is over.  single != 0: all of x is staged once per workgroup and stays (area A then is as
 // large as the reduction data); single == 0: x is restaged (in one or more chunks) for every group
 // of row blocks and the reduction data may run over it.
-// THREADS bounds the workgroup: 512 wherever eight waves are launched, which leaves the compiler 256 registers.  Bounded by 1024,
-// with 128, two row groups at int2 and int3 spilled inside the main loop (14336 x 4096 int2, B = 4: 9.8 -> 8.75 us).
+// THREADS bounds the workgroup: 512 for two row groups, which leaves the compiler 256 registers.  Bounded by 1024,
+// with 128, they spilled inside the main loop at int2 and int3 (14336 x 4096 int2, B = 4: 9.8 -> 8.75 us).
 template <int R, int RG, int D, int THREADS>
 __global__ __launch_bounds__(THREADS) void gemv_kernel(GemvArgs a, int bp, int CB, int KS, int ngroups, int x_off,
                                                     int single_flag) {
@@ -630,9 +630,11 @@ static mq_status launch_gemv(const GemvArgs &a, int nw, int ks, hipStream_t st) 
         gemv_kernel<R, RG, D, THREADS><<<dim3(grid), dim3(64 * nw), lds, st>>>(a, bp, CB, ks, ngroups, (int)x_off, single);
         return launch_status();
     };
-    if constexpr (RG == 1)  // (K is cut into sixteen only where the rows are few)
+    // (K is cut into sixteen only where the rows are few; 128 registers are enough for one row group but at int3)
+    if constexpr (RG == 1 && R != 3) return launch(std::integral_constant<int, 1024>{});
+    if constexpr (RG == 1)
         if (nw > 8) return launch(std::integral_constant<int, 1024>{});
-    return launch(std::integral_constant<int, 512>{});
+    if constexpr (RG == 2 || R == 3) return launch(std::integral_constant<int, 512>{});
 }
 
 }  // namespace mq
@@ -687,7 +689,12 @@ static mq_status gemv_dispatch(const uint16_t *x, const uint8_t *packed, const u
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (ovf) {
-        // extra precision: the sparse additions first, as 16-bit sums into y; the dense kernel below adds them to
+        // extra precision: small batches on tall planes form the sparse additions in the same launch
+        const GemvList list{ovf->row_ptr, ovf->col_idx, (int)std::min<int64_t>(ovf->capacity, 0x3FFFFFFF)};
+        bool handled = false;
+        const mq_status qs = launch_gemv_quad(a, r, &list, st, &handled);
+        if (qs != MQ_OK || handled) return qs;
+        // elsewhere they come first, as 16-bit sums into y; the dense kernel below adds them to
         // its products before it scales and overwrites y
         const mq_status os = launch_overflow_sums(x, ovf->row_ptr, ovf->col_idx, ovf->capacity, B, N, K, y, st);
         if (os != MQ_OK) return os;
@@ -699,7 +706,7 @@ static mq_status gemv_dispatch(const uint16_t *x, const uint8_t *packed, const u
     }
     {
         bool handled = false;
-        const mq_status qs = launch_gemv_quad(a, r, st, &handled);
+        const mq_status qs = launch_gemv_quad(a, r, nullptr, st, &handled);
         if (qs != MQ_OK || handled) return qs;
         const mq_status rs = launch_gemv_reg(a, r, st, &handled);
         if (rs != MQ_OK || handled) return rs;

@@ -1,6 +1,7 @@
 // The sparse additions of the extra-precision GEMV (errata section: weights whose r-bit code rounds up to 2^r
 // carry "an extra bit"; the section asks for sparse additions of those bits on top of the dense low-bit plane):
 //     osum[b, n] = sum over the overflow columns k of row n of x[b, k]
+// (tall planes with up to four sequences form them next to the product, in mq_gemv_quad.hip)
 // for every output, written as a 16-bit number (ovf_sum_pack: half precision of the sum / 256) into the output
 // buffer y itself, where the GEMV kernel that follows on the same stream picks it up in its epilogue
 // (y[b, n] = alpha_n (2^s (codes . x + osum) - z_n sum x)) before it overwrites y.  No scratch memory is needed

@@ -22,6 +22,7 @@
 // epilogue through sum_k x_k * offset_k, which comes out of the activation registers next to
 // sum_k x_k (the zero-point term).
 #include <algorithm>
+#include <type_traits>
 
 #include "mq_gemv.h"
 
@@ -98,14 +99,94 @@ __device__ __forceinline__ void quad_dword(uint32_t d, int dwi, const u32x2 (&xr
     }
 }
 
+// Waves of a workgroup that walk the list, next to nw that stream the plane: four or eight in all, because a workgroup's waves are
+// dealt to the four SIMDs from the first one on (three workgroups of 3 + 2 waves do not share a compute unit), and at least one per
+// streaming wave.  36864 x 4608 int2, 5 % of the entries: 3 + 5 waves take 20.8 / 22.4 / 24.9 us at B = 1 / 2 / 4, 3 + 1 waves
+// 29.6 / 32.3 / 53.2, a launch of its own for the list 26.4 / 27.7 / 30.9.
+constexpr int list_waves(int nw) { return nw < 3 ? 4 - nw : 8 - nw; }
+
+// The sum over the sixteen lanes of a row of lanes, in all of them.
+__device__ __forceinline__ float row16_sum(float v) {
+    auto dpp_add = [](float x, auto ctrl) {
+        const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true);
+        return x + __int_as_float(moved);
+    };
+    v = dpp_add(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+    v = dpp_add(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+    v = dpp_add(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    return dpp_add(v, std::integral_constant<int, 0x140>{});  // row_mirror
+}
+
+// osum[4 t + b] = sum of x[b] over the list entries range[2 t] .. range[2 t + 1) of row t, for `rows` rows: sixteen lanes to a row
+// (rows dealt round-robin), eight entries per lane and window of 128; the first windows of a group's next row are requested before
+// the current row is summed.  The activations lie in LDS in rows of xpitch bytes; column `zeros` holds zeros.
+__device__ __forceinline__ void list_sums(const GemvArgs &a, const GemvList &list, const uint8_t *xbuf, int xpitch, int zeros, const int *range, int rows,
+                                          int tid, int groups, float *osum) {
+    const int lane16 = tid & 15, grp = tid >> 4;
+    constexpr int W = 2;
+    // (columns are read in whole dwords: with an odd capacity the last dword reaches two bytes past the last entry, inside the
+    // same aligned dword; that half is never used)
+    const __amdgpu_buffer_rsrc_t rcol = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(list.col_idx), 0, (int)std::min<int64_t>(((int64_t)list.cap * 2 + 3) & ~3ll, 0x7FFFFFFF), 0x00020000);
+    u32x4 cur[W], nxt[W];
+    auto request = [&](u32x4 (&dst)[W], int p0, int p1, int first_window) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int idx0 = (p0 & ~7) + (first_window + w) * 128 + lane16 * 8;
+            dst[w] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rcol, idx0 < p1 ? (uint32_t)idx0 * 2u : kOutOfRange, 0, kStreamed));
+        }
+    };
+    if (grp < rows) request(cur, range[2 * grp], range[2 * grp + 1], 0);
+    for (int t = grp; t < rows; t += groups) {
+        const int p0 = range[2 * t], p1 = range[2 * t + 1];
+        if (t + groups < rows) request(nxt, range[2 * (t + groups)], range[2 * (t + groups) + 1], 0);
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int w0 = 0; (p0 & ~7) + w0 * 128 < p1; w0 += W) {
+            if (w0 > 0) request(cur, p0, p1, w0);
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int idx0 = (p0 & ~7) + (w0 + w) * 128 + lane16 * 8;
+                if ((p0 & ~7) + (w0 + w) * 128 >= p1) break;   // uniform over the group
+                uint32_t at[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t col = (j & 1) ? (cur[w][j >> 1] >> 16) : (cur[w][j >> 1] & 0xFFFFu);
+                    at[j] = 2u * (idx0 + j >= p0 && idx0 + j < p1 ? col : (uint32_t)zeros);
+                }
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (b < a.B) {
+                        const uint8_t *xrow = xbuf + b * xpitch;
+                        float v[8];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) v[j] = bf16_bits_to_float(*reinterpret_cast<const uint16_t *>(xrow + at[j]));
+                        s[b] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+                    }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            if (b < a.B) s[b] = row16_sum(s[b]);
+        if (lane16 < 4) osum[4 * t + lane16] = lane16 == 0 ? s[0] : lane16 == 1 ? s[1] : lane16 == 2 ? s[2] : s[3];
+#pragma unroll
+        for (int w = 0; w < W; ++w) cur[w] = nxt[w];
+    }
+}
+
 // R = bits per code (4 or 2), NL = 128-byte lines of a row per K slice, S = tiles in a wave's ring.
 // Workgroup = KS * RW waves; wave (ks, rw) = (wave % KS, wave / KS) takes the slices ks, ks + KS, ...
 // (one "round" each) of the workgroup's row blocks number rw, rw + RW, ...  The workgroup owns every
 // G-th row block (G = workgroups in the grid): its c-th one is row block c * G + blockIdx, c < CH, so
 // that at any time the requests of the whole grid fall into one narrow window of the matrix that
 // moves from its first row to its last.
-template <int R, int NL, int S>
-__global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int RW, int CH, int NSL) {
+//
+// With a list the workgroup's last waves (list_waves) form the sums of x over the overflow list of its rows (see mq_gemv_ovf.hip for what
+// they are) while the others stream the plane: both are short of neither memory nor arithmetic, but each alone waits for its own
+// chain.  They use the staged activations, sixteen lanes to a row; the sums meet the products in the epilogue.
+struct NoList {};
+template <int R, int NL, int S, typename List>
+__global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int RW, int CH, int NSL, List list) {
+    constexpr bool LIST = std::is_same_v<List, GemvList>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     constexpr int CPD = 32 / R;      // codes per dword
     constexpr int QD = CPD / 4;      // quads per dword
@@ -114,7 +195,7 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
 
     const int tid = threadIdx.x, lane = tid & 63, nthreads = blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int NW = nthreads >> 6;
+    const int NW = KS * RW;                        // waves that stream the plane
     const int ks = wave % KS, rw = wave / KS;
     const int li = lane >> 3, lc = lane & 7;       // fetch: row li (+ 8), piece lc of the line
     const int i = lane & 15, g = lane >> 4;        // compute: row i, pieces g and g + 4
@@ -124,11 +205,12 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
     const int G = gridDim.x, wg = blockIdx.x;
     const int nblk = (NRB - wg + G - 1) / G;             // row blocks of this workgroup (>= 1)
     const int nv = max(0, (nblk - rw + RW - 1) / RW);    // visits per round of this wave (wave-uniform)
-    const int nr = (NSL - ks + KS - 1) / KS;             // rounds of this wave: slices ks + KS r < NSL
+    const bool streams = !LIST || wave < NW;
+    const int nr = streams ? (NSL - ks + KS - 1) / KS : 0;  // rounds of this wave: slices ks + KS r < NSL
     const int nsteps = nr * nv * NL;
 
     float *sums = reinterpret_cast<float *>(lds);
-    uint8_t *ring = lds + kSumsBytes + wave * (S * kTileBytes);                          // S tiles of 16 rows x 128 bytes
+    uint8_t *ring = lds + kSumsBytes + min(wave, NW - 1) * (S * kTileBytes);                          // S tiles of 16 rows x 128 bytes
     f32x4 *ypart = reinterpret_cast<f32x4 *>(lds + kSumsBytes + NW * S * kTileBytes);    // [NSL][CH * 16]
     // activations of the whole workgroup: row b at b * xpitch, natural order, zero-filled up to a whole 512-k block
     const int kblocks = (a.K + 511) >> 9;
@@ -141,7 +223,7 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
         const_cast<uint16_t *>(a.x), 0, (int)((uint32_t)a.B * (uint32_t)a.K * 2u), 0x00020000);
 
     // ---- activations -> LDS (direct loads, 1 KB = 512 k of one batch entry per wave instruction) --------
-    for (int j = wave; j < a.B * kblocks; j += NW) {
+    for (int j = wave; j < a.B * kblocks; j += nthreads >> 6) {
         const int bj = j / kblocks, kb = j - bj * kblocks;
         const int k = kb * 512 + lane * 8;
         const uint32_t vo = k < a.K ? ((uint32_t)bj * (uint32_t)a.K + (uint32_t)k) * 2u : kOutOfRange;
@@ -149,6 +231,25 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
                                                  vo, 0, 0, 0);
     }
 
+    // LIST: the sums [row of the workgroup][4 batch entries], and the rows' ranges of the list (clamped to what it holds)
+    float *osum = reinterpret_cast<float *>(const_cast<uint8_t *>(xbuf) + a.B * xpitch);
+    int *range = reinterpret_cast<int *>(osum + CH * 16 * 4);
+    if constexpr (LIST) {
+        if (wave >= NW) {
+            // entries outside a row read the zeros behind the last block of an activation row
+            const int ltid = tid - 64 * NW, lthreads = nthreads - 64 * NW;
+            for (int t = ltid; t < a.B * 8; t += lthreads)
+                *reinterpret_cast<uint32_t *>(const_cast<uint8_t *>(xbuf) + (t >> 3) * xpitch + kblocks * 1024 + (t & 7) * 4) = 0u;
+            for (int t = ltid; t < nblk * 16; t += lthreads) {
+                const int row = ((t >> 4) * G + wg) * 16 + (t & 15);
+                range[2 * t] = row < a.N ? min(list.row_ptr[row], list.cap) : 0;
+                range[2 * t + 1] = row < a.N ? min(list.row_ptr[row + 1], list.cap) : 0;
+            }
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            list_sums(a, list, reinterpret_cast<const uint8_t *>(xbuf), xpitch, kblocks * 512, range, nblk * 16, ltid, lthreads >> 4, osum);
+        }
+    }
     // alpha and z of the first outputs this thread will write, requested ahead.
     // output idx = (b * nblk + c) * 16 + i: row (c * G + wg) * 16 + i of batch entry b
     const int total_out = a.B * nblk * 16;
@@ -192,12 +293,14 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
         }
         islot = islot + 1 == S ? 0 : islot + 1;
     };
+    if (streams) {
 #pragma unroll
-    for (int st = 0; st < S; ++st) issue_next();  // the first S steps are requested now
-    // the staged activations are older than the 2 S weight loads requested since, and loads return in order
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * S) : "memory");
-    // (the bare barrier: a fence here would wait for the tiles still on their way, which no other wave reads)
-    __builtin_amdgcn_s_barrier();
+        for (int st = 0; st < S; ++st) issue_next();  // the first S steps are requested now
+        // the staged activations are older than the 2 S weight loads requested since, and loads return in order
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * S) : "memory");
+        // (the bare barrier: a fence here would wait for the tiles still on their way, which no other wave reads)
+        __builtin_amdgcn_s_barrier();
+    }
 
     // ---- activations of a slice -> registers --------------------------------------------------------
     // pair p of line ln, lane (g, t, b): quad 4 p + t of the lane's stream of the line, i.e. the dwords
@@ -328,7 +431,10 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
         float dot = 0.f;
         for (int k = 0; k < NSL; ++k) dot += ypart[k * CH * 16 + r][bb];
         // extra precision: the overflow sum of this output waits in y (the kernel before this one wrote it)
-        if (a.add_y && live) dot += ovf_sum_unpack(a.y[(size_t)bb * a.N + row]);
+        if constexpr (LIST)
+            dot += osum[r * 4 + bb];
+        else if (a.add_y && live)
+            dot += ovf_sum_unpack(a.y[(size_t)bb * a.N + row]);
         float al, ze;
         if (m < PF) {
             al = m == 0 ? pal[0] : pal[1];
@@ -355,24 +461,26 @@ struct QuadPlan {
     size_t lds;
 };
 
-template <int R, int NL, int S>
-mq_status launch_quad(const GemvArgs &a, const QuadPlan &p, hipStream_t st) {
-    auto kern = gemv_quad_kernel<R, NL, S>;
-    if (p.lds > 65536 && !allow_lds<gemv_quad_kernel<R, NL, S>>((int)p.lds)) return MQ_ERR_DEVICE;
-    kern<<<dim3(p.grid), dim3(64 * p.ks * p.rw), p.lds, st>>>(a, p.ks, p.rw, p.ch, p.nsl);
+template <int R, int NL, int S, typename List>
+mq_status launch_quad_list(const GemvArgs &a, const QuadPlan &p, const List &list, hipStream_t st) {
+    const int nw = p.ks * p.rw + (std::is_same_v<List, GemvList> ? list_waves(p.ks * p.rw) : 0);
+    if (p.lds > 65536 && !allow_lds<gemv_quad_kernel<R, NL, S, List>>((int)p.lds)) return MQ_ERR_DEVICE;
+    gemv_quad_kernel<R, NL, S, List><<<dim3(p.grid), dim3(64 * nw), p.lds, st>>>(a, p.ks, p.rw, p.ch, p.nsl, list);
     return launch_status();
 }
+template <int R, int NL, int S>
+mq_status launch_quad(const GemvArgs &a, const QuadPlan &p, const GemvList *list, hipStream_t st) {
+    return list ? launch_quad_list<R, NL, S>(a, p, *list, st) : launch_quad_list<R, NL, S>(a, p, NoList{}, st);
+}
 
-}  // namespace
-
-mq_status launch_gemv_quad(const GemvArgs &a, int r, hipStream_t st, bool *handled) {
-    *handled = false;
-    if (a.B > 4 || (r != 2 && r != 4) || a.post == kPostResidual) return MQ_OK;
+// false: the call is outside what this kernel is used for
+bool quad_plan(const GemvArgs &a, int r, bool list, QuadPlan *out) {
+    if (a.B > 4 || (r != 2 && r != 4) || a.post == kPostResidual) return false;
     const int lines = (a.KB + 127) / 128;
     const int nrb = (a.N + 15) / 16;
     // Measured against the general kernel on 4096..36864 rows: 0.85-0.9x the time at 36864 x 4608, level or
     // slower at 14336 rows and below, where a launch is bound by latencies and not by bytes.
-    if (nrb < 1024) return MQ_OK;
+    if (nrb < 1024) return false;
     // Lines per slice: no padded lines if possible, then about four slices per row (measured over the
     // decode shapes: fewer leave a workgroup with too few waves, more spend their time filling activation
     // registers), one round.
@@ -385,7 +493,6 @@ mq_status launch_gemv_quad(const GemvArgs &a, int r, hipStream_t st, bool *handl
             if (best < 0 || cost < best_cost) best = nl, best_cost = cost;
         }
         p.nl = best;
-        if (p.nl < 1 || p.nl > 4) return MQ_ERR_SHAPE;
     }
     p.nsl = (lines + p.nl - 1) / p.nl;
     // Slices per round: all of them up to eight waves, otherwise the largest divisor (every wave the
@@ -397,7 +504,11 @@ mq_status launch_gemv_quad(const GemvArgs &a, int r, hipStream_t st, bool *handl
                 p.ks = d;
                 break;
             }
-    if (p.ks < 1 || p.ks > 8) return MQ_ERR_SHAPE;
+    // With the list only where at least as many waves are left for it.  Launch of its own -> here, 5 % of the entries unless noted:
+    // 16384 x 1024, B = 2 10.7 -> 8.7 us; 20000 x 4096, B = 3 21.2 -> 16.1; 28672 x 8192, B = 2 32.0 -> 26.8; 73728 x 4608, B = 1
+    // 39.8 -> 30.3; int4 28672 x 4096, B = 4 25.8 -> 21.5; four waves at 12.5 % of the entries and B = 4 28.9 -> 31.3.  Five to
+    // seven streaming waves: level at 5, 32.8 -> 27.9 us or 47.3 -> 67.4 (2 and 12.5 % of the entries) at 6, 18.9 -> 35.1 at 7.
+    if (list && list_waves(p.ks) < p.ks) return false;
     // waves per compute unit the grid is sized for (measured on 16384..73728 rows: 12 is best at B = 1, within 2 % of the
     // best everywhere; at B = 4, where a wave's activation registers take four times as long to fill, 8 is 5-10 % faster
     // on the tall planes; 6, 16 and 24 are slower)
@@ -405,18 +516,17 @@ mq_status launch_gemv_quad(const GemvArgs &a, int r, hipStream_t st, bool *handl
     // Row-block waves per workgroup and row blocks per workgroup: the whole grid resident at once
     // (wpc waves per compute unit), every wave the same number of visits where the shape allows.
     p.rw = 1;
-    if (p.rw < 1 || p.rw * p.ks > 8) return MQ_ERR_SHAPE;
     const int nw = p.ks * p.rw;
-    const int per_cu = std::max(1, wpc / nw);
+    int per_cu = std::max(1, wpc / nw);
+    if (list) per_cu = std::min(per_cu, 16 / (nw + list_waves(nw)));  // (128 registers: sixteen waves to a compute unit)
     const int capacity = 256 * per_cu;
     const int visits = (int)cdiv(nrb, (int64_t)capacity * p.rw);  // per wave and round
     p.ch = visits * p.rw;
-    if (p.ch < 1) return MQ_ERR_SHAPE;
     p.grid = (int)cdiv(nrb, p.ch);
     p.ch = (int)cdiv(nrb, p.grid);  // (the most row blocks any workgroup gets)
     // Ring depth, as far as the LDS of a compute unit (160 KB, shared by per_cu workgroups) allows.
     const size_t fixed = kSumsBytes + (size_t)p.nsl * p.ch * 16 * sizeof(f32x4) +
-                         (size_t)a.B * (((size_t)a.K + 511) / 512 * 1024 + kXPad);
+                         (size_t)a.B * (((size_t)a.K + 511) / 512 * 1024 + kXPad) + (list ? (size_t)p.ch * 16 * 24 : 0);
     const size_t budget = (size_t)160 * 1024 / per_cu;
     p.depth = 0;
     for (int d : {3, 2}) {  // (deeper rings measured slower: three steps in flight per wave are enough)
@@ -424,15 +534,23 @@ mq_status launch_gemv_quad(const GemvArgs &a, int r, hipStream_t st, bool *handl
         p.depth = d;
         break;
     }
-    if (p.depth == 0) return MQ_OK;
+    if (p.depth == 0) return false;
     p.lds = fixed + (size_t)nw * p.depth * kTileBytes;
-    if (p.lds > 160 * 1024 || (int64_t)a.N * a.KB > 0x7FFFFFFFll || (int64_t)a.B * a.K * 2 > 0x7FFFFFFFll)
-        return MQ_OK;
-    *handled = true;
+    if (p.lds > 160 * 1024 || (int64_t)a.N * a.KB > 0x7FFFFFFFll || (int64_t)a.B * a.K * 2 > 0x7FFFFFFFll) return false;
+    *out = p;
+    return true;
+}
+
+}  // namespace
+
+mq_status launch_gemv_quad(const GemvArgs &a, int r, const GemvList *list, hipStream_t st, bool *handled) {
+    QuadPlan p{};
+    *handled = quad_plan(a, r, list != nullptr, &p);
+    if (!*handled) return MQ_OK;
 #define MQ_QUAD_CASE(R_, NL_)                                             \
     if (r == R_ && p.nl == NL_) {                                         \
-        if (p.depth == 3) return launch_quad<R_, NL_, 3>(a, p, st);       \
-        if (p.depth == 2) return launch_quad<R_, NL_, 2>(a, p, st);       \
+        if (p.depth == 3) return launch_quad<R_, NL_, 3>(a, p, list, st);       \
+        if (p.depth == 2) return launch_quad<R_, NL_, 2>(a, p, list, st);       \
     }
     MQ_QUAD_CASE(2, 1) MQ_QUAD_CASE(2, 2) MQ_QUAD_CASE(2, 3) MQ_QUAD_CASE(2, 4)
     MQ_QUAD_CASE(4, 1) MQ_QUAD_CASE(4, 2) MQ_QUAD_CASE(4, 3) MQ_QUAD_CASE(4, 4)
