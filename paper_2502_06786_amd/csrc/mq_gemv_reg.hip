@@ -151,31 +151,64 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
     const bool has_b = i < a.B;
     const uint16_t *xrow = a.x + (size_t)(has_b ? i : 0) * a.K;
     constexpr int XPD = OPL / 8;   // 16-byte pieces of activations per weight dword
-    // the pieces of a slice as they lie in memory
+    // The pieces of a slice as they lie in memory.  A lane needs 64 (int2: 128) contiguous bytes per half line.  If each lane loads
+    // its own, the four lane groups of one load touch four lines of a row.  TURNED: they read neighbouring 16 bytes
+    // instead, one line per row, and arrange_x turns registers against groups: register c of group g arrives as the piece that
+    // register g of group c needs (int2 has two such squares, of the even and of the odd registers).  One kernel, up to 16 waves
+    // per compute unit that load at once: 36864 x 4608 at B = 16, int2 21.7 -> 19.1 us, int4 24.8 -> 23.1.  The split form has
+    // four waves per compute unit, and the turn before the first product costs it as much as the loads save: 4096 x 14336 int4
+    // 15.2 us turned, 14.8 not, B = 8 13.8 and 13.4; int2 13.6 and 13.9; 2304 x 9216 int2, B = 8, 9.1 and 8.9.
+    // (Two adds per load instead of a test against the row's end for each: 15.3 -> 14.8 and 13.7 -> 13.4 of these.)
+    constexpr bool TURNED = !SPLIT;
     auto request_x = [&](int slice) {
 #pragma unroll
         for (int ln = 0; ln < NL; ++ln)
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                const int bytew = (slice * NL + ln) * 128 + (g + 4 * (d >> 2)) * 16 + 4 * (d & 3);  // of the dword, in the packed row
-                const u32x4 *q = reinterpret_cast<const u32x4 *>(xrow + (has_b && bytew < a.KB ? bytew * CPB : 0));
+            for (int h = 0; h < 2; ++h) {
+                // (rows of the plane are whole lines, and slices whole lines of a row)
+                const u32x4 *q = reinterpret_cast<const u32x4 *>(xrow + ((slice * NL + ln) * 128 + h * 64) * CPB) +
+                                 (TURNED ? g : g * (OPL / 2));
 #pragma unroll
-                for (int p = 0; p < XPD; ++p) xr[ln][d * XPD + p] = q[p];
+                for (int c = 0; c < OPL / 2; ++c) xr[ln][h * (OPL / 2) + c] = q[TURNED ? 4 * c : c];
             }
     };
-    // the same in the order of the unpacked codes, zeros past the batch and the row; adds to the sums
-    auto arrange_x = [&](int slice) {
+    // registers r0 .. r3 of the four groups of sixteen lanes, turned: register c of group g <- register g of group c
+    auto turn = [](u32x4 &r0, u32x4 &r1, u32x4 &r2, u32x4 &r3) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const auto s02 = __builtin_amdgcn_permlane32_swap(r0[d], r2[d], false, false);
+            const auto s13 = __builtin_amdgcn_permlane32_swap(r1[d], r3[d], false, false);
+            const auto s01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+            const auto s23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+            r0[d] = s01[0], r1[d] = s01[1], r2[d] = s23[0], r3[d] = s23[1];
+        }
+    };
+    // the same in the order of the unpacked codes, zeros past the batch; adds to the sums
+    auto arrange_x = [&]() {
 #pragma unroll
         for (int ln = 0; ln < NL; ++ln) {
 #pragma unroll
+            for (int h = 0; TURNED && h < 2; ++h) {
+                u32x4 *x = &xr[ln][h * (OPL / 2)];
+                if constexpr (R == 2) {
+                    u32x4 t[8];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) t[c] = x[c];
+                    turn(t[0], t[2], t[4], t[6]);
+                    turn(t[1], t[3], t[5], t[7]);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x[c] = t[2 * c], x[4 + c] = t[2 * c + 1];
+                } else {
+                    turn(x[0], x[1], x[2], x[3]);
+                }
+            }
+#pragma unroll
             for (int d = 0; d < 8; ++d) {
-                const int bytew = (slice * NL + ln) * 128 + (g + 4 * (d >> 2)) * 16 + 4 * (d & 3);
-                const bool valid = has_b && bytew < a.KB;
                 u32x4 x0 = xr[ln][d * XPD];
-                if (!valid) x0 = u32x4{0u, 0u, 0u, 0u};
+                if (!has_b) x0 = u32x4{0u, 0u, 0u, 0u};
                 if constexpr (R == 2) {
                     u32x4 x1 = xr[ln][d * XPD + 1];
-                    if (!valid) x1 = u32x4{0u, 0u, 0u, 0u};
+                    if (!has_b) x1 = u32x4{0u, 0u, 0u, 0u};
                     xr[ln][d * 2] = u32x4{pair_lo(x0.x, x1.x), pair_hi(x0.x, x1.x), pair_lo(x0.y, x1.y), pair_hi(x0.y, x1.y)};
                     xr[ln][d * 2 + 1] = u32x4{pair_lo(x0.z, x1.z), pair_hi(x0.z, x1.z), pair_lo(x0.w, x1.w), pair_hi(x0.w, x1.w)};
                 } else {
@@ -221,7 +254,7 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
 #pragma unroll
     for (int st = 0; st < S; ++st) issue_next();
     __builtin_amdgcn_sched_barrier(0);
-    if (works) arrange_x(SB + ks);
+    if (works) arrange_x();
 
     // ---- main loop -------------------------------------------------------------------------------------
     static_assert(S >= 2 && S <= 16, "ring depth");
@@ -297,7 +330,7 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
                     s1 = s2 = 0.f;
                     if (++rcur < nr) {
                         request_x(SB + ks + KS * rcur);
-                        arrange_x(SB + ks + KS * rcur);
+                        arrange_x();
                     }
                 }
             }
