@@ -39,9 +39,9 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(const u32x4 *__restrict
 
 // The same loop on the other bf16 shape, 16x16x32, with two waves per SIMD (512 threads) and 24
 // independent 16x16 accumulators per wave: per product half the flops of a 32x32x16 one for the same
-// operand registers and a quarter of the accumulator registers.  One wave per SIMD issues these
-// products at little more than half rate, two waves at nearly full rate, and on N(0,1) operands the
-// loop sustains more than the 32x32x16 loop at any occupancy (the chip is power-limited there).
+// operand registers and a quarter of the accumulator registers.  On N(0,1) operands the loop sustains
+// more than the 32x32x16 loop at any occupancy (the chip is power-limited there).  (One wave per SIMD is
+// slow in this loop because its operands are indexed at run time; with operands read from LDS it is not.)
 __global__ __launch_bounds__(512) void probe_mfma16_kernel(const u32x4 *__restrict__ ops, int64_t iters,
                                                            float *__restrict__ sink) {
     constexpr int NACC = 24;
