@@ -245,7 +245,9 @@ mq_status mq_gemv_sliced(const uint16_t *x, const uint8_t *packed, const uint16_
  *   ws      device, 16-byte aligned, at least mq_workspace_bytes(MQ_OP_GEMV, B, N, K, r) bytes (else
  *           MQ_ERR_WORKSPACE); contents undefined on entry and exit; calls that share it must not overlap
  * Shapes the split form is not used for (B <= 4, r not in {4, 2}, packed rows that are not whole 128-byte lines or
- * shorter than 1664 bytes, more than 8192 rows) run exactly as mq_gemv_sliced does and leave ws untouched.
+ * shorter than 1664 bytes, more than 8192 rows, or so many for their length that a workgroup's partial results do not fit
+ * next to its ring of weights, e.g. 8192 rows of 36864 codes at r = 4) run exactly as mq_gemv_sliced does and leave ws
+ * untouched.
  */
 mq_status mq_gemv_sliced_ws(const uint16_t *x, const uint8_t *packed, const uint16_t *alpha_bf16,
                             const uint16_t *zero_bf16, const mq_overflow *ovf,

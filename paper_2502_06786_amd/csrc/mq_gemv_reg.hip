@@ -13,13 +13,14 @@
 #include <algorithm>
 
 #include "mq_gemv.h"
+#include "mq_plan.h"
 
 namespace mq {
 
 namespace {
 typedef __attribute__((address_space(3))) void *lds_ptr;
 constexpr uint32_t kE128 = 0x43004300u, kE32 = 0x42004200u, kE8 = 0x41004100u;
-constexpr int kTile = 2048;      // 16 rows x 128 bytes
+constexpr int kTile = GEMV_TILE; // 16 rows x 128 bytes
 constexpr int kStreamed = 2;     // non-temporal weight loads
 
 __device__ __forceinline__ f32x4 mfma16(const u32x4 &a, const u32x4 &b, const f32x4 &c) {
@@ -440,44 +441,17 @@ mq_status launch_reg(const GemvArgs &a, const RegPlan &p, hipStream_t st) {
 
 // the split form: groups of p.ks slices in blockIdx.y, then the reduction
 template <int R, int NL, int S>
-mq_status launch_reg_split(const GemvArgs &a, const RegPlan &p, int groups, void *ws, hipStream_t st) {
+mq_status launch_reg_split(const GemvArgs &a, const GemvSplitPlan &p, void *ws, hipStream_t st) {
     auto kern = gemv_reg_kernel<R, NL, S, 256, true>;
     if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, 256, true>>((int)p.lds)) return MQ_ERR_DEVICE;
     const int nrb = (a.N + 15) / 16;
     f32x4 *pdot = static_cast<f32x4 *>(ws);
-    float *psum = reinterpret_cast<float *>(pdot + (size_t)groups * nrb * 64);
-    kern<<<dim3(p.grid, groups), dim3(64 * p.ks), p.lds, st>>>(a, p.ks, 1, p.ch, p.nsl, pdot, psum);
+    float *psum = reinterpret_cast<float *>(pdot + (size_t)p.groups * nrb * 64);
+    kern<<<dim3(p.grid, p.groups), dim3(64 * p.ks), p.lds, st>>>(a, p.ks, 1, p.ch, p.nsl, pdot, psum);
     mq_status s = launch_status();
     if (s != MQ_OK) return s;
-    split_reduce_kernel<<<dim3((nrb * 64 + 255) / 256), dim3(256), 0, st>>>(a, groups, pdot, psum);
+    split_reduce_kernel<<<dim3((nrb * 64 + 255) / 256), dim3(256), 0, st>>>(a, p.groups, pdot, psum);
     return launch_status();
-}
-
-// Ring depth of the split form: with four waves to a compute unit three int4 tiles each are not enough in flight (4096 x 14336, B = 16:
-// 16.0 us with three, 14.9 with six, 14.8 with eight; 4608 x 36864: 31.2, 28.7, 28.8); an int2 tile takes twice as long to work on
-// (13.7, 14.0, 14.1; 9.3, 9.4, 9.4 on 2304 x 9216 at B = 8).
-constexpr int split_depth(int r) { return r == 4 ? 6 : 3; }
-
-// Split plan: workgroups of four waves (four slices), every wave visiting p.ch row blocks; about one workgroup per
-// compute unit (measured best on 4096 x 14336 and 4608 x 36864 at B = 8 and 16: 13 us against 25, 25 against 94; two
-// to four per compute unit cost 10-35 % more, their activation loads grow with the number of workgroups).
-// Used for long rows and few of them: at least four groups of slices and at most 8192 rows; elsewhere the one-kernel
-// forms are level or faster (4096 x 4096, 14336 x 4096 and taller: 1.0-1.5x the time).
-bool split_plan(const GemvArgs &a, int r, RegPlan *p, int *groups) {
-    if (a.B <= 4 || (r != 2 && r != 4) || (a.KB & 127) != 0 || (int64_t)a.N * a.KB > 0x7FFFFFFFll) return false;
-    const int lines = a.KB >> 7, nrb = (a.N + 15) / 16;
-    p->nl = r == 2 ? 1 : 2;
-    if (lines % p->nl) p->nl = 1;
-    p->nsl = lines / p->nl;
-    p->ks = std::min(4, p->nsl);
-    *groups = (p->nsl + p->ks - 1) / p->ks;
-    if (*groups < 4 || a.N > 8192) return false;
-    p->depth = split_depth(r);
-    const int row_groups = std::max(1, 256 / *groups);
-    p->ch = (nrb + row_groups - 1) / row_groups;
-    p->grid = (nrb + p->ch - 1) / p->ch;
-    p->lds = (size_t)p->ks * 128 + (size_t)p->ks * p->depth * kTile + (size_t)p->ks * p->ch * 1024;
-    return p->lds <= 160 * 1024;
 }
 
 }  // namespace
@@ -528,24 +502,22 @@ mq_status launch_gemv_reg(const GemvArgs &a, int r, hipStream_t st, bool *handle
 
 size_t gemv_split_workspace_bytes(int64_t B, int64_t N, int64_t K, int r) {
     if (B < 1 || N < 1 || K < 1 || (r != 2 && r != 4) || (K * r) % 8 != 0) return 0;
-    const int64_t kb = K * r / 8;
-    if (kb & 127) return 0;
-    const int64_t lines = kb >> 7, nl = (r == 4 && lines % 2 == 0) ? 2 : 1, nsl = lines / nl;
-    const int64_t groups = (nsl + 3) / 4, nrb = (N + 15) / 16;
-    if (B <= 4 || groups < 4 || N > 8192) return 0;   // (the conditions of split_plan)
-    return (size_t)(groups * nrb * 1024 + groups * 128);
+    const GemvSplitPlan p = gemv_split_cut(B, N, K * r / 8, r);
+    return (size_t)p.groups * (((size_t)N + 15) / 16 * 1024 + 128);
 }
 
 mq_status launch_gemv_reg_split(const GemvArgs &a, int r, void *ws, size_t ws_bytes, hipStream_t st, bool *handled) {
-    *handled = false;
-    RegPlan p{};
-    int groups = 0;
-    if (!split_plan(a, r, &p, &groups)) return MQ_OK;
+    const GemvSplitPlan p = make_gemv_split_plan(a.B, a.N, a.KB, r);
+    *handled = p.depth > 0;
+    if (!*handled) return MQ_OK;
     if (!ws || ws_bytes < gemv_split_workspace_bytes(a.B, a.N, a.K, r) || !aligned16(ws)) return MQ_ERR_WORKSPACE;
-    *handled = true;
-    if (r == 2) return launch_reg_split<2, 1, split_depth(2)>(a, p, groups, ws, st);
-    if (p.nl == 2) return launch_reg_split<4, 2, split_depth(4)>(a, p, groups, ws, st);
-    return launch_reg_split<4, 1, split_depth(4)>(a, p, groups, ws, st);
+#define MQ_SPLIT_CASE(R_, NL_, S_) \
+    if (r == R_ && p.nl == NL_ && p.depth == S_) return launch_reg_split<R_, NL_, S_>(a, p, ws, st);
+    MQ_SPLIT_CASE(2, 1, 3)
+    MQ_SPLIT_CASE(4, 1, 6) MQ_SPLIT_CASE(4, 1, 4) MQ_SPLIT_CASE(4, 1, 3)
+    MQ_SPLIT_CASE(4, 2, 6) MQ_SPLIT_CASE(4, 2, 4) MQ_SPLIT_CASE(4, 2, 3)
+#undef MQ_SPLIT_CASE
+    return MQ_ERR_SHAPE;  // (cannot happen: these are the depths that the plan chooses from)
 }
 
 }  // namespace mq

@@ -291,4 +291,54 @@ inline DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
     return DwPlan{4, tiles_n, tiles_k, tiles_n * tiles_k * batch, 0, 1, 0};
 }
 
+// ============================================================================================
+// decode GEMV with K split over workgroups (mq_gemv_reg.hip)
+// ============================================================================================
+constexpr int GEMV_TILE = 2048;                  // 16 rows x one 128-byte line
+
+// Workgroups of four waves (a slice of nl lines of a row each, `groups` of them side by side), every wave visiting ch blocks of 16
+// rows; about one workgroup per compute unit (measured best on 4096 x 14336 and 4608 x 36864 at B = 8 and 16: 13 us against 25, 25
+// against 94; two to four per compute unit cost 10-35 % more, their activation loads grow with the number of workgroups).
+// Used for long rows and few of them: at least four groups of slices and at most 8192 rows; elsewhere the one-kernel
+// forms are level or faster (4096 x 4096, 14336 x 4096 and taller: 1.0-1.5x the time).
+struct GemvSplitPlan {
+    int groups, nl, nsl, ks;   // groups == 0: the form is not used
+    int depth, ch, grid;       // depth: tiles in a wave's ring; 0: the form does not fit
+    size_t lds;
+};
+// How K is cut (all that the size of the workspace depends on).
+inline GemvSplitPlan gemv_split_cut(int64_t B, int64_t N, int64_t KB, int r) {
+    GemvSplitPlan p{};
+    if (B <= 4 || (r != 2 && r != 4) || (KB & 127) != 0 || N > 8192) return p;
+    const int64_t lines = KB >> 7;
+    p.nl = r == 4 && lines % 2 == 0 ? 2 : 1;
+    const int64_t nsl = lines / p.nl, groups = cdiv(nsl, 4);
+    if (groups < 4) return p;
+    p.nsl = (int)nsl;
+    p.ks = 4;
+    p.groups = (int)groups;
+    return p;
+}
+// The ring is the deepest that fits next to the partial results, one workgroup to a compute unit: with four waves there three
+// int4 tiles each are not enough in flight (4096 x 14336, B = 16: 16.0 us with three, 14.9 with six, 14.8 with eight; 4608 x
+// 36864: 31.2, 28.7, 28.8).  An int2 tile takes twice as long to work on (13.7, 14.0, 14.1; 2304 x 9216 at B = 8 9.3, 9.4, 9.4).
+// A shorter ring is still far better than the kernel that does not split K: 8192 x 28672, B = 16 32.2 us with four tiles, 35.2 with
+// three, 50.2 there; 7168 x 36864 38.2 with three, 100.0; 4608 x 26880 29.8, 77.9 (8192 x 14080: 25.7 and 30.6, but 23.6 and 21.9 at B = 5).
+inline GemvSplitPlan make_gemv_split_plan(int64_t B, int64_t N, int64_t KB, int r) {
+    GemvSplitPlan p = gemv_split_cut(B, N, KB, r);
+    if (p.groups == 0 || N * KB > 0x7FFFFFFFll) return p;
+    const int nrb = (int)cdiv(N, 16), row_groups = std::max(1, 256 / p.groups);
+    p.ch = (nrb + row_groups - 1) / row_groups;
+    p.grid = (nrb + p.ch - 1) / p.ch;
+    for (int depth : {6, 4, 3}) {
+        if (r == 2 && depth > 3) continue;
+        p.lds = (size_t)p.ks * 128 + (size_t)p.ks * depth * GEMV_TILE + (size_t)p.ks * p.ch * 1024;
+        if (p.lds <= 160 * 1024) {
+            p.depth = depth;
+            break;
+        }
+    }
+    return p;
+}
+
 }  // namespace mq

@@ -26,12 +26,18 @@ extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out
     const DwPlan p = make_dw_plan(M, N, K, batch);
     out[0] = p.hb, out[1] = p.whole, out[2] = p.rest, out[3] = p.parts;
 }
+extern "C" void plan_gemv_split(int64_t B, int64_t N, int64_t K, int r, int64_t *out) {
+    const GemvSplitPlan p = make_gemv_split_plan(B, N, K * r / 8, r);
+    out[0] = p.groups, out[1] = p.nl, out[2] = p.depth, out[3] = p.ch;
+}
 '''
 
 # form: "split" (K cut into `ranges`), "wide" (256-channel tiles), "tiled"; blocks: tile height in blocks of 32 tokens
 Forward = namedtuple("Forward", "form blocks ranges")
 Dx = namedtuple("Dx", "blocks ranges")              # ranges: of channels
 Dw = namedtuple("Dw", "side whole cut ranges")      # tiles of side x side: run whole, cut into `ranges` of tokens each
+# decode with K split: groups of four slices of `lines` lines, ring of `depth` tiles per wave (0: the form does not fit), row blocks per wave
+GemvSplit = namedtuple("GemvSplit", "groups lines depth blocks")
 
 
 @functools.lru_cache(maxsize=None)
@@ -42,7 +48,7 @@ def _lib():
         f.write(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, src, "-o", so], check=True)
     lib = ctypes.CDLL(so)
-    for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw):
+    for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw, lib.plan_gemv_split):
         f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
         f.restype = None
     return lib
@@ -68,3 +74,7 @@ def dx(M, N, K, nr):
 def dw(M, N, K, gradients=1):
     hb, whole, rest, parts = _ask("plan_dw", M, N, K, gradients)
     return Dw(64 * hb, whole, rest, parts)
+
+
+def gemv_split(B, N, K, r):
+    return GemvSplit(*_ask("plan_gemv_split", B, N, K, r))

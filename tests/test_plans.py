@@ -1,7 +1,8 @@
 """Rules on sizes (no GPU): what the launches that follow from them rely on."""
 import pytest
 
-from tests import plans, test_gpu_dw_tiles, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide
+from tests import (plans, test_gpu_dw_tiles, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide,
+                   test_gpu_gemv_split_ring)
 
 cdiv = lambda a, b: -(-a // b)
 
@@ -16,6 +17,24 @@ def test_tiles_of_a_forward_fit_one_launch(nr, K):
         p = plans.forward(M, N, K, nr)
         channels = 256 if p.form == "wide" else 128
         assert cdiv(M, 32 * p.blocks) * cdiv(N, channels) < 1 << 31, (M, N, p)
+
+
+@pytest.mark.parametrize("B", [5, 16])
+def test_split_decode_takes_the_ring_that_fits(B):
+    """A shorter ring, and not another form, where six tiles do not fit: up to 33 blocks of 16 rows per wave the split form is taken
+    (three tiles: 512 + 24576 + 33 x 4096 bytes of LDS)."""
+    for N, K in [(8192, 28672), (7168, 36864), (7680, 30720), (8192, 14080), (4608, 26880), (8192, 14592), (4096, 14336), (4608, 36864)]:
+        p = plans.gemv_split(B, N, K, 4)
+        assert p.depth == (6 if p.blocks <= 27 else 4 if p.blocks <= 31 else 3) and p.blocks <= 33, (N, K, p)
+    seen = set()
+    for K in range(6912, 36865, 256):
+        for N in range(16, 8193, 112):
+            p = plans.gemv_split(B, N, K, 4)
+            assert (p.depth > 0) == (p.groups >= 4 and p.blocks <= 33), (N, K, p)
+            seen.add(p.depth)
+            q = plans.gemv_split(B, N, K, 2)
+            assert q.depth == (3 if q.groups >= 4 and q.blocks <= 33 else 0), (N, K, q)
+    assert seen == {0, 3, 4, 6}
 
 
 # ---- the sizes of the GPU tests take the forms that they are there for -------------------------------------------------
@@ -53,3 +72,14 @@ def test_dw_sizes():
         (128, False, True), (256, True, False), (256, False, True), (256, True, True)]
     for M, N, K, rs in test_gpu_dw_tiles.CLIP_CASES:
         assert N % plans.dw(M, N, K, len(rs)).side and K % plans.dw(M, N, K, len(rs)).side
+
+
+def test_split_decode_sizes():
+    forms = [plans.gemv_split(5, N, K, 4) for N, K in test_gpu_gemv_split_ring.CASES]
+    assert all(p.groups >= 4 for p in forms)
+    assert {(p.lines, p.depth) for p in forms} == {(n, d) for n in (1, 2) for d in (6, 4, 3)} | {(1, 0)}
+    # tiles of the busiest wave against the places of a ring of six: fewer, as many, one more (one line to a slice), many more
+    assert {p.blocks for p in forms if p.depth == 6 and p.lines == 1} >= {1, 5, 6, 7}
+    assert {2 * p.blocks for p in forms if p.depth == 6 and p.lines == 2} >= {2, 4, 6, 8}
+    # a last group of fewer than four slices, with one line and with two
+    assert {p.lines for (N, K), p in zip(test_gpu_gemv_split_ring.CASES, forms) if K // 256 // p.lines % 4} == {1, 2}
