@@ -12,6 +12,7 @@
 #include <type_traits>
 
 #include "mq_gemv.h"
+#include "mq_plan.h"
 
 namespace mq {
 
@@ -75,7 +76,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 // product depends on its own batch entry only).  A lane whose 16 bytes lie past the end of the row
 // re-reads the row's last 16 bytes; any bit pattern unpacks to finite numbers, and those meet
 // activations that were staged as zeros.
-constexpr int kSumBytes = 1024;  // [0, 32): per-half-wave parts of sum_k x; [32, 64): of sum_k x * offset_k
+constexpr int kSumBytes = GEMV_SUM_BYTES;  // [0, 32): per-half-wave parts of sum_k x; [32, 64): of sum_k x * offset_k
 constexpr uint32_t kOOB = 0x80000000u;
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
@@ -93,9 +94,8 @@ __device__ __forceinline__ uint32_t and_or(uint32_t v, uint32_t mask_s, uint32_t
 // load: 128 bytes (16 per lane) for r = 8, 4, 2, and 96 bytes (12 per lane) for the bit streams of
 // r = 6 and r = 3, whose codes straddle any power-of-two boundary but fill 12 bytes exactly
 // (16 resp. 32 codes).  A lane's piece unpacks to XV matrix-core operands of 8 codes each.
-constexpr int line_bytes(int r) { return (r == 6 || r == 3) ? 96 : 128; }
+// (line_bytes, line_codes: mq_plan.h)
 constexpr int piece_bytes(int r) { return line_bytes(r) / 8; }
-constexpr int line_codes(int r) { return line_bytes(r) * 8 / r; }            // k values per line
 constexpr int operands_per_piece(int r) { return line_codes(r) / 8 / 8; }    // XV
 typedef uint32_t u32x3_a4 __attribute__((ext_vector_type(3), aligned(4)));  // a 12-byte piece as one load
 
@@ -246,8 +246,8 @@ __device__ __forceinline__ void gemv_segment(const u32x4 (&wt)[RG], const uint8_
 // loop is over.  single != 0: all of x is staged once per workgroup and stays (area A then is as
 // large as the reduction data); single == 0: x is restaged (in one or more chunks) for every group
 // of row blocks and the reduction data may run over it.
-// THREADS bounds the workgroup: 512 for two row groups, which leaves the compiler 256 registers.  Bounded by 1024,
-// with 128, they spilled inside the main loop at int2 and int3 (14336 x 4096 int2, B = 4: 9.8 -> 8.75 us).
+// THREADS bounds the workgroup, and with it the registers: 256 with 512 threads, 128 with 1024 (gemv_roomy and GemvPlan::tight in
+// mq_plan.h choose).
 template <int R, int RG, int D, int THREADS>
 __global__ __launch_bounds__(THREADS) void gemv_kernel(GemvArgs a, int bp, int CB, int KS, int ngroups, int x_off,
                                                     int single_flag) {
@@ -582,59 +582,20 @@ __global__ __launch_bounds__(THREADS) void gemv_kernel(GemvArgs a, int bp, int C
 }
 
 template <int R, int RG, int D>
-static mq_status launch_gemv(const GemvArgs &a, int nw, int ks, hipStream_t st) {
+static mq_status launch_gemv(const GemvArgs &a, const GemvPlan &p, hipStream_t st) {
+    static_assert(RG <= 2, "partial sums are laid over the transposition tiles");
     int bp = 1;
     while (bp < a.B) bp <<= 1;
-    constexpr int SSPB = 512 / line_codes(R);  // weight lines per 512-k block of x
-    const int lines = (a.KB + line_bytes(R) - 1) / line_bytes(R);
-    const int blocks_all = (lines + SSPB - 1) / SSPB;  // 512-k blocks that cover K
-    // area A: the 2 KB transposition tiles of the waves (reused for the K-split partial sums, which
-    // need RG <= 2 KB per wave)
-    static_assert(RG <= 2, "partial sums are laid over the transposition tiles");
-    auto area_bytes = [&](int nw_, int) { return (size_t)nw_ * 2048; };
-    constexpr size_t kLdsMax = 160 * 1024 - kSumBytes;
-    // all of x at once when it fits behind the reduction data; otherwise chunks that are a multiple of
-    // KS * D lines, so that the register ring of every wave is in the same phase at each chunk
-    // boundary, restaged for every group of row blocks, with the reduction data laid over them
-    int CB = blocks_all, single = 1;
-    size_t x_off = area_bytes(nw, ks);
-    size_t lds = kSumBytes + x_off + (size_t)blocks_all * bp * 1024;
-    if (lds > kLdsMax + kSumBytes) {
-        single = 0;
-        // chunks of whole 512-k blocks whose line count is a multiple of KS; eight waves per workgroup
-        // (more row-block groups, a smaller area A), the largest KS whose chunk still fits
-        nw = 8;
-        if (ks > nw) ks = nw;
-        int cap_blocks = 0;
-        for (;; ks >>= 1) {
-            cap_blocks = (int)(std::min<size_t>(131072, kLdsMax - area_bytes(nw, ks)) / (bp * 1024));
-            if (ks == 1 || cap_blocks * SSPB >= ks) break;
-        }
-        const int unit = std::max(ks, SSPB);  // (both are powers of two)
-        CB = cap_blocks * SSPB / unit * unit / SSPB;
-        if (CB < 1) return MQ_ERR_SHAPE;  // (cannot happen: at KS = 1 at least seven 16 KB blocks fit)
-        x_off = area_bytes(nw, ks);
-        lds = kSumBytes + x_off + (size_t)CB * bp * 1024;
-    }
-    const int rw = nw / ks;
-    const int ngroups = (int)cdiv(a.N, 16 * RG * rw);
-    // resident workgroups: 16 waves and 160 KB of LDS per compute unit, 256 compute units
-    const int wpc = 16;
-    const int per_cu = std::max(1, std::min(wpc / nw, (int)((160 * 1024) / lds)));
-    const int capacity = 256 * per_cu;
-    const int rounds = (ngroups + capacity - 1) / capacity;
-    const int grid = (ngroups + rounds - 1) / rounds;
     auto launch = [&](auto threads_tag) {
         constexpr int THREADS = decltype(threads_tag)::value;
-        if (lds > 65536 && !allow_lds<gemv_kernel<R, RG, D, THREADS>>((int)lds)) return MQ_ERR_DEVICE;
-        gemv_kernel<R, RG, D, THREADS><<<dim3(grid), dim3(64 * nw), lds, st>>>(a, bp, CB, ks, ngroups, (int)x_off, single);
+        if (p.lds > 65536 && !allow_lds<gemv_kernel<R, RG, D, THREADS>>((int)p.lds)) return MQ_ERR_DEVICE;
+        gemv_kernel<R, RG, D, THREADS><<<dim3(p.grid), dim3(64 * p.nw), p.lds, st>>>(a, bp, p.blocks, p.ks, p.ngroups, (int)p.x_off, p.single);
         return launch_status();
     };
-    // (K is cut into sixteen only where the rows are few; 128 registers are enough for one row group but at int3)
-    if constexpr (RG == 1 && R != 3) return launch(std::integral_constant<int, 1024>{});
-    if constexpr (RG == 1)
-        if (nw > 8) return launch(std::integral_constant<int, 1024>{});
-    if constexpr (RG == 2 || R == 3) return launch(std::integral_constant<int, 512>{});
+    if constexpr (!gemv_roomy(R, RG)) return launch(std::integral_constant<int, RG == 1 ? 1024 : 512>{});
+    if constexpr (gemv_roomy(R, RG) && !(R == 3 && RG == 2))
+        if (p.tight) return launch(std::integral_constant<int, 1024>{});
+    if constexpr (gemv_roomy(R, RG)) return launch(std::integral_constant<int, 512>{});
 }
 
 }  // namespace mq
@@ -712,25 +673,9 @@ static mq_status gemv_dispatch(const uint16_t *x, const uint8_t *packed, const u
         if (rs != MQ_OK || handled) return rs;
     }
 
-    // Rows per wave (16 RG): every activation operand read from LDS serves RG matrix-core products, so
-    // tall matrices take two row groups; short ones keep RG = 1 for more waves (measured on the decode
-    // shapes at B = 4 and 16: 4096 rows run 10-25 % faster with RG = 1, 14336 rows level or faster with 2;
-    // at B = 1 the columns are idle anyway and 11008 and 14336 rows run 6-13 % faster with RG = 1.  A
-    // deeper ring did not help at any of these sizes: D = 4 and 5 were 2-10 % slower than 3).
-    const int rg = (N >= 8192 && (B > 2 || N >= 16384)) ? 2 : 1;
-    // K-split: about 2048 waves in total (8 per compute unit measured best across the decode shapes:
-    // enough loads in flight, and the whole grid resident at once) when there are few row blocks,
-    // none when the rows alone provide them.  Workgroups have 8 waves (KS of them per row block),
-    // or KS when that is larger.
-    const int64_t segs = cdiv(kb, line_bytes(r));  // weight lines per row
-    const int64_t row_blocks = cdiv(N, 16 * rg);
-    int ks = 1;
-    // (short matrices with batched activations: shorter slices pay off; at 14336 rows they cost 15-25 %)
-    const int64_t wave_budget = (B >= 4 && rg == 1) ? 4096 : 2048;
-    while (ks < 16 && row_blocks * ks * 2 <= wave_budget && 2 * ks <= segs) ks <<= 1;
-    const int nw = ks > 8 ? ks : 8;
+    const GemvPlan p = make_gemv_plan(B, N, kb, r);
 #define MQ_GEMV_CASE(R_, RG_, D_) \
-    if (r == R_ && rg == RG_) return launch_gemv<R_, RG_, D_>(a, nw, ks, st);
+    if (r == R_ && p.rg == RG_) return launch_gemv<R_, RG_, D_>(a, p, st);
     MQ_GEMV_CASE(2, 1, 3) MQ_GEMV_CASE(2, 2, 2)
     MQ_GEMV_CASE(4, 1, 4) MQ_GEMV_CASE(4, 2, 2)
     MQ_GEMV_CASE(8, 1, 4) MQ_GEMV_CASE(8, 2, 2)

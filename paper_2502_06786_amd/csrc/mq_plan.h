@@ -292,6 +292,93 @@ inline DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
 }
 
 // ============================================================================================
+// decode GEMV, general form (mq_gemv.hip)
+// ============================================================================================
+constexpr int line_bytes(int r) { return (r == 6 || r == 3) ? 96 : 128; }  // what eight neighbouring lanes fetch of a row
+constexpr int line_codes(int r) { return line_bytes(r) * 8 / r; }          // k values per line
+constexpr int GEMV_SUM_BYTES = 1024;
+
+// The kernel has two row groups per wave (rg) at most.  These forms take more than 128 registers if they may: 147 and 131 at int2
+// and int6 with two row groups, 134 and 156 at int3 with one and two.  Held to 128 they spill inside the main loop (14336 x 4096
+// int2, B = 4: 9.8 us instead of 8.75), but two workgroups of eight waves fit a compute unit.
+constexpr bool gemv_roomy(int r, int rg) { return r == 3 || (rg == 2 && (r == 2 || r == 6)); }
+
+struct GemvPlan {
+    int rg, ks, nw;           // 16-row groups per wave, waves that share a row block along K, waves of a workgroup
+    int blocks, single;       // 512-k blocks of x staged at a time; all of x at once
+    int ngroups, grid;        // groups of row blocks a workgroup takes at a time, workgroups
+    bool tight;               // held to 128 registers (forms that are gemv_roomy)
+    size_t x_off, lds;
+};
+inline GemvPlan make_gemv_plan(int64_t B, int64_t N, int64_t KB, int r) {
+    GemvPlan p{};
+    // Rows per wave (16 RG): every activation operand read from LDS serves RG matrix-core products, so
+    // tall matrices take two row groups; short ones keep RG = 1 for more waves (measured on the decode
+    // shapes at B = 4 and 16: 4096 rows run 10-25 % faster with RG = 1, 14336 rows level or faster with 2;
+    // at B = 1 the columns are idle anyway and 11008 and 14336 rows run 6-13 % faster with RG = 1.  A
+    // deeper ring did not help at any of these sizes: D = 4 and 5 were 2-10 % slower than 3).
+    p.rg = (N >= 8192 && (B > 2 || N >= 16384)) ? 2 : 1;
+    // K-split: about 2048 waves in total (8 per compute unit measured best across the decode shapes:
+    // enough loads in flight, and the whole grid resident at once) when there are few row blocks,
+    // none when the rows alone provide them.  Workgroups have 8 waves (KS of them per row block),
+    // or KS when that is larger.
+    const int64_t lines = cdiv(KB, line_bytes(r));  // weight lines per row
+    const int64_t row_blocks = cdiv(N, 16 * p.rg);
+    p.ks = 1;
+    // (short matrices with batched activations: shorter slices pay off; at 14336 rows they cost 15-25 %)
+    const int64_t wave_budget = (B >= 4 && p.rg == 1) ? 4096 : 2048;
+    while (p.ks < 16 && row_blocks * p.ks * 2 <= wave_budget && 2 * p.ks <= lines) p.ks <<= 1;
+    p.nw = p.ks > 8 ? p.ks : 8;
+
+    int bp = 1;
+    while (bp < B) bp <<= 1;
+    const int SSPB = 512 / line_codes(r);             // weight lines per 512-k block of x
+    const int blocks_all = (int)cdiv(lines, SSPB);    // 512-k blocks that cover K
+    // area A: the 2 KB transposition tiles of the waves (reused for the K-split partial sums, which
+    // need RG <= 2 KB per wave)
+    constexpr size_t kLds = 160 * 1024;
+    // all of x at once when it fits behind the reduction data; otherwise chunks that are a multiple of
+    // KS * D lines, so that the register ring of every wave is in the same phase at each chunk
+    // boundary, restaged for every group of row blocks, with the reduction data laid over them
+    p.blocks = blocks_all;
+    p.single = 1;
+    p.x_off = (size_t)p.nw * 2048;
+    p.lds = GEMV_SUM_BYTES + p.x_off + (size_t)blocks_all * bp * 1024;
+    if (p.lds > kLds) {
+        p.single = 0;
+        // chunks of whole 512-k blocks whose line count is a multiple of KS; eight waves per workgroup
+        // (more row-block groups, a smaller area A), the largest KS whose chunk still fits (at KS = 1 at least seven 16 KB blocks)
+        p.nw = 8;
+        if (p.ks > p.nw) p.ks = p.nw;
+        p.x_off = (size_t)p.nw * 2048;
+        int cap_blocks = 0;
+        for (;; p.ks >>= 1) {
+            cap_blocks = (int)(std::min<size_t>(131072, kLds - GEMV_SUM_BYTES - p.x_off) / (bp * 1024));
+            if (p.ks == 1 || cap_blocks * SSPB >= p.ks) break;
+        }
+        const int unit = std::max(p.ks, SSPB);  // (both are powers of two)
+        p.blocks = cap_blocks * SSPB / unit * unit / SSPB;
+        p.lds = GEMV_SUM_BYTES + p.x_off + (size_t)p.blocks * bp * 1024;
+    }
+    const int rw = p.nw / p.ks;
+    p.ngroups = (int)cdiv(N, 16 * p.rg * rw);
+    // resident workgroups: 16 waves and 160 KB of LDS per compute unit, 256 compute units
+    const int per_cu = std::max(1, std::min(16 / p.nw, (int)(kLds / p.lds)));
+    // A roomy form runs one workgroup to a compute unit.  Where there are more of them than compute units and two would fit, it
+    // is held to 128 registers at int3 with one row group (K is cut into eight, a second round is a cold start: 6000 x 4096,
+    // B = 4 13.3 -> 10.7 us, 4112 x 4096 12.2 -> 9.8), and at int2 and int6 where rows are short and the main loop little of the
+    // work (65600 x 1152 int2, B = 5 16.0 -> 14.5 us, 72704 x 512 int6, B = 1 18.0 -> 16.7; but 70656 x 2048 int6 44.5 -> 45.8, 70000 x 2944 int2, B = 8 26.5 -> 27.7); at int3
+    // with two row groups the spills cost more than the second round (65600 x 1024 17.3 and 18.3 us, 73728 x 4608 49.9 and 59.1).
+    // Workgroups of sixteen waves are bounded by 1024 threads in any case.
+    const bool pairs = per_cu > 1 && p.ngroups > 256;
+    p.tight = p.nw > 8 || (pairs && (p.rg == 1 || (r == 6 && lines <= 8) || (r == 2 && lines <= 5)));
+    const int capacity = 256 * per_cu;  // (a workgroup too many for a roomy form starts when a compute unit is free)
+    const int rounds = (p.ngroups + capacity - 1) / capacity;
+    p.grid = (p.ngroups + rounds - 1) / rounds;
+    return p;
+}
+
+// ============================================================================================
 // decode GEMV with K split over workgroups (mq_gemv_reg.hip)
 // ============================================================================================
 constexpr int GEMV_TILE = 2048;                  // 16 rows x one 128-byte line

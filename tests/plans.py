@@ -26,6 +26,10 @@ extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out
     const DwPlan p = make_dw_plan(M, N, K, batch);
     out[0] = p.hb, out[1] = p.whole, out[2] = p.rest, out[3] = p.parts;
 }
+extern "C" void plan_gemv(int64_t B, int64_t N, int64_t K, int r, int64_t *out) {
+    const GemvPlan p = make_gemv_plan(B, N, K * r / 8, r);
+    out[0] = p.rg, out[1] = gemv_roomy(r, p.rg) ? (p.tight ? 128 : 256) : 0, out[2] = p.ngroups, out[3] = p.lds;
+}
 extern "C" void plan_gemv_split(int64_t B, int64_t N, int64_t K, int r, int64_t *out) {
     const GemvSplitPlan p = make_gemv_split_plan(B, N, K * r / 8, r);
     out[0] = p.groups, out[1] = p.nl, out[2] = p.depth, out[3] = p.ch;
@@ -36,6 +40,8 @@ extern "C" void plan_gemv_split(int64_t B, int64_t N, int64_t K, int r, int64_t 
 Forward = namedtuple("Forward", "form blocks ranges")
 Dx = namedtuple("Dx", "blocks ranges")              # ranges: of channels
 Dw = namedtuple("Dw", "side whole cut ranges")      # tiles of side x side: run whole, cut into `ranges` of tokens each
+# decode, general form: 16-row groups per wave, registers the kernel is held to (0: it needs no more than 128), workgroups' worth of rows, LDS
+Gemv = namedtuple("Gemv", "row_groups registers groups lds")
 # decode with K split: groups of four slices of `lines` lines, ring of `depth` tiles per wave (0: the form does not fit), row blocks per wave
 GemvSplit = namedtuple("GemvSplit", "groups lines depth blocks")
 
@@ -48,7 +54,7 @@ def _lib():
         f.write(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, src, "-o", so], check=True)
     lib = ctypes.CDLL(so)
-    for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw, lib.plan_gemv_split):
+    for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw, lib.plan_gemv, lib.plan_gemv_split):
         f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
         f.restype = None
     return lib
@@ -74,6 +80,10 @@ def dx(M, N, K, nr):
 def dw(M, N, K, gradients=1):
     hb, whole, rest, parts = _ask("plan_dw", M, N, K, gradients)
     return Dw(64 * hb, whole, rest, parts)
+
+
+def gemv(B, N, K, r):
+    return Gemv(*_ask("plan_gemv", B, N, K, r))
 
 
 def gemv_split(B, N, K, r):

@@ -2,7 +2,7 @@
 import pytest
 
 from tests import (plans, test_gpu_dw_tiles, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide,
-                   test_gpu_gemv_split_ring)
+                   test_gpu_gemv_registers, test_gpu_gemv_split_ring)
 
 cdiv = lambda a, b: -(-a // b)
 
@@ -17,6 +17,27 @@ def test_tiles_of_a_forward_fit_one_launch(nr, K):
         p = plans.forward(M, N, K, nr)
         channels = 256 if p.form == "wide" else 128
         assert cdiv(M, 32 * p.blocks) * cdiv(N, channels) < 1 << 31, (M, N, p)
+
+
+def test_decode_workgroups_share_compute_units():
+    """Two workgroups of eight waves share a compute unit at 128 registers only: int3 sizes with more workgroups than compute units
+    rely on it wherever their activations leave the LDS for two."""
+    seen = set()
+    for B in (1, 4, 5, 8, 16):
+        for N in range(512, 8192, 176):
+            for K in range(256, 12289, 256):
+                p = plans.gemv(B, N, K, 3)
+                assert p.row_groups == 1
+                shared = p.groups > 256 and 2 * p.lds <= 160 * 1024
+                if shared:
+                    assert p.registers == 128, (B, N, K, p)
+                seen.add((shared, p.registers))
+    assert seen == {(True, 128), (False, 128), (False, 256)}
+    assert [plans.gemv(4, N, K, 3).registers for N, K in ((6000, 4096), (7168, 3584), (4112, 4096), (4000, 2048), (14336, 4096), (73728, 4608))] == [
+        128, 128, 128, 256, 256, 256]
+    # one workgroup to a compute unit as long as there are no more of them
+    assert plans.gemv(4, 14336, 4096, 2).registers == plans.gemv(16, 28672, 4096, 6).registers == plans.gemv(4, 65536, 512, 6).registers == 256
+    assert {plans.gemv(B, N, K, r).registers for B, N, K, r in ((4, 14336, 4096, 4), (16, 4096, 4096, 8), (1, 4096, 4096, 2))} == {0}
 
 
 @pytest.mark.parametrize("B", [5, 16])
@@ -83,3 +104,8 @@ def test_split_decode_sizes():
     assert {2 * p.blocks for p in forms if p.depth == 6 and p.lines == 2} >= {2, 4, 6, 8}
     # a last group of fewer than four slices, with one line and with two
     assert {p.lines for (N, K), p in zip(test_gpu_gemv_split_ring.CASES, forms) if K // 256 // p.lines % 4} == {1, 2}
+
+
+def test_decode_register_sizes():
+    seen = {(r, p.row_groups, p.registers) for r, p in ((r, plans.gemv(B, N, K, r)) for B, N, K, r in test_gpu_gemv_registers.CASES)}
+    assert seen == {(3, 1, 128), (3, 1, 256), (3, 2, 256), (2, 2, 128), (2, 2, 256), (6, 2, 128), (6, 2, 256)}
