@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "mq_gemv.h"
+#include "mq_plan.h"
 
 namespace mq {
 
@@ -35,9 +36,9 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kE128 = 0x43004300u, kE32 = 0x42004200u, kE8 = 0x41004100u;  // (128,128) (32,32) (8,8)
 constexpr uint32_t kOutOfRange = 0x80000000u;
 constexpr int kStreamed = 2;  // cache policy of the weight loads: non-temporal (each byte is read once; measured 7-9 % more read bandwidth)
-constexpr int kSumsBytes = 1024;  // float [16 waves][4 batch entries][2]
-constexpr int kTileBytes = 2048;  // per wave
-constexpr int kXPad = 32;         // row pitch of the staged activations = whole 1 KB blocks + this (bank shift per batch entry)
+constexpr int kSumsBytes = QUAD_SUM_BYTES;  // float [16 waves][4 batch entries][2]
+constexpr int kTileBytes = GEMV_TILE;       // per wave
+constexpr int kXPad = QUAD_X_PAD; // row pitch of the staged activations = whole 1 KB blocks + this (bank shift per batch entry)
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
 template <int ABID>
@@ -99,12 +100,6 @@ __device__ __forceinline__ void quad_dword(uint32_t d, int dwi, const u32x2 (&xr
     }
 }
 
-// Waves of a workgroup that walk the list, next to nw that stream the plane: four or eight in all, because a workgroup's waves are
-// dealt to the four SIMDs from the first one on (three workgroups of 3 + 2 waves do not share a compute unit), and at least one per
-// streaming wave.  36864 x 4608 int2, 5 % of the entries: 3 + 5 waves take 20.8 / 22.4 / 24.9 us at B = 1 / 2 / 4, 3 + 1 waves
-// 29.6 / 32.3 / 53.2, a launch of its own for the list 26.4 / 27.7 / 30.9.
-constexpr int list_waves(int nw) { return nw < 3 ? 4 - nw : 8 - nw; }
-
 // The sum over the sixteen lanes of a row of lanes, in all of them.
 __device__ __forceinline__ float row16_sum(float v) {
     auto dpp_add = [](float x, auto ctrl) {
@@ -117,12 +112,20 @@ __device__ __forceinline__ float row16_sum(float v) {
     return dpp_add(v, std::integral_constant<int, 0x140>{});  // row_mirror
 }
 
-// osum[4 t + b] = sum of x[b] over the list entries range[2 t] .. range[2 t + 1) of row t, for `rows` rows: sixteen lanes to a row
-// (rows dealt round-robin), eight entries per lane and window of 128; the first windows of a group's next row are requested before
-// the current row is summed.  The activations lie in LDS in rows of xpitch bytes; column `zeros` holds zeros.
+// osum[4 t + b] = sum of x[b] over the list entries range[2 t] .. range[2 t + 1) of row t, for `rows` rows (a multiple of 16): sixteen
+// lanes to a row, eight entries per lane and window of 128; the first windows of the next row of these lanes are requested before
+// the current row is summed.  Rows are dealt round-robin to `groups` groups of sixteen lanes or, SHARED, four at a time to the wave
+// that asks for them at the counter `taken`.  The activations lie in LDS in rows of xpitch bytes; column `zeros` holds zeros.
+template <bool SHARED>
 __device__ __forceinline__ void list_sums(const GemvArgs &a, const GemvList &list, const uint8_t *xbuf, int xpitch, int zeros, const int *range, int rows,
-                                          int tid, int groups, float *osum) {
-    const int lane16 = tid & 15, grp = tid >> 4;
+                                          int tid, int groups, int *taken, float *osum) {
+    const int lane16 = tid & 15;
+    auto after = [&](int t) {
+        if constexpr (!SHARED) return t + groups;
+        int first = 0;
+        if ((tid & 63) == 0) first = atomicAdd(taken, 4);
+        return __builtin_amdgcn_readfirstlane(first) + ((tid >> 4) & 3);
+    };
     constexpr int W = 2;
     // (columns are read in whole dwords: with an odd capacity the last dword reaches two bytes past the last entry, inside the
     // same aligned dword; that half is never used)
@@ -136,10 +139,11 @@ __device__ __forceinline__ void list_sums(const GemvArgs &a, const GemvList &lis
             dst[w] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rcol, idx0 < p1 ? (uint32_t)idx0 * 2u : kOutOfRange, 0, kStreamed));
         }
     };
-    if (grp < rows) request(cur, range[2 * grp], range[2 * grp + 1], 0);
-    for (int t = grp; t < rows; t += groups) {
-        const int p0 = range[2 * t], p1 = range[2 * t + 1];
-        if (t + groups < rows) request(nxt, range[2 * (t + groups)], range[2 * (t + groups) + 1], 0);
+    int t = SHARED ? after(0) : tid >> 4;
+    if (t < rows) request(cur, range[2 * t], range[2 * t + 1], 0);
+    while (t < rows) {
+        const int p0 = range[2 * t], p1 = range[2 * t + 1], next = after(t);
+        if (next < rows) request(nxt, range[2 * next], range[2 * next + 1], 0);
         float s[4] = {0.f, 0.f, 0.f, 0.f};
         for (int w0 = 0; (p0 & ~7) + w0 * 128 < p1; w0 += W) {
             if (w0 > 0) request(cur, p0, p1, w0);
@@ -168,6 +172,7 @@ __device__ __forceinline__ void list_sums(const GemvArgs &a, const GemvList &lis
         for (int b = 0; b < 4; ++b)
             if (b < a.B) s[b] = row16_sum(s[b]);
         if (lane16 < 4) osum[4 * t + lane16] = lane16 == 0 ? s[0] : lane16 == 1 ? s[1] : lane16 == 2 ? s[2] : s[3];
+        t = next;
 #pragma unroll
         for (int w = 0; w < W; ++w) cur[w] = nxt[w];
     }
@@ -184,9 +189,10 @@ __device__ __forceinline__ void list_sums(const GemvArgs &a, const GemvList &lis
 // they are) while the others stream the plane: both are short of neither memory nor arithmetic, but each alone waits for its own
 // chain.  They use the staged activations, sixteen lanes to a row; the sums meet the products in the epilogue.
 struct NoList {};
+struct SharedList : GemvList {};   // QuadPlan::shared
 template <int R, int NL, int S, typename List>
 __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int RW, int CH, int NSL, List list) {
-    constexpr bool LIST = std::is_same_v<List, GemvList>;
+    constexpr bool SHARED = std::is_same_v<List, SharedList>, LIST = SHARED || std::is_same_v<List, GemvList>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     constexpr int CPD = 32 / R;      // codes per dword
     constexpr int QD = CPD / 4;      // quads per dword
@@ -234,6 +240,7 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
     // LIST: the sums [row of the workgroup][4 batch entries], and the rows' ranges of the list (clamped to what it holds)
     float *osum = reinterpret_cast<float *>(const_cast<uint8_t *>(xbuf) + a.B * xpitch);
     int *range = reinterpret_cast<int *>(osum + CH * 16 * 4);
+    int *taken = range + CH * 16 * 2;   // SHARED: rows of the list that a wave has taken
     if constexpr (LIST) {
         if (wave >= NW) {
             // entries outside a row read the zeros behind the last block of an activation row
@@ -245,9 +252,10 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
                 range[2 * t] = row < a.N ? min(list.row_ptr[row], list.cap) : 0;
                 range[2 * t + 1] = row < a.N ? min(list.row_ptr[row + 1], list.cap) : 0;
             }
+            if (ltid == 0) *taken = 0;
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
-            list_sums(a, list, reinterpret_cast<const uint8_t *>(xbuf), xpitch, kblocks * 512, range, nblk * 16, ltid, lthreads >> 4, osum);
+            if constexpr (!SHARED) list_sums<false>(a, list, xbuf, xpitch, kblocks * 512, range, nblk * 16, ltid, lthreads >> 4, taken, osum);
         }
     }
     // alpha and z of the first outputs this thread will write, requested ahead.
@@ -406,6 +414,8 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
     }
     // every request of this wave (the last ones are out of range) is back before its tiles are given up
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // the list's waves come here at once, the others when their part of the plane is done
+    if constexpr (SHARED) list_sums<true>(a, list, xbuf, xpitch, kblocks * 512, range, nblk * 16, tid, 0, taken, osum);
 #pragma unroll
     for (int m = 4; m < 64; m <<= 1) {  // over the lanes of one batch entry
         s1 += __shfl_xor(s1, m);
@@ -456,96 +466,25 @@ __global__ __launch_bounds__(512) void gemv_quad_kernel(GemvArgs a, int KS, int 
     }
 }
 
-struct QuadPlan {
-    int nl, nsl, ks, rw, ch, grid, depth;
-    size_t lds;
-};
-
 template <int R, int NL, int S, typename List>
 mq_status launch_quad_list(const GemvArgs &a, const QuadPlan &p, const List &list, hipStream_t st) {
-    const int nw = p.ks * p.rw + (std::is_same_v<List, GemvList> ? list_waves(p.ks * p.rw) : 0);
+    const int nw = p.ks * p.rw + p.list_waves;
     if (p.lds > 65536 && !allow_lds<gemv_quad_kernel<R, NL, S, List>>((int)p.lds)) return MQ_ERR_DEVICE;
     gemv_quad_kernel<R, NL, S, List><<<dim3(p.grid), dim3(64 * nw), p.lds, st>>>(a, p.ks, p.rw, p.ch, p.nsl, list);
     return launch_status();
 }
 template <int R, int NL, int S>
 mq_status launch_quad(const GemvArgs &a, const QuadPlan &p, const GemvList *list, hipStream_t st) {
-    return list ? launch_quad_list<R, NL, S>(a, p, *list, st) : launch_quad_list<R, NL, S>(a, p, NoList{}, st);
-}
-
-// false: the call is outside what this kernel is used for
-bool quad_plan(const GemvArgs &a, int r, bool list, QuadPlan *out) {
-    if (a.B > 4 || (r != 2 && r != 4) || a.post == kPostResidual) return false;
-    const int lines = (a.KB + 127) / 128;
-    const int nrb = (a.N + 15) / 16;
-    // Measured against the general kernel on 4096..36864 rows: 0.85-0.9x the time at 36864 x 4608, level or
-    // slower at 14336 rows and below, where a launch is bound by latencies and not by bytes.
-    if (nrb < 1024) return false;
-    // Lines per slice: no padded lines if possible, then about four slices per row (measured over the
-    // decode shapes: fewer leave a workgroup with too few waves, more spend their time filling activation
-    // registers), one round.
-    QuadPlan p{};
-    {
-        int best = -1, best_cost = 0;
-        for (int nl = 1; nl <= 4; ++nl) {
-            const int nsl = (lines + nl - 1) / nl, pad = nsl * nl - lines;
-            const int cost = pad * 8 + (nsl > 8 ? 4 : 0) + std::abs(nsl - 4);
-            if (best < 0 || cost < best_cost) best = nl, best_cost = cost;
-        }
-        p.nl = best;
-    }
-    p.nsl = (lines + p.nl - 1) / p.nl;
-    // Slices per round: all of them up to eight waves, otherwise the largest divisor (every wave the
-    // same number of rounds), otherwise eight.
-    p.ks = std::min(p.nsl, 8);
-    if (p.nsl > 8)
-        for (int d = 8; d >= 5; --d)
-            if (p.nsl % d == 0) {
-                p.ks = d;
-                break;
-            }
-    // With the list only where at least as many waves are left for it.  Launch of its own -> here, 5 % of the entries unless noted:
-    // 16384 x 1024, B = 2 10.7 -> 8.7 us; 20000 x 4096, B = 3 21.2 -> 16.1; 28672 x 8192, B = 2 32.0 -> 26.8; 73728 x 4608, B = 1
-    // 39.8 -> 30.3; int4 28672 x 4096, B = 4 25.8 -> 21.5; four waves at 12.5 % of the entries and B = 4 28.9 -> 31.3.  Five to
-    // seven streaming waves: level at 5, 32.8 -> 27.9 us or 47.3 -> 67.4 (2 and 12.5 % of the entries) at 6, 18.9 -> 35.1 at 7.
-    if (list && list_waves(p.ks) < p.ks) return false;
-    // waves per compute unit the grid is sized for (measured on 16384..73728 rows: 12 is best at B = 1, within 2 % of the
-    // best everywhere; at B = 4, where a wave's activation registers take four times as long to fill, 8 is 5-10 % faster
-    // on the tall planes; 6, 16 and 24 are slower)
-    const int wpc = a.B > 2 ? 8 : 12;
-    // Row-block waves per workgroup and row blocks per workgroup: the whole grid resident at once
-    // (wpc waves per compute unit), every wave the same number of visits where the shape allows.
-    p.rw = 1;
-    const int nw = p.ks * p.rw;
-    int per_cu = std::max(1, wpc / nw);
-    if (list) per_cu = std::min(per_cu, 16 / (nw + list_waves(nw)));  // (128 registers: sixteen waves to a compute unit)
-    const int capacity = 256 * per_cu;
-    const int visits = (int)cdiv(nrb, (int64_t)capacity * p.rw);  // per wave and round
-    p.ch = visits * p.rw;
-    p.grid = (int)cdiv(nrb, p.ch);
-    p.ch = (int)cdiv(nrb, p.grid);  // (the most row blocks any workgroup gets)
-    // Ring depth, as far as the LDS of a compute unit (160 KB, shared by per_cu workgroups) allows.
-    const size_t fixed = kSumsBytes + (size_t)p.nsl * p.ch * 16 * sizeof(f32x4) +
-                         (size_t)a.B * (((size_t)a.K + 511) / 512 * 1024 + kXPad) + (list ? (size_t)p.ch * 16 * 24 : 0);
-    const size_t budget = (size_t)160 * 1024 / per_cu;
-    p.depth = 0;
-    for (int d : {3, 2}) {  // (deeper rings measured slower: three steps in flight per wave are enough)
-        if (fixed + (size_t)nw * d * kTileBytes > budget) continue;
-        p.depth = d;
-        break;
-    }
-    if (p.depth == 0) return false;
-    p.lds = fixed + (size_t)nw * p.depth * kTileBytes;
-    if (p.lds > 160 * 1024 || (int64_t)a.N * a.KB > 0x7FFFFFFFll || (int64_t)a.B * a.K * 2 > 0x7FFFFFFFll) return false;
-    *out = p;
-    return true;
+    if (!list) return launch_quad_list<R, NL, S>(a, p, NoList{}, st);
+    if (p.shared) return launch_quad_list<R, NL, S>(a, p, SharedList{*list}, st);
+    return launch_quad_list<R, NL, S>(a, p, *list, st);
 }
 
 }  // namespace
 
 mq_status launch_gemv_quad(const GemvArgs &a, int r, const GemvList *list, hipStream_t st, bool *handled) {
-    QuadPlan p{};
-    *handled = quad_plan(a, r, list != nullptr, &p);
+    const QuadPlan p = make_quad_plan(a.B, a.N, a.K, a.KB, r, list != nullptr);
+    *handled = p.depth > 0 && a.post != kPostResidual;
     if (!*handled) return MQ_OK;
 #define MQ_QUAD_CASE(R_, NL_)                                             \
     if (r == R_ && p.nl == NL_) {                                         \

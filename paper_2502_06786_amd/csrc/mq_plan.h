@@ -291,6 +291,106 @@ inline DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
     return DwPlan{4, tiles_n, tiles_k, tiles_n * tiles_k * batch, 0, 1, 0};
 }
 
+constexpr int GEMV_TILE = 2048;                  // decode: 16 rows x one 128-byte line
+
+// ============================================================================================
+// decode GEMV for up to four sequences on tall planes (mq_gemv_quad.hip)
+// ============================================================================================
+constexpr int QUAD_SUM_BYTES = 1024;
+constexpr int QUAD_X_PAD = 32;
+
+// Waves of a workgroup that walk the list, next to nw that stream the plane: four or eight in all, because a workgroup's waves are
+// dealt to the four SIMDs from the first one on (three workgroups of 3 + 2 waves do not share a compute unit), and at least one per
+// streaming wave.  36864 x 4608 int2, 5 % of the entries: 3 + 5 waves take 20.8 / 22.4 / 24.9 us at B = 1 / 2 / 4, 3 + 1 waves
+// 29.6 / 32.3 / 53.2, a launch of its own for the list 26.4 / 27.7 / 30.9.
+constexpr int quad_list_waves(int nw) { return nw < 3 ? 4 - nw : 8 - nw; }
+
+// With four waves for the list and three or four sequences the list of a dense matrix outlasts the plane: there the waves that
+// stream the plane take rows of the list as well when they are done.  28672 x 4096, B = 4: at 12.5 % of the entries (uniform codes
+// at int2) 30.5 -> 27.6 us, int4 31.4 -> 29.6 (a launch of its own for the list 27.9 and 30.0), at 5 % 19.6 -> 18.5 and 20.6 -> 20.8,
+// at 2 % 16.3 -> 16.6 and 17.4 -> 18.1; 16384 x 4096, two row blocks per workgroup, all of whose rows are taken by then, 13.5
+// and 19.2 us at 5 and 12.5 % either way (15.6 and 18.9).  Elsewhere the counter costs more than it gives: 16384 x 1024, B = 2 8.2
+// -> 8.9 us.
+constexpr bool quad_list_shared(int nw, int64_t B) { return nw == 4 && B >= 3; }
+
+struct QuadPlan {
+    int nl, nsl, ks, rw, ch, grid;
+    int depth;                 // tiles in a wave's ring; 0: the form is not used
+    int list_waves;            // 0: without a list
+    bool shared;               // quad_list_shared
+    size_t lds;
+};
+inline QuadPlan make_quad_plan(int64_t B, int64_t N, int64_t K, int64_t KB, int r, bool list) {
+    QuadPlan p{};
+    if (B > 4 || (r != 2 && r != 4)) return p;
+    const int lines = (int)cdiv(KB, 128);
+    const int nrb = (int)cdiv(N, 16);
+    // Measured against the general kernel on 4096..36864 rows: 0.85-0.9x the time at 36864 x 4608, level or
+    // slower at 14336 rows and below, where a launch is bound by latencies and not by bytes.
+    if (nrb < 1024) return p;
+    // Lines per slice: no padded lines if possible, then about four slices per row (measured over the
+    // decode shapes: fewer leave a workgroup with too few waves, more spend their time filling activation
+    // registers), one round.
+    {
+        int best = -1, best_cost = 0;
+        for (int nl = 1; nl <= 4; ++nl) {
+            const int nsl = (lines + nl - 1) / nl, pad = nsl * nl - lines;
+            const int cost = pad * 8 + (nsl > 8 ? 4 : 0) + (nsl > 4 ? nsl - 4 : 4 - nsl);
+            if (best < 0 || cost < best_cost) best = nl, best_cost = cost;
+        }
+        p.nl = best;
+    }
+    p.nsl = (lines + p.nl - 1) / p.nl;
+    // Slices per round: all of them up to eight waves, otherwise the largest divisor (every wave the
+    // same number of rounds), otherwise eight.
+    p.ks = std::min(p.nsl, 8);
+    if (p.nsl > 8)
+        for (int d = 8; d >= 5; --d)
+            if (p.nsl % d == 0) {
+                p.ks = d;
+                break;
+            }
+    // With the list only where at least as many waves are left for it.  Launch of its own -> here, 5 % of the entries unless noted:
+    // 16384 x 1024, B = 2 10.3 -> 8.3 us; 20000 x 2048, B = 3 16.1 -> 12.3; 28672 x 8192, B = 2 30.5 -> 25.6; 73728 x 4608, B = 1
+    // 37.5 -> 28.7; int4 28672 x 4096, B = 4 24.4 -> 20.8; 36864 x 4608 at 12.5 %, B = 4 38.5 -> 33.9.  Five to
+    // seven streaming waves: level at 5, 32.8 -> 27.9 us or 47.3 -> 67.4 (2 and 12.5 % of the entries) at 6, 18.9 -> 35.1 at 7.
+    // (Lists denser than those of uniform codes are faster in a launch of their own, by 3-15 % at 25 % of the entries from B = 2 on;
+    // the host knows how much a list can hold and not how much it does.)
+    if (list && quad_list_waves(p.ks) < p.ks) return p;
+    // waves per compute unit the grid is sized for (measured on 16384..73728 rows: 12 is best at B = 1, within 2 % of the
+    // best everywhere; at B = 4, where a wave's activation registers take four times as long to fill, 8 is 5-10 % faster
+    // on the tall planes; 6, 16 and 24 are slower)
+    const int wpc = B > 2 ? 8 : 12;
+    // Row-block waves per workgroup and row blocks per workgroup: the whole grid resident at once
+    // (wpc waves per compute unit), every wave the same number of visits where the shape allows.
+    p.rw = 1;
+    const int nw = p.ks * p.rw;
+    int per_cu = std::max(1, wpc / nw);
+    if (list) {
+        p.list_waves = quad_list_waves(nw);
+        p.shared = quad_list_shared(nw, B);
+        per_cu = std::min(per_cu, 16 / (nw + p.list_waves));  // (128 registers: sixteen waves to a compute unit)
+    }
+    const int capacity = 256 * per_cu;
+    const int visits = (int)cdiv(nrb, (int64_t)capacity * p.rw);  // per wave and round
+    p.ch = visits * p.rw;
+    p.grid = (int)cdiv(nrb, p.ch);
+    p.ch = (int)cdiv(nrb, p.grid);  // (the most row blocks any workgroup gets)
+    // Ring depth, as far as the LDS of a compute unit (160 KB, shared by per_cu workgroups) allows.
+    const size_t fixed = QUAD_SUM_BYTES + (size_t)p.nsl * p.ch * 256 + (size_t)B * (((size_t)K + 511) / 512 * 1024 + QUAD_X_PAD) +
+                         (list ? (size_t)p.ch * 16 * 24 + 16 : 0);
+    const size_t budget = (size_t)160 * 1024 / per_cu;
+    if (N * KB > 0x7FFFFFFFll || B * K * 2 > 0x7FFFFFFFll) return p;
+    for (int d : {3, 2}) {  // (deeper rings measured slower: three steps in flight per wave are enough)
+        p.lds = fixed + (size_t)nw * d * GEMV_TILE;
+        if (p.lds <= budget) {
+            p.depth = d;
+            break;
+        }
+    }
+    return p;
+}
+
 // ============================================================================================
 // decode GEMV, general form (mq_gemv.hip)
 // ============================================================================================
@@ -381,8 +481,6 @@ inline GemvPlan make_gemv_plan(int64_t B, int64_t N, int64_t KB, int r) {
 // ============================================================================================
 // decode GEMV with K split over workgroups (mq_gemv_reg.hip)
 // ============================================================================================
-constexpr int GEMV_TILE = 2048;                  // 16 rows x one 128-byte line
-
 // Workgroups of four waves (a slice of nl lines of a row each, `groups` of them side by side), every wave visiting ch blocks of 16
 // rows; about one workgroup per compute unit (measured best on 4096 x 14336 and 4608 x 36864 at B = 8 and 16: 13 us against 25, 25
 // against 94; two to four per compute unit cost 10-35 % more, their activation loads grow with the number of workgroups).

@@ -26,6 +26,10 @@ extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out
     const DwPlan p = make_dw_plan(M, N, K, batch);
     out[0] = p.hb, out[1] = p.whole, out[2] = p.rest, out[3] = p.parts;
 }
+extern "C" void plan_quad(int64_t B, int64_t N, int64_t K, int r, int list, int64_t *out) {
+    const QuadPlan p = make_quad_plan(B, N, K, K * r / 8, r, list);
+    out[0] = p.depth > 0 ? p.ks * p.rw : 0, out[1] = p.nl, out[2] = p.list_waves, out[3] = p.shared;
+}
 extern "C" void plan_gemv(int64_t B, int64_t N, int64_t K, int r, int64_t *out) {
     const GemvPlan p = make_gemv_plan(B, N, K * r / 8, r);
     out[0] = p.rg, out[1] = gemv_roomy(r, p.rg) ? (p.tight ? 128 : 256) : 0, out[2] = p.ngroups, out[3] = p.lds;
@@ -40,6 +44,9 @@ extern "C" void plan_gemv_split(int64_t B, int64_t N, int64_t K, int r, int64_t 
 Forward = namedtuple("Forward", "form blocks ranges")
 Dx = namedtuple("Dx", "blocks ranges")              # ranges: of channels
 Dw = namedtuple("Dw", "side whole cut ranges")      # tiles of side x side: run whole, cut into `ranges` of tokens each
+# decode, up to four sequences on tall planes: waves that stream the plane (0: another form), lines per slice, waves for the list, whether
+# the former help with it
+Quad = namedtuple("Quad", "waves lines list_waves shared")
 # decode, general form: 16-row groups per wave, registers the kernel is held to (0: it needs no more than 128), workgroups' worth of rows, LDS
 Gemv = namedtuple("Gemv", "row_groups registers groups lds")
 # decode with K split: groups of four slices of `lines` lines, ring of `depth` tiles per wave (0: the form does not fit), row blocks per wave
@@ -57,6 +64,8 @@ def _lib():
     for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw, lib.plan_gemv, lib.plan_gemv_split):
         f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
         f.restype = None
+    lib.plan_quad.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int64)]
+    lib.plan_quad.restype = None
     return lib
 
 
@@ -80,6 +89,11 @@ def dx(M, N, K, nr):
 def dw(M, N, K, gradients=1):
     hb, whole, rest, parts = _ask("plan_dw", M, N, K, gradients)
     return Dw(64 * hb, whole, rest, parts)
+
+
+def quad(B, N, K, r, with_list=False):
+    waves, lines, list_waves, shared = _ask("plan_quad", B, N, K, r, int(with_list))
+    return Quad(waves, lines, list_waves, bool(shared))
 
 
 def gemv(B, N, K, r):

@@ -1,6 +1,6 @@
 """The decode GEMV that forms the sums over the overflow list in its own launch (up to four sequences, 16384 rows and more): ragged
 last row blocks, rows of the plane that end inside a line, activations that end inside a staged block, rows without and full of
-entries, windows that are continued, and a list that was cut short."""
+entries, windows that are continued, and a list that was cut short.  test_plans.py checks which split of the waves each size takes."""
 import numpy as np
 import pytest
 import torch
@@ -19,9 +19,18 @@ def mq():
     return mq_
 
 
-@pytest.mark.parametrize("N,K,r,B,short", [
+# (six slices of 9216 columns leave too few waves: a launch of its own for the list)
+FALLBACK = [(16384, 9216, 2, 3, False)]
+IN_ONE_LAUNCH = [
     (16384, 1088, 2, 1, False), (16389, 960, 2, 4, False), (16400, 4608, 2, 2, False), (16400, 4608, 2, 2, True),
-    (20000, 2112, 4, 3, False), (18001, 512, 4, 4, True), (16384, 9216, 2, 3, False), (36864, 1536, 2, 1, False)])
+    (20000, 2112, 4, 3, False), (18001, 512, 4, 4, True), (36864, 1536, 2, 1, False),
+    # one streaming wave; four, whose own part is done before the list's or not, with one to four lines per slice
+    (16385, 512, 2, 1, False), (16399, 256, 4, 4, False), (16391, 448, 2, 4, True),
+    (16390, 4096, 2, 1, False), (16390, 4096, 2, 3, False), (28677, 4032, 2, 4, False), (16500, 2048, 2, 4, True), (20011, 4096, 4, 3, True),
+    (16401, 8192, 2, 1, False), (16397, 6144, 2, 3, False), (33000, 960, 4, 4, False)]
+
+
+@pytest.mark.parametrize("N,K,r,B,short", IN_ONE_LAUNCH + FALLBACK)
 def test_list_in_the_same_launch(mq, oracle, N, K, r, B, short):
     g = torch.Generator().manual_seed(N + K + B)
     t = first_overflow_code(r)

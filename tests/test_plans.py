@@ -2,7 +2,7 @@
 import pytest
 
 from tests import (plans, test_gpu_dw_tiles, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide,
-                   test_gpu_gemv_registers, test_gpu_gemv_split_ring)
+                   test_gpu_gemv_list, test_gpu_gemv_registers, test_gpu_gemv_split_ring)
 
 cdiv = lambda a, b: -(-a // b)
 
@@ -109,3 +109,24 @@ def test_split_decode_sizes():
 def test_decode_register_sizes():
     seen = {(r, p.row_groups, p.registers) for r, p in ((r, plans.gemv(B, N, K, r)) for B, N, K, r in test_gpu_gemv_registers.CASES)}
     assert seen == {(3, 1, 128), (3, 1, 256), (3, 2, 256), (2, 2, 128), (2, 2, 256), (6, 2, 128), (6, 2, 256)}
+
+
+def test_decode_list_sizes():
+    plan = lambda N, K, r, B, short: plans.quad(B, N, K, r, with_list=True)
+    assert all(plan(*c).waves == 0 < plans.quad(c[3], *c[:3]).waves for c in test_gpu_gemv_list.FALLBACK)
+    forms = [(c, plan(*c)) for c in test_gpu_gemv_list.IN_ONE_LAUNCH]
+    assert {p[0:1] + p[2:] for _, p in forms} == {(1, 3, False), (2, 2, False), (3, 5, False), (4, 4, False), (4, 4, True)}
+    assert all(p.shared == (p.waves == 4 and c[3] >= 3) for c, p in forms)
+    assert {p.lines for _, p in forms if p.shared} == {1, 2, 3, 4}
+
+
+def test_every_wave_of_a_list_has_a_streaming_wave_or_shares():
+    """Wherever the list is as long as the plane for four streaming waves, they help with it."""
+    for N in (16384, 28672, 73728):
+        for K in range(256, 16385, 64):
+            for r in (2, 4):
+                for B in (1, 2, 3, 4):
+                    p = plans.quad(B, N, K, r, with_list=True)
+                    if p.waves:
+                        assert p.list_waves >= p.waves and p.waves + p.list_waves in (4, 8)
+                        assert p.shared == (p.waves == 4 and B >= 3)
