@@ -49,9 +49,12 @@ __device__ __forceinline__ void static_for(F &&f) {
 // dW 685 -> 625 (the clock rises from 1.72 to 2.0 GHz).  In assembly because the register allocator, given the
 // builtin, does not keep 240 and more accumulator registers in place: it moved them about with hundreds of copies per stage.
 // The compiler does not see a matrix product here, so the waits it would place are ours: an operand written by a vector
-// instruction (not one read from LDS) is used two instructions later at the earliest, and an accumulator is read or copied eight
-// cycles after its product at the earliest, which mfma16_settle() behind the last product of a stage sees to (the matrix core is
-// still busy then).
+// instruction (not one read from LDS) is used two wait states later at the earliest, and an accumulator is read or copied eight
+// wait states after its product at the earliest.  The schedules keep the last two products of a step free of conversions, and
+// mfma16_settle() stands behind the last product of a stage (the matrix core is still busy then).  Copies that the register
+// allocator makes are its own choice: tests/test_matrix_waits.py follows every path through the compiled kernels, over the ends
+// of loops too, and fails where one comes too close.  (Two wait states inside the assembly of the first product of each step
+// would rule out most of that and cost 0.1 of 14.0 us with 77 tokens on 4096 x 4096, 0.5 of 187 us on the largest single forward.)
 // FILE_A: the accumulator file or (where two workgroups share a compute unit and it holds 128 registers) the vector file.
 template <bool FILE_A = true>
 __device__ __forceinline__ void mfma16_acc(f32x4 &acc, const u32x4 &a, const u32x4 &b) {
