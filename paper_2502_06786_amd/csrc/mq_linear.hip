@@ -724,7 +724,9 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     for (int j = 0; j < RB / 2; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xb + j * 1024);
 
     // one stage; cb = LDS buffer of this stage
-    auto tile = [&](int mt, int cb) {
+    // (MORE = false, the last stage of the small tiles: nothing to prepare)
+    auto tile = [&](int mt, int cb, auto more_tag) {
+        constexpr bool MORE = decltype(more_tag)::value;
         const int nb = cb + 1 == DW_NST ? 0 : cb + 1;   // buffer of the next stage
         const int ib = cb == 0 ? DW_NST - 1 : cb - 1;   // buffer of stage mt + NST - 1 (= the one of stage mt - 1)
         const uint8_t *cur = smem + cb * DW_STAGE, *nxt = smem + nb * DW_STAGE;
@@ -735,8 +737,8 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
             if constexpr (half == 0) {
                 if constexpr (q < HJ) xf[HJ + q] = *reinterpret_cast<const u32x4 *>(cur + xb + (HJ + q) * 1024);
                 constexpr int L0 = LPS * q / H, L1 = LPS * (q + 1) / H;
-                if constexpr (L1 > L0) issue_one(mt + DW_NST - 1, ib, L0);
-            } else {
+                if constexpr (MORE && L1 > L0) issue_one(mt + DW_NST - 1, ib, L0);
+            } else if constexpr (MORE) {
                 if constexpr (q - H < HJ) xf[q - H] = *reinterpret_cast<const u32x4 *>(nxt + xb + (q - H) * 1024);
                 if constexpr (q % HJ == HJ - 1) gf[rb] = *reinterpret_cast<const u32x4 *>(nxt + gb + rb * 1024);
             }
@@ -745,14 +747,20 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         mfma16_settle();
     };
 
-    for (int mt = mt0, cb = 0; mt < mt1; ++mt) {
+    // The small tiles have a copy of the code for the last stage, which does not wait for one that nobody multiplies: with few
+    // tokens there is no other (4096 x 4096, 19 tokens 20.6 -> 19.6 us).  With 256 accumulator registers the copy is not worth its
+    // moves (fwd_main_loop).
+    constexpr bool APART = HB == 2;
+    int cb = 0;
+    for (int mt = mt0; mt < mt1 - (APART ? 1 : 0); ++mt) {
         // Stage mt + 1 must be resident (operands read for it inside this stage); the loads of stages mt + 2 and mt + 3 may stay
         // in flight; after the barrier the buffer of stage mt - 1, all of whose operands have been multiplied, is free for stage
         // mt + 4.
         stage_barrier<(DW_NST - 3) * LPS, RB + RB / 2>();
-        tile(mt, cb);
+        tile(mt, cb, std::true_type{});
         cb = cb + 1 == DW_NST ? 0 : cb + 1;
     }
+    if constexpr (APART) tile(mt1 - 1, cb, std::false_type{});
     wait_vm0();  // loads of stages that nobody consumes must have landed before the workgroup ends
 
     // Two neighbouring column blocks exchange half of their lanes, after which a store instruction writes 32 consecutive k (one
