@@ -50,7 +50,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 // builtin, does not keep 240 and more accumulator registers in place: it moved them about with hundreds of copies per stage.
 // The compiler does not see a matrix product here, so the waits it would place are ours: an operand written by a vector
 // instruction (not one read from LDS) is used two wait states later at the earliest, and an accumulator is read or copied eight
-// wait states after its product at the earliest.  The schedules keep the last two products of a step free of conversions, and
+// wait states after its product at the earliest.  The schedules keep the last two products of a step free of conversions (not those
+// whose last conversions belong to a bit-width that the next step comes to five products later), and
 // mfma16_settle() stands behind the last product of a stage (the matrix core is still busy then).  Copies that the register
 // allocator makes are its own choice: tests/test_matrix_waits.py follows every path through the compiled kernels, over the ends
 // of loops too, and fails where one comes too close.  (Two wait states inside the assembly of the first product of each step
@@ -170,8 +171,12 @@ __device__ __forceinline__ void convert_step(uint32_t d, const SliceParam &p, ui
 //   LOADS global loads and CODES reads of the next stage's code bytes: in LONG stages the former over both steps and the latter
 //   early in step 0; in short ones, in which loads are waited for, the former in step 0, and the latter once the bytes of this stage
 //   are used up, which saves copying them;
-//   IN_PLACE: the operands of a token block are read at its last product, otherwise at the first BLOCKS products.
-template <int NM, int GROUP, int BLOCKS, int PAIRS, int PERIOD, bool HAS8, int STEP, int LOADS, bool LONG, int CODES, bool IN_PLACE>
+//   IN_PLACE: the operands of a token block are read at its last product, otherwise at the first BLOCKS products;
+//   LOW: tiles of up to 64 tokens, where a stage is as long as its instructions and its loads take and the products wait for
+//   both: the loads go behind the first products, before the conversions there;
+//   FREE: products at the end of a step without conversions behind them (mfma16_acc).
+template <int NM, int GROUP, int BLOCKS, int PAIRS, int PERIOD, bool HAS8, int STEP, int LOADS, bool LONG, int CODES, bool IN_PLACE,
+          bool LOW, int FREE>
 struct StepSchedule {
     int conv[NM + 1] = {};                // conversion steps before product q
     int load[NM + 1] = {}, code[NM + 1] = {};
@@ -186,7 +191,8 @@ struct StepSchedule {
             code[q + 1] = code[q];
             for (int l = 0; l < LOADS; ++l) {
                 const int block = l * (LONG ? 2 : 1) * BLOCKS / LOADS;
-                if (block / BLOCKS == STEP && block % BLOCKS * GROUP + 1 == q) ++load[q + 1], uses[q] += 3;
+                const int behind = !LOW ? block % BLOCKS * GROUP + 1 : NM < 2 * LOADS ? 0 : l;
+                if (block / BLOCKS == STEP && behind == q) ++load[q + 1], uses[q] += 3;
                 if (q == 0 && block / BLOCKS < STEP) ++first_load;
             }
             for (int e = 0; STEP == 0 && e < CODES; ++e)
@@ -196,11 +202,11 @@ struct StepSchedule {
         int total = 0;
         for (int e = 0; e < PAIRS; ++e) total += HAS8 && e % PERIOD == 0 ? 3 : 4;
         // room for conversion steps behind each product, at the least number of instructions per product for which they all fit;
-        // they are dealt out in proportion to it.  The last two products stay free (mfma16_acc).
+        // they are dealt out in proportion to it.
         int room[NM] = {}, rooms = 0, seen = 0, most = 1;
         for (int budget = 3; rooms < total; ++budget) {
             rooms = 0;
-            for (int q = 0; q < NM; ++q) rooms += room[q] = q < NM - 2 && uses[q] < budget ? (budget - uses[q]) / 2 : 0;
+            for (int q = 0; q < NM; ++q) rooms += room[q] = q < NM - FREE && uses[q] < budget ? (budget - uses[q]) / 2 : 0;
         }
         for (int q = 0; q < NM; ++q) {
             seen += room[q];
@@ -253,8 +259,9 @@ struct FwdArgs {
 };
 
 // Where an accumulator lives: with three bit-widths and 96 tokens two workgroups share a compute unit, each with 128 accumulator
-// registers, and four of the 36 blocks go to the vector file.
-constexpr bool fwd_acc_in_file_a(int nr, int mb, int i, int tb) { return !(nr == 3 && mb == 3 && tb == 5 && i > 0); }
+// registers, and four of the 36 blocks go to the vector file; so do the few of one bit-width in low tiles, where the vector file has
+// room and copies between two pieces of code are not needed.
+constexpr bool fwd_acc_in_file_a(int nr, int mb, int i, int tb) { return !(nr == 3 && mb == 3 && tb == 5 && i > 0) && !(nr == 1 && mb <= 2); }
 
 // The contraction of one workgroup: acc[i][rb][tb] = sum over k in [64 kt0, k_end) of code_i[channels 16 rb .. of this wave][k] *
 // X[tokens m0 + 16 tb ..][k], for all bit-widths i and token blocks tb of the tile at (m0, n0).  Four waves; wave w owns
@@ -354,8 +361,12 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     // step is therefore cut into small pieces (StepSchedule), fenced so that the compiler keeps them between the MFMAs: the
     // conversions of the next step's code operands, the reads of its activation operands, the global loads of stage kt + 3, in
     // step 0 the code bytes of the next stage.  (After the last stage that is a stage of zeros,
-    // which nobody multiplies: a copy of the code for the last stage made the compiler move accumulators between the two.)
-    auto tile = [&](int kt) {
+    // which nobody multiplies: a copy of the code for the last stage makes the compiler move accumulators between the two.  One
+    // bit-width in low tiles has that copy, MORE = false: its accumulators are few, and a range of K is five to ten stages, of
+    // which the one that prepares nothing is 0.1 us shorter.)
+    constexpr bool LOW = MB <= 2, APART = LOW && NR == 1;
+    auto tile = [&](int kt, auto more_tag) {
+        constexpr bool MORE = decltype(more_tag)::value;
         constexpr int NM = 4 * NR * MB;
         const uint8_t *cur = smem + (kt & 3) * STAGE;
         const uint8_t *nxt = smem + ((kt + 1) & 3) * STAGE;
@@ -372,19 +383,27 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
         }
         static_for<2>([&](auto t_tag) {
             constexpr int t = decltype(t_tag)::value;
-            constexpr StepSchedule<NM, 2 * NR, 2 * MB, 4 * NR, NR, HAS8, t, LPS, NR * MB >= 12, 2, XS == 1> plan;
+            constexpr StepSchedule<NM, 2 * NR, 2 * MB, 4 * NR, NR, HAS8, t, LPS, NR * MB >= 12, 2, XS == 1, LOW, LOW && NR == 3 ? 0 : 2> plan;
+            constexpr bool PREPARE = MORE || t == 0;   // there is a next step
             const uint8_t *src = t == 0 ? cur + xa[1] : nxt + xa[0];
             uint32_t tmp[plan.width][4];
+            auto loads = [&](auto q_tag) {
+                constexpr int q = decltype(q_tag)::value;
+                static_for<MORE ? plan.load[q + 1] - plan.load[q] : 0>([&](auto u_tag) {
+                    issue_one(kt + 3, plan.first_load + plan.load[q] + decltype(u_tag)::value);
+                });
+            };
             static_for<NM>([&](auto q_tag) {
                 constexpr int q = decltype(q_tag)::value, tb = q / (2 * NR), i = q % (2 * NR) / 2, rb = q % 2;
                 mfma16_acc<fwd_acc_in_file_a(NR, MB, i, tb)>(acc[i][rb][tb], wf[t][i][rb], xf[t % XS][tb]);
-                if constexpr (XS == 2 && q < 2 * MB) xf[1 - t % XS][q] = *reinterpret_cast<const u32x4 *>(src + q * 2048);
-                if constexpr (XS == 1 && q % (2 * NR) == 2 * NR - 1) xf[0][tb] = *reinterpret_cast<const u32x4 *>(src + tb * 2048);
-                static_for<plan.code[q + 1] - plan.code[q]>([&](auto u_tag) {
+                if constexpr (PREPARE && XS == 2 && q < 2 * MB) xf[1 - t % XS][q] = *reinterpret_cast<const u32x4 *>(src + q * 2048);
+                if constexpr (PREPARE && XS == 1 && q % (2 * NR) == 2 * NR - 1) xf[0][tb] = *reinterpret_cast<const u32x4 *>(src + tb * 2048);
+                if constexpr (LOW) loads(q_tag);
+                static_for<MORE ? plan.code[q + 1] - plan.code[q] : 0>([&](auto u_tag) {
                     constexpr int e = plan.code[q] + decltype(u_tag)::value;
                     rawn[e] = *reinterpret_cast<const u32x4 *>(nxt + qa + e * 1024);
                 });
-                static_for<plan.conv[q + 1] - plan.conv[q]>([&](auto u_tag) {
+                static_for<PREPARE ? plan.conv[q + 1] - plan.conv[q] : 0>([&](auto u_tag) {
                     constexpr int c = plan.conv[q] + decltype(u_tag)::value, pair = plan.pair[c], step = plan.step[c];
                     constexpr int ci = pair % NR, crb = pair / NR / 2, half = pair / NR % 2;
                     u32x4 &out = wf[1 - t][ci][crb];
@@ -395,24 +414,25 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
                         out[2 * half + 1] = hi;
                     }
                 });
-                static_for<plan.load[q + 1] - plan.load[q]>([&](auto u_tag) {
-                    issue_one(kt + 3, plan.first_load + plan.load[q] + decltype(u_tag)::value);
-                });
+                if constexpr (!LOW) loads(q_tag);
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
         mfma16_settle();
-        raw[0] = rawn[0];
-        raw[1] = rawn[1];
+        if constexpr (MORE) {
+            raw[0] = rawn[0];
+            raw[1] = rawn[1];
+        }
     };
 
-    for (int kt = 0; kt < nkt; ++kt) {
+    for (int kt = 0; kt < nkt - (APART ? 1 : 0); ++kt) {
         // Stage kt + 1 must be resident for the operand prefetch of this iteration; the
         // loads of stage kt + 2 may stay in flight.  After the barrier every wave is done with
         // stage kt - 1, whose buffer stage kt + 3 reuses.
         stage_barrier<LPS, 2 * MB>();
-        tile(kt);
+        tile(kt, std::true_type{});
     }
+    if constexpr (APART) tile(nkt - 1, std::false_type{});  // (resident since the barrier of the stage before, or of the prologue)
     wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
 }
 

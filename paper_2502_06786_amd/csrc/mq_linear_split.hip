@@ -71,7 +71,7 @@ template <int NR, bool LOSS>
 __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, int mb) {
     __shared__ float red[4][4];
     const FwdArgs &a = s.f;
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g4 = lane >> 4, l16 = lane & 15, rb = g & 1;
     const int w = blockIdx.x & 3, tb = (int)(blockIdx.x >> 2) % mb * 2 + (g >> 1), tile = (int)(blockIdx.x >> 2) / mb;
     const int tiles = a.tiles_m * a.tiles_n;

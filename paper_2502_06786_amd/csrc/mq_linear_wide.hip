@@ -120,7 +120,8 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
             constexpr int CSLOT = t == 0 ? SLOT : NEXT;       // bit-width of the operands that are converted
             constexpr bool IS8 = HAS8 && CSLOT == 0;
             // (the code bytes of a new n tile are read; those of its other bit-widths are at hand)
-            constexpr StepSchedule<NM, RB, 2 * MB, 2 * RB, 1, IS8, t, LPS, NRS == 3 && MB >= 4, NEXT == 0 ? RB : 0, XS == 1> plan;
+            constexpr StepSchedule<NM, RB, 2 * MB, 2 * RB, 1, IS8, t, LPS, NRS == 3 && MB >= 4, NEXT == 0 ? RB : 0, XS == 1,
+                                   false, 2> plan;
             const uint8_t *src = t == 0 ? cur + xa[1] : nxt + xa[0];
             uint32_t tmp[plan.width][4];
             static_for<NM>([&](auto q_tag) {
