@@ -32,6 +32,7 @@ namespace mq {
 // ============================================================================================
 // row stride of the staging tile of the epilogue: the 8-byte writes of sixteen tokens and the 16-byte read-back spread over all banks
 constexpr int FWD_OS = FWD_BN * 2 + 16;
+static_assert(FWD_OS % 16 == 0, "rows of the staging tile are read in aligned pieces of 16 bytes");
 constexpr int fwd_lds(int mb, int nr) {
     const int stages = FWD_STAGES * (mb * 32 * 128 + FWD_Q_TILE), staging = nr * mb * 32 * FWD_OS;
     return stages > staging ? stages : staging;
@@ -39,10 +40,10 @@ constexpr int fwd_lds(int mb, int nr) {
 
 // One workgroup = 4 waves (one per SIMD, so each may use the whole 512-entry register file) on a
 // (32 MB)-token x 128-channel tile; wave w owns channels [32 w, 32 w + 32) for all tokens, i.e.
-// MB x NR accumulator blocks of 32 x 32.  The converted code operand of a wave is then reused by
-// MB MFMAs per bit-width, which keeps the VALU slicing work at a fraction of the MFMA time.
+// 4 MB NR accumulator blocks of 16 x 16.  A converted code operand (16 channels) is then reused by
+// 2 MB MFMAs, which keeps the VALU slicing work at a fraction of the MFMA time.
 // LDS holds four stages of 64 k: stage kt is computed while stage kt + 1 is resident (the operands
-// of the next 16-wide k step are fetched into registers behind the MFMAs of the current one, also
+// of the next 32-wide k step are fetched into registers behind the MFMAs of the current one, also
 // across the stage boundary) and stages kt + 2, kt + 3 are in flight, so a load has two full
 // iterations to arrive.
 //
@@ -126,9 +127,10 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
     }
     // LOSS: the lane's chunks of the target are requested now, behind the parameter loads, and
     // arrive while the accumulators are converted and staged.  With the largest accumulator sets
-    // there are registers for some of them only (the counts below are the largest that compile
-    // without spills); the others are requested after the staging and arrive while the first ones
-    // are consumed.
+    // there are registers for some of them only; the others are requested after the staging and arrive
+    // while the first ones are consumed.  (Nothing spills with these counts but at 96 tokens and three
+    // bit-widths, whose two workgroups per compute unit leave 256 registers to a wave: three outside the
+    // main loop, two of them without the objective too.)
     constexpr int CHUNKS = BM * 16 / 256;
     constexpr int EARLY = NR * MB > 12 || (NR == 3 && MB == 3) ? 2 : (NR * MB == 12 ? CHUNKS / 2 : CHUNKS);
     u32x4 tpre[LOSS ? CHUNKS : 1];

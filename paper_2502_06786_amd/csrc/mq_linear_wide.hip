@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
     }
 
     // ---- epilogue: rows of the product are k, columns tokens; dX = acc - c[m] --------------------
-    // assembled in LDS as [token][k] bf16 (rows padded by 8 bytes) and stored as whole 512-byte rows
+    // assembled in LDS as [token][k] bf16 (rows of DX_OS bytes) and stored as whole 512-byte rows
     __syncthreads();
     // c[m] = sum over the column ranges of the prep kernel, in their order.  The partial sums of all the
     // lane's tokens are requested four ranges at a time (one memory round trip per

@@ -78,7 +78,10 @@ constexpr int DX_MB = 5;                        // most 32-token blocks per wave
 constexpr int DX_RB = 2;                        // 32-row blocks of k per wave
 constexpr int DX_BK = 4 * 32 * DX_RB;           // k rows per workgroup (4 waves)
 constexpr int DX_Q_TILE = DX_BK * 64;
-constexpr int DX_OS = DX_BK * 2 + 16;           // row stride of the output staging tile
+// Row stride of the output staging tile: 16 bytes more than a row, so that the 8-byte writes of sixteen tokens spread over all banks
+// and the read-back in pieces of 16 bytes stays aligned.
+constexpr int DX_OS = DX_BK * 2 + 16;
+static_assert(DX_OS % 16 == 0, "rows of the staging tile are read in aligned pieces of 16 bytes");
 constexpr int dx_lds(int mb) {                  // four stages; the staging tile of the epilogue is smaller
     return 4 * (mb * 4096 + DX_Q_TILE);
 }
