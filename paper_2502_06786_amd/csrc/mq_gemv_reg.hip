@@ -86,7 +86,8 @@ __device__ __forceinline__ void finish_outputs(const GemvArgs &a, int b, int row
 // workgroup's CH row blocks c * G + blockIdx.
 // SPLIT: blockIdx.y picks a group of KS slices (one round); the workgroup leaves its partial products and activation
 // sums in global memory (pdot [groups][row blocks][64] x 4 floats, psum [groups][16][2]) for split_reduce_kernel.
-template <int R, int NL, int S, int MAXT, bool SPLIT>
+// TURNED: how the activations reach the registers (below; reg_turned chooses).
+template <int R, int NL, int S, int MAXT, bool SPLIT, bool TURNED>
 __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int RW, int CH, int NSL_all, f32x4 *pdot,
                                                         float *psum) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -155,12 +156,9 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
     // The pieces of a slice as they lie in memory.  A lane needs 64 (int2: 128) contiguous bytes per half line.  If each lane loads
     // its own, the four lane groups of one load touch four lines of a row.  TURNED: they read neighbouring 16 bytes
     // instead, one line per row, and arrange_x turns registers against groups: register c of group g arrives as the piece that
-    // register g of group c needs (int2 has two such squares, of the even and of the odd registers).  One kernel, up to 16 waves
-    // per compute unit that load at once: 36864 x 4608 at B = 16, int2 21.7 -> 19.1 us, int4 24.8 -> 23.1.  The split form has
-    // four waves per compute unit, and the turn before the first product costs it as much as the loads save: 4096 x 14336 int4
-    // 15.2 us turned, 14.8 not, B = 8 13.8 and 13.4; int2 13.6 and 13.9; 2304 x 9216 int2, B = 8, 9.1 and 8.9.
-    // (Two adds per load instead of a test against the row's end for each: 15.3 -> 14.8 and 13.7 -> 13.4 of these.)
-    constexpr bool TURNED = !SPLIT;
+    // register g of group c needs (two such squares, of the even and of the odd registers).
+    // (Two adds per load instead of a test against the row's end for each: 4096 x 14336 int4 15.3 -> 14.8 us, B = 8 13.7 -> 13.4.)
+    static_assert(!TURNED || R == 2, "squares of registers");
     auto request_x = [&](int slice) {
 #pragma unroll
         for (int ln = 0; ln < NL; ++ln)
@@ -189,19 +187,14 @@ __global__ __launch_bounds__(MAXT) void gemv_reg_kernel(GemvArgs a, int KS, int 
 #pragma unroll
         for (int ln = 0; ln < NL; ++ln) {
 #pragma unroll
-            for (int h = 0; TURNED && h < 2; ++h) {
-                u32x4 *x = &xr[ln][h * (OPL / 2)];
-                if constexpr (R == 2) {
-                    u32x4 t[8];
+            for (int h = 0; h < (TURNED ? 2 : 0); ++h) {
+                u32x4 *x = &xr[ln][h * (OPL / 2)], t[8];
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) t[c] = x[c];
-                    turn(t[0], t[2], t[4], t[6]);
-                    turn(t[1], t[3], t[5], t[7]);
+                for (int c = 0; c < 8; ++c) t[c] = x[c];
+                turn(t[0], t[2], t[4], t[6]);
+                turn(t[1], t[3], t[5], t[7]);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) x[c] = t[2 * c], x[4 + c] = t[2 * c + 1];
-                } else {
-                    turn(x[0], x[1], x[2], x[3]);
-                }
+                for (int c = 0; c < 4; ++c) x[c] = t[2 * c], x[4 + c] = t[2 * c + 1];
             }
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
@@ -431,19 +424,28 @@ struct RegPlan {
     size_t lds;
 };
 
-template <int R, int NL, int S, int MAXT>
+template <int R, int NL, int S, bool TURNED = false>
 mq_status launch_reg(const GemvArgs &a, const RegPlan &p, hipStream_t st) {
-    auto kern = gemv_reg_kernel<R, NL, S, MAXT, false>;
-    if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, MAXT, false>>((int)p.lds)) return MQ_ERR_DEVICE;
+    auto kern = gemv_reg_kernel<R, NL, S, 1024, false, TURNED>;
+    if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, 1024, false, TURNED>>((int)p.lds)) return MQ_ERR_DEVICE;
     kern<<<dim3(p.grid), dim3(64 * p.ks), p.lds, st>>>(a, p.ks, 1, p.ch, p.nsl, nullptr, nullptr);
     return launch_status();
 }
 
+// Turned where many rows of activations meet many waves that load at once: int2 (twice the pieces of int4) from twelve sequences and
+// four slices on.  Turned and not, B = 16: 36864 x 8192 33.1 and 35.5 us, 73728 x 4608 34.8 and 36.0, 73728 x 2048 16.8 and 17.5,
+// 36864 x 4608 18.2 and 18.4, 36864 x 1024 10.9 and 10.7; B = 13: 73728 x 4608 33.2 and 33.8, 32768 x 4608 16.3 and 16.2; B = 8: 32768 x
+// 1024 10.7 and 10.1, 32768 x 4608 15.1 and 14.9; B = 5: 49152 x 2048 12.7 and 12.0, 32768 x 512 7.6 and 7.0.  int4 is level
+// at 16 (73728 x 4608 42.4 and 42.7, 49152 x 4608 26.9 and 26.5) and slower below (49152 x 1024, B = 8 11.4 and 10.6).  The split form
+// has four waves per compute unit, and the turn before the first product costs it as much as the loads save: 4096 x 14336 int4
+// 15.2 us turned, 14.8 not, B = 8 13.8 and 13.4; int2 13.6 and 13.9; 2304 x 9216 int2, B = 8, 9.1 and 8.9.
+bool reg_turned(int r, int B, int slices) { return r == 2 && B >= 12 && slices >= 4; }
+
 // the split form: groups of p.ks slices in blockIdx.y, then the reduction
 template <int R, int NL, int S>
 mq_status launch_reg_split(const GemvArgs &a, const GemvSplitPlan &p, void *ws, hipStream_t st) {
-    auto kern = gemv_reg_kernel<R, NL, S, 256, true>;
-    if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, 256, true>>((int)p.lds)) return MQ_ERR_DEVICE;
+    auto kern = gemv_reg_kernel<R, NL, S, 256, true, false>;
+    if (p.lds > 65536 && !allow_lds<gemv_reg_kernel<R, NL, S, 256, true, false>>((int)p.lds)) return MQ_ERR_DEVICE;
     const int nrb = (a.N + 15) / 16;
     f32x4 *pdot = static_cast<f32x4 *>(ws);
     float *psum = reinterpret_cast<float *>(pdot + (size_t)p.groups * nrb * 64);
@@ -489,10 +491,11 @@ mq_status launch_gemv_reg(const GemvArgs &a, int r, hipStream_t st, bool *handle
         }
     if (!p.depth || (int64_t)a.N * a.KB > 0x7FFFFFFFll) return MQ_OK;
     *handled = true;
-#define MQ_REG_CASE(R_, NL_)                                                   \
-    if (r == R_ && p.nl == NL_) {                                              \
-        if (p.depth == 3) return launch_reg<R_, NL_, 3, 1024>(a, p, st);       \
-        return launch_reg<R_, NL_, 2, 1024>(a, p, st);                         \
+    if (reg_turned(r, a.B, p.nsl)) return p.depth == 3 ? launch_reg<2, 1, 3, true>(a, p, st) : launch_reg<2, 1, 2, true>(a, p, st);
+#define MQ_REG_CASE(R_, NL_)                                             \
+    if (r == R_ && p.nl == NL_) {                                        \
+        if (p.depth == 3) return launch_reg<R_, NL_, 3>(a, p, st);       \
+        return launch_reg<R_, NL_, 2>(a, p, st);                         \
     }
     MQ_REG_CASE(2, 1) MQ_REG_CASE(4, 1) MQ_REG_CASE(4, 2)
 #undef MQ_REG_CASE
