@@ -86,24 +86,29 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
 #pragma unroll
     for (int i = 0; i < NR; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int splits = tm * 32 * mb + tb * 16 < a.M ? s.splits : 0;  // (a block past the tokens has not been stored)
-    for (int p0 = 0; p0 < splits; p0 += 4) {  // the loads of four ranges are in flight together
-        f32x4 v[4][NR];
-        float r[4];
+    // the loads of up to four ranges are in flight together (counted at compile time: a test around each load would be a branch)
+    auto add = [&](auto count_tag, int p0) {
+        constexpr int COUNT = decltype(count_tag)::value;
+        f32x4 v[COUNT][NR];
+        float r[COUNT];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const bool live = p0 + p < splits;
-            r[p] = live ? s.rs_part[(p0 + p) * rs_step + m] : 0.f;
+        for (int p = 0; p < COUNT; ++p) {
+            r[p] = s.rs_part[(p0 + p) * rs_step + m];
 #pragma unroll
-            for (int i = 0; i < NR; ++i)
-                v[p][i] = live ? __builtin_nontemporal_load(src + (p0 + p) * step + (size_t)i * mb * 1024) : f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < NR; ++i) v[p][i] = __builtin_nontemporal_load(src + (p0 + p) * step + (size_t)i * mb * 1024);
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
+        for (int p = 0; p < COUNT; ++p) {
             rs += r[p];
 #pragma unroll
             for (int i = 0; i < NR; ++i) sum[i] += v[p][i];
         }
-    }
+    };
+    int p0 = 0;
+    for (; p0 + 4 <= splits; p0 += 4) add(std::integral_constant<int, 4>{}, p0);
+    if (splits - p0 == 3) add(std::integral_constant<int, 3>{}, p0);
+    if (splits - p0 == 2) add(std::integral_constant<int, 2>{}, p0);
+    if (splits - p0 == 1) add(std::integral_constant<int, 1>{}, p0);
 
     u32x2 y[NR];
     float err[NR];
