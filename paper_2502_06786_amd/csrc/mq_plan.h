@@ -1,6 +1,7 @@
-// How the calls of the linear layer are cut into tiles, ranges and rounds: rules on sizes, host arithmetic without HIP.
+// How the calls of the linear layer and of the decode GEMV are cut into tiles, ranges and rounds: rules on sizes, host arithmetic
+// without HIP.
 //
-// The constants and the times beside them were fitted to kernels on the 32x32x16 product.  With the 16x16x32 product the large
+// The constants of the linear layer and the times beside them were fitted to kernels on the 32x32x16 product.  With the 16x16x32 product the large
 // sizes are 7-18 % faster and the choices are on average 2.4 / 2.7 / 1.8 % slower than the best (forward, 1 / 2 / 3 bit-widths; dX
 // 0.8 / 1.2 % at one / three).  A refit of the forward gave 1.6 / 2.3 / 1.0 % and made 25 of 570 sizes 4-15 % slower: not taken.
 #pragma once
