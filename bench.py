@@ -366,9 +366,9 @@ def measured_peaks(torch, mq):
         return 8 * nb
     replay()
     res["hbm_read_85MB_GBs"] = round(timed(replay, reps=5) / 1e9, 1)
-    res["note"] = ("library probes mq_probe_mfma (32x32x16 products, 1024 waves, 12 accumulators each, ~10 ms: the "
-                   "shape and occupancy of the fused kernels), mq_probe_mfma16 (16x16x32 products, 2048 waves, 24 "
-                   "accumulators each) and mq_probe_read; published peaks: 2500 TFLOP/s, 8000 GB/s")
+    res["note"] = ("library probes mq_probe_mfma (32x32x16 products, 1024 waves, 12 accumulators each, ~10 ms), "
+                   "mq_probe_mfma16 (16x16x32 products, the shape of the fused kernels, 2048 waves, 24 accumulators each) "
+                   "and mq_probe_read; published peaks: 2500 TFLOP/s, 8000 GB/s")
     return res
 
 
