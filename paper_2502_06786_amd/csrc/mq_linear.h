@@ -84,6 +84,39 @@ __device__ __forceinline__ void mfma16_settle() {
 // contraction a group takes is free as long as both operands agree.
 __device__ __forceinline__ int group_chunk(int g4) { return (0x9C >> (2 * g4)) & 3; }  // 0, 3, 1, 2
 
+// 16 bytes per lane, from `offset` (per lane) behind a descriptor's base, to `at` + 16 lane in LDS.  In assembly because
+// the compiler lets a transposing read wait for all direct-to-LDS loads that it has seen, those of the stages that are to
+// stay on their way too (stage_barrier waits for the right ones).  It writes no register but m0, which nothing else uses in a kernel
+// that loads its tiles with it alone (the compiler refuses it in the list of clobbered registers).  One wait state covers m0.  A
+// descriptor is fixed by scalar_rsrc(), in case the compiler gets it there with vector instructions (five wait states to a load that
+// reads it), which stand in load_to_lds; a schedule that uses the pieces keeps five instructions between descriptor and load.
+__device__ __forceinline__ u32x4 scalar_rsrc(const void *base, int bytes) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    u32x4 rsrc = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32)) & 0xFFFFu,
+                  (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+    asm volatile("" : "+s"(rsrc));
+    return rsrc;
+}
+__device__ __forceinline__ void load_to_lds(const u32x4 &rsrc, uint32_t offset, uint32_t at) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(offset), "s"(rsrc), "s"(at) : "memory");
+}
+// the same in two pieces for a schedule that puts a matrix product (and so a wait state) between them
+template <int PLUS>
+__device__ __forceinline__ void aim_load_to_lds(uint32_t at) {
+    asm volatile("s_add_u32 m0, %0, %1" ::"s"(at), "n"(PLUS) : "scc");
+}
+__device__ __forceinline__ void aimed_load_to_lds(const u32x4 &rsrc, uint32_t offset) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(offset), "s"(rsrc) : "memory");
+}
+
+// Four elements of one column per lane from a tile whose rows are the contraction index: a transposing read takes 8 bytes from every lane,
+// so sixteen lanes bring four rows of sixteen elements (four lanes a row), and gives each of them one column of those rows.
+__device__ __forceinline__ u32x2 read_turned16(const uint8_t *at) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(at)));
+}
+
 // Per-lane byte offset (row * ld_bytes + chunk * 16) of instruction `inst` of this wave for a bf16
 // tile, and the element column of the chunk (for the tail predicate).
 template <int NWAVES>

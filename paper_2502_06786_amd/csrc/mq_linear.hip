@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256) void rowsum_kernel(const uint16_t *__restrict_
 // backward, preparation (HBM-bound): one pass over the nr gradient tensors produces
 //   As_i[m, n] = bf16(lambda_i * alpha_n * 2^s_i * dY_i[m, n])     (operand of the dX contraction)
 //   c[m]       = sum_i sum_n As_i[m, n] * (bias_i + z_n / 2^s_i)   (what the 128 + code form and z add to dX[m, :])
-//   GT[n, m]   = bf16(sum_i lambda_i * dY_i[m, n])                  (transposed operand of the dW GEMM, in token blocks)
+//   G[m, n]    = bf16(sum_i lambda_i * dY_i[m, n])                  (operand of the dW GEMM, turned or in pieces: dw_turns)
 // ============================================================================================
 struct PrepArgs {
     const uint16_t *dY[3];
@@ -370,28 +370,35 @@ struct PrepArgs {
     float mult[3];       // 2^s_i
     float bias[3];       // 128 for sliced slots, 0 for the r = 8 slot
     float *cpart;        // [nsplit][M] partial sums of c over column ranges, or null
-    uint16_t *GT;        // [M / 32][N][32] (blocks of 32 tokens; see DwArgs) or null; a piece of 8 tokens that straddles M ends with zeros
+    uint16_t *G;         // the summed gradient in pieces of 32 tokens x 64 columns (summed_at), or null; zeros past M
+    int turn;            // G is [M / 32][N][32] instead
     int nr, M, N;
     int cols_per_split;  // multiple of 64
     int strips, nsplit;  // token strips, column ranges
-    // > 0: no sum; gradient i alone, times lam[i], goes to GT + i * gt_step (As and cpart are null, `each` times as many workgroups)
+    // > 0: no sum; gradient i alone, times lam[i], goes to G + i * g_step (As and cpart are null, `each` times as many workgroups)
     int each;
-    int64_t gt_step;
+    int64_t g_step;
     // the transposed copies that the same launch makes (null: not wanted): the codes for dX, the input for dW
     const uint8_t *Q;
     uint8_t *QT;         // [K, N]
     const uint16_t *X;
-    uint16_t *XT;        // [M / 32][K][32], as GT
+    uint16_t *XT;        // [M / 32][K][32], zeros past M
     int K;
 };
 
 constexpr int PREP_ROWS = 32;
 constexpr int PREP_MAX_SPLIT = 16;
 
+// Where G[m, n] is: [M / 32][N / 64][32][64], the last piece of columns as narrow as what is left of N.  A workgroup of dW reads 32
+// tokens x 256 columns at a time, 16 KB in one place here.  From rows of N columns each they are 32 pieces far apart, and three lines
+// instead of two where a row is no multiple of 128 bytes (18432 x 2304, 4096 tokens, both operands by rows 325 us, both in pieces 310).
+__device__ __forceinline__ size_t summed_at(int m, int n, int N) {
+    return ((size_t)(m >> 5) * N + (n & ~63)) * 32 + (m & 31) * min(64, N - (n & ~63)) + (n & 63);
+}
+
 // Workgroup (strip, split) walks 32 token rows across one range of columns in 32 x 64 tiles: thread
 // (r, ch) = (t / 8, t % 8) owns eight consecutive columns of row r, so a row segment is one 128-byte
-// line per gradient tensor.  The summed gradient tile is turned through LDS and leaves as 64-byte
-// row segments of GT.
+// line per gradient tensor.  Where the summed gradient is wanted turned, its tile goes through LDS and leaves as 64-byte row segments.
 template <bool GATED>
 __device__ __forceinline__ void prep_gradients(const PrepArgs &a, int strip, int split, uint16_t (*tile)[PREP_ROWS + 2]) {
     const int t = threadIdx.x, r = t >> 3, ch = t & 7;
@@ -470,18 +477,20 @@ __device__ __forceinline__ void prep_gradients(const PrepArgs &a, int strip, int
                 if (want_as) *reinterpret_cast<u32x4 *>(a.As[i] + (size_t)m * a.N + n) = o;
             }
         }
-        if (a.GT) {
+        if (a.turn) {
             __syncthreads();  // the previous tile has been written out
 #pragma unroll
             for (int j = 0; j < 8; ++j) tile[ch * 8 + j][r] = (uint16_t)float_to_bf16_bits(g[j]);
             __syncthreads();
-            const int nn = t >> 2, part = t & 3;  // 64 rows of GT, four 16-byte pieces each
-            if (n0 + nn < a.N && m0 + part * 8 < a.M) {  // (a piece that straddles M ends with zeros)
+            const int nn = t >> 2, part = t & 3;  // 64 columns, four 16-byte pieces each
+            if (n0 + nn < a.N) {
                 const uint32_t *src = reinterpret_cast<const uint32_t *>(&tile[nn][part * 8]);
-                *reinterpret_cast<u32x4 *>(a.GT + ((size_t)strip * a.N + n0 + nn) * 32 + part * 8) =
+                *reinterpret_cast<u32x4 *>(a.G + ((size_t)strip * a.N + n0 + nn) * 32 + part * 8) =
                     u32x4{src[0], src[1], src[2], src[3]};
             }
-        }
+        } else if (a.G && n < a.N)
+            *reinterpret_cast<u32x4 *>(a.G + summed_at(m, n, a.N)) =
+                u32x4{pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3]), pack_bf16x2(g[4], g[5]), pack_bf16x2(g[6], g[7])};
     }
     if (a.cpart) {
         c += __shfl_xor(c, 1, 64);
@@ -558,7 +567,7 @@ __device__ __forceinline__ void transpose_input(const PrepArgs &a, int tm, int t
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         const int m = m0 + 32 * b + 8 * piece;
-        if (k < a.K && m < a.M)  // (a piece that straddles M ends with zeros)
+        if (k < a.K && (m & ~31) < a.M)
             *reinterpret_cast<u32x4 *>(a.XT + ((size_t)(m >> 5) * a.K + k) * 32 + (m & 31)) =
                 *reinterpret_cast<const u32x4 *>(tile + xt_at(b, t >> 2) + 4 * piece);
     }
@@ -578,7 +587,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
             const int i = b / gradients;
             a.dY[0] = i == 0 ? a.dY[0] : i == 1 ? a.dY[1] : a.dY[2];
             a.lam[0] = i == 0 ? a.lam[0] : i == 1 ? a.lam[1] : a.lam[2];
-            a.GT += i * a.gt_step;
+            a.G += i * a.g_step;
             a.nr = 1;
             b %= gradients;
         }
@@ -598,36 +607,38 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(PrepArgs a) {
 }
 
 // ============================================================================================
-// backward dW: dW[n, k] (+)= sum_m GT[n, m] * XT[k, m]   (plain bf16 GEMM, fp32 out)
+// backward dW: dW[n, k] (+)= sum_m G[m, n] * X[m, k]   (plain bf16 GEMM, fp32 out)
 // ============================================================================================
 struct DwArgs {
-    // Both operands come in blocks of 32 tokens, [M / 32][rows][32]: the 64-byte row segments that one LDS stage takes
-    // from a tile's 256 rows are then one contiguous 16 KB piece of memory, i.e. whole 128-byte lines.  (With rows of
-    // M tokens a stage would use half of every line it touches and the other half 32 tokens later, when the line has
-    // left the first-level cache: twice the traffic between the caches.)
-    const uint16_t *GT;  // [M / 32][N][32]
-    const uint16_t *XT;  // [M / 32][K][32]
-    float *dW;           // [N, K]
-    float *part;         // [split tiles][parts][side][side]: partial tiles of the tiles that are cut
+    // TURN: the operand of each gradient is [M, N] as the caller has it, or in pieces (summed_at), X is [M, K].  Otherwise both come
+    // turned, in blocks of 32 tokens, [M / 32][rows][32]: the 64-byte row segments that one LDS stage takes from a tile's 256 rows
+    // are then one contiguous 16 KB piece of memory, i.e. whole 128-byte lines.
+    const uint16_t *G[3];
+    const uint16_t *X;
+    int in_pieces;
+    float *dW;             // [N, K] per gradient
+    float *part;           // [split tiles][parts][side][side]: partial tiles of the tiles that are cut
     int M, N, K;
     int accumulate;
     int tiles_n, tiles_k;
-    int whole;           // work items [0, whole) are whole tiles; the others are token ranges of the remaining tiles
-    int parts;           // token ranges per remaining tile
-    int64_t gt_step;     // several gradients against the same X: tile t belongs to gradient t / (tiles_n tiles_k), whose
-                         // operand is that many times gt_step elements after GT and whose result N K after dW
-};
+    int whole;             // work items [0, whole) are whole tiles; the others are token ranges of the remaining tiles
+    int parts;             // token ranges per remaining tile
+};  // (several gradients against the same X: tile t belongs to gradient t / (tiles_n tiles_k))
 
 static DwPlan dw_plan(int64_t M, int64_t N, int64_t K, int batch) { return remembered<DwPlan>(make_dw_plan, M, N, K, batch); }
 
 // Same pipeline as the forward and dX kernels (one wave per SIMD, direct-to-LDS stages, operand work fenced in between the
-// MFMAs), without any code conversion: both operands are bf16 rows with the contraction index (tokens) contiguous.  The four
+// MFMAs), without any code conversion.  The four
 // waves form a 2 x 2 grid over the tile.  HB = 4, a 256 x 256 tile, 128 x 128 per wave: 64 accumulators of 16 x 16 (all 256
 // accumulator registers), 16 operand reads per 64 MFMAs - the square wave tile is what keeps the LDS traffic (32 KB read + 16 KB
 // written per 16 tokens and compute unit, 94 bytes per clock at the matrix-core rate) under the 128 bytes per clock the LDS
 // delivers.  HB = 2, a 128 x 128 tile, 64 x 64 per wave: 16 accumulators, 8 reads per 16 MFMAs, two workgroups to a compute
-// unit.  Stages are one 32-token step deep (64-byte rows); five of them fill the LDS (HB = 2: half of it).
-template <int HB>
+// unit.  Stages are one 32-token step deep; five of them fill the LDS (HB = 2: half of it).
+//
+// TURN: the contraction index (tokens) runs across the rows of both operands, as the caller left them, and the LDS turns them on the
+// way to the registers (ds_read_b64_tr_b16: four tokens of sixteen columns at a time), so that no transposed copies are
+// written and read back.  See dw_turns for what it costs and where it is used.
+template <int HB, bool TURN>
 __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -661,7 +672,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     const uint32_t tiles = (uint32_t)(a.tiles_n * a.tiles_k);
     const uint32_t grad = lid / tiles;
     lid %= tiles;
-    const uint16_t *GT = a.GT + grad * a.gt_step;
+    const uint16_t *G = grad == 0 ? a.G[0] : grad == 1 ? a.G[1] : a.G[2];
     if (!to_part) dst = a.dW + (size_t)grad * a.N * a.K;
     constexpr int GROUP = 4;
     const int width = GROUP * a.tiles_k;
@@ -671,38 +682,79 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
     const int tk = (int)(lid % width) / gsz;
     const int n0 = tn * DW_BN, k0 = tk * DW_BK;
 
-    uint32_t off0;
-    int colb;  // byte column of this lane's 16-byte piece inside a 64-byte row
-    u8_tile_lane<4>(wave, lane, 0, 64u, off0, colb);
-    const uint32_t rstep = 64u * 64u;  // 64 rows further down
+    // TURN: LDS layout of an operand's stage: pieces of 8 tokens x 64 columns (1 KB, what one load instruction of a wave writes), piece
+    // (token group g, column group c) at (g + 4 c) KB; inside, eight rows of 128 bytes, in which the block of columns 16 p .. is at
+    // position p ^ (row / 2 % 2) ^ 2 (g % 2).  A transposing read takes 32 bytes of four rows for each group of sixteen lanes, lane
+    // group g those of token group g: those of neighbouring groups then fall on all 64 banks.
+    // Wave w loads token group w, instruction i column group i, eight neighbouring lanes a whole 128-byte line of a row (two pieces
+    // of 64 bytes, apart in the wave: 8 % longer).
+    const int lpos = ((lane >> 1) & 3) ^ ((lane >> 4) & 1) ^ (2 * (wave & 1));
+    const int lrow = 8 * wave + (lane >> 3), lcol = lpos * 16 + (lane & 1) * 8;
+    uint32_t goff[AL], xoff[BL];   // byte offsets inside a stage of 32 tokens, out of range for columns past the operand's end
+    if constexpr (TURN) {
+#pragma unroll
+        for (int i = 0; i < AL; ++i) {
+            const int row = a.in_pieces ? min(64, a.N - n0 - 64 * i) : a.N;   // elements of a row
+            goff[i] = n0 + lcol + 64 * i < a.N ? (uint32_t)(lrow * row + lcol + (a.in_pieces ? 2048 : 64) * i) * 2u : kOOB;
+        }
+#pragma unroll
+        for (int i = 0; i < BL; ++i) xoff[i] = k0 + lcol + 64 * i < a.K ? (uint32_t)(lrow * a.K + lcol + 64 * i) * 2u : kOOB;
+    } else {
+        uint32_t off0;
+        int col;
+        u8_tile_lane<4>(wave, lane, 0, 64u, off0, col);   // 64 rows of 64 bytes per instruction
+#pragma unroll
+        for (int i = 0; i < AL; ++i) goff[i] = off0 + i * 4096u;
+#pragma unroll
+        for (int i = 0; i < BL; ++i) xoff[i] = off0 + i * 4096u;
+    }
+    const bool g_blocks = !TURN || a.in_pieces;   // 32 tokens of N elements each are one block of memory
 
-    // Load i of the stage of token block mt into LDS buffer `buf`.  The descriptors of a stage start at the tile's
-    // first row inside that block and end with the block, so rows past N (K) are out of range; a block or a piece
-    // past M or the range is requested at an out-of-range offset.  Both are answered with zeros without touching memory, so the
-    // loads in flight are the same every stage.  Stages are requested in their order: the bases walk along.
-    const int m_end = min(a.M, mt1 * DW_BM);
-    const uint16_t *g_base = GT + ((size_t)mt0 * a.N + n0) * 32, *x_base = a.XT + ((size_t)mt0 * a.K + k0) * 32;
-    const size_t g_block = (size_t)a.N * 32, x_block = (size_t)a.K * 32;
-    const uint64_t g_bytes = (uint64_t)(a.N - n0) * 64, x_bytes = (uint64_t)(a.K - k0) * 64;
-    auto issue_one = [&](int mt, int buf, int i) {
-        uint8_t *base = smem + buf * DW_STAGE;
-        const uint32_t o = (mt * DW_BM + colb / 2 < m_end) ? off0 : kOOB;
-        if (i < AL)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(g_base, g_bytes), (lds_ptr)(base + (wave + i * 4) * 1024), 16,
-                                                     o + (uint32_t)i * rstep, 0, 0, 0);
-        else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(x_base, x_bytes), (lds_ptr)(base + DW_A_TILE + (wave + (i - AL) * 4) * 1024), 16,
-                                                     o + (uint32_t)(i - AL) * rstep, 0, 0, 0);
-        if (i == LPS - 1) {
-            g_base += g_block;
-            x_base += x_block;
+    // The descriptors of a stage start at the tile's first column in the first of its 32 tokens and end with the last token of the range
+    // (or of M; a block of memory, which has zeros past M, with the block), so what is past it is out of range and answered with zeros
+    // without touching memory: the loads in flight are the same every stage.  Stages are requested in their order: the bases walk along.
+    const uint16_t *g_base = G + (size_t)mt0 * DW_BM * a.N + (size_t)n0 * (g_blocks ? DW_BM : 1);
+    const uint16_t *x_base = a.X + (size_t)mt0 * DW_BM * a.K + (size_t)k0 * (TURN ? 1 : DW_BM);
+    const size_t g_block = (size_t)a.N * DW_BM, x_block = (size_t)a.K * DW_BM;
+    int rows_left = min(a.M, mt1 * DW_BM) - mt0 * DW_BM;   // from the stage that is requested next
+    u32x4 g_rsrc, x_rsrc;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr)(smem) + wave * 1024);
+    auto next_stage = [&] {
+        // (31 rows of 2^22 columns and a tile are less than 2^31 bytes)
+        const int rows = min(max(rows_left, 0), DW_BM);
+        g_rsrc = scalar_rsrc(g_base, g_blocks ? (rows > 0 ? a.N - n0 : 0) * (2 * DW_BM) : max(rows * a.N - n0, 0) * 2);
+        x_rsrc = scalar_rsrc(x_base, TURN ? max(rows * a.K - k0, 0) * 2 : (rows > 0 ? a.K - k0 : 0) * (2 * DW_BM));
+        g_base += g_block;
+        x_base += x_block;
+        rows_left -= DW_BM;
+    };
+    // LDS fragment offsets inside a stage (TURN: by the block of 16 columns in its group of 64): lane (l16, g4) ends up with eight
+    // tokens of column l16 of a block, those of group g4 (otherwise of its chunk of a row of 32)
+    uint32_t gb[TURN ? 4 : 1], xb[TURN ? 4 : 1];
+    if constexpr (TURN) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const uint32_t at = (uint32_t)(g4 * 1024 + (l16 >> 2) * 128 + ((p ^ (l16 >> 3) ^ (2 * (g4 & 1))) << 5) + (l16 & 3) * 8);
+            gb[p] = at + (uint32_t)(wn * (RB / 4) * 4096);
+            xb[p] = at + (uint32_t)(DW_A_TILE + wk * (RB / 4) * 4096);
+        }
+    } else {
+        const uint32_t at = (uint32_t)(l16 * 64) + ((uint32_t)(group_chunk(g4) ^ ((l16 >> 2) & 3)) << 4);
+        gb[0] = at + (uint32_t)(wn * RB * 1024);
+        xb[0] = at + (uint32_t)(DW_A_TILE + wk * RB * 1024);
+    }
+    auto read_half = [&](u32x4 &dst, const uint8_t *stage, const auto &at, auto block_tag, auto half_tag) {
+        constexpr int B = decltype(block_tag)::value, HALF = decltype(half_tag)::value;
+        if constexpr (TURN) {
+            const u32x2 v = read_turned16(stage + at[B & 3] + (B >> 2) * 4096 + HALF * 512);
+            dst[2 * HALF] = v[0];
+            dst[2 * HALF + 1] = v[1];
+        } else if constexpr (HALF == 0) {   // (one read brings both)
+            dst = *reinterpret_cast<const u32x4 *>(stage + at[0] + B * 1024);
         }
     };
-
-    // LDS fragment offsets inside a stage: lane (l16, g4) takes eight tokens of row l16 of a block of 16
-    const uint32_t chunk = (uint32_t)(group_chunk(g4) ^ ((l16 >> 2) & 3)) << 4;
-    const uint32_t gb = (uint32_t)(wn * 16 * RB + l16) * 64u + chunk;
-    const uint32_t xb = (uint32_t)DW_A_TILE + (uint32_t)(wk * 16 * RB + l16) * 64u + chunk;
+    constexpr std::integral_constant<int, 0> first{};
+    constexpr std::integral_constant<int, 1> second{};
 
     f32x4 acc[RB][RB];   // [block of n][block of k]: rows 4 g4 .. 4 g4 + 3, column l16 of the block
 #pragma unroll
@@ -711,38 +763,54 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         for (int j = 0; j < RB; ++j) acc[rb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
 #pragma unroll
-    for (int st = 0; st < DW_NST - 1; ++st)
+    for (int st = 0; st < DW_NST - 1; ++st) {
+        next_stage();
 #pragma unroll
-        for (int i = 0; i < LPS; ++i) issue_one(mt0 + st, st, i);
+        for (int i = 0; i < LPS; ++i)
+            load_to_lds(i < AL ? g_rsrc : x_rsrc, i < AL ? goff[i] : xoff[i - AL], lds0 + st * DW_STAGE + (i < AL ? i * 4096 : DW_A_TILE + (i - AL) * 4096));
+    }
     stage_barrier<(DW_NST - 2) * LPS, 0>();
 
     // The products of a stage come in two halves, over the first and over the second half of the columns' blocks.  Every operand
     // has one register: the second half of the columns is read in the first half of the stage, the first half of the columns and
     // each block of rows, as soon as it is done with, are read for the next stage in the second half.
     u32x4 gf[RB], xf[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) gf[rb] = *reinterpret_cast<const u32x4 *>(smem + gb + rb * 1024);
-#pragma unroll
-    for (int j = 0; j < RB / 2; ++j) xf[j] = *reinterpret_cast<const u32x4 *>(smem + xb + j * 1024);
+    static_for<RB>([&](auto rb) {
+        read_half(gf[decltype(rb)::value], smem, gb, rb, first);
+        read_half(gf[decltype(rb)::value], smem, gb, rb, second);
+    });
+    static_for<RB / 2>([&](auto j) {
+        read_half(xf[decltype(j)::value], smem, xb, j, first);
+        read_half(xf[decltype(j)::value], smem, xb, j, second);
+    });
 
     // one stage; cb = LDS buffer of this stage
     // (MORE = false, the last stage of the small tiles: nothing to prepare)
-    auto tile = [&](int mt, int cb, auto more_tag) {
+    auto tile = [&](int cb, auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
         const int nb = cb + 1 == DW_NST ? 0 : cb + 1;   // buffer of the next stage
-        const int ib = cb == 0 ? DW_NST - 1 : cb - 1;   // buffer of stage mt + NST - 1 (= the one of stage mt - 1)
+        const int ib = cb == 0 ? DW_NST - 1 : cb - 1;   // buffer of the stage NST - 1 further on (= the one of the stage before)
         const uint8_t *cur = smem + cb * DW_STAGE, *nxt = smem + nb * DW_STAGE;
+        const uint32_t fill = lds0 + ib * DW_STAGE;
+        if constexpr (MORE) next_stage();
+        __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto q_tag) {
             constexpr int q = decltype(q_tag)::value, H = NM / 2, HJ = RB / 2;
             constexpr int half = q / H, rb = q % H / HJ, j = half * HJ + q % HJ;
             mfma16_acc<HB == 4>(acc[rb][j], gf[rb], xf[j]);
+            // one read, and one instruction of a load, behind a product
             if constexpr (half == 0) {
-                if constexpr (q < HJ) xf[HJ + q] = *reinterpret_cast<const u32x4 *>(cur + xb + (HJ + q) * 1024);
-                constexpr int L0 = LPS * q / H, L1 = LPS * (q + 1) / H;
-                if constexpr (MORE && L1 > L0) issue_one(mt + DW_NST - 1, ib, L0);
+                if constexpr (q < 2 * HJ) read_half(xf[HJ + q / 2], cur, xb, std::integral_constant<int, HJ + q / 2>{}, std::integral_constant<int, q % 2>{});
+                constexpr int EVERY = H / LPS, l = q / EVERY;   // (three instructions at least between next_stage and the first aim)
+                static_assert(EVERY >= 2 && H % LPS == 0, "a product between the two pieces of a load");
+                if constexpr (MORE && q % EVERY == EVERY - 2) aim_load_to_lds<l < AL ? l * 4096 : DW_A_TILE + (l - AL) * 4096>(fill);
+                if constexpr (MORE && q % EVERY == EVERY - 1) aimed_load_to_lds(l < AL ? g_rsrc : x_rsrc, l < AL ? goff[l < AL ? l : 0] : xoff[l < AL ? 0 : l - AL]);
             } else if constexpr (MORE) {
-                if constexpr (q - H < HJ) xf[q - H] = *reinterpret_cast<const u32x4 *>(nxt + xb + (q - H) * 1024);
-                if constexpr (q % HJ == HJ - 1) gf[rb] = *reinterpret_cast<const u32x4 *>(nxt + gb + rb * 1024);
+                constexpr int p = q - H;
+                if constexpr (p < 2 * HJ) read_half(xf[p / 2], nxt, xb, std::integral_constant<int, p / 2>{}, std::integral_constant<int, p % 2>{});
+                if constexpr (p % HJ == 0 && p > 0) read_half(gf[rb - 1], nxt, gb, std::integral_constant<int, rb - 1>{}, second);
+                if constexpr (p % HJ == HJ - 1) read_half(gf[rb], nxt, gb, std::integral_constant<int, rb>{}, first);
+                if constexpr (p == H - 1) read_half(gf[rb], nxt, gb, std::integral_constant<int, rb>{}, second);
             }
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -758,11 +826,12 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         // Stage mt + 1 must be resident (operands read for it inside this stage); the loads of stages mt + 2 and mt + 3 may stay
         // in flight; after the barrier the buffer of stage mt - 1, all of whose operands have been multiplied, is free for stage
         // mt + 4.
-        stage_barrier<(DW_NST - 3) * LPS, RB + RB / 2>();
-        tile(mt, cb, std::true_type{});
+        // (a counter of reads in flight ends at 15)
+        stage_barrier<(DW_NST - 3) * LPS, std::min(15, (TURN ? 2 : 1) * (RB + RB / 2))>();
+        tile(cb, std::true_type{});
         cb = cb + 1 == DW_NST ? 0 : cb + 1;
     }
-    if constexpr (APART) tile(mt1 - 1, cb, std::false_type{});
+    if constexpr (APART) tile(cb, std::false_type{});
     wait_vm0();  // loads of stages that nobody consumes must have landed before the workgroup ends
 
     // Two neighbouring column blocks exchange half of their lanes, after which a store instruction writes 32 consecutive k (one
@@ -861,7 +930,7 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(DwArgs a) {
 // ============================================================================================
 
 struct BwdWorkspace {
-    size_t cvec, as[3], gt, xt, qt, dwp, dxp, total;
+    size_t cvec, as[3], g, qt, xt, dwp, dxp, total;
 };
 
 static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr, const DxPlan &dx, const DwPlan &dw) {
@@ -873,14 +942,14 @@ static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr, const Dx
         w.as[i] = o;
         if (i < nr) o += align256((size_t)M * N * 2);
     }
-    const size_t m32 = ((size_t)M + 31) & ~(size_t)31;   // the transposed operands of dW come in blocks of 32 tokens
-    w.gt = o;
+    const size_t m32 = ((size_t)M + 31) & ~(size_t)31;   // the operands of dW come in blocks of 32 tokens
+    w.g = o;
     o += align256(m32 * N * 2);
     w.qt = o;
     o += align256((size_t)N * K);
     w.xt = o;
     o += align256(m32 * K * 2);
-    // dX is done before dW begins: their partial sums share their place
+    // dW is done before dX begins: their partial sums share their place
     w.dxp = w.dwp = o;
     o += align256(std::max(dw.part_bytes, dx.part_bytes));
     w.total = o;
@@ -901,20 +970,21 @@ static mq_status check_rs(const int *rs, int nr) {
     return MQ_OK;
 }
 
-template <int HB>
+template <int HB, bool TURN>
 static mq_status launch_dw_side(const DwArgs &w, const DwPlan &plan, hipStream_t st) {
-    if (!allow_lds<dw_kernel<HB>>(dw_lds(HB))) return MQ_ERR_DEVICE;
-    dw_kernel<HB><<<dim3(plan.whole + plan.rest * plan.parts), dim3(256), dw_lds(HB), st>>>(w);
+    if (!allow_lds<dw_kernel<HB, TURN>>(dw_lds(HB))) return MQ_ERR_DEVICE;
+    dw_kernel<HB, TURN><<<dim3(plan.whole + plan.rest * plan.parts), dim3(256), dw_lds(HB), st>>>(w);
     if (plan.rest > 0) dw_reduce_kernel<HB><<<dim3(plan.rest * HB * HB), dim3(256), 0, st>>>(w);
     return launch_status();
 }
 
-static mq_status launch_dw(DwArgs w, const DwPlan &plan, hipStream_t st) {
+static mq_status launch_dw(DwArgs w, const DwPlan &plan, bool turn, hipStream_t st) {
     w.tiles_n = plan.tiles_n;
     w.tiles_k = plan.tiles_k;
     w.whole = plan.whole;
     w.parts = plan.parts;
-    return plan.hb == 2 ? launch_dw_side<2>(w, plan, st) : launch_dw_side<4>(w, plan, st);
+    if (turn) return plan.hb == 2 ? launch_dw_side<2, true>(w, plan, st) : launch_dw_side<4, true>(w, plan, st);
+    return plan.hb == 2 ? launch_dw_side<2, false>(w, plan, st) : launch_dw_side<4, false>(w, plan, st);
 }
 
 template <int NR, bool HAS8, bool EP, int MB, bool LOSS>
@@ -1218,15 +1288,15 @@ static mq_status launch_prep(PrepArgs &p, bool gated, hipStream_t st) {
     return launch_status();
 }
 
-// Workspace of dw_each: the transposed gradients, X, and the partial tiles
+// Workspace of dw_each: the gradients and X, turned or scaled, and the partial tiles
 struct EachWorkspace {
-    size_t gt_step, xt, dwp, total;  // gt_step in bytes
+    size_t g_step, xt, dwp, total;  // g_step in bytes
 };
 static EachWorkspace each_layout(int64_t M, int64_t N, int64_t K, int nr, const DwPlan &dw) {
     EachWorkspace w;
     const size_t m32 = ((size_t)M + 31) & ~(size_t)31;
-    w.gt_step = align256(m32 * N * 2);
-    w.xt = w.gt_step * nr;
+    w.g_step = align256(m32 * N * 2);
+    w.xt = w.g_step * nr;
     w.dwp = w.xt + align256(m32 * K * 2);
     w.total = w.dwp + align256(dw.part_bytes);
     return w;
@@ -1238,37 +1308,47 @@ size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr, bool least) {
 
 // (no argument checks: the caller has made those of mq_linear_bwd)
 mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lambda, int64_t M, int64_t N, int64_t K, int nr,
-                  float *G, uint8_t *ws, size_t ws_bytes, hipStream_t st) {
+                  float *out, uint8_t *ws, size_t ws_bytes, hipStream_t st) {
     DwPlan cut = dw_plan(M, N, K, nr);
     if (ws_bytes < each_layout(M, N, K, nr, cut).total) cut = dw_plan_whole(N, K, nr);
     const EachWorkspace lay = each_layout(M, N, K, nr, cut);
-    PrepArgs p{};
+    DwArgs w{};
+    bool scaled = false;
     for (int i = 0; i < nr; ++i) {
-        p.dY[i] = dY[i];
-        p.lam[i] = lambda ? lambda[i] : 1.0f;
+        scaled = scaled || (lambda && lambda[i] != 1.0f);
+        w.G[i] = dY[i];
     }
-    for (int i = 0; i < 3; ++i) p.mult[i] = 1.0f;
-    p.GT = reinterpret_cast<uint16_t *>(ws);
-    p.gt_step = (int64_t)(lay.gt_step / 2);
-    p.each = p.nr = nr;
-    p.M = (int)M;
-    p.N = (int)N;
-    p.K = (int)K;
-    p.X = X;
-    p.XT = reinterpret_cast<uint16_t *>(ws + lay.xt);
-    mq_status s = launch_prep(p, false, st);
-    if (s != MQ_OK) return s;
-    DwArgs w;
-    w.GT = p.GT;
-    w.gt_step = p.gt_step;
-    w.XT = p.XT;
-    w.dW = G;
+    const bool turn = dw_turns(N, K, nr, !scaled);
+    w.in_pieces = scaled;
+    w.X = X;
+    if (scaled || !turn) {  // otherwise the operands are taken as they stand
+        PrepArgs p{};
+        for (int i = 0; i < nr; ++i) {
+            p.dY[i] = dY[i];
+            p.lam[i] = lambda ? lambda[i] : 1.0f;
+            w.G[i] = reinterpret_cast<uint16_t *>(ws + i * lay.g_step);
+        }
+        for (int i = 0; i < 3; ++i) p.mult[i] = 1.0f;
+        p.G = reinterpret_cast<uint16_t *>(ws);
+        p.turn = !turn;
+        p.g_step = (int64_t)(lay.g_step / 2);
+        p.each = p.nr = nr;
+        p.M = (int)M;
+        p.N = (int)N;
+        p.K = (int)K;
+        if (!turn) {
+            p.X = X;
+            w.X = p.XT = reinterpret_cast<uint16_t *>(ws + lay.xt);
+        }
+        const mq_status s = launch_prep(p, false, st);
+        if (s != MQ_OK) return s;
+    }
+    w.dW = out;
     w.part = reinterpret_cast<float *>(ws + lay.dwp);
     w.M = (int)M;
     w.N = (int)N;
     w.K = (int)K;
-    w.accumulate = 0;
-    return launch_dw(w, cut, st);
+    return launch_dw(w, cut, turn, st);
 }
 
 // gated: the output gradients come from GU and dA (see PrepArgs) instead of dY
@@ -1348,7 +1428,9 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.alpha = alpha;
     p.zero = zero;
     p.cpart = dX ? reinterpret_cast<float *>(base + lay.cvec) : nullptr;
-    p.GT = dW ? reinterpret_cast<uint16_t *>(base + lay.gt) : nullptr;
+    // (the operand of dW is a single gradient as it stands where it is not scaled)
+    const bool single = !gated && nr == 1 && p.lam[0] == 1.0f, turn = dw_turns(N, K, 1, single), plain_g = single && turn;
+    p.G = dW && !plain_g ? reinterpret_cast<uint16_t *>(base + lay.g) : nullptr;
     p.nr = nr;
     p.M = (int)M;
     p.N = (int)N;
@@ -1356,13 +1438,31 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.K = (int)K;
     p.Q = Q;
     p.QT = dX ? base + lay.qt : nullptr;
+    p.turn = p.G && !turn;
     p.X = X;
-    p.XT = dW ? reinterpret_cast<uint16_t *>(base + lay.xt) : nullptr;
+    p.XT = dW && !turn ? reinterpret_cast<uint16_t *>(base + lay.xt) : nullptr;
     p.each = 0;
-    p.gt_step = 0;
-    s = launch_prep(p, gated, st);
-    if (s != MQ_OK) return s;
+    p.g_step = 0;
+    if (dX || p.G) {
+        s = launch_prep(p, gated, st);
+        if (s != MQ_OK) return s;
+    }
 
+    // dW comes first: it reads X and possibly a gradient where they stand, and dX may take the place of either
+    if (dW) {
+        DwArgs w{};
+        w.G[0] = plain_g ? dY[0] : p.G;
+        w.in_pieces = !plain_g;
+        w.X = turn ? X : p.XT;
+        w.dW = dW;
+        w.part = reinterpret_cast<float *>(base + lay.dwp);
+        w.M = (int)M;
+        w.N = (int)N;
+        w.K = (int)K;
+        w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
+        const mq_status dws = launch_dw(w, dw_cut, turn, st);
+        if (dws != MQ_OK) return dws;
+    }
     if (dX) {
         // slot order of the kernel: the r = 8 bit-width (if any) first
         DxArgs d;
@@ -1389,20 +1489,6 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         d.part = reinterpret_cast<float *>(base + lay.dxp);
         const mq_status ds = launch_dx(d, dx_cut, nr, has8 != 0, ep, st);
         if (ds != MQ_OK) return ds;
-    }
-    if (dW) {
-        DwArgs w;
-        w.GT = p.GT;
-        w.XT = p.XT;
-        w.dW = dW;
-        w.part = reinterpret_cast<float *>(base + lay.dwp);
-        w.M = (int)M;
-        w.N = (int)N;
-        w.K = (int)K;
-        w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
-        w.gt_step = 0;
-        const mq_status dws = launch_dw(w, dw_cut, st);
-        if (dws != MQ_OK) return dws;
     }
     return launch_status();
 }

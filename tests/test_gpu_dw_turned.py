@@ -1,0 +1,48 @@
+"""dW by operands as they stand, turned by the LDS, and by transposed copies (dw_turns in csrc/mq_plan.h): small integers, so that every sum
+is exact in fp32 whatever its order.  Columns that end inside a group of 64, tokens that end inside a block of 32, either tile."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [  # M, N, K
+    (1, 16, 48),
+    (33, 144, 272),
+    (95, 2064, 1040),
+    (257, 2304, 1152),     # rows of whole lines
+    (2049, 336, 1392),     # ranges of tokens
+    (40, 14352, 2064),     # copies
+    (70, 7040, 7168),      # copies, 256-tiles
+    (130, 2320, 9232),     # as they stand, 256-tiles
+]
+
+
+@pytest.fixture(scope="module")
+def mq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_06786_amd as mq_
+
+    return mq_
+
+
+def _ints(seed, *shape):
+    return torch.randint(-3, 4, shape, generator=torch.Generator().manual_seed(seed)).to(torch.bfloat16).cuda()
+
+
+@pytest.mark.parametrize("lam", [None, (0.5, 2.0)])
+@pytest.mark.parametrize("nr", [1, 2])
+@pytest.mark.parametrize("M,N,K", SIZES)
+def test_exact(mq, M, N, K, nr, lam):
+    X, dY = _ints(M, M, K), [_ints(7 + i, M, N) for i in range(nr)]
+    Q, one = torch.zeros(N, K, dtype=torch.uint8, device="cuda"), torch.ones(N, device="cuda")
+    lam = lam and lam[:nr]
+    total = sum(d.float() * (lam[i] if lam else 1.0) for i, d in enumerate(dY))
+    want = total.t().contiguous() @ X.float()
+    _, dW = mq.mq_linear_bwd(X, Q, one, one, dY, lam, (4, 2)[:nr], need_dX=False)
+    assert torch.equal(dW, want)
+    # dX in the place of X, and of the only gradient where the shapes agree: both are read before it is written
+    dX, dW2 = mq.mq_linear_bwd(X.clone(), Q, one, one, dY, lam, (4, 2)[:nr])
+    mine = X.clone()
+    mq.mq_linear_bwd(mine, Q, one, one, dY, lam, (4, 2)[:nr], dX=mine, dW=dW)
+    assert torch.equal(mine, dX) and torch.equal(dW, want) and torch.equal(dW2, want)
