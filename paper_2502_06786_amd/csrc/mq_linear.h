@@ -160,9 +160,26 @@ __device__ __forceinline__ SliceParam slice_param(int r) {
 // Four codes (one dword) -> two dwords of bf16 pairs, in four steps of two independent instructions each, so that a step fits
 // behind a matrix product without waiting for the one before it (a wave issues a dependent vector instruction only every eight
 // cycles, and a 16x16x32 product takes sixteen).  t carries the values between the steps; the empty asm keeps a step where it is.
-template <bool IS8, bool EP, int STEP>
+// A code of r = 2 depends on the upper three bits of the byte alone, rounding and clamp included: KIND_2 looks four of them up with one
+// byte permutation, five instructions instead of eight.  14336 x 4096, 2011 tokens, r = 2 181.4 -> 173.7 us a call; the forward with the
+// objective at r = 8/4/2, 14336 x 3584, 8192 tokens 1926 -> 1880 us, dX level (power is the limit); 2304 x 9216, 1999 tokens 203 -> 198 and 219 -> 214.
+// The operand's bits are the same.
+enum CodeKind { KIND_ANY, KIND_8, KIND_2 };
+constexpr CodeKind code_kind(bool is8, bool is2) { return is8 ? KIND_8 : is2 ? KIND_2 : KIND_ANY; }
+template <CodeKind KIND, bool EP, int STEP>
 __device__ __forceinline__ void convert_step(uint32_t d, const SliceParam &p, uint32_t (&t)[4], uint32_t &lo, uint32_t &hi) {
-    if constexpr (IS8) {  // int8 -> fp32 -> bf16 (exact, codes <= 255)
+    if constexpr (KIND == KIND_2) {
+        if constexpr (STEP == 0) t[0] = d >> 5;
+        if constexpr (STEP == 1) t[0] &= 0x07070707u;
+        if constexpr (STEP == 2) t[0] = __builtin_amdgcn_perm(EP ? 0x04030302u : 0x03030302u, 0x02010100u, t[0]);
+        if constexpr (STEP == 3) {
+            lo = __builtin_amdgcn_perm(kMagic128, t[0], 0x05010500u);   // (byte 5 of the pair: 0x43)
+            hi = __builtin_amdgcn_perm(kMagic128, t[0], 0x05030502u);
+            asm volatile("" : "+v"(lo), "+v"(hi));
+        } else {
+            asm volatile("" : "+v"(t[0]));
+        }
+    } else if constexpr (KIND == KIND_8) {  // int8 -> fp32 -> bf16 (exact, codes <= 255)
         if constexpr (STEP < 2) {
             t[2 * STEP] = __float_as_uint((float)((d >> (16 * STEP)) & 0xFFu));
             t[2 * STEP + 1] = __float_as_uint((float)((d >> (16 * STEP + 8)) & 0xFFu));
@@ -255,12 +272,12 @@ struct StepSchedule {
     }
 };
 // all four steps at once (prologues)
-template <bool IS8, bool EP>
+template <CodeKind KIND, bool EP>
 __device__ __forceinline__ u32x4 convert_eight(uint32_t d0, uint32_t d1, const SliceParam &p) {
     uint32_t o[4], t[4];
     static_for<8>([&](auto c_tag) {
         constexpr int c = decltype(c_tag)::value, half = c / 4;
-        convert_step<IS8, EP, c % 4>(half ? d1 : d0, p, t, o[2 * half], o[2 * half + 1]);
+        convert_step<KIND, EP, c % 4>(half ? d1 : d0, p, t, o[2 * half], o[2 * half + 1]);
     });
     return u32x4{o[0], o[1], o[2], o[3]};
 }
@@ -297,11 +314,12 @@ struct FwdArgs {
 constexpr bool fwd_acc_in_file_a(int nr, int mb, int i, int tb) { return !(nr == 3 && mb == 3 && tb == 5 && i > 0) && !(nr == 1 && mb <= 2); }
 
 // The contraction of one workgroup: acc[i][rb][tb] = sum over k in [64 kt0, k_end) of code_i[channels 16 rb .. of this wave][k] *
-// X[tokens m0 + 16 tb ..][k], for all bit-widths i and token blocks tb of the tile at (m0, n0).  Four waves; wave w owns
+// X[tokens m0 + 16 tb ..][k], for all bit-widths i and token blocks tb of the tile at (m0, n0) (LAST2: the last
+// bit-width is 2).  Four waves; wave w owns
 // channels [32 w, 32 w + 32) of the tile for all its tokens; lane (l16, g4) ends up with channels 4 g4 .. 4 g4 + 3 of token l16 of
 // a block.  ROWSUM: also rsum[j] += this thread's share (chunk t % 8 of
 // row t / 8) of sum_k X for the token blocks in rs_mask.
-template <int NR, bool HAS8, bool EP, int MB, bool ROWSUM>
+template <int NR, bool HAS8, bool LAST2, bool EP, int MB, bool ROWSUM>
 __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, int m0, int n0, int kt0, int nkt, int k_end,
                                               f32x4 (&acc)[NR][2][2 * MB], float (&rsum)[MB], uint32_t rs_mask) {
     constexpr int BM = 32 * MB;
@@ -382,12 +400,12 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     for (int rb = 0; rb < 2; ++rb) raw[rb] = *reinterpret_cast<const u32x4 *>(smem + qa + rb * 1024);
 #pragma unroll
     for (int tb = 0; tb < 2 * MB; ++tb) xf[0][tb] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + tb * 2048);
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
+    static_for<NR>([&](auto i_tag) {
+        constexpr int i = decltype(i_tag)::value;
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
-            wf[0][i][rb] = HAS8 && i == 0 ? convert_eight<true, EP>(raw[rb][0], raw[rb][1], sp[i])
-                                          : convert_eight<false, EP>(raw[rb][0], raw[rb][1], sp[i]);
+            wf[0][i][rb] = convert_eight<code_kind(HAS8 && i == 0, LAST2 && i == NR - 1), EP>(raw[rb][0], raw[rb][1], sp[i]);
+    });
 
     // One stage of 64 k: two 32-wide steps of 4 NR MB MFMAs.  A wave issues in order, so whatever
     // is queued behind an MFMA that waits for the matrix pipe waits with it; the other work of a
@@ -442,7 +460,7 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
                     constexpr int ci = pair % NR, crb = pair / NR / 2, half = pair / NR % 2;
                     u32x4 &out = wf[1 - t][ci][crb];
                     uint32_t lo = out[2 * half], hi = out[2 * half + 1];
-                    convert_step<HAS8 && ci == 0, EP, step>(t == 0 ? raw[crb][2 + half] : rawn[crb][half], sp[ci], tmp[plan.at[c]], lo, hi);
+                    convert_step<code_kind(HAS8 && ci == 0, LAST2 && ci == NR - 1), EP, step>(t == 0 ? raw[crb][2 + half] : rawn[crb][half], sp[ci], tmp[plan.at[c]], lo, hi);
                     if constexpr (step == (HAS8 && ci == 0 ? 2 : 3)) {
                         out[2 * half] = lo;
                         out[2 * half + 1] = hi;
@@ -494,6 +512,8 @@ struct DxArgs {
 DxPlan dx_plan(int64_t M, int64_t N, int64_t K, int nr);
 // the forward at one bit-width (plain or gated), mb as fwd_wide_mb has chosen it
 mq_status launch_fwd_wide(const FwdArgs &f, int mb, bool has8, bool ep, hipStream_t st);
+// whether the kernels have a form for bit-widths in slot order with r = 2 last: 2, any two and 8/./2
+constexpr bool has_last2(int nr, bool has8) { return nr == 2 || (nr == 1) != has8; }
 mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st);
 
 }  // namespace mq

@@ -49,7 +49,7 @@ constexpr int fwd_lds(int mb, int nr) {
 //
 // With three bit-widths and two or three token blocks, two workgroups fit a compute unit (at most 80 KB of LDS and 256
 // registers each): one converts, stages and stores its outputs while the other multiplies.
-template <int NR, bool HAS8, bool EP, int MB, bool LOSS>
+template <int NR, bool HAS8, bool LAST2, bool EP, int MB, bool LOSS>
 __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     constexpr int BM = 32 * MB;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
 
     f32x4 acc[NR][2][2 * MB];
     float no_rowsum[MB];
-    fwd_main_loop<NR, HAS8, EP, MB, false>(a, smem, m0, n0, 0, (a.K + BKT - 1) / BKT, a.K, acc, no_rowsum, 0u);
+    fwd_main_loop<NR, HAS8, LAST2, EP, MB, false>(a, smem, m0, n0, 0, (a.K + BKT - 1) / BKT, a.K, acc, no_rowsum, 0u);
 
     // ---- epilogue ---------------------------------------------------------------------------
     // a lane holds channels 4 g4 .. 4 g4 + 3 of token l16 per 16 x 16 block.
@@ -987,31 +987,33 @@ static mq_status launch_dw(DwArgs w, const DwPlan &plan, bool turn, hipStream_t 
     return plan.hb == 2 ? launch_dw_side<2, false>(w, plan, st) : launch_dw_side<4, false>(w, plan, st);
 }
 
-template <int NR, bool HAS8, bool EP, int MB, bool LOSS>
+template <int NR, bool HAS8, bool LAST2, bool EP, int MB, bool LOSS>
 static mq_status launch_fwd_mb(FwdArgs a, hipStream_t st, int64_t *blocks) {
     a.tiles_m = (int)cdiv(a.M, 32 * MB);
     a.tiles_n = (int)cdiv(a.N, FWD_BN);
     *blocks = (int64_t)a.tiles_m * a.tiles_n;
-    if (!allow_lds<fwd_kernel<NR, HAS8, EP, MB, LOSS>>(fwd_lds(MB, NR))) return MQ_ERR_DEVICE;
-    fwd_kernel<NR, HAS8, EP, MB, LOSS><<<dim3(a.tiles_m * a.tiles_n), dim3(256), fwd_lds(MB, NR), st>>>(a);
+    if (!allow_lds<fwd_kernel<NR, HAS8, LAST2, EP, MB, LOSS>>(fwd_lds(MB, NR))) return MQ_ERR_DEVICE;
+    fwd_kernel<NR, HAS8, LAST2, EP, MB, LOSS><<<dim3(a.tiles_m * a.tiles_n), dim3(256), fwd_lds(MB, NR), st>>>(a);
     return launch_status();
 }
 
-template <int NR, bool HAS8, bool EP, bool LOSS>
+template <int NR, bool HAS8, bool LAST2, bool EP, bool LOSS>
 static mq_status launch_fwd(const FwdArgs &a, hipStream_t st, int64_t *blocks) {
     constexpr int HI = fwd_mb(NR), LO = HI - 1;
     int mb = HI;
     fwd_tiled_cost(a.M, a.N, a.K, NR, &mb);
     if constexpr (NR == 3) {
-        if (mb == 2) return launch_fwd_mb<NR, HAS8, EP, 2, LOSS>(a, st, blocks);
-        if (mb == 3) return launch_fwd_mb<NR, HAS8, EP, 3, LOSS>(a, st, blocks);
+        if (mb == 2) return launch_fwd_mb<NR, HAS8, LAST2, EP, 2, LOSS>(a, st, blocks);
+        if (mb == 3) return launch_fwd_mb<NR, HAS8, LAST2, EP, 3, LOSS>(a, st, blocks);
     }
-    return mb == LO ? launch_fwd_mb<NR, HAS8, EP, LO, LOSS>(a, st, blocks) : launch_fwd_mb<NR, HAS8, EP, HI, LOSS>(a, st, blocks);
+    return mb == LO ? launch_fwd_mb<NR, HAS8, LAST2, EP, LO, LOSS>(a, st, blocks) : launch_fwd_mb<NR, HAS8, LAST2, EP, HI, LOSS>(a, st, blocks);
 }
 
 template <int NR, bool HAS8, bool LOSS>
 static mq_status launch_fwd_ep(const FwdArgs &a, bool ep, hipStream_t st, int64_t *blocks) {
-    return ep ? launch_fwd<NR, HAS8, true, LOSS>(a, st, blocks) : launch_fwd<NR, HAS8, false, LOSS>(a, st, blocks);
+    if constexpr (has_last2(NR, HAS8))
+        if (a.r[NR - 1] == 2) return ep ? launch_fwd<NR, HAS8, true, true, LOSS>(a, st, blocks) : launch_fwd<NR, HAS8, true, false, LOSS>(a, st, blocks);
+    return ep ? launch_fwd<NR, HAS8, false, true, LOSS>(a, st, blocks) : launch_fwd<NR, HAS8, false, false, LOSS>(a, st, blocks);
 }
 
 template <bool LOSS>
@@ -1318,7 +1320,7 @@ mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lam
         scaled = scaled || (lambda && lambda[i] != 1.0f);
         w.G[i] = dY[i];
     }
-    const bool turn = dw_turns(N, K, nr, !scaled);
+    const bool turn = dw_turns(M, N, K, nr, !scaled);
     w.in_pieces = scaled;
     w.X = X;
     if (scaled || !turn) {  // otherwise the operands are taken as they stand
@@ -1429,7 +1431,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.zero = zero;
     p.cpart = dX ? reinterpret_cast<float *>(base + lay.cvec) : nullptr;
     // (the operand of dW is a single gradient as it stands where it is not scaled)
-    const bool single = !gated && nr == 1 && p.lam[0] == 1.0f, turn = dw_turns(N, K, 1, single), plain_g = single && turn;
+    const bool single = !gated && nr == 1 && p.lam[0] == 1.0f, turn = dw_turns(M, N, K, 1, single), plain_g = single && turn;
     p.G = dW && !plain_g ? reinterpret_cast<uint16_t *>(base + lay.g) : nullptr;
     p.nr = nr;
     p.M = (int)M;

@@ -21,7 +21,7 @@ struct FwdSplitArgs {
     int splits;
 };
 
-template <int NR, bool HAS8, bool EP, int MB>
+template <int NR, bool HAS8, bool LAST2, bool EP, int MB>
 __global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(FwdSplitArgs s) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const FwdArgs &a = s.f;
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(Fw
         if (j % a.tiles_n == tn) rs_mask |= 1u << j;
     }
     f32x4 acc[NR][2][2 * MB];
-    fwd_main_loop<NR, HAS8, EP, MB, true>(a, smem, m0, n0, kt0, kt1 - kt0, min(a.K, kt1 * BKT), acc, rsum, rs_mask);
+    fwd_main_loop<NR, HAS8, LAST2, EP, MB, true>(a, smem, m0, n0, kt0, kt1 - kt0, min(a.K, kt1 * BKT), acc, rsum, rs_mask);
 
 #pragma unroll
     for (int j = 0; j < MB; ++j)
@@ -194,22 +194,32 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
 // ---- host side ------------------------------------------------------------------------------------
 namespace {
 
-template <int NR, bool HAS8, bool EP, int MB>
+template <int NR, bool HAS8, bool LAST2, bool EP, int MB>
 mq_status launch_split_mb(const FwdSplitArgs &s, hipStream_t st) {
-    if (!allow_lds<fwd_split_kernel<NR, HAS8, EP, MB>>(split_lds(MB))) return MQ_ERR_DEVICE;
-    fwd_split_kernel<NR, HAS8, EP, MB><<<dim3(s.f.tiles_m * s.f.tiles_n * s.splits), dim3(256), split_lds(MB), st>>>(s);
+    if (!allow_lds<fwd_split_kernel<NR, HAS8, LAST2, EP, MB>>(split_lds(MB))) return MQ_ERR_DEVICE;
+    fwd_split_kernel<NR, HAS8, LAST2, EP, MB><<<dim3(s.f.tiles_m * s.f.tiles_n * s.splits), dim3(256), split_lds(MB), st>>>(s);
     return launch_status();
+}
+
+template <int NR, bool HAS8, bool LAST2, bool EP>
+mq_status launch_split_form(const FwdSplitArgs &s, int mb, hipStream_t st) {
+    switch (mb) {
+        case 1: return launch_split_mb<NR, HAS8, LAST2, EP, 1>(s, st);
+        case 2: return launch_split_mb<NR, HAS8, LAST2, EP, 2>(s, st);
+        case 3: return launch_split_mb<NR, HAS8, LAST2, EP, 3>(s, st);
+    }
+    if constexpr (split_mb(NR) == 4) return launch_split_mb<NR, HAS8, LAST2, EP, 4>(s, st);
+    return MQ_ERR_SHAPE;  // (make_split_plan stays within split_mb)
 }
 
 template <int NR, bool HAS8, bool EP>
 mq_status launch_split(const FwdSplitArgs &s, int mb, hipStream_t st) {
-    switch (mb) {
-        case 1: return launch_split_mb<NR, HAS8, EP, 1>(s, st);
-        case 2: return launch_split_mb<NR, HAS8, EP, 2>(s, st);
-        case 3: return launch_split_mb<NR, HAS8, EP, 3>(s, st);
-    }
-    if constexpr (split_mb(NR) == 4) return launch_split_mb<NR, HAS8, EP, 4>(s, st);
-    return MQ_ERR_SHAPE;  // (make_split_plan stays within split_mb)
+    // (one bit-width only: the look-up is a chain of dependent instructions, which low tiles at several bit-widths have nothing to put
+    // between: 3440 x 1504, 20 tokens, r = 8/4/2 9.0 -> 9.6 us, 6288 x 3728, 60 tokens, 4/2 14.4 -> 15.0; 2512 x 3088, 213
+    // tokens, r = 2 15.6 -> 14.5)
+    if constexpr (NR == 1 && has_last2(NR, HAS8))
+        if (s.f.r[NR - 1] == 2) return launch_split_form<NR, HAS8, true, EP>(s, mb, st);
+    return launch_split_form<NR, HAS8, false, EP>(s, mb, st);
 }
 
 template <int NR>

@@ -21,7 +21,7 @@ static_assert(dx_lds(DX_MB) >= 32 * DX_MB * DX_OS && dx_lds(1) >= 32 * DX_OS, "t
 // stage loop is unrolled over the bit-widths so that the kind of code conversion is a compile-time
 // property of each copy of the stage body.
 //
-template <int NRS, bool HAS8, bool EP, int MB>
+template <int NRS, bool HAS8, bool LAST2, bool EP, int MB>
 __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, int m0, int k0, int nt0, int nt1, f32x4 (&acc)[2 * DX_RB][2 * MB]) {
     constexpr int RB = 2 * DX_RB;        // 16-row blocks per wave
     constexpr int A_TILE = MB * 4096;
@@ -105,7 +105,7 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
 #pragma unroll
     for (int tb = 0; tb < 2 * MB; ++tb) xf[0][tb] = *reinterpret_cast<const u32x4 *>(smem + xa[0] + tb * 2048);
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) wf[0][rb] = convert_eight<HAS8, EP>(raw[rb][0], raw[rb][1], sp[0]);
+    for (int rb = 0; rb < RB; ++rb) wf[0][rb] = convert_eight<code_kind(HAS8, LAST2 && NRS == 1), EP>(raw[rb][0], raw[rb][1], sp[0]);
 
     // One stage: two 32-wide steps, the other work in between the MFMAs as in fwd_main_loop.  st = index of this stage; the loads
     // issued in step 0 fetch stage st + 3.
@@ -118,7 +118,7 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
         static_for<2>([&](auto t_tag) {
             constexpr int t = decltype(t_tag)::value;
             constexpr int CSLOT = t == 0 ? SLOT : NEXT;       // bit-width of the operands that are converted
-            constexpr bool IS8 = HAS8 && CSLOT == 0;
+            constexpr bool IS8 = HAS8 && CSLOT == 0, IS2 = LAST2 && CSLOT == NRS - 1;
             // (the code bytes of a new n tile are read; those of its other bit-widths are at hand)
             constexpr StepSchedule<NM, RB, 2 * MB, 2 * RB, 1, IS8, t, LPS, NRS == 3 && MB >= 4, NEXT == 0 ? RB : 0, XS == 1,
                                    false, 2> plan;
@@ -137,7 +137,7 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
                     constexpr int c = plan.conv[q] + decltype(u_tag)::value, crb = plan.pair[c] / 2, half = plan.pair[c] % 2;
                     u32x4 &out = wf[1 - t][crb];
                     uint32_t lo = out[2 * half], hi = out[2 * half + 1];
-                    convert_step<IS8, EP, plan.step[c]>(t == 0 ? raw[crb][2 + half] : NEXT == 0 ? rawn[crb][half] : raw[crb][half], sp[CSLOT],
+                    convert_step<code_kind(IS8, IS2), EP, plan.step[c]>(t == 0 ? raw[crb][2 + half] : NEXT == 0 ? rawn[crb][half] : raw[crb][half], sp[CSLOT],
                                                         tmp[plan.at[c]], lo, hi);
                     if constexpr (plan.step[c] == (IS8 ? 2 : 3)) {
                         out[2 * half] = lo;
@@ -175,7 +175,7 @@ __device__ __forceinline__ void wide_main_loop(const DxArgs &a, uint8_t *smem, i
 
 // a.splits > 1: workgroup (range, tile) contracts one range of n tiles and leaves its fp32 accumulators in a.part in the
 // order its lanes hold them (each store a whole 1 KB per wave); dx_finish_kernel adds the ranges.
-template <int NRS, bool HAS8, bool EP, int MB>
+template <int NRS, bool HAS8, bool LAST2, bool EP, int MB>
 __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void dx_kernel(DxArgs a) {
     const int m0 = tm * BM, k0 = tk * DX_BK;
 
     f32x4 acc[RB][2 * MB];
-    wide_main_loop<NRS, HAS8, EP, MB>(a, smem, m0, k0, nt0, nt1, acc);
+    wide_main_loop<NRS, HAS8, LAST2, EP, MB>(a, smem, m0, k0, nt0, nt1, acc);
 
     if (a.splits > 1) {
         f32x4 *dst = reinterpret_cast<f32x4 *>(a.part) + ((size_t)split * tiles + lid) * (RB * 2 * MB * 256) + threadIdx.x;
@@ -314,7 +314,7 @@ struct FwdWideArgs {
     int gate;
 };
 
-template <bool HAS8, bool EP, int MB>
+template <bool HAS8, bool LAST2, bool EP, int MB>
 __global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
     const int m0 = tm * BM, n0 = tn * DX_BK, N = a.K;
 
     f32x4 acc[RB][2 * MB];
-    wide_main_loop<1, HAS8, EP, MB>(a, smem, m0, n0, 0, (a.N + BKT - 1) / BKT, acc);
+    wide_main_loop<1, HAS8, LAST2, EP, MB>(a, smem, m0, n0, 0, (a.N + BKT - 1) / BKT, acc);
 
     __syncthreads();  // every wave is done with the operand stages
     float rs[2 * MB];
@@ -399,39 +399,46 @@ __global__ __launch_bounds__(256) void fwd_wide_kernel(FwdWideArgs w) {
 // ---- host side ------------------------------------------------------------------------------------
 namespace {
 
-template <bool HAS8, bool EP, int MB>
+template <bool HAS8, bool LAST2, bool EP, int MB>
 mq_status launch_fwd_wide_mb(const FwdWideArgs &w, hipStream_t st) {
-    if (!allow_lds<fwd_wide_kernel<HAS8, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
-    fwd_wide_kernel<HAS8, EP, MB><<<dim3(w.d.tiles_m * w.d.tiles_k), dim3(256), dx_lds(MB), st>>>(w);
+    if (!allow_lds<fwd_wide_kernel<HAS8, LAST2, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
+    fwd_wide_kernel<HAS8, LAST2, EP, MB><<<dim3(w.d.tiles_m * w.d.tiles_k), dim3(256), dx_lds(MB), st>>>(w);
     return launch_status();
 }
 
-template <bool HAS8, bool EP>
+template <bool HAS8, bool LAST2, bool EP>
 mq_status launch_fwd_wide_one(const FwdWideArgs &w, int mb, hipStream_t st) {
     switch (mb) {
-        case 3: return launch_fwd_wide_mb<HAS8, EP, 3>(w, st);
-        case 4: return launch_fwd_wide_mb<HAS8, EP, 4>(w, st);
-        case 5: return launch_fwd_wide_mb<HAS8, EP, 5>(w, st);
-        default: return launch_fwd_wide_mb<HAS8, EP, 6>(w, st);
+        case 3: return launch_fwd_wide_mb<HAS8, LAST2, EP, 3>(w, st);
+        case 4: return launch_fwd_wide_mb<HAS8, LAST2, EP, 4>(w, st);
+        case 5: return launch_fwd_wide_mb<HAS8, LAST2, EP, 5>(w, st);
+        default: return launch_fwd_wide_mb<HAS8, LAST2, EP, 6>(w, st);
     }
 }
 
-template <int NRS, bool HAS8, bool EP, int MB>
+template <int NRS, bool HAS8, bool LAST2, bool EP, int MB>
 mq_status launch_dx_mb(const DxArgs &d, hipStream_t st) {
-    if (!allow_lds<dx_kernel<NRS, HAS8, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
-    dx_kernel<NRS, HAS8, EP, MB><<<dim3(d.tiles_m * d.tiles_k * d.splits), dim3(256), dx_lds(MB), st>>>(d);
+    if (!allow_lds<dx_kernel<NRS, HAS8, LAST2, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
+    dx_kernel<NRS, HAS8, LAST2, EP, MB><<<dim3(d.tiles_m * d.tiles_k * d.splits), dim3(256), dx_lds(MB), st>>>(d);
     return launch_status();
+}
+
+template <int NRS, bool HAS8, bool LAST2, bool EP>
+mq_status launch_dx_form(const DxArgs &d, int mb, hipStream_t st) {
+    switch (mb) {
+        case 1: return launch_dx_mb<NRS, HAS8, LAST2, EP, 1>(d, st);
+        case 2: return launch_dx_mb<NRS, HAS8, LAST2, EP, 2>(d, st);
+        case 3: return launch_dx_mb<NRS, HAS8, LAST2, EP, 3>(d, st);
+        case 4: return launch_dx_mb<NRS, HAS8, LAST2, EP, 4>(d, st);
+        default: return launch_dx_mb<NRS, HAS8, LAST2, EP, 5>(d, st);
+    }
 }
 
 template <int NRS, bool HAS8, bool EP>
 mq_status launch_dx_one(const DxArgs &d, int mb, hipStream_t st) {
-    switch (mb) {
-        case 1: return launch_dx_mb<NRS, HAS8, EP, 1>(d, st);
-        case 2: return launch_dx_mb<NRS, HAS8, EP, 2>(d, st);
-        case 3: return launch_dx_mb<NRS, HAS8, EP, 3>(d, st);
-        case 4: return launch_dx_mb<NRS, HAS8, EP, 4>(d, st);
-        default: return launch_dx_mb<NRS, HAS8, EP, 5>(d, st);
-    }
+    if constexpr (has_last2(NRS, HAS8))
+        if (d.r[NRS - 1] == 2) return launch_dx_form<NRS, HAS8, true, EP>(d, mb, st);
+    return launch_dx_form<NRS, HAS8, false, EP>(d, mb, st);
 }
 
 template <int NRS>
@@ -466,8 +473,9 @@ mq_status launch_fwd_wide(const FwdArgs &f, int mb, bool has8, bool ep, hipStrea
     w.Y = f.Y[0];
     w.A = f.A[0];
     w.gate = f.gate;
-    if (has8) return launch_fwd_wide_one<true, false>(w, mb, st);  // the code of r = 8 is never rounded up past the byte
-    return ep ? launch_fwd_wide_one<false, true>(w, mb, st) : launch_fwd_wide_one<false, false>(w, mb, st);
+    if (has8) return launch_fwd_wide_one<true, false, false>(w, mb, st);  // the code of r = 8 is never rounded up past the byte
+    if (w.d.r[0] == 2) return ep ? launch_fwd_wide_one<false, true, true>(w, mb, st) : launch_fwd_wide_one<false, true, false>(w, mb, st);
+    return ep ? launch_fwd_wide_one<false, false, true>(w, mb, st) : launch_fwd_wide_one<false, false, false>(w, mb, st);
 }
 
 mq_status launch_dx(DxArgs d, const DxPlan &plan, int nr, bool has8, bool ep, hipStream_t st) {
