@@ -91,10 +91,10 @@ size_t affine_workspace_bytes(int64_t M, int64_t N, int64_t K);
 size_t dw_each_bytes(int64_t M, int64_t N, int64_t K, int nr, bool least = false);
 mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lambda, int64_t M, int64_t N, int64_t K, int nr,
                   float *G, uint8_t *ws, size_t ws_bytes, hipStream_t st);
-// losses[i] = inv_mn * sum over the workgroups of partial[workgroup][i] (rows of 4 floats), in a
+// losses[i] = inv_mn * sum over the workgroups of partial[workgroup][slot ? slot[i] : i] (rows of 4 floats), in a
 // fixed order; one small launch on `st` (mq_loss.hip)
 mq_status launch_loss_finish(const float *partial, int64_t blocks, int nr, float inv_mn, float *losses,
-                             hipStream_t st);
+                             hipStream_t st, const int *slot = nullptr);
 
 // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  This maps the hardware
 // id to a logical id such that each XCD owns one contiguous range of logical ids, so that tiles

@@ -313,25 +313,17 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
             if (lane == 0) red[wave * 4 + i] = v;
         }
         __syncthreads();
-        if (threadIdx.x < 4) {
-            float v = 0.f;
-            if ((int)threadIdx.x < NR)
-                for (int w = 0; w < 4; ++w) v += red[w * 4 + threadIdx.x];
-            a.partial[(size_t)blockIdx.x * 4 + threadIdx.x] = v;
-        }
+        float v = 0.f;
+        if ((int)threadIdx.x < NR)
+            for (int w = 0; w < 4; ++w) v += red[w * 4 + threadIdx.x];
+        leave_sums<NR>(a, v, reinterpret_cast<double *>(smem + 1024));
     }
 }
 
-// out[i] = in[slot_i]: the losses of the fused forward, from slot order back to the caller's order
-__global__ void permute3_kernel(const float *in, float *out, int nr, int s0, int s1, int s2) {
-    if (threadIdx.x == 0 && nr > 0) out[0] = in[s0];
-    if (threadIdx.x == 1 && nr > 1) out[1] = in[s1];
-    if (threadIdx.x == 2 && nr > 2) out[2] = in[s2];
-}
-
-// sum_k X[m, k] in fp32, one wave per row
+// sum_k X[m, k] in fp32, one wave per row (and clears the counter of a forward with the objective, unless null)
 __global__ __launch_bounds__(256) void rowsum_kernel(const uint16_t *__restrict__ X, int M, int K,
-                                                     float *__restrict__ out) {
+                                                     float *__restrict__ out, uint32_t *__restrict__ arrived) {
+    if (arrived && blockIdx.x == 0 && threadIdx.x == 0) *arrived = 0u;
     const int lane = threadIdx.x & 63;
     const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
@@ -992,6 +984,7 @@ static mq_status launch_fwd_mb(FwdArgs a, hipStream_t st, int64_t *blocks) {
     a.tiles_m = (int)cdiv(a.M, 32 * MB);
     a.tiles_n = (int)cdiv(a.N, FWD_BN);
     *blocks = (int64_t)a.tiles_m * a.tiles_n;
+    if (*blocks > kLossArrivals) a.arrived = nullptr;
     if (!allow_lds<fwd_kernel<NR, HAS8, LAST2, EP, MB, LOSS>>(fwd_lds(MB, NR))) return MQ_ERR_DEVICE;
     fwd_kernel<NR, HAS8, LAST2, EP, MB, LOSS><<<dim3(a.tiles_m * a.tiles_n), dim3(256), fwd_lds(MB, NR), st>>>(a);
     return launch_status();
@@ -1027,18 +1020,18 @@ static mq_status launch_fwd_any(const FwdArgs &a, int nr, bool has8, bool ep, hi
 
 // Workspace of the forward: the tiled kernel's row sums at offset 0, the objective's partial sums (a bound over both
 // forms: the tiled kernel at its smallest token tile, 64 tokens, or the finishing kernel of the split form) and the
-// losses in slot order, and what the split form keeps.
+// counter that goes with them, and what the split form keeps.
 struct FwdWorkspace {
-    size_t loss, slots, rs_part, part, total;
+    size_t loss, counter, rs_part, part, total;
 };
 static FwdWorkspace fwd_layout(int64_t M, int64_t N, const FwdSplitPlan &plan, bool loss) {
     FwdWorkspace w;
     w.loss = align256((size_t)M * 4);
     const int64_t blocks = std::max<int64_t>(cdiv(M, 64) * cdiv(N, FWD_BN), plan.mb ? plan.loss_blocks : 0);
-    w.slots = w.loss + (loss ? (size_t)blocks * 16 : 0);
-    w.rs_part = align256(w.slots + 256);
+    w.counter = w.loss + (loss ? (size_t)blocks * 16 : 0);
+    w.rs_part = align256(w.counter + 256);
     w.part = w.rs_part + (plan.mb ? align256(plan.rs_bytes) : 0);
-    w.total = plan.mb ? w.part + plan.part_bytes : w.slots + 256;
+    w.total = plan.mb ? w.part + plan.part_bytes : w.counter + 256;
     return w;
 }
 
@@ -1162,8 +1155,12 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         a.bias = loss->bias;
         a.mix = loss->mix ? 1 : 0;
         a.partial = reinterpret_cast<float *>(base + lay.loss);
+        a.arrived = reinterpret_cast<uint32_t *>(base + lay.counter);
+        a.losses = loss->losses;
+        a.inv_mn = (float)(1.0 / mn);
         for (int i = 0; i < nr; ++i) {
             const int sl = slot_of[i];
+            a.loss_slot[i] = sl;
             a.dY[sl] = loss->dY[i];
             const int th = loss->teacher ? loss->teacher[i] : -1;
             a.teacher[sl] = th < 0 ? -1 : slot_of[th];
@@ -1177,21 +1174,13 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         s = launch_fwd_split(a, plan, nr, has8, ep, loss != nullptr, reinterpret_cast<float *>(base + lay.part),
                              reinterpret_cast<float *>(base + lay.rs_part), st, &blocks);
     } else {
-        rowsum_kernel<<<dim3((unsigned)cdiv(M, 4)), dim3(256), 0, st>>>(X, (int)M, (int)K, static_cast<float *>(ws));
+        rowsum_kernel<<<dim3((unsigned)cdiv(M, 4)), dim3(256), 0, st>>>(X, (int)M, (int)K, static_cast<float *>(ws), a.arrived);
         const int wide = nr == 1 && !loss ? fwd_wide_mb(M, N, K, nullptr) : 0;
         s = wide ? launch_fwd_wide(a, wide, has8, ep, st)
             : loss ? launch_fwd_any<true>(a, nr, has8, ep, st, &blocks) : launch_fwd_any<false>(a, nr, has8, ep, st, &blocks);
     }
-    if (s != MQ_OK || !loss) return s;
-    // the kernel's sums are in slot order: where that is not the caller's order (an r = 8 that is
-    // not first) they are finished into the tail of the workspace and permuted
-    float *slot_losses = reinterpret_cast<float *>(base + lay.slots);
-    bool same = true;
-    for (int i = 0; i < nr; ++i) same = same && slot_of[i] == i;
-    s = launch_loss_finish(a.partial, blocks, nr, (float)(1.0 / mn), same ? loss->losses : slot_losses, st);
-    if (s != MQ_OK || same) return s;
-    permute3_kernel<<<dim3(1), dim3(64), 0, st>>>(slot_losses, loss->losses, nr, slot_of[0], slot_of[1], slot_of[2]);
-    return launch_status();
+    if (s != MQ_OK || !loss || blocks <= kLossArrivals) return s;
+    return launch_loss_finish(a.partial, blocks, nr, a.inv_mn, loss->losses, st, slot_of);
 }
 
 // 16-byte chunks of zeros (a kernel, not a memset node: callers may capture the stream into a graph)

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kLossBlock) void l2_loss_kernel(LossArgs a) {
 // One workgroup, a chain of memory round trips and nothing else: four rows of partial sums per thread are in flight together
 // (one at a time and one bit-width after the other, 5824 rows took 16.7 us; now 5.5 us).
 __global__ __launch_bounds__(256) void l2_loss_finish_kernel(const float *partial, int64_t blocks, int nr, float inv_mn,
-                                                             float *losses) {
+                                                             float *losses, int s0, int s1, int s2) {
     __shared__ double red[4][3];
     double v[3] = {0.0, 0.0, 0.0};
     for (int64_t b0 = threadIdx.x; b0 < blocks; b0 += 1024) {
@@ -105,8 +105,8 @@ __global__ __launch_bounds__(256) void l2_loss_finish_kernel(const float *partia
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][i] = v[i];
     }
     __syncthreads();
-    const int i = threadIdx.x;
-    if (i < nr) losses[i] = (float)((red[0][i] + red[1][i] + red[2][i] + red[3][i]) * (double)inv_mn);
+    const int i = threadIdx.x == 0 ? s0 : threadIdx.x == 1 ? s1 : s2;
+    if ((int)threadIdx.x < nr) losses[threadIdx.x] = (float)((red[0][i] + red[1][i] + red[2][i] + red[3][i]) * (double)inv_mn);
 }
 
 inline int64_t loss_blocks(int64_t M, int64_t N) {
@@ -117,8 +117,8 @@ inline int64_t loss_blocks(int64_t M, int64_t N) {
 }  // namespace
 
 mq_status launch_loss_finish(const float *partial, int64_t blocks, int nr, float inv_mn, float *losses,
-                             hipStream_t st) {
-    l2_loss_finish_kernel<<<dim3(1), dim3(256), 0, st>>>(partial, blocks, nr, inv_mn, losses);
+                             hipStream_t st, const int *slot) {
+    l2_loss_finish_kernel<<<dim3(1), dim3(256), 0, st>>>(partial, blocks, nr, inv_mn, losses, slot ? slot[0] : 0, slot ? slot[1] : 1, slot ? slot[2] : 2);
     return launch_status();
 }
 
