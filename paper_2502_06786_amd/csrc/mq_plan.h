@@ -301,10 +301,11 @@ inline DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
 // reads, and rows far apart in memory: 18432 x 2304, 4096 tokens 286 -> 314 us, 2304 x 9216, 1999 tokens 231 -> 256), up to 40 % where a
 // row by itself is no multiple of the 128 bytes of a line (3600 x 1808, 700 tokens, three gradients 36 -> 49), of 2 M N K flops a
 // gradient at 1.4 PFLOP/s.
-// Few tokens make small copies, and dW is bound by its own size then: 4960 x 3712, 229 tokens 21 -> 23.5 us, preparation the same.
+// Few tokens make small copies, and dW is bound by its own size then: 4960 x 3712, 229 tokens 21 -> 23.5 us, preparation the same;
+// the block of 1392 and 1408 columns, 886 tokens (copies of 10 MB) 254 -> 261 us a call.
 inline bool dw_turns(int64_t M, int64_t N, int64_t K, int batch, bool alone) {
-    if (M < 768) return false;
     const double copies = (double)K + (alone ? (double)batch * N : 0.0);
+    if (M < 768 || (double)M * copies * 4.0 < 16.0 * 1048576.0) return false;
     const bool lines = K % 64 == 0 && (!alone || N % 64 == 0);
     return copies * 4.0 / 5.1e6 > (lines ? 0.1 : 0.4) * 2.0 * batch * (double)N * K / 1.4e9;
 }

@@ -6,14 +6,13 @@ import torch
 pytestmark = pytest.mark.gpu
 
 SIZES = [  # M, N, K
-    (1, 16, 48),
-    (33, 144, 272),
-    (95, 2064, 1040),
-    (257, 2304, 1152),     # rows of whole lines
-    (2049, 336, 1392),     # ranges of tokens
-    (40, 14352, 2064),     # copies
+    (33, 144, 272),        # copies
+    (2049, 336, 1392),     # copies, ranges of tokens
     (70, 7040, 7168),      # copies, 256-tiles
-    (130, 2320, 9232),     # as they stand, 256-tiles
+    (1001, 272, 9232),     # as they stand: rows of a part of a line
+    (1100, 2304, 4160),    # rows of whole lines
+    (2050, 1040, 2064),    # ranges of tokens
+    (770, 2320, 9232),     # 256-tiles
 ]
 
 
