@@ -205,6 +205,8 @@ mq_status mq_linear_fwd_multi_noalloc(const uint16_t *X, const uint8_t *Q, const
  *   dX      [M, K] bf16 out, or NULL to skip
  *   dW      [N, K] fp32 out (accumulated into with MQ_FLAG_ACCUM_DW), or NULL to skip
  *   ws      workspace of at least mq_workspace_bytes(MQ_OP_LINEAR_BWD, M, N, K, nr)
+ * dX and dW may lie over the inputs, wholly or in part (what they overlap is read or copied before it is written), but not
+ * over each other or ws.
  * K must be a multiple of 16 and N a multiple of 16.  M is free.
  * M == 0: dW (a sum over no tokens) is set to zero unless MQ_FLAG_ACCUM_DW; N == 0: dX is set to zero.
  * The bf16 rounding of lambda_i * alpha_n * dY_i (dX) and of

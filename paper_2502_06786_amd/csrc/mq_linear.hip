@@ -1420,7 +1420,8 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.zero = zero;
     p.cpart = dX ? reinterpret_cast<float *>(base + lay.cvec) : nullptr;
     // (the operand of dW is a single gradient as it stands where it is not scaled)
-    const bool single = !gated && nr == 1 && p.lam[0] == 1.0f, turn = dw_turns(M, N, K, 1, single), plain_g = single && turn;
+    const bool single = !gated && nr == 1 && p.lam[0] == 1.0f;
+    const bool turn = dW && dw_turns_in_place(M, N, K, X, single ? dY[0] : nullptr, dW), plain_g = single && turn;
     p.G = dW && !plain_g ? reinterpret_cast<uint16_t *>(base + lay.g) : nullptr;
     p.nr = nr;
     p.M = (int)M;
@@ -1439,7 +1440,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         if (s != MQ_OK) return s;
     }
 
-    // dW comes first: it reads X and possibly a gradient where they stand, and dX may take the place of either
+    // dW comes first: it reads X and possibly a gradient where they stand, and dX may lie over either
     if (dW) {
         DwArgs w{};
         w.G[0] = plain_g ? dY[0] : p.G;

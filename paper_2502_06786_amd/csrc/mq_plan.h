@@ -310,6 +310,20 @@ inline bool dw_turns(int64_t M, int64_t N, int64_t K, int batch, bool alone) {
     return copies * 4.0 / 5.1e6 > (lines ? 0.1 : 0.4) * 2.0 * batch * (double)N * K / 1.4e9;
 }
 
+// Whether two pieces of memory share a byte.
+inline bool bytes_meet(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa < pb + b_bytes && pb < pa + a_bytes;
+}
+
+// The same for a backward, whose dW may lie over an input: X, and the gradient if it is the operand as it stands (dY; otherwise null), are
+// then copied first, since workgroups still read them while others store their part of dW.
+inline bool dw_turns_in_place(int64_t M, int64_t N, int64_t K, const void *X, const void *dY, const void *dW) {
+    const size_t dw_bytes = (size_t)N * K * 4;
+    if (bytes_meet(dW, dw_bytes, X, (size_t)M * K * 2) || (dY && bytes_meet(dW, dw_bytes, dY, (size_t)M * N * 2))) return false;
+    return dw_turns(M, N, K, 1, dY != nullptr);
+}
+
 constexpr int GEMV_TILE = 2048;                  // decode: 16 rows x one 128-byte line
 
 // ============================================================================================

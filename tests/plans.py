@@ -26,6 +26,9 @@ extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out
     const DwPlan p = make_dw_plan(M, N, K, batch);
     out[0] = p.hb, out[1] = p.whole, out[2] = p.rest, out[3] = p.parts;
 }
+extern "C" int plan_dw_in_place(int64_t M, int64_t N, int64_t K, int64_t X, int64_t dY, int64_t dW) {
+    return dw_turns_in_place(M, N, K, (const void *)X, (const void *)dY, (const void *)dW);
+}
 extern "C" void plan_quad(int64_t B, int64_t N, int64_t K, int r, int list, int64_t *out) {
     const QuadPlan p = make_quad_plan(B, N, K, K * r / 8, r, list);
     out[0] = p.depth > 0 ? p.ks * p.rw : 0, out[1] = p.nl, out[2] = p.list_waves, out[3] = p.shared;
@@ -64,6 +67,7 @@ def _lib():
     for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw, lib.plan_gemv, lib.plan_gemv_split):
         f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
         f.restype = None
+    lib.plan_dw_in_place.argtypes = [ctypes.c_int64] * 6
     lib.plan_quad.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int64)]
     lib.plan_quad.restype = None
     return lib
@@ -89,6 +93,11 @@ def dx(M, N, K, nr):
 def dw(M, N, K, gradients=1):
     hb, whole, rest, parts = _ask("plan_dw", M, N, K, gradients)
     return Dw(64 * hb, whole, rest, parts)
+
+
+def dw_in_place(M, N, K, X, dY, dW):
+    """Whether the dW of a backward reads its operands as they stand; addresses, dY None where the gradient is summed or scaled."""
+    return bool(_lib().plan_dw_in_place(M, N, K, X, dY or 0, dW))
 
 
 def quad(B, N, K, r, with_list=False):

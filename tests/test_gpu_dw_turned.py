@@ -45,3 +45,26 @@ def test_exact(mq, M, N, K, nr, lam):
     mine = X.clone()
     mq.mq_linear_bwd(mine, Q, one, one, dY, lam, (4, 2)[:nr], dX=mine, dW=dW)
     assert torch.equal(mine, dX) and torch.equal(dW, want) and torch.equal(dW2, want)
+
+
+OVER = (1100, 2304, 4160)   # takes operands as they stand
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("nr", [1, 2])
+@pytest.mark.parametrize("what", ["X", "dY"])
+@pytest.mark.parametrize("first", [0, 2304 * 4160 * 2 - 8])   # from the first element of dW, over its last 16 bytes
+def test_dW_over_an_input(mq, what, first, nr, accumulate):
+    M, N, K = OVER
+    X, dY = _ints(M, M, K), [_ints(7 + i, M, N) for i in range(nr)]
+    Q, one = torch.zeros(N, K, dtype=torch.uint8, device="cuda"), torch.ones(N, device="cuda")
+    room = torch.zeros(N * K + M * K, device="cuda")
+    dW = room[:N * K].view(N, K)
+    place = lambda t: room.view(torch.bfloat16)[first:first + t.numel()].view(t.shape).copy_(t)
+    inputs = (place(X), dY) if what == "X" else (X, [place(dY[0])] + dY[1:])
+    before = dW.clone()   # (with accumulation the bits of the input are what is added to)
+    want_dX, want = mq.mq_linear_bwd(X, Q, one, one, dY, None, (4, 2)[:nr], dW=before, accumulate_dW=accumulate)
+    dX, _ = mq.mq_linear_bwd(inputs[0], Q, one, one, inputs[1], None, (4, 2)[:nr], dW=dW, accumulate_dW=accumulate)
+    assert torch.equal(dW, want) and torch.equal(dX, want_dX)
+    if not accumulate:
+        assert torch.equal(dW, sum(d.float() for d in dY).t().contiguous() @ X.float())

@@ -1,7 +1,7 @@
 """Rules on sizes (no GPU): what the launches that follow from them rely on."""
 import pytest
 
-from tests import (plans, test_gpu_dw_tiles, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide,
+from tests import (plans, test_gpu_dw_tiles, test_gpu_dw_turned, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide,
                    test_gpu_gemv_list, test_gpu_gemv_registers, test_gpu_gemv_split_ring)
 
 cdiv = lambda a, b: -(-a // b)
@@ -93,6 +93,20 @@ def test_dw_sizes():
         (128, False, True), (256, True, False), (256, False, True), (256, True, True)]
     for M, N, K, rs in test_gpu_dw_tiles.CLIP_CASES:
         assert N % plans.dw(M, N, K, len(rs)).side and K % plans.dw(M, N, K, len(rs)).side
+
+
+def test_dw_over_an_input_is_from_copies():
+    """While dW is stored, workgroups still read operands that are taken as they stand: X and a gradient that dW meets are copied."""
+    M, N, K = test_gpu_dw_turned.OVER
+    X, dY, dW = 1 << 40, 2 << 40, 3 << 40
+    for grad in (dY, None):
+        assert plans.dw_in_place(M, N, K, X, grad, dW)
+        # next to each other is apart
+        assert plans.dw_in_place(M, N, K, X, grad, X + M * K * 2) and plans.dw_in_place(M, N, K, X, grad, X - N * K * 4)
+        assert not any(plans.dw_in_place(M, N, K, X, grad, X + d) for d in (0, 16, M * K * 2 - 16, 16 - N * K * 4))
+    assert plans.dw_in_place(M, N, K, X, dY, dY + M * N * 2) and plans.dw_in_place(M, N, K, X, dY, dY - N * K * 4)
+    assert not any(plans.dw_in_place(M, N, K, X, dY, dY + d) for d in (0, 16, M * N * 2 - 16, 16 - N * K * 4))
+    assert plans.dw_in_place(M, N, K, X, None, dY)   # summed or scaled: the preparation has read it
 
 
 def test_split_decode_sizes():
