@@ -88,8 +88,9 @@ __device__ __forceinline__ int group_chunk(int g4) { return (0x9C >> (2 * g4)) &
 // the compiler lets a transposing read wait for all direct-to-LDS loads that it has seen, those of the stages that are to
 // stay on their way too (stage_barrier waits for the right ones).  It writes no register but m0, which nothing else uses in a kernel
 // that loads its tiles with it alone (the compiler refuses it in the list of clobbered registers).  One wait state covers m0.  A
-// descriptor is fixed by scalar_rsrc(), in case the compiler gets it there with vector instructions (five wait states to a load that
-// reads it), which stand in load_to_lds; a schedule that uses the pieces keeps five instructions between descriptor and load.
+// descriptor is fixed by scalar_rsrc(), in case the compiler gets it there with vector instructions (kDescriptorWait wait states to a
+// load that reads it): they stand in load_to_lds; a schedule that uses the pieces counts the instructions between descriptor and load.
+constexpr int kDescriptorWait = 5;
 __device__ __forceinline__ u32x4 scalar_rsrc(const void *base, int bytes) {
     const uint64_t p = reinterpret_cast<uint64_t>(base);
     u32x4 rsrc = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32)) & 0xFFFFu,

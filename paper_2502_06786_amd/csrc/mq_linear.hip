@@ -784,7 +784,12 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         const int ib = cb == 0 ? DW_NST - 1 : cb - 1;   // buffer of the stage NST - 1 further on (= the one of the stage before)
         const uint8_t *cur = smem + cb * DW_STAGE, *nxt = smem + nb * DW_STAGE;
         const uint32_t fill = lds0 + ib * DW_STAGE;
-        if constexpr (MORE) next_stage();
+        // products from one load to the next; instructions between the descriptors and the first load that reads one: products, reads, aim
+        constexpr int EVERY = NM / 2 / LPS, READS = std::min(EVERY, RB), BETWEEN = EVERY + (TURN ? READS : (READS + 1) / 2) + 1;
+        if constexpr (MORE) {
+            next_stage();
+            if constexpr (BETWEEN < kDescriptorWait) asm volatile("s_nop %0" ::"n"(std::max(kDescriptorWait - 1 - BETWEEN, 0)));
+        }
         __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto q_tag) {
             constexpr int q = decltype(q_tag)::value, H = NM / 2, HJ = RB / 2;
@@ -793,7 +798,7 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
             // one read, and one instruction of a load, behind a product
             if constexpr (half == 0) {
                 if constexpr (q < 2 * HJ) read_half(xf[HJ + q / 2], cur, xb, std::integral_constant<int, HJ + q / 2>{}, std::integral_constant<int, q % 2>{});
-                constexpr int EVERY = H / LPS, l = q / EVERY;   // (three instructions at least between next_stage and the first aim)
+                constexpr int l = q / EVERY;
                 static_assert(EVERY >= 2 && H % LPS == 0, "a product between the two pieces of a load");
                 if constexpr (MORE && q % EVERY == EVERY - 2) aim_load_to_lds<l < AL ? l * 4096 : DW_A_TILE + (l - AL) * 4096>(fill);
                 if constexpr (MORE && q % EVERY == EVERY - 1) aimed_load_to_lds(l < AL ? g_rsrc : x_rsrc, l < AL ? goff[l < AL ? l : 0] : xoff[l < AL ? 0 : l - AL]);

@@ -1,8 +1,10 @@
-"""The waits around the matrix products that are written as inline assembly (csrc/mq_linear.h), in the compiled library.
+"""The waits around the matrix products and the direct-to-LDS loads that are written as inline assembly (csrc/mq_linear.h), in the
+compiled library.
 
 The compiler does not see those products and places no waits for them.  The rules it keeps for its own: an operand that a vector
 instruction has written is read two wait states later at the earliest, a result of the 16x16x32 product is read or written by
-anything but the next product into it eight wait states later at the earliest.  Every path through the kernels is followed for that
+anything but the next product into it eight wait states later at the earliest.  A scalar register that a vector instruction has
+written is read by a load or store five wait states later at the earliest, m0 by a direct-to-LDS load one.  Every path through the kernels is followed for that
 long, over branches and the ends of loops."""
 import os
 import re
@@ -15,13 +17,13 @@ from paper_2502_06786_amd import build as mq_build
 
 OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
 KERNELS = re.compile(r"_ZN2mq\d+(fwd_kernel|fwd_split_kernel|fwd_wide_kernel|dx_kernel|dw_kernel)I")
-OPERAND_WAIT, RESULT_WAIT = 2, 8
+OPERAND_WAIT, RESULT_WAIT, DESCRIPTOR_WAIT, M0_WAIT = 2, 8, 5, 1
 PRODUCT = "v_mfma_f32_16x16x32_bf16"
 
 
-def _registers(text):
+def _registers(text, kinds="va"):
     out = set()
-    for kind, one, lo, hi in re.findall(r"(?<![\w.])([va])(?:(\d+)|\[(\d+):(\d+)\])(?!\w)", text):
+    for kind, one, lo, hi in re.findall(rf"(?<![\w.])([{kinds}])(?:(\d+)|\[(\d+):(\d+)\])(?!\w)", text):
         out.update((kind, i) for i in (range(int(lo), int(hi) + 1) if lo else [int(one)]))
     return out
 
@@ -61,6 +63,9 @@ def parse(lines):
 def violations(code):
     found = []
 
+    def memory(other):
+        return other[0].startswith(("buffer_", "global_", "flat_", "scratch_"))
+
     def follow(i, regs, wait, bad):
         seen, stack = {}, [(f, wait) for f in code[i][5]]
         while stack:
@@ -83,6 +88,12 @@ def violations(code):
             follow(i, written, RESULT_WAIT, bad)
         elif text.startswith("v_") and written:
             follow(i, written, OPERAND_WAIT, lambda other, regs: other[4] and bool(regs & other[2]))
+        op, _, args = text.partition(" ")
+        scalars = _registers(args.split(",")[0], "s") if op.startswith("v_") else set()
+        if scalars:
+            follow(i, scalars, DESCRIPTOR_WAIT, lambda other, regs: memory(other) and bool(regs & _registers(other[0], "s")))
+        if op.startswith("s_") and args.split(",")[0].strip() == "m0":
+            follow(i, {"m0"}, M0_WAIT, lambda other, regs: memory(other) and other[0].endswith(" lds"))
     return found
 
 
@@ -101,6 +112,14 @@ def test_the_scan_sees_what_it_looks_for():
     assert len(violations(code(p, "s_nop 6", "v_accvgpr_read_b32 v9, a3", "s_endpgm"))) == 1
     assert not violations(code(p, "s_nop 7", "global_store_dwordx4 v[12:13], a[0:3], off", "s_endpgm"))
     assert len(violations(code(p, "s_nop 6", "global_store_dwordx4 v[12:13], a[0:3], off", "s_endpgm"))) == 1
+    # descriptors and m0
+    load = "buffer_load_dwordx4 v5, s[8:11], 0 offen lds"
+    assert len(violations(code("v_readfirstlane_b32 s9, v1", "s_nop 3", load, "s_endpgm"))) == 1
+    assert not violations(code("v_readfirstlane_b32 s9, v1", "s_nop 4", load, "s_endpgm"))
+    assert not violations(code("v_readfirstlane_b32 s12, v1", load, "s_endpgm"))
+    assert len(violations(code("v_readfirstlane_b32 s8, v1", p, "s_mov_b32 s3, s4", q, "s_nop 0", load, "s_endpgm"))) == 1
+    assert len(violations(code("s_add_u32 m0, s4, 0x1000", load, "s_endpgm"))) == 1
+    assert not violations(code("s_add_u32 m0, s4, 0x1000", p, load, "s_endpgm"))
     # around the end of a loop: the write is the last instruction but one, the product the first
     assert len(violations(code("s_nop 7", p, "s_nop 7", "v_add_u32 v1, v1, v2", "s_cbranch_scc1 65532 @0x4", "s_endpgm"))) == 1
     assert not violations(code("s_nop 7", p, "s_nop 7", "v_add_u32 v1, v1, v2", "s_cbranch_scc1 65531 @0x0", "s_endpgm"))
@@ -113,7 +132,7 @@ def test_products_of_the_library(tmp_path):
         pytest.skip("no llvm-objdump")
     shutil.copy(mq_build.LIB, tmp_path / "lib.so")
     subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
-    kernels = products = 0
+    kernels = products = loads = 0
     for name in sorted(os.listdir(tmp_path)):
         if "gfx950" not in name:
             continue
@@ -125,5 +144,6 @@ def test_products_of_the_library(tmp_path):
             code = parse(part.split("\n")[1:])
             kernels += 1
             products += sum(c[4] for c in code)
+            loads += sum(c[0].endswith(" lds") for c in code)
             assert not violations(code), (m.group(1), violations(code)[:3])
-    assert kernels > 100 and products > 5000
+    assert kernels > 100 and products > 5000 and loads > 500
