@@ -1314,7 +1314,7 @@ mq_status dw_each(const uint16_t *X, const uint16_t *const *dY, const float *lam
         scaled = scaled || (lambda && lambda[i] != 1.0f);
         w.G[i] = dY[i];
     }
-    const bool turn = dw_turns(M, N, K, nr, !scaled);
+    const bool turn = dw_turns(M, N, K, nr, !scaled, scaled, cut.hb);
     w.in_pieces = scaled;
     w.X = X;
     if (scaled || !turn) {  // otherwise the operands are taken as they stand
@@ -1426,7 +1426,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.cpart = dX ? reinterpret_cast<float *>(base + lay.cvec) : nullptr;
     // (the operand of dW is a single gradient as it stands where it is not scaled)
     const bool single = !gated && nr == 1 && p.lam[0] == 1.0f;
-    const bool turn = dW && dw_turns_in_place(M, N, K, X, single ? dY[0] : nullptr, dW), plain_g = single && turn;
+    const bool turn = dW && dw_turns_in_place(M, N, K, X, single ? dY[0] : nullptr, dW, dX || !single, dw_cut.hb), plain_g = single && turn;
     p.G = dW && !plain_g ? reinterpret_cast<uint16_t *>(base + lay.g) : nullptr;
     p.nr = nr;
     p.M = (int)M;

@@ -295,19 +295,27 @@ inline DwPlan dw_plan_whole(int64_t N, int64_t K, int batch) {
     return DwPlan{4, tiles_n, tiles_k, tiles_n * tiles_k * batch, 0, 1, 0};
 }
 
-// Whether dW takes its operands by rows of tokens and lets the LDS turn them (dw_kernel's TURN), or transposed copies that the
-// preparation makes of them.  The copies are 4 bytes per element of X, and of the gradients if they could be taken as they stand
-// (alone: not scaled or summed), written and read back at about 5 TB/s; without them the kernel is about 10 % slower (twice as many LDS
-// reads, and rows far apart in memory: 18432 x 2304, 4096 tokens 286 -> 314 us, 2304 x 9216, 1999 tokens 231 -> 256), up to 40 % where a
-// row by itself is no multiple of the 128 bytes of a line (3600 x 1808, 700 tokens, three gradients 36 -> 49), of 2 M N K flops a
-// gradient at 1.4 PFLOP/s.
-// Few tokens make small copies, and dW is bound by its own size then: 4960 x 3712, 229 tokens 21 -> 23.5 us, preparation the same;
-// the block of 1392 and 1408 columns, 886 tokens (copies of 10 MB) 254 -> 261 us a call.
-inline bool dw_turns(int64_t M, int64_t N, int64_t K, int batch, bool alone) {
-    const double copies = (double)K + (alone ? (double)batch * N : 0.0);
-    if (M < 768 || (double)M * copies * 4.0 < 16.0 * 1048576.0) return false;
+// Whether dW takes its operands by rows of tokens and lets the LDS turn them (dw_kernel's TURN), or transposed copies that a preparation
+// makes of them.  The copies are 4 bytes per element of X, and of the gradients if they could be taken as they stand (alone: not scaled or
+// summed), written and read back at 5.1 TB/s.  Without them the kernel reads the LDS twice as often and rows far apart in memory:
+// 10 to 20 % longer on 256-tiles (18432 x 2304, 4096 tokens 286 -> 314 us, 2304 x 9216, 1999 tokens 231 -> 256), 30 to 70 % on
+// 128-tiles (hb = 2), up to 40 % where a row by itself is no multiple of the 128 bytes of a line (3600 x 1808, 700 tokens, three
+// gradients 36 -> 49); of 2 M N K flops a gradient at 1.4 PFLOP/s.  The preparation is a launch of its own, 4 us, unless it runs anyhow (prep:
+// operands of dX, a summed or scaled gradient); beside its other work the copies cost less than their bytes.
+//
+// Whole calls at 1671 pairs of times (700 sizes of 512 to 14336 rows and columns, 90 to 8192 tokens; backward with and without dX, clip
+// gradients): where operands are taken as they stand a call is 0.887 times as long on average, longer by more than 0.5 % at three
+// sizes (2034 tokens through 2560 x 4096 103.6 -> 105.4 us).  128-tiles with a preparation were up to 13 % slower in a backward (59 of 100
+// sizes by more than 1 %), 19 % without dX (2816 x 1408, 8192 tokens, one scaled gradient 85 -> 99 us).
+// Few tokens make small copies: 4960 x 3712, 229 tokens 21 -> 23.5 us, preparation the same; the block of 1392 and 1408 columns, 886
+// tokens (copies of 10 MB) 254 -> 261 us a call.  (A single gradient without dX would gain below these limits too.)
+inline bool dw_turns(int64_t M, int64_t N, int64_t K, int batch, bool alone, bool prep, int hb) {
+    const double columns = (double)K + (alone ? (double)batch * N : 0.0);
+    if (M < 768 || (double)M * columns * 4.0 < 16.0 * 1048576.0) return false;
+    const double copies = columns * 4.0 / 5.1e6, products = 2.0 * batch * (double)N * K / 1.4e9;   // us per token
+    if (hb == 2) return !prep && M * copies + 4.0 > 0.7 * M * products;
     const bool lines = K % 64 == 0 && (!alone || N % 64 == 0);
-    return copies * 4.0 / 5.1e6 > (lines ? 0.1 : 0.4) * 2.0 * batch * (double)N * K / 1.4e9;
+    return copies > (!lines ? 0.4 : prep ? 0.22 : 0.13) * products;
 }
 
 // Whether two pieces of memory share a byte.
@@ -318,10 +326,10 @@ inline bool bytes_meet(const void *a, size_t a_bytes, const void *b, size_t b_by
 
 // The same for a backward, whose dW may lie over an input: X, and the gradient if it is the operand as it stands (dY; otherwise null), are
 // then copied first, since workgroups still read them while others store their part of dW.
-inline bool dw_turns_in_place(int64_t M, int64_t N, int64_t K, const void *X, const void *dY, const void *dW) {
+inline bool dw_turns_in_place(int64_t M, int64_t N, int64_t K, const void *X, const void *dY, const void *dW, bool prep, int hb) {
     const size_t dw_bytes = (size_t)N * K * 4;
     if (bytes_meet(dW, dw_bytes, X, (size_t)M * K * 2) || (dY && bytes_meet(dW, dw_bytes, dY, (size_t)M * N * 2))) return false;
-    return dw_turns(M, N, K, 1, dY != nullptr);
+    return dw_turns(M, N, K, 1, dY != nullptr, prep, hb);
 }
 
 constexpr int GEMV_TILE = 2048;                  // decode: 16 rows x one 128-byte line

@@ -26,8 +26,11 @@ extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out
     const DwPlan p = make_dw_plan(M, N, K, batch);
     out[0] = p.hb, out[1] = p.whole, out[2] = p.rest, out[3] = p.parts;
 }
+extern "C" int plan_dw_turns(int64_t M, int64_t N, int64_t K, int batch, int alone, int prep) {
+    return dw_turns(M, N, K, batch, alone, prep, make_dw_plan(M, N, K, batch).hb);
+}
 extern "C" int plan_dw_in_place(int64_t M, int64_t N, int64_t K, int64_t X, int64_t dY, int64_t dW) {
-    return dw_turns_in_place(M, N, K, (const void *)X, (const void *)dY, (const void *)dW);
+    return dw_turns_in_place(M, N, K, (const void *)X, (const void *)dY, (const void *)dW, true, make_dw_plan(M, N, K, 1).hb);
 }
 extern "C" void plan_quad(int64_t B, int64_t N, int64_t K, int r, int list, int64_t *out) {
     const QuadPlan p = make_quad_plan(B, N, K, K * r / 8, r, list);
@@ -68,6 +71,7 @@ def _lib():
         f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
         f.restype = None
     lib.plan_dw_in_place.argtypes = [ctypes.c_int64] * 6
+    lib.plan_dw_turns.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
     lib.plan_quad.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int64)]
     lib.plan_quad.restype = None
     return lib
@@ -95,8 +99,13 @@ def dw(M, N, K, gradients=1):
     return Dw(64 * hb, whole, rest, parts)
 
 
+def dw_turns(M, N, K, gradients=1, alone=True, prep=True):
+    """Whether dW takes its operands as they stand; alone: gradients neither summed nor scaled, prep: a preparation runs anyhow."""
+    return bool(_lib().plan_dw_turns(M, N, K, gradients, alone, prep))
+
+
 def dw_in_place(M, N, K, X, dY, dW):
-    """Whether the dW of a backward reads its operands as they stand; addresses, dY None where the gradient is summed or scaled."""
+    """Whether the dW of a backward with dX reads its operands as they stand; addresses, dY None where the gradient is summed or scaled."""
     return bool(_lib().plan_dw_in_place(M, N, K, X, dY or 0, dW))
 
 

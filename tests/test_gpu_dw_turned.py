@@ -1,18 +1,26 @@
 """dW by operands as they stand, turned by the LDS, and by transposed copies (dw_turns in csrc/mq_plan.h): small integers, so that every sum
-is exact in fp32 whatever its order.  Columns that end inside a group of 64, tokens that end inside a block of 32, either tile."""
+is exact in fp32 whatever its order.  Columns that end inside a group of 64 and inside a tile, tokens that end inside a block of 32,
+either tile, whole and in ranges of tokens.  (test_plans.py checks that the sizes take the forms that they are here for.)"""
 import pytest
 import torch
+
+from tests.util import bf16_bits, rel_l2
 
 pytestmark = pytest.mark.gpu
 
 SIZES = [  # M, N, K
     (33, 144, 272),        # copies
-    (2049, 336, 1392),     # copies, ranges of tokens
-    (70, 7040, 7168),      # copies, 256-tiles
-    (1001, 272, 9232),     # as they stand: rows of a part of a line
+    (840, 224, 288),
+    (1041, 160, 304),      # in ranges
+    (1028, 2160, 3872),    # 256-tiles
+    (1200, 1712, 9424),    # 256-tiles, the last ones in ranges
+    (1194, 3376, 160),     # as it stands: a single gradient without dX
+    (3329, 160, 1120),     # in ranges
+    (1391, 1456, 11168),   # 256-tiles, the last ones in ranges; with dX too
+    (1040, 1040, 7264),    # 256-tiles; a summed or scaled gradient in pieces
+    (2987, 1232, 3248),    # in ranges
     (1100, 2304, 4160),    # rows of whole lines
-    (2050, 1040, 2064),    # ranges of tokens
-    (770, 2320, 9232),     # 256-tiles
+    (1286, 2288, 7360),    # of one operand only, in pieces; the last ones in ranges
 ]
 
 
@@ -40,11 +48,48 @@ def test_exact(mq, M, N, K, nr, lam):
     want = total.t().contiguous() @ X.float()
     _, dW = mq.mq_linear_bwd(X, Q, one, one, dY, lam, (4, 2)[:nr], need_dX=False)
     assert torch.equal(dW, want)
-    # dX in the place of X, and of the only gradient where the shapes agree: both are read before it is written
+    # dX in the place of X, which is read before
     dX, dW2 = mq.mq_linear_bwd(X.clone(), Q, one, one, dY, lam, (4, 2)[:nr])
     mine = X.clone()
     mq.mq_linear_bwd(mine, Q, one, one, dY, lam, (4, 2)[:nr], dX=mine, dW=dW)
     assert torch.equal(mine, dX) and torch.equal(dW, want) and torch.equal(dW2, want)
+
+
+SQUARE = (1201, 2880)   # tokens, rows and columns
+
+
+def test_dX_over_the_gradient(mq):
+    M, N = SQUARE
+    X, dY = _ints(M, M, N), _ints(7, M, N)
+    Q, one = torch.zeros(N, N, dtype=torch.uint8, device="cuda"), torch.ones(N, device="cuda")
+    want_dX, want = mq.mq_linear_bwd(X, Q, one, one, [dY], None, (4,))
+    assert torch.equal(want, dY.float().t().contiguous() @ X.float())
+    mine = dY.clone()
+    _, dW = mq.mq_linear_bwd(X, Q, one, one, [mine], None, (4,), dX=mine)
+    assert torch.equal(dW, want) and torch.equal(mine, want_dX)
+
+
+CLIP_SIZES = [  # M, N, K: three gradients, one contraction each
+    (1115, 1200, 224),
+    (1767, 1056, 160),     # in ranges
+    (1050, 272, 7280),     # 256-tiles; scaled gradients in pieces
+    (3369, 160, 5520),     # in ranges
+]
+
+
+@pytest.mark.parametrize("lam", [None, (0.3, 0.5, 1.0)])
+@pytest.mark.parametrize("M,N,K", CLIP_SIZES)
+def test_several_gradients(mq, oracle, M, N, K, lam):
+    g = torch.Generator().manual_seed(M)
+    randn = lambda *shape, scale=1.0: torch.randn(*shape, generator=g) * scale
+    W, X, dY = randn(N, K, scale=0.02), randn(M, K).to(torch.bfloat16), [randn(M, N, scale=1e-2).to(torch.bfloat16) for _ in range(3)]
+    gamma, beta = torch.rand(N, generator=g) * 0.4 + 0.5, torch.rand(N, generator=g) * 0.4 + 0.5
+    Q, a, z = mq.mq_quantize_int8(W.cuda(), gamma.cuda(), beta.cuda())
+    got = mq.mq_linear_bwd_clip(W.cuda(), X.cuda(), Q, a, z, [d.cuda() for d in dY], lam, (8, 4, 2), gamma.cuda(), beta.cuda(), want_dalpha_dzero=True)
+    want = oracle.clip_factor_grads(W.numpy(), bf16_bits(X), [bf16_bits(d) for d in dY], lam or (1.0,) * 3, (8, 4, 2), gamma.numpy(), beta.numpy())
+    for name, mine, ref in zip(("dgamma", "dbeta", "dalpha", "dzero"), got, want):
+        # scaled operands are rounded to bf16 once (2^-9.5 rms each), the fp32 sums add next to nothing
+        assert rel_l2(mine.cpu().numpy(), ref) <= 1e-2, name
 
 
 OVER = (1100, 2304, 4160)   # takes operands as they stand

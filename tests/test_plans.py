@@ -95,6 +95,27 @@ def test_dw_sizes():
         assert N % plans.dw(M, N, K, len(rs)).side and K % plans.dw(M, N, K, len(rs)).side
 
 
+def test_dw_turned_sizes():
+    def form(M, N, K, n=1):
+        p = plans.dw(M, N, K, n)
+        alone, prep = [plans.dw_turns(M, N, K, n, True, p_) for p_ in (False, True)], plans.dw_turns(M, N, K, n, False, True)
+        return p.side, p.whole > 0, p.cut > 0, *alone, prep
+
+    # side, whole tiles, tiles in ranges; as they stand: one gradient without dX, with dX, a summed or scaled one (in pieces)
+    seen = {form(*size) for size in test_gpu_dw_turned.SIZES}
+    assert seen == {(128, True, False, False, False, False), (128, False, True, False, False, False),
+                    (128, True, False, True, False, False), (128, False, True, True, False, False),
+                    (256, True, False, False, False, False), (256, True, True, False, False, False),
+                    (256, True, True, True, True, False), (256, True, False, True, True, True),
+                    (256, False, True, True, True, True), (256, True, True, False, False, True)}
+    ragged = {form(M, N, K) for M, N, K in test_gpu_dw_turned.SIZES if N % 64 and K % 64 and M % 32}
+    assert seen - ragged == {(256, True, True, False, False, True)}
+    assert [form(*size, 3)[:4] + form(*size, 3)[5:] for size in test_gpu_dw_turned.CLIP_SIZES] == [
+        (128, True, False, True, False), (128, False, True, True, False), (256, True, False, True, True), (256, False, True, True, True)]
+    M, N = test_gpu_dw_turned.SQUARE
+    assert plans.dw_turns(M, N, N, 1, True, True)
+
+
 def test_dw_over_an_input_is_from_copies():
     """While dW is stored, workgroups still read operands that are taken as they stand: X and a gradient that dW meets are copied."""
     M, N, K = test_gpu_dw_turned.OVER
