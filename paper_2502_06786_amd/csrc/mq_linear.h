@@ -494,54 +494,38 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
     wait_vm0();  // zero-fill loads of dead stages must not land in the staging area below
 }
 
-// Ends a workgroup of a kernel that evaluates the objective: its sums (`v` of slot t in thread t < 4) go to a.partial.  With a counter,
-// the workgroup that finds all others arrived adds them, in the order of the workgroups whichever it is, and writes the losses: a launch
-// less, 2 to 4 us of one workgroup and its call (16 tokens, 256 x 256, a training step 50 -> 45 us; 370 tokens, 3312 x 2608 120.7 -> 119.1).
-// Nobody waits for anybody.  The sums and the counter are written and read past the caches that XCDs do not share (agent scope);
-// the sums are there before the counter counts them because the wave waits for its stores in between.  In large grids that wait, which
-// a workgroup that just ends does not make, costs every round of them more than the launch (kLossArrivals).
-// red: 128 bytes of LDS, aligned to 8, that nobody else uses any more.
-constexpr int64_t kLossArrivals = 512;
+// Ends a workgroup of a kernel that evaluates the objective: its sums (`v` of slot t in thread t < 4) go to a.partial.  With a counter
+// (kLossArrivals), the workgroup that finds all others arrived adds them, in the order of the workgroups whichever it is, and writes the
+// losses.  Nobody waits for anybody.  The sums and the counter are written and read past the caches that XCDs do not share (agent scope);
+// the sums are there before the counter counts them because the wave waits for its stores in between.
 template <int NR>
-__device__ __forceinline__ void leave_sums(const FwdArgs &a, float v, double *red) {
-    uint32_t *last = reinterpret_cast<uint32_t *>(red + 12);
+__device__ __forceinline__ void leave_sums(const FwdArgs &a, float v) {
+    static_assert(kLossArrivals <= 64, "one wave adds the sums, a workgroup's in a lane");
+    if (threadIdx.x >= 64) return;
     if (!a.arrived) {
         if (threadIdx.x < 4) a.partial[(size_t)blockIdx.x * 4 + threadIdx.x] = v;
         return;
     }
-    if (threadIdx.x < 64) {
-        if (threadIdx.x < 4)
-            __hip_atomic_store(a.partial + (size_t)blockIdx.x * 4 + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_vm0();
-        if (threadIdx.x == 0) *last = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!*last) return;
+    if (threadIdx.x < 4) __hip_atomic_store(a.partial + (size_t)blockIdx.x * 4 + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_vm0();
+    uint32_t before = 0;
+    if (threadIdx.x == 0) before = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) != gridDim.x - 1) return;
+    wait_vm0();   // (nothing below is loaded before the count is known)
     double sum[NR];
 #pragma unroll
-    for (int i = 0; i < NR; ++i) sum[i] = 0.0;
-    for (uint32_t b0 = threadIdx.x; b0 < gridDim.x; b0 += 1024) {  // four rows per thread in flight together
-        float x[4][NR];
+    for (int i = 0; i < NR; ++i)
+        sum[i] = threadIdx.x < gridDim.x ? (double)__hip_atomic_load(a.partial + (size_t)threadIdx.x * 4 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int i = 0; i < NR; ++i)
-                x[u][i] = b0 + u * 256 < gridDim.x ? __hip_atomic_load(a.partial + (size_t)(b0 + u * 256) * 4 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int i = 0; i < NR; ++i) sum[i] += (double)x[u][i];
-    }
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) sum[i] += __shfl_xor(sum[i], o, 64);
-        if ((threadIdx.x & 63) == 0) red[(threadIdx.x >> 6) * 3 + i] = sum[i];
-    }
-    __syncthreads();
     if ((int)threadIdx.x < NR) {
-        const int sl = threadIdx.x == 0 ? a.loss_slot[0] : threadIdx.x == 1 ? a.loss_slot[1] : a.loss_slot[2];
-        a.losses[threadIdx.x] = (float)((red[sl] + red[3 + sl] + red[6 + sl] + red[9 + sl]) * (double)a.inv_mn);
+        const int slot = threadIdx.x == 0 ? a.loss_slot[0] : threadIdx.x == 1 ? a.loss_slot[1] : a.loss_slot[2];
+        double mine = sum[0];
+#pragma unroll
+        for (int i = 1; i < NR; ++i) mine = slot == i ? sum[i] : mine;
+        a.losses[threadIdx.x] = (float)(mine * (double)a.inv_mn);
     }
 }
 

@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
         float v = 0.f;
         if ((int)threadIdx.x < NR)
             for (int w = 0; w < 4; ++w) v += red[w * 4 + threadIdx.x];
-        leave_sums<NR>(a, v, reinterpret_cast<double *>(smem + 1024));
+        leave_sums<NR>(a, v);
     }
 }
 

@@ -72,7 +72,6 @@ __global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(Fw
 template <int NR, bool LOSS>
 __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, int mb) {
     __shared__ float red[4][4];
-    __shared__ double ends[LOSS ? 16 : 1];
     const FwdArgs &a = s.f;
     const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g4 = lane >> 4, l16 = lane & 15, rb = g & 1;
@@ -188,7 +187,7 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
             if (lane == 0) red[g][i] = v;
         }
         __syncthreads();
-        leave_sums<NR>(a, (int)threadIdx.x < NR ? red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x] : 0.f, ends);
+        leave_sums<NR>(a, (int)threadIdx.x < NR ? red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x] : 0.f);
     }
 }
 

@@ -110,6 +110,14 @@ inline int fwd_wide_mb(int64_t M, int64_t N, int64_t K, double *ns) {
     return choice;
 }
 
+// The losses of a forward with the objective: in grids of up to this many workgroups the last one to arrive finishes them (leave_sums),
+// in larger ones a launch of one workgroup.  All workgroups add to one word, about 10 ns each; the launch takes 0.6 us between kernels and
+// half a microsecond of the host.  Calls with the counter against calls with the launch at three bit-widths (2000 sizes each way; replayed
+// from a graph, one after the other): 0.96 and 0.95 times as long up to 44 workgroups, 0.97 and 0.96 at 48 to 60.  At 128 (two rows of sums in a
+// lane, 0.27 us more for everyone): 1.01 and 1.00 at 64 to 88, 1.03 and 1.02 at 92 to 124.  At 512 (sums added by all four waves): 1.04 and 1.02 at 128
+// to 180, 1.10 at 256 to 360 and 1.13 at 364 to 504 in the form that cuts K, whole tiles 1.01.
+constexpr int64_t kLossArrivals = 64;
+
 // ---- few tokens: K split over workgroups (mq_linear_split.hip) --------------------------------
 // most 32-token blocks per workgroup: at one bit-width two workgroups of three share a compute unit, one of four has it alone,
 // and no size was found for which the rule below would take it

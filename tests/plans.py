@@ -18,6 +18,7 @@ extern "C" void plan_forward(int64_t M, int64_t N, int64_t K, int nr, int64_t *o
     fwd_tiled_cost(M, N, K, nr, &tiled);
     out[0] = p.mb, out[1] = p.splits, out[2] = nr == 1 ? fwd_wide_mb(M, N, K, nullptr) : 0, out[3] = tiled;
 }
+extern "C" int plan_loss_arrivals(void) { return (int)kLossArrivals; }
 extern "C" void plan_dx(int64_t M, int64_t N, int64_t K, int nr, int64_t *out) {
     const DxPlan p = make_dx_plan(M, N, K, nr);
     out[0] = p.mb, out[1] = p.splits;
@@ -88,6 +89,18 @@ def forward(M, N, K, nr, objective=False):
     if mb:
         return Forward("split", mb, splits)
     return Forward("wide", wide, 1) if wide and not objective else Forward("tiled", tiled, 1)
+
+
+def loss_workgroups(M, N, K, nr):
+    """Form and workgroups of the kernel that leaves the sums of a forward with the objective."""
+    form, blocks, _ = forward(M, N, K, nr, objective=True)
+    tiles = -(-M // (32 * blocks)) * -(-N // 128)
+    return form, 4 * blocks * tiles if form == "split" else tiles
+
+
+def loss_arrivals():
+    """Most workgroups among which the last one to arrive finishes the losses."""
+    return _lib().plan_loss_arrivals()
 
 
 def dx(M, N, K, nr):

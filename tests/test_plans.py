@@ -2,7 +2,7 @@
 import pytest
 
 from tests import (plans, test_gpu_dw_tiles, test_gpu_dw_turned, test_gpu_dx_split, test_gpu_forward_low_tiles, test_gpu_forward_split, test_gpu_forward_wide,
-                   test_gpu_gemv_list, test_gpu_gemv_registers, test_gpu_gemv_split_ring)
+                   test_gpu_gemv_list, test_gpu_gemv_registers, test_gpu_gemv_split_ring, test_gpu_loss_arrivals)
 
 cdiv = lambda a, b: -(-a // b)
 
@@ -128,6 +128,15 @@ def test_dw_over_an_input_is_from_copies():
     assert plans.dw_in_place(M, N, K, X, dY, dY + M * N * 2) and plans.dw_in_place(M, N, K, X, dY, dY - N * K * 4)
     assert not any(plans.dw_in_place(M, N, K, X, dY, dY + d) for d in (0, 16, M * N * 2 - 16, 16 - N * K * 4))
     assert plans.dw_in_place(M, N, K, X, None, dY)   # summed or scaled: the preparation has read it
+
+
+def test_loss_sizes():
+    """The last workgroup to arrive finishes the losses in grids of up to so many: sizes on either side, and right at it, in either form."""
+    limit, seen = plans.loss_arrivals(), {"tiled": set(), "split": set()}
+    for M, N, K, rs in test_gpu_loss_arrivals.SIZES:
+        form, workgroups = plans.loss_workgroups(M, N, K, len(rs))
+        seen[form].add(workgroups)
+    assert seen == {"tiled": {1, limit - 1, limit, limit + 1}, "split": {4, limit - 4, limit, limit + 4}}
 
 
 def test_split_decode_sizes():
