@@ -162,9 +162,11 @@ __device__ __forceinline__ SliceParam slice_param(int r) {
 // behind a matrix product without waiting for the one before it (a wave issues a dependent vector instruction only every eight
 // cycles, and a 16x16x32 product takes sixteen).  t carries the values between the steps; the empty asm keeps a step where it is.
 // A code of r = 2 depends on the upper three bits of the byte alone, rounding and clamp included: KIND_2 looks four of them up with one
-// byte permutation, five instructions instead of eight.  14336 x 4096, 2011 tokens, r = 2 181.4 -> 173.7 us a call; the forward with the
-// objective at r = 8/4/2, 14336 x 3584, 8192 tokens 1926 -> 1880 us, dX level (power is the limit); 2304 x 9216, 1999 tokens 203 -> 198 and 219 -> 214.
-// The operand's bits are the same.
+// byte permutation, five instructions instead of eight.  The operand's bits are the same.  Whole calls with the look-up against calls without
+// at 2670 pairs of times (512 to 14336 rows and columns, 17 to 4096 tokens): r = 2 alone dX 0.965 times as long, forward 0.971 (with the
+// objective 0.975); r = 8/2 dX 0.975, forward in whole tiles 0.973 (0.984); 4/2 dX 0.986, forward 0.990 (0.993); 8/4/2 forward 0.992
+// (0.989; tiles of 64 and 96 tokens 0.994 (0.988), 1.7 % longer at worst), dX 0.992 to 0.996 up to 96 tokens a tile and level above
+// (launch_dx_mb).
 enum CodeKind { KIND_ANY, KIND_8, KIND_2 };
 constexpr CodeKind code_kind(bool is8, bool is2) { return is8 ? KIND_8 : is2 ? KIND_2 : KIND_ANY; }
 template <CodeKind KIND, bool EP, int STEP>

@@ -418,8 +418,10 @@ mq_status launch_fwd_wide_one(const FwdWideArgs &w, int mb, hipStream_t st) {
 
 template <int NRS, bool HAS8, bool LAST2, bool EP, int MB>
 mq_status launch_dx_mb(const DxArgs &d, hipStream_t st) {
-    if (!allow_lds<dx_kernel<NRS, HAS8, LAST2, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
-    dx_kernel<NRS, HAS8, LAST2, EP, MB><<<dim3(d.tiles_m * d.tiles_k * d.splits), dim3(256), dx_lds(MB), st>>>(d);
+    // (three bit-widths in tiles of 128 and 160 tokens: 0.9997 times as long with the look-up, 0.977 to 1.016 at 95 sizes)
+    constexpr bool LOOKED_UP = LAST2 && !(NRS == 3 && MB >= 4);
+    if (!allow_lds<dx_kernel<NRS, HAS8, LOOKED_UP, EP, MB>>(dx_lds(MB))) return MQ_ERR_DEVICE;
+    dx_kernel<NRS, HAS8, LOOKED_UP, EP, MB><<<dim3(d.tiles_m * d.tiles_k * d.splits), dim3(256), dx_lds(MB), st>>>(d);
     return launch_status();
 }
 
