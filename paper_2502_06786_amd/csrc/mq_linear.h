@@ -327,8 +327,8 @@ constexpr bool fwd_acc_in_file_a(int nr, int mb, int i, int tb) { return !(nr ==
 // channels [32 w, 32 w + 32) of the tile for all its tokens; lane (l16, g4) ends up with channels 4 g4 .. 4 g4 + 3 of token l16 of
 // a block.  ROWSUM: also rsum[j] += this thread's share (chunk t % 8 of
 // row t / 8) of sum_k X for the token blocks in rs_mask.
-template <int NR, bool HAS8, bool LAST2, bool EP, int MB, bool ROWSUM>
-__device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, int m0, int n0, int kt0, int nkt, int k_end,
+template <int NR, bool HAS8, bool LAST2, bool EP, int MB, bool ROWSUM, typename Args>
+__device__ __forceinline__ void fwd_main_loop(const Args &a, uint8_t *smem, int m0, int n0, int kt0, int nkt, int k_end,
                                               f32x4 (&acc)[NR][2][2 * MB], float (&rsum)[MB], uint32_t rs_mask) {
     constexpr int BM = 32 * MB;
     constexpr int X_TILE = BM * 128;
@@ -499,25 +499,26 @@ __device__ __forceinline__ void fwd_main_loop(const FwdArgs &a, uint8_t *smem, i
 // Ends a workgroup of a kernel that evaluates the objective: its sums (`v` of slot t in thread t < 4) go to a.partial.  With a counter
 // (kLossArrivals), the workgroup that finds all others arrived adds them, in the order of the workgroups whichever it is, and writes the
 // losses.  Nobody waits for anybody.  The sums and the counter are written and read past the caches that XCDs do not share (agent scope);
-// the sums are there before the counter counts them because the wave waits for its stores in between.
-template <int NR>
-__device__ __forceinline__ void leave_sums(const FwdArgs &a, float v) {
+// the sums are there before the counter counts them because the wave waits for its stores in between.  (workgroups: of the launch.  Asked of
+// gridDim it would add 256 bytes to the arguments of every launch of a kernel that asks for nothing else there.)
+template <int NR, typename Args>
+__device__ __forceinline__ void leave_sums(const Args &a, float v, uint32_t workgroups, float *partial, uint32_t *arrived) {
     static_assert(kLossArrivals <= 64, "one wave adds the sums, a workgroup's in a lane");
     if (threadIdx.x >= 64) return;
-    if (!a.arrived) {
-        if (threadIdx.x < 4) a.partial[(size_t)blockIdx.x * 4 + threadIdx.x] = v;
+    if (!arrived) {
+        if (threadIdx.x < 4) partial[(size_t)blockIdx.x * 4 + threadIdx.x] = v;
         return;
     }
-    if (threadIdx.x < 4) __hip_atomic_store(a.partial + (size_t)blockIdx.x * 4 + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x < 4) __hip_atomic_store(partial + (size_t)blockIdx.x * 4 + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wait_vm0();
     uint32_t before = 0;
-    if (threadIdx.x == 0) before = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__builtin_amdgcn_readfirstlane(before) != gridDim.x - 1) return;
+    if (threadIdx.x == 0) before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) != workgroups - 1) return;
     wait_vm0();   // (nothing below is loaded before the count is known)
     double sum[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i)
-        sum[i] = threadIdx.x < gridDim.x ? (double)__hip_atomic_load(a.partial + (size_t)threadIdx.x * 4 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        sum[i] = threadIdx.x < workgroups ? (double)__hip_atomic_load(partial + (size_t)threadIdx.x * 4 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll

@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, MB <= 3 ? 2 : 1) void fwd_kernel(FwdArgs a) {
         float v = 0.f;
         if ((int)threadIdx.x < NR)
             for (int w = 0; w < 4; ++w) v += red[w * 4 + threadIdx.x];
-        leave_sums<NR>(a, v);
+        leave_sums<NR>(a, v, a.tiles_m * a.tiles_n, a.partial, a.arrived);
     }
 }
 
@@ -1154,13 +1154,13 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         a.A[slot_of[i]] = gate ? gated_out[i] : nullptr;
         a.r[slot_of[i]] = rs[i];
     }
+    a.arrived = reinterpret_cast<uint32_t *>(base + lay.counter);
     const double mn = (double)M * (double)N;
     if (loss) {
         a.T = loss->target;
         a.bias = loss->bias;
         a.mix = loss->mix ? 1 : 0;
         a.partial = reinterpret_cast<float *>(base + lay.loss);
-        a.arrived = reinterpret_cast<uint32_t *>(base + lay.counter);
         a.losses = loss->losses;
         a.inv_mn = (float)(1.0 / mn);
         for (int i = 0; i < nr; ++i) {
@@ -1179,7 +1179,7 @@ static mq_status fwd_run(const uint16_t *X, const uint8_t *Q, const float *alpha
         s = launch_fwd_split(a, plan, nr, has8, ep, loss != nullptr, reinterpret_cast<float *>(base + lay.part),
                              reinterpret_cast<float *>(base + lay.rs_part), st, &blocks);
     } else {
-        rowsum_kernel<<<dim3((unsigned)cdiv(M, 4)), dim3(256), 0, st>>>(X, (int)M, (int)K, static_cast<float *>(ws), a.arrived);
+        rowsum_kernel<<<dim3((unsigned)cdiv(M, 4)), dim3(256), 0, st>>>(X, (int)M, (int)K, static_cast<float *>(ws), loss ? a.arrived : nullptr);
         const int wide = nr == 1 && !loss ? fwd_wide_mb(M, N, K, nullptr) : 0;
         s = wide ? launch_fwd_wide(a, wide, has8, ep, st)
             : loss ? launch_fwd_any<true>(a, nr, has8, ep, st, &blocks) : launch_fwd_any<false>(a, nr, has8, ep, st, &blocks);

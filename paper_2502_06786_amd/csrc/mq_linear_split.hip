@@ -14,17 +14,60 @@
 
 namespace mq {
 
-struct FwdSplitArgs {
-    FwdArgs f;
+struct FwdRanges {
     float *part;     // [split][tile][bit-width][block of 16 channels][block of 16 tokens][256] four channels of one token each
     float *rs_part;  // [split][tiles_m * 32 MB] sums of X over the split's range of K
     int splits;
 };
+// The kernels' arguments: a launch costs by their bytes, and a kernel of a few microseconds by the lines that it reads of them.  With all of
+// FwdArgs in both, and a branch on the counter at the end of the first, plain calls of one to three bit-widths took 1.1 to 1.6 % longer
+// replayed from a graph, 2.7 to 3.5 % one after the other (235 sizes of up to 350 tokens).
+struct FwdSplitArgs {  // (names as in FwdArgs)
+    const uint16_t *X;
+    const uint8_t *Q;
+    int M, N, K;
+    int r[3];
+    int tiles_m, tiles_n;
+    FwdRanges s;
+    float *arrived;    // the counter of the finishing kernel, to be cleared
+};
+struct FwdPlainArgs {
+    int M, N;
+    int r[3];
+    int tiles_m, tiles_n;
+    const float *alpha, *zero;
+    uint16_t *Y[3];
+    int gate;
+    uint16_t *A[3];
+};
+struct FwdLossArgs {
+    int M, N;
+    int r[3];
+    int tiles_m, tiles_n;
+    const float *alpha, *zero, *bias;
+    uint16_t *Y[3];
+    const uint16_t *T;
+    uint16_t *dY[3];
+    int teacher[3];
+    float coef[3];
+    int mix;
+    float *partial;
+    uint32_t *arrived;
+    float *losses;
+    int loss_slot[3];
+    float inv_mn;
+};
+template <bool LOSS>
+struct FwdFinishArgs {
+    FwdRanges s;
+    int mb;
+    std::conditional_t<LOSS, FwdLossArgs, FwdPlainArgs> f;
+};
 
 template <int NR, bool HAS8, bool LAST2, bool EP, int MB>
-__global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(FwdSplitArgs s) {
+__global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(FwdSplitArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const FwdArgs &a = s.f;
+    const FwdRanges &s = a.s;
     constexpr int BM = 32 * MB;
     const int tiles = a.tiles_m * a.tiles_n;
     // Neighbouring ids, which share an XCD's L2, are token tiles of one channel tile (the same codes), then channel tiles
@@ -52,7 +95,11 @@ __global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(Fw
             v += __shfl_xor(v, 1, 64);
             v += __shfl_xor(v, 2, 64);
             v += __shfl_xor(v, 4, 64);
-            if ((threadIdx.x & 7) == 0) s.rs_part[(size_t)split * a.tiles_m * BM + m0 + j * 32 + (threadIdx.x >> 3)] = v;
+            // (the lanes beside clear the counter of the kernel that finishes, with the same store: at the head of this one 77 tokens, 4096 x
+            // 4096 took 14.27 instead of 13.97 us)
+            const bool sums = (threadIdx.x & 7) == 0;
+            float *to = sums ? s.rs_part + (size_t)split * a.tiles_m * BM + m0 + j * 32 + (threadIdx.x >> 3) : a.arrived;
+            if ((threadIdx.x & 7) < 2) *to = sums ? v : 0.f;
         }
     f32x4 *dst = reinterpret_cast<f32x4 *>(s.part) + ((size_t)split * tiles + tile) * (NR * MB * 4 * 256) + threadIdx.x;
 #pragma unroll
@@ -62,17 +109,24 @@ __global__ __launch_bounds__(256, NR * MB <= 9 ? 2 : 1) void fwd_split_kernel(Fw
 #pragma unroll
             for (int tb = 0; tb < 2 * MB; ++tb)
                 if (m0 + 16 * tb < a.M) dst[((i * 2 + rb) * 2 * MB + tb) * 256] = acc[i][rb][tb];
-    // for the kernel that finishes (at the head of this one: 77 tokens, 4096 x 4096 13.97 -> 14.27 us)
-    if (blockIdx.x == 0 && threadIdx.x == 0 && a.arrived) *a.arrived = 0u;
 }
 
 // Adds the K ranges and finishes the outputs.  Workgroup = (tile, 32 tokens, 32 channels): its waves take the four 16 x 16
 // blocks and write 64 contiguous bytes of 32 tokens.  The arithmetic per output is that of the
 // tiled forward kernel's epilogue.
 template <int NR, bool LOSS>
-__global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, int mb) {
+__global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdFinishArgs<LOSS> p) {
     __shared__ float red[4][4];
-    const FwdArgs &a = s.f;
+    const auto &a = p.f;
+    const FwdRanges &s = p.s;
+    const int mb = p.mb;
+    float *partial = nullptr;
+    uint32_t *arrived = nullptr;
+    if constexpr (LOSS) {  // (asked for at the end they are two more trips to memory)
+        partial = a.partial;
+        arrived = a.arrived;
+        asm volatile("" : "+s"(partial), "+s"(arrived));
+    }
     const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g4 = lane >> 4, l16 = lane & 15, rb = g & 1;
     const int w = blockIdx.x & 3, tb = (int)(blockIdx.x >> 2) % mb * 2 + (g >> 1), tile = (int)(blockIdx.x >> 2) / mb;
@@ -187,7 +241,7 @@ __global__ __launch_bounds__(256) void fwd_split_finish_kernel(FwdSplitArgs s, i
             if (lane == 0) red[g][i] = v;
         }
         __syncthreads();
-        leave_sums<NR>(a, (int)threadIdx.x < NR ? red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x] : 0.f);
+        leave_sums<NR>(a, (int)threadIdx.x < NR ? red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x] : 0.f, tiles * mb * 4, partial, arrived);
     }
 }
 
@@ -197,7 +251,7 @@ namespace {
 template <int NR, bool HAS8, bool LAST2, bool EP, int MB>
 mq_status launch_split_mb(const FwdSplitArgs &s, hipStream_t st) {
     if (!allow_lds<fwd_split_kernel<NR, HAS8, LAST2, EP, MB>>(split_lds(MB))) return MQ_ERR_DEVICE;
-    fwd_split_kernel<NR, HAS8, LAST2, EP, MB><<<dim3(s.f.tiles_m * s.f.tiles_n * s.splits), dim3(256), split_lds(MB), st>>>(s);
+    fwd_split_kernel<NR, HAS8, LAST2, EP, MB><<<dim3(s.tiles_m * s.tiles_n * s.s.splits), dim3(256), split_lds(MB), st>>>(s);
     return launch_status();
 }
 
@@ -218,7 +272,7 @@ mq_status launch_split(const FwdSplitArgs &s, int mb, hipStream_t st) {
     // between: 3440 x 1504, 20 tokens, r = 8/4/2 9.0 -> 9.6 us, 6288 x 3728, 60 tokens, 4/2 14.4 -> 15.0; 2512 x 3088, 213
     // tokens, r = 2 15.6 -> 14.5)
     if constexpr (NR == 1 && has_last2(NR, HAS8))
-        if (s.f.r[NR - 1] == 2) return launch_split_form<NR, HAS8, true, EP>(s, mb, st);
+        if (s.r[NR - 1] == 2) return launch_split_form<NR, HAS8, true, EP>(s, mb, st);
     return launch_split_form<NR, HAS8, false, EP>(s, mb, st);
 }
 
@@ -234,11 +288,16 @@ mq_status launch_split_nr(const FwdSplitArgs &s, int mb, bool has8, bool ep, hip
 }
 
 template <int NR>
-mq_status launch_finish(const FwdSplitArgs &s, int mb, bool loss, hipStream_t st, int64_t blocks) {
-    if (loss)
-        fwd_split_finish_kernel<NR, true><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, mb);
-    else
-        fwd_split_finish_kernel<NR, false><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, mb);
+mq_status launch_finish(const FwdRanges &s, const FwdArgs &f, int mb, bool loss, hipStream_t st, int64_t blocks) {
+    if (loss) {
+        const FwdLossArgs a{f.M, f.N, {f.r[0], f.r[1], f.r[2]}, f.tiles_m, f.tiles_n, f.alpha, f.zero, f.bias, {f.Y[0], f.Y[1], f.Y[2]}, f.T,
+                            {f.dY[0], f.dY[1], f.dY[2]}, {f.teacher[0], f.teacher[1], f.teacher[2]}, {f.coef[0], f.coef[1], f.coef[2]}, f.mix,
+                            f.partial, f.arrived, f.losses, {f.loss_slot[0], f.loss_slot[1], f.loss_slot[2]}, f.inv_mn};
+        fwd_split_finish_kernel<NR, true><<<dim3((unsigned)blocks), dim3(256), 0, st>>>({s, mb, a});
+    } else {
+        const FwdPlainArgs a{f.M, f.N, {f.r[0], f.r[1], f.r[2]}, f.tiles_m, f.tiles_n, f.alpha, f.zero, {f.Y[0], f.Y[1], f.Y[2]}, f.gate, {f.A[0], f.A[1], f.A[2]}};
+        fwd_split_finish_kernel<NR, false><<<dim3((unsigned)blocks), dim3(256), 0, st>>>({s, mb, a});
+    }
     return launch_status();
 }
 
@@ -250,20 +309,18 @@ FwdSplitPlan fwd_split_plan(int64_t M, int64_t N, int64_t K, int nr) {
 
 mq_status launch_fwd_split(const FwdArgs &f, const FwdSplitPlan &plan, int nr, bool has8, bool ep, bool loss, float *part, float *rs_part,
                            hipStream_t st, int64_t *blocks) {
-    FwdSplitArgs s;
-    s.f = f;
-    s.f.tiles_m = (int)cdiv(f.M, 32 * plan.mb);
-    s.f.tiles_n = (int)cdiv(f.N, FWD_BN);
-    s.part = part;
-    s.rs_part = rs_part;
-    s.splits = plan.splits;
+    FwdArgs a = f;
+    a.tiles_m = (int)cdiv(f.M, 32 * plan.mb);
+    a.tiles_n = (int)cdiv(f.N, FWD_BN);
     *blocks = plan.loss_blocks;
-    if (*blocks > kLossArrivals) s.f.arrived = nullptr;
+    if (*blocks > kLossArrivals) a.arrived = nullptr;
+    const FwdRanges ranges{part, rs_part, plan.splits};
+    const FwdSplitArgs s{a.X, a.Q, a.M, a.N, a.K, {a.r[0], a.r[1], a.r[2]}, a.tiles_m, a.tiles_n, ranges, reinterpret_cast<float *>(f.arrived)};
     mq_status e = nr == 1 ? launch_split_nr<1>(s, plan.mb, has8, ep, st) : nr == 2 ? launch_split_nr<2>(s, plan.mb, has8, ep, st)
                                                                                     : launch_split_nr<3>(s, plan.mb, has8, ep, st);
     if (e != MQ_OK) return e;
-    return nr == 1 ? launch_finish<1>(s, plan.mb, loss, st, *blocks) : nr == 2 ? launch_finish<2>(s, plan.mb, loss, st, *blocks)
-                                                                               : launch_finish<3>(s, plan.mb, loss, st, *blocks);
+    return nr == 1 ? launch_finish<1>(ranges, a, plan.mb, loss, st, *blocks) : nr == 2 ? launch_finish<2>(ranges, a, plan.mb, loss, st, *blocks)
+                                                                                       : launch_finish<3>(ranges, a, plan.mb, loss, st, *blocks);
 }
 
 }  // namespace mq

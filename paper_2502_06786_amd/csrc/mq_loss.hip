@@ -84,6 +84,7 @@ __global__ __launch_bounds__(kLossBlock) void l2_loss_kernel(LossArgs a) {
 __global__ __launch_bounds__(256) void l2_loss_finish_kernel(const float *partial, int64_t blocks, int nr, float inv_mn,
                                                              float *losses, int s0, int s1, int s2) {
     __shared__ double red[4][3];
+    asm volatile("" : "+s"(s0), "+s"(s1), "+s"(s2), "+s"(losses), "+s"(inv_mn));  // (fetched now)
     double v[3] = {0.0, 0.0, 0.0};
     for (int64_t b0 = threadIdx.x; b0 < blocks; b0 += 1024) {
         f32x4 x[4];
