@@ -946,7 +946,7 @@ static BwdWorkspace bwd_layout(int64_t M, int64_t N, int64_t K, int nr, const Dx
     o += align256((size_t)N * K);
     w.xt = o;
     o += align256(m32 * K * 2);
-    // dW is done before dX begins: their partial sums share their place
+    // one of dX and dW is done before the other begins: their partial sums share their place
     w.dxp = w.dwp = o;
     o += align256(std::max(dw.part_bytes, dx.part_bytes));
     w.total = o;
@@ -1426,7 +1426,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
     p.cpart = dX ? reinterpret_cast<float *>(base + lay.cvec) : nullptr;
     // (the operand of dW is a single gradient as it stands where it is not scaled)
     const bool single = !gated && nr == 1 && p.lam[0] == 1.0f;
-    const bool turn = dW && dw_turns_in_place(M, N, K, X, single ? dY[0] : nullptr, dW, dX || !single, dw_cut.hb), plain_g = single && turn;
+    const bool turn = dW && dw_turns_in_place(M, N, K, X, single ? dY[0] : nullptr, dX, dW, dX || !single, dw_cut.hb), plain_g = single && turn;
     p.G = dW && !plain_g ? reinterpret_cast<uint16_t *>(base + lay.g) : nullptr;
     p.nr = nr;
     p.M = (int)M;
@@ -1445,22 +1445,7 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         if (s != MQ_OK) return s;
     }
 
-    // dW comes first: it reads X and possibly a gradient where they stand, and dX may lie over either
-    if (dW) {
-        DwArgs w{};
-        w.G[0] = plain_g ? dY[0] : p.G;
-        w.in_pieces = !plain_g;
-        w.X = turn ? X : p.XT;
-        w.dW = dW;
-        w.part = reinterpret_cast<float *>(base + lay.dwp);
-        w.M = (int)M;
-        w.N = (int)N;
-        w.K = (int)K;
-        w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
-        const mq_status dws = launch_dw(w, dw_cut, turn, st);
-        if (dws != MQ_OK) return dws;
-    }
-    if (dX) {
+    auto form_dx = [&]() -> mq_status {
         // slot order of the kernel: the r = 8 bit-width (if any) first
         DxArgs d;
         int order[3] = {0, 0, 0}, has8 = 0, pos = 0;
@@ -1484,9 +1469,27 @@ static mq_status bwd_run(bool gated, const uint16_t *X, const uint8_t *Q, const 
         d.N = (int)N;
         d.K = (int)K;
         d.part = reinterpret_cast<float *>(base + lay.dxp);
-        const mq_status ds = launch_dx(d, dx_cut, nr, has8 != 0, ep, st);
-        if (ds != MQ_OK) return ds;
-    }
+        return launch_dx(d, dx_cut, nr, has8 != 0, ep, st);
+    };
+    auto form_dw = [&]() -> mq_status {
+        DwArgs w{};
+        w.G[0] = plain_g ? dY[0] : p.G;
+        w.in_pieces = !plain_g;
+        w.X = turn ? X : p.XT;
+        w.dW = dW;
+        w.part = reinterpret_cast<float *>(base + lay.dwp);
+        w.M = (int)M;
+        w.N = (int)N;
+        w.K = (int)K;
+        w.accumulate = (flags & MQ_FLAG_ACCUM_DW) ? 1 : 0;
+        return launch_dw(w, dw_cut, turn, st);
+    };
+    // (operands that dW takes as they stand are not stored over by dX: dw_turns_in_place)
+    const bool first = dW && !turn && dw_first(M, N, K);
+    if (first) s = form_dw();
+    if (s == MQ_OK && dX) s = form_dx();
+    if (s == MQ_OK && dW && !first) s = form_dw();
+    if (s != MQ_OK) return s;
     return launch_status();
 }
 }  // namespace mq

@@ -30,8 +30,9 @@ extern "C" void plan_dw(int64_t M, int64_t N, int64_t K, int batch, int64_t *out
 extern "C" int plan_dw_turns(int64_t M, int64_t N, int64_t K, int batch, int alone, int prep) {
     return dw_turns(M, N, K, batch, alone, prep, make_dw_plan(M, N, K, batch).hb);
 }
-extern "C" int plan_dw_in_place(int64_t M, int64_t N, int64_t K, int64_t X, int64_t dY, int64_t dW) {
-    return dw_turns_in_place(M, N, K, (const void *)X, (const void *)dY, (const void *)dW, true, make_dw_plan(M, N, K, 1).hb);
+extern "C" int plan_dw_first(int64_t M, int64_t N, int64_t K) { return dw_first(M, N, K); }
+extern "C" int plan_dw_in_place(int64_t M, int64_t N, int64_t K, int64_t X, int64_t dY, int64_t dX, int64_t dW) {
+    return dw_turns_in_place(M, N, K, (const void *)X, (const void *)dY, (const void *)dX, (const void *)dW, true, make_dw_plan(M, N, K, 1).hb);
 }
 extern "C" void plan_quad(int64_t B, int64_t N, int64_t K, int r, int list, int64_t *out) {
     const QuadPlan p = make_quad_plan(B, N, K, K * r / 8, r, list);
@@ -71,7 +72,8 @@ def _lib():
     for f in (lib.plan_forward, lib.plan_dx, lib.plan_dw, lib.plan_gemv, lib.plan_gemv_split):
         f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
         f.restype = None
-    lib.plan_dw_in_place.argtypes = [ctypes.c_int64] * 6
+    lib.plan_dw_in_place.argtypes = [ctypes.c_int64] * 7
+    lib.plan_dw_first.argtypes = [ctypes.c_int64] * 3
     lib.plan_dw_turns.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
     lib.plan_quad.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int64)]
     lib.plan_quad.restype = None
@@ -117,9 +119,15 @@ def dw_turns(M, N, K, gradients=1, alone=True, prep=True):
     return bool(_lib().plan_dw_turns(M, N, K, gradients, alone, prep))
 
 
-def dw_in_place(M, N, K, X, dY, dW):
-    """Whether the dW of a backward with dX reads its operands as they stand; addresses, dY None where the gradient is summed or scaled."""
-    return bool(_lib().plan_dw_in_place(M, N, K, X, dY or 0, dW))
+def dw_first(M, N, K):
+    """Whether a backward from copies forms dW before dX."""
+    return bool(_lib().plan_dw_first(M, N, K))
+
+
+def dw_in_place(M, N, K, X, dY, dX, dW):
+    """Whether the dW of a backward with a preparation reads its operands as they stand; addresses, dY None where the gradient is summed or scaled,
+    dX None where it is not wanted."""
+    return bool(_lib().plan_dw_in_place(M, N, K, X, dY or 0, dX or 0, dW))
 
 
 def quad(B, N, K, r, with_list=False):

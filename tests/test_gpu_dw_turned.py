@@ -48,7 +48,7 @@ def test_exact(mq, M, N, K, nr, lam):
     want = total.t().contiguous() @ X.float()
     _, dW = mq.mq_linear_bwd(X, Q, one, one, dY, lam, (4, 2)[:nr], need_dX=False)
     assert torch.equal(dW, want)
-    # dX in the place of X, which is read before
+    # dX in the place of X, which is then copied before
     dX, dW2 = mq.mq_linear_bwd(X.clone(), Q, one, one, dY, lam, (4, 2)[:nr])
     mine = X.clone()
     mq.mq_linear_bwd(mine, Q, one, one, dY, lam, (4, 2)[:nr], dX=mine, dW=dW)

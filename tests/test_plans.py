@@ -116,18 +116,27 @@ def test_dw_turned_sizes():
     assert plans.dw_turns(M, N, N, 1, True, True)
 
 
-def test_dw_over_an_input_is_from_copies():
-    """While dW is stored, workgroups still read operands that are taken as they stand: X and a gradient that dW meets are copied."""
+def test_either_order_of_a_backward():
+    """Where dX and dW, whole or in ranges, share the place of their partial sums, both orders are met: sizes against the oracle, and exact ones."""
+    for sizes in ([c[:3] for c in test_gpu_dw_tiles.CASES], test_gpu_dw_turned.SIZES):
+        assert {plans.dw_first(*size) for size in sizes if not plans.dw_turns(*size, alone=False)} == {False, True}
+
+
+def test_outputs_over_an_input_take_copies():
+    """Workgroups of dW read operands that are taken as they stand while others store dW, and after dX has been stored: X and a gradient that an
+    output meets are copied."""
     M, N, K = test_gpu_dw_turned.OVER
-    X, dY, dW = 1 << 40, 2 << 40, 3 << 40
+    X, dY, dX, dW = (i << 40 for i in range(1, 5))
+    x_bytes, dy_bytes, dw_bytes = M * K * 2, M * N * 2, N * K * 4
     for grad in (dY, None):
-        assert plans.dw_in_place(M, N, K, X, grad, dW)
-        # next to each other is apart
-        assert plans.dw_in_place(M, N, K, X, grad, X + M * K * 2) and plans.dw_in_place(M, N, K, X, grad, X - N * K * 4)
-        assert not any(plans.dw_in_place(M, N, K, X, grad, X + d) for d in (0, 16, M * K * 2 - 16, 16 - N * K * 4))
-    assert plans.dw_in_place(M, N, K, X, dY, dY + M * N * 2) and plans.dw_in_place(M, N, K, X, dY, dY - N * K * 4)
-    assert not any(plans.dw_in_place(M, N, K, X, dY, dY + d) for d in (0, 16, M * N * 2 - 16, 16 - N * K * 4))
-    assert plans.dw_in_place(M, N, K, X, None, dY)   # summed or scaled: the preparation has read it
+        assert plans.dw_in_place(M, N, K, X, grad, dX, dW) and plans.dw_in_place(M, N, K, X, grad, None, dW)
+        for at, in_bytes in ((X, x_bytes), (dY, dy_bytes)):
+            place = {"dW": lambda p: plans.dw_in_place(M, N, K, X, grad, dX, p), "dX": lambda p: plans.dw_in_place(M, N, K, X, grad, p, dW)}
+            for out, out_bytes in (("dW", dw_bytes), ("dX", x_bytes)):
+                # next to each other is apart
+                assert place[out](at + in_bytes) and place[out](at - out_bytes)
+                # (a gradient that is summed or scaled has been read by the preparation)
+                assert {place[out](at + d) for d in (0, 16, in_bytes - 16, 16 - out_bytes)} == {at == dY and grad is None}
 
 
 def test_loss_sizes():
