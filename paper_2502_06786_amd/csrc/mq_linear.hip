@@ -720,6 +720,22 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         x_base += x_block;
         rows_left -= DW_BM;
     };
+    // Load l of that stage into LDS buffer `buf` as the compiler's own load, for the small tiles of copies: it deals the scalar instructions of a
+    // stage over the products.  With all of them at the start of a stage, where nothing else runs (or in pieces behind the products of its second half),
+    // dW calls of 768 tokens and more take 1.02 times as long, of fewer 1.007 (560 sizes); 256-tiles 0.993.
+    constexpr bool COMPILED = HB == 2 && !TURN;
+    auto compiled_load = [&](auto l_tag, int buf) {
+        constexpr int l = decltype(l_tag)::value;
+        const int bytes = rows_left > 0 ? (l < AL ? a.N - n0 : a.K - k0) * (2 * DW_BM) : 0;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(l < AL ? g_base : x_base, bytes),
+                                                 (lds_ptr)(smem + buf * DW_STAGE + wave * 1024 + (l < AL ? l * 4096 : DW_A_TILE + (l - AL) * 4096)), 16,
+                                                 l < AL ? goff[l < AL ? l : 0] : xoff[l < AL ? 0 : l - AL], 0, 0, 0);
+        if (l == LPS - 1) {
+            g_base += g_block;
+            x_base += x_block;
+            rows_left -= DW_BM;
+        }
+    };
     // LDS fragment offsets inside a stage (TURN: by the block of 16 columns in its group of 64): lane (l16, g4) ends up with eight
     // tokens of column l16 of a block, those of group g4 (otherwise of its chunk of a row of 32)
     uint32_t gb[TURN ? 4 : 1], xb[TURN ? 4 : 1];
@@ -756,10 +772,14 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
 
 #pragma unroll
     for (int st = 0; st < DW_NST - 1; ++st) {
-        next_stage();
+        if constexpr (COMPILED) {
+            static_for<LPS>([&](auto l) { compiled_load(l, st); });
+        } else {
+            next_stage();
 #pragma unroll
-        for (int i = 0; i < LPS; ++i)
-            load_to_lds(i < AL ? g_rsrc : x_rsrc, i < AL ? goff[i] : xoff[i - AL], lds0 + st * DW_STAGE + (i < AL ? i * 4096 : DW_A_TILE + (i - AL) * 4096));
+            for (int i = 0; i < LPS; ++i)
+                load_to_lds(i < AL ? g_rsrc : x_rsrc, i < AL ? goff[i] : xoff[i - AL], lds0 + st * DW_STAGE + (i < AL ? i * 4096 : DW_A_TILE + (i - AL) * 4096));
+        }
     }
     stage_barrier<(DW_NST - 2) * LPS, 0>();
 
@@ -783,13 +803,11 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
         const int nb = cb + 1 == DW_NST ? 0 : cb + 1;   // buffer of the next stage
         const int ib = cb == 0 ? DW_NST - 1 : cb - 1;   // buffer of the stage NST - 1 further on (= the one of the stage before)
         const uint8_t *cur = smem + cb * DW_STAGE, *nxt = smem + nb * DW_STAGE;
-        const uint32_t fill = lds0 + ib * DW_STAGE;
+        [[maybe_unused]] const uint32_t fill = lds0 + ib * DW_STAGE;
         // products from one load to the next; instructions between the descriptors and the first load that reads one: products, reads, aim
         constexpr int EVERY = NM / 2 / LPS, READS = std::min(EVERY, RB), BETWEEN = EVERY + (TURN ? READS : (READS + 1) / 2) + 1;
-        if constexpr (MORE) {
-            next_stage();
-            if constexpr (BETWEEN < kDescriptorWait) asm volatile("s_nop %0" ::"n"(std::max(kDescriptorWait - 1 - BETWEEN, 0)));
-        }
+        static_assert(COMPILED || BETWEEN >= kDescriptorWait, "wait states between a descriptor and the load that reads it");
+        if constexpr (MORE && !COMPILED) next_stage();
         __builtin_amdgcn_sched_barrier(0);
         static_for<NM>([&](auto q_tag) {
             constexpr int q = decltype(q_tag)::value, H = NM / 2, HJ = RB / 2;
@@ -800,8 +818,9 @@ __global__ __launch_bounds__(256) void dw_kernel(DwArgs a) {
                 if constexpr (q < 2 * HJ) read_half(xf[HJ + q / 2], cur, xb, std::integral_constant<int, HJ + q / 2>{}, std::integral_constant<int, q % 2>{});
                 constexpr int l = q / EVERY;
                 static_assert(EVERY >= 2 && H % LPS == 0, "a product between the two pieces of a load");
-                if constexpr (MORE && q % EVERY == EVERY - 2) aim_load_to_lds<l < AL ? l * 4096 : DW_A_TILE + (l - AL) * 4096>(fill);
-                if constexpr (MORE && q % EVERY == EVERY - 1) aimed_load_to_lds(l < AL ? g_rsrc : x_rsrc, l < AL ? goff[l < AL ? l : 0] : xoff[l < AL ? 0 : l - AL]);
+                if constexpr (MORE && COMPILED && q % EVERY == EVERY - 1) compiled_load(std::integral_constant<int, l>{}, ib);
+                if constexpr (MORE && !COMPILED && q % EVERY == EVERY - 2) aim_load_to_lds<l < AL ? l * 4096 : DW_A_TILE + (l - AL) * 4096>(fill);
+                if constexpr (MORE && !COMPILED && q % EVERY == EVERY - 1) aimed_load_to_lds(l < AL ? g_rsrc : x_rsrc, l < AL ? goff[l < AL ? l : 0] : xoff[l < AL ? 0 : l - AL]);
             } else if constexpr (MORE) {
                 constexpr int p = q - H;
                 if constexpr (p < 2 * HJ) read_half(xf[p / 2], nxt, xb, std::integral_constant<int, p / 2>{}, std::integral_constant<int, p % 2>{});
