@@ -211,7 +211,7 @@ def main():
                               "algorithmic_bytes": L.N * L.K + 2 * L.M * L.K + 8 * L.M * L.N,
                               "traffic": FWD_TRAFFIC_BYTES[cfg][L.name]}
     traffics = [per_linear[L.name]["traffic"] for L in layers]
-    roofline = {"bound": "mfma", "kernel": "mq::fwd_kernel<3, true, false, MB, true> (r = 8/4/2 with the objective in the epilogue)",
+    roofline = {"bound": "mfma", "kernel": "mq::fwd_kernel<3, true, true, false, MB, true> (r = 8/4/2 with the objective in the epilogue)",
                 "achieved": round(fwd_tf, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(fwd_tf / PEAK_BF16_TFLOPS, 4),
                 "traffic": None if any(t is None for t in traffics) else int(sum(traffics) / len(traffics)),
@@ -237,7 +237,7 @@ def main():
                              "dW_call_ms": round(ms_dw, 4), "dW_TFLOPs": round(tdw, 1), "dW_frac": round(tdw / PEAK_BF16_TFLOPS, 4)}
     plain_ms = sum(v["avg_launch_ms"] for v in plain.values())
     plain_tf = flops_fwd / (plain_ms * 1e-3) / 1e12
-    roofline["plain_forward"] = {"kernel": "mq::fwd_kernel<3, true, false, MB, false> (mq_linear_fwd_multi: Y_r stored, no objective)",
+    roofline["plain_forward"] = {"kernel": "mq::fwd_kernel<3, true, true, false, MB, false> (mq_linear_fwd_multi: Y_r stored, no objective)",
                                  "achieved": round(plain_tf, 2), "frac": round(plain_tf / PEAK_BF16_TFLOPS, 4),
                                  "per_linear": plain}
     bwd_split["note"] = ("mq_linear_bwd with only dX (prep pass + code transpose + dx_kernel, 6 MNK flops) and with only dW "
